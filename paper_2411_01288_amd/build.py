@@ -60,28 +60,39 @@ def _sgprs(text: str):
     return regs
 
 
-def lint_staging_hazards(src: str = "gemm_bf16.hip") -> None:
-    """The direct-to-LDS staging loads are inline assembly, so the compiler's hazard recogniser does
-    not see them.  One hazard matters: a vector-memory instruction must not read a scalar register
-    within five wait states of a VECTOR instruction writing it (v_readfirstlane of a uniform value
-    kept in vector registers, v_readlane of a spilled scalar).  This reads the generated ISA and
-    refuses the build if a staging load (or a global load with a scalar base, the form of the
-    row-offset loads) reads such a register too early."""
-    res = subprocess.run(["hipcc", *FLAGS, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", "-"],
-                         stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"hipcc -S failed on {src}")
+def _vgprs(text: str):
+    """Vector register numbers named in an operand string: v7, v[4:7]."""
+    regs = set()
+    for a, b in re.findall(r"\bv\[(\d+):(\d+)\]", text):
+        regs.update(range(int(a), int(b) + 1))
+    regs.update(int(n) for n in re.findall(r"\bv(\d+)\b", text))
+    return regs
+
+
+def lint_asm_hazards(text: str) -> list:
+    """Wait-state hazards in generated ISA that the compiler's hazard recogniser does not cover, as a list of
+    (line, instruction, registers); empty when there is none.
+
+    1. A vector-memory instruction must not read a scalar register within five wait states of a VECTOR
+       instruction writing it (v_readfirstlane of a uniform value kept in vector registers, v_readlane of a
+       spilled scalar).  Checked for the inline-assembly loads and stores: the direct-to-LDS staging
+       loads, global loads with a scalar base (the row-offset loads), buffer stores.
+    2. A vector instruction must not write a data register of a store of more than 8 bytes within two wait
+       states behind it.  (The compiler leaves no gap where a buffer store's scalar offset is a register.)"""
     window = []   # (wait states this instruction provides, scalar registers a vector instruction wrote)
+    stores = []   # (wait states since the store, its data registers, text)
     bad = []
-    for ln, line in enumerate(res.stdout.splitlines(), 1):
+    for ln, line in enumerate(text.splitlines(), 1):
         t = line.strip()
         if not t or t[0] in ";." or t.endswith(":") or t.startswith(("//", "#")):
             if t.endswith(":"):
                 window = []          # a label: the predecessors are unknown, start over
             continue
         op = t.split()[0]
-        if (op.startswith("buffer_load") and t.endswith("lds")) or (op.startswith("global_load") and "s[" in t):
-            need, used = 5, _sgprs(t.split(None, 1)[1])
+        ops = t.split(None, 1)[1] if " " in t or "\t" in t else ""
+        if ((op.startswith("buffer_load") and t.endswith("lds")) or (op.startswith("global_load") and "s[" in t)
+                or op.startswith("buffer_store")):
+            need, used = 5, _sgprs(ops)
             for states, written in reversed(window):
                 if need <= 0:
                     break
@@ -91,14 +102,30 @@ def lint_staging_hazards(src: str = "gemm_bf16.hip") -> None:
                 need -= states
         written = set()
         if op.startswith(("v_readfirstlane", "v_readlane")) or (op.startswith("v_cmp") and "_e64" in op):
-            written = _sgprs(t.split(None, 1)[1].split(",")[0])
+            written = _sgprs(ops.split(",")[0])
+        elif op.startswith("v_"):
+            vec = _vgprs(ops.split(",")[0])
+            bad += [(ln, f"{txt} | {t}", sorted(vec & data)) for states, data, txt in stores if vec & data]
         states = 1
         if op == "s_nop":
             states = int(t.split()[1]) + 1
         window.append((states, written))
         del window[:-8]
+        stores = [(n + states, data, txt) for n, data, txt in stores if n + states < 2]
+        if re.match(r"(buffer|global|flat)_store_dwordx[34]", op):
+            stores.append((0, _vgprs(ops.split(",")[0 if op.startswith("buffer") else 1]), t))
+    return bad
+
+
+def lint_staging_hazards(src: str = "gemm_bf16.hip") -> None:
+    """Refuses the build if the generated ISA of `src` holds a hazard (see lint_asm_hazards)."""
+    res = subprocess.run(["hipcc", *FLAGS, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", "-"],
+                         stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"hipcc -S failed on {src}")
+    bad = lint_asm_hazards(res.stdout)
     if bad:
-        raise RuntimeError(f"{src}: staging loads read scalar registers too soon after a vector write: {bad[:5]}")
+        raise RuntimeError(f"{src}: wait-state hazards: {bad[:5]}")
 
 
 def build_library(jobs: int = 7) -> str:

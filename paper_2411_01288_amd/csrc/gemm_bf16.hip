@@ -167,6 +167,18 @@ __device__ __forceinline__ void dtl_load(rsrc_t r, uint32_t voff, uint32_t soff)
                  : "memory");
 }
 
+// A 16-byte-per-lane store to (voff + soff) of a buffer resource.  The hardware fetches the data of a
+// store of more than 8 bytes over the cycles behind its issue: a vector instruction that overwrites one of
+// its data registers within two wait states changes what is stored.  The compiler leaves that gap only
+// where the scalar offset is no register, which is not enough on gfx950: with two wavefronts on a SIMD the
+// first word of a 16-byte chunk was lost here and there.  So the gap is part of the statement.
+__device__ __forceinline__ void buf_store16(u32x4 data, rsrc_t r, int voff, int soff) {
+    asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen\n\ts_nop 1"
+                 :
+                 : "v"(data), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff))
+                 : "memory");
+}
+
 // K-contiguous operand (R rows x BK k, ROWB bytes per row in memory order along k).
 // Instruction q (= wave + NW*i) fills RPQ = 1024/ROWB rows: lane l -> row RPQ*q + l/CPRK,
 // position l%CPRK.
@@ -846,22 +858,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         constexpr int RPI_O = 1024 / RPB;            // rows per store instruction
         constexpr int NST = BAND / RPI_O;            // store instructions per band and output
         const int mv_w = min(TM, mvalid - wrow0), nv_w = min(TN, nvalid - wcol0);
-        const int obytes = __builtin_amdgcn_readfirstlane(
-            (mv_w > 0 && nv_w > 0) ? ((mv_w - 1) * (int)ldo + nv_w) * ESZ : 0);
+        const int obytes = (mv_w > 0 && nv_w > 0) ? ((mv_w - 1) * (int)ldo + nv_w) * ESZ : 0;
         const size_t o0 = ((size_t)(m0 + wrow0) * ldo + (size_t)(n0 + wcol0)) * ESZ;
-        // (wave-uniform, but derived from the wave number: say so, or every store is wrapped in a loop
-        // over the distinct resources of the lanes)
-        auto uniform_ptr = [](uint8_t* p_) {
-            const uint64_t b = (uint64_t)p_;
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-            return (uint8_t*)(((uint64_t)hi << 32) | lo);
-        };
         uint8_t* obase0 = TOKENS ? reinterpret_cast<uint8_t*>(tok_out) : reinterpret_cast<uint8_t*>(g.out0);
-        const __amdgpu_buffer_rsrc_t ro0 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(obase0 + o0), 0, obytes, 0x00020000);
-        __amdgpu_buffer_rsrc_t ro1 = ro0;
-        if constexpr (OP == OP_FC1)
-            ro1 = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(reinterpret_cast<uint8_t*>(g.out1) + o0), 0, obytes, 0x00020000);
+        const rsrc_t ro0 = make_rsrc(obase0 + o0, (uint32_t)obytes);
+        rsrc_t ro1 = ro0;
+        if constexpr (OP == OP_FC1) ro1 = make_rsrc(reinterpret_cast<uint8_t*>(g.out1) + o0, (uint32_t)obytes);
         const int ldo_b = __builtin_amdgcn_readfirstlane((int)ldo * ESZ);   // bytes per output row
         int ovoff[NST];
         {
@@ -902,8 +904,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         };
         auto band_store_one = [&](int i, int t) __attribute__((always_inline)) {
             const int soff = (i * BAND + RPI_O * t) * ldo_b;
-            __builtin_amdgcn_raw_buffer_store_b128(d0[t], ro0, ovoff[t], soff, 0);
-            if constexpr (OP == OP_FC1) __builtin_amdgcn_raw_buffer_store_b128(d1[t], ro1, ovoff[t], soff, 0);
+            buf_store16(d0[t], ro0, ovoff[t], soff);
+            if constexpr (OP == OP_FC1) buf_store16(d1[t], ro1, ovoff[t], soff);
         };
         auto band_stores = [&](int i, bool with_stores) __attribute__((always_inline)) {
             if (with_stores) {
