@@ -56,9 +56,9 @@ MoeWorkspace layout(const MoeDims& D, int dtype, void* base) {
     w.dout = take(A * d * es);
     w.dpre = take(A * f * es);
     w.dxp = take(A * d * es);
-    {   // column-sum staging: the prologue's tiles, or (bf16) two partial rows per 256-row GEMM tile
+    {   // column-sum staging: the prologue's tiles, or (16-bit) the partial rows of the DGRAD2 tiles
         size_t rows = colsum_partial_rows(D);
-        const size_t rows_gemm = A / 128 + 2 * (size_t)D.E;
+        const size_t rows_gemm = (A / (size_t)gemm_dgrad2_row_tile(D) + (size_t)D.E) * (size_t)gemm_colpart_rows_per_tile();
         if (rows < rows_gemm) rows = rows_gemm;
         w.colpart = (float*)take(rows * (d > f ? d : f) * 4);
     }

@@ -140,7 +140,7 @@ struct MoeWorkspace {
     size_t total_bytes;
 };
 
-int gemm_row_tile();                 // rows of a bf16 row-GEMM tile
+int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path
 int gemm_colpart_rows_per_tile();    // DGRAD2 writes this many column-sum partial rows per row tile
 int wgrad_chunk_len(const MoeDims& D);          // tokens per split-K chunk (host policy)
 size_t wgrad_max_slots(const MoeDims& D);

@@ -14,8 +14,8 @@
 // What is kept from the paper: rows of a tile all belong to one expert, so a tile needs one
 // expert's weights; rows are addressed through the re-index vector, so nothing is padded to a
 // capacity and nothing is dropped.  What is not: the 16x16x16 warp tiles, the per-expert serial
-// loop of Alg. 4 and the padded (-1) re-index vector.  Here a workgroup owns a 256x256 tile,
-// each 64-lane wavefront a grid of 16x16x32 bf16 MFMA blocks, operands go from
+// loop of Alg. 4 and the padded (-1) re-index vector.  Here a workgroup owns a 256x256 or (small
+// problems) a 128x128 tile, each 64-lane wavefront a grid of 16x16x32 bf16 MFMA blocks, operands go from
 // global memory straight into LDS (no registers in between) as [row][64 k] with a 16-byte XOR
 // swizzle (conflict-free 128-bit reads); operands whose contraction index is the slow one in
 // memory (weights in the forward GEMMs, both operands of the token contractions) keep their
@@ -23,6 +23,7 @@
 // individually (ragged tails are masked, not padded), long segments of the token contractions
 // are split into chunks whose partial tiles are reduced in a fixed order, and workgroup ids are
 // remapped so that the 32 CUs of one XCD work on neighbouring tiles.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -38,7 +39,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int BK = 64;            // contraction elements per block of the K loop (one 128-byte line per row)
 constexpr int NSLOT = 5;          // LDS ring: five slots, each holds one operand's share of a block
 constexpr int kXcds = 8;         // workgroup i is dispatched to XCD i % 8
-constexpr int kGroupM = 4;       // row tiles per L2-sharing group
+constexpr int group_rows(int bm) { return 1024 / bm; }   // row tiles per L2-sharing group: 1024 rows' worth
 constexpr int kSplitBelow = 128; // row GEMMs with fewer groups cut their last ngroups % 8 groups across the XCDs
 
 enum Op { OP_FC1 = 0, OP_FC2, OP_DGRAD2, OP_DGRAD1, OP_WGRAD2, OP_WGRAD1 };
@@ -59,8 +60,10 @@ struct GemmArgs {
     int topk, E, K, N, M;
     int a_rows;           // FC1: rows of the gathered operand (tokens T)
     int chunk_len;        // token contraction: max tokens per work item
-    const int32_t* worklist;  // see build_worklists
-    int rt_cap;           // row-tile capacity of the work list
+    const int32_t* row_tiles; // row GEMM: its row tiles and their number (see build_worklists)
+    const int32_t* n_row_tiles;
+    const int32_t* items;     // token contraction: its items and their number
+    const int32_t* n_items;
 };
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -223,17 +226,19 @@ struct StageKS {
     static constexpr int CPR = RB / 16;         // chunks per k-row
     static constexpr int RPI = 1024 / RB;       // k-rows per instruction
     static constexpr int NI = BK / RPI / NW;    // instructions per wave and block
-    static_assert(RPI >= 1 && (BK / RPI) % NW == 0 && RPI * NW == 8 && CPR >= 16, "unsupported staging shape");
-    // instruction i of a wave covers k-rows RPI*wave + kin + 8 i: (k & 3) is the same for all i and
-    // ((k >> 3) & 1) = i & 1, so a lane needs two offsets (even and odd i)
-    struct Lane { uint32_t voff[2]; };
+    static constexpr int STEP = RPI * NW;       // k-rows from one instruction of a wave to its next one
+    static_assert(RPI >= 1 && (BK / RPI) % NW == 0 && (STEP == 8 || STEP == 16) && CPR >= 16, "unsupported staging shape");
+    // instruction i of a wave covers k-rows RPI*wave + kin + STEP i: (k & 3) is the same for all i and
+    // ((k >> 3) & 1) too (STEP 16) or i & 1 (STEP 8), so a lane needs one offset or two (even and odd i)
+    static constexpr int NV = STEP == 8 ? 2 : 1;
+    struct Lane { uint32_t voff[NV]; };
     // (row_bytes = 0 when the k-rows are gathered: the row part of the offset then comes from a table)
     __device__ static __forceinline__ Lane lane_init(int wave, int lane, uint32_t row_bytes, int col0) {
         const int kin = lane / CPR;                          // k-row inside the instruction
-        const int k = (RPI * wave + kin);                    // k-row of instruction i = 0  (< 8)
+        const int k = (RPI * wave + kin);                    // k-row of instruction i = 0  (< STEP)
         Lane ln;
 #pragma unroll
-        for (int odd = 0; odd < 2; ++odd) {
+        for (int odd = 0; odd < NV; ++odd) {
             const int c = (lane % CPR) ^ ks_key(k + 8 * odd);
             ln.voff[odd] = (uint32_t)k * row_bytes + (uint32_t)(col0 + 8 * c) * 2u;
         }
@@ -241,13 +246,13 @@ struct StageKS {
     }
     // gathered k-rows: instruction i fetches the rows whose byte offsets are roff[i] (per lane)
     __device__ static __forceinline__ void load_gathered(rsrc_t r, const uint32_t (&roff)[NI], const Lane& ln, int i) {
-        dtl_load(r, roff[i] + ln.voff[i & 1], 0u);
+        dtl_load(r, roff[i] + ln.voff[i % NV], 0u);
     }
     __device__ static __forceinline__ void prep(uint32_t lds_slot, int wave, int i) {
         dtl_m0(lds_slot + (uint32_t)(wave + NW * i) * 1024u);
     }
     __device__ static __forceinline__ void load(rsrc_t r, uint32_t soff, uint32_t ld_bytes, const Lane& ln, int i) {
-        dtl_load(r, ln.voff[i & 1], soff + (uint32_t)(RPI * NW * i) * ld_bytes);
+        dtl_load(r, ln.voff[i % NV], soff + (uint32_t)(STEP * i) * ld_bytes);
     }
 };
 
@@ -255,12 +260,13 @@ struct StageKS {
 // Work decomposition
 // ---------------------------------------------------------------------------------------------
 
-// Inside one set of tm x tn tiles: groups of kGroupM row tiles, row tile fastest inside a group.
+// Inside one set of tm x tn tiles: groups of GM row tiles, row tile fastest inside a group.
+template <int GM>
 __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& tile_m, int& tile_n) {
-    const int per_group = kGroupM * tn;
+    const int per_group = GM * tn;
     const int group = local / per_group;
-    const int first = group * kGroupM;
-    const int gsz = min(kGroupM, tm - first);
+    const int first = group * GM;
+    const int gsz = min(GM, tm - first);
     const int in = local - group * per_group;
     tile_m = first + in % gsz;
     tile_n = in / gsz;
@@ -270,67 +276,104 @@ __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& til
 // lists: they are part of what the forward pass leaves in the workspace), so that a
 // workgroup finds its tile with two scalar loads instead of a walk over all experts (which cost a
 // 256x256 tile of a d = 2048 contraction about a tenth of its time, with the CU idle meanwhile).
-//   wl[0] = number of row tiles, wl[1] = number of token-contraction items,
-//   wl[2], wl[3] = 1 when the fused backward grid of the second / first linear layer starts with
-//                  its token contraction (see gemm_bf16_pair), else 0
-//   wl[4 + 4 t ...]            row tile t:  expert, first perm row, rows (1..bm), unused
-//   wl[4 + 4 rt_cap + 4 i ...] item i:      expert, first perm row, end perm row, split-K slot
+//   header (kWlHeader ints): number of 256-row tiles, of 128-row tiles, of token-contraction items;
+//       then 1 or 0: the fused backward grid of the second / first linear layer starts with its
+//       token contraction (see gemm_bf16_pair)
+//   row tiles of 256 rows, of 128 rows, four ints each:  expert, first perm row, rows, unused
+//   items, four ints each:                               expert, first perm row, end perm row, split-K slot
 // Row tiles are numbered expert-major (tiles never straddle experts; experts without rows have
 // none).  Items are numbered expert-major then chunk: item i covers at most L rows of one expert;
 // slot >= 0 numbers the partial tile buffer of an expert that was cut into several chunks, -1
 // means the expert is one chunk and its tile goes straight to the output.
+enum WlHeader { WL_TILES256 = 0, WL_TILES128, WL_ITEMS, WL_ORDER2, WL_ORDER1 };
+constexpr int kWlHeader = 8;
+
 __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restrict__ offsets, int E,
-                                                        int bm, int L, int32_t* __restrict__ wl,
-                                                        int rt_cap, int d, int f) {
-    __shared__ int s_t[1024], s_c[1024], s_s[1024];
-    const int e = threadIdx.x;
-    int b = 0, n = 0, nt = 0, nc = 0, ns = 0;
-    if (e < E) {
-        b = offsets[e]; n = offsets[e + 1] - b;
-        nt = ceil_div(n, bm); nc = ceil_div(n, L); ns = nc > 1 ? nc : 0;
+                                                        int L, int32_t* __restrict__ wl,
+                                                        int rt_cap256, int rt_cap128, int d, int f) {
+    constexpr int NQ = 4;                      // 256-row tiles, 128-row tiles, items, split-K slots
+    __shared__ int s_end[NQ][1024];            // inclusive sums over the experts
+    __shared__ int s_off[1025];
+    __shared__ int s_wave[NQ + 1][16];
+    const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
+    int n = 0, b = 0;
+    if (e < E) { b = offsets[e]; n = offsets[e + 1] - b; }
+    const int nc = ceil_div(n, L);
+    int v[NQ] = {ceil_div(n, 256), ceil_div(n, 128), nc, nc > 1 ? nc : 0};
+    int longest = min(L, n);
+    s_off[e] = b;
+    if (e == E - 1) s_off[E] = b + n;
+    // inclusive scans: inside each wavefront by shuffles, the wavefronts' sums through LDS
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int u = __shfl_up(v[q], off);
+            if (lane >= off) v[q] += u;
+        }
+        longest = max(longest, __shfl_xor(longest, off));
     }
-    s_t[e] = nt; s_c[e] = nc; s_s[e] = ns;
+    if (lane == 63) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) s_wave[q][wave] = v[q];
+        s_wave[NQ][wave] = longest;
+    }
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {      // inclusive scans
-        int vt = 0, vc = 0, vs = 0;
-        if (e >= off) { vt = s_t[e - off]; vc = s_c[e - off]; vs = s_s[e - off]; }
-        __syncthreads();
-        s_t[e] += vt; s_c[e] += vc; s_s[e] += vs;
-        __syncthreads();
+    for (int w = 0; w < wave; ++w)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q] += s_wave[q][w];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) s_end[q][e] = v[q];
+    __syncthreads();
+    // the expert that holds number i: the first one whose inclusive sum exceeds i
+    auto find = [&](int q, int i) {
+        int lo = 0, hi = E - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_end[q][mid] > i) hi = mid; else lo = mid + 1;
+        }
+        return lo;
+    };
+    int4* tiles256 = reinterpret_cast<int4*>(wl + kWlHeader);
+    int4* tiles128 = tiles256 + rt_cap256;
+    int4* items = tiles128 + rt_cap128;
+    for (int q = 0; q < 2; ++q) {
+        const int bm = q == 0 ? 256 : 128;
+        int4* dst = q == 0 ? tiles256 : tiles128;
+        for (int i = e; i < s_end[q][E - 1]; i += 1024) {
+            const int x = find(q, i);
+            const int r0 = (i - (x > 0 ? s_end[q][x - 1] : 0)) * bm;
+            dst[i] = make_int4(x, s_off[x] + r0, min(bm, s_off[x + 1] - s_off[x] - r0), 0);
+        }
     }
-    if (e >= E) return;
-    int t0 = s_t[e] - nt, c0 = s_c[e] - nc, slot0 = s_s[e] - ns;
-    for (int i = 0; i < nt; ++i) {
-        int32_t* q = wl + 4 + 4 * (t0 + i);
-        q[0] = e; q[1] = b + i * bm; q[2] = min(bm, n - i * bm); q[3] = 0;
+    for (int i = e; i < s_end[2][E - 1]; i += 1024) {
+        const int x = find(2, i);
+        const int first = x > 0 ? s_end[2][x - 1] : 0, c = i - first;
+        const int slot = s_end[2][x] - first > 1 ? (x > 0 ? s_end[3][x - 1] : 0) + c : -1;
+        items[i] = make_int4(x, s_off[x] + c * L, min(s_off[x + 1], s_off[x] + c * L + L), slot);
     }
-    int32_t* items = wl + 4 + 4 * rt_cap;
-    for (int c = 0; c < nc; ++c) {
-        int32_t* q = items + 4 * (c0 + c);
-        q[0] = e; q[1] = b + c * L; q[2] = min(b + n, b + c * L + L); q[3] = nc > 1 ? slot0 + c : -1;
-    }
-    if (e == E - 1) {
+    if (e == 0) {
         // the longest token-contraction item, in rows; a fused backward grid starts with the token
         // contraction when that item runs at least eight times as long as a tile of the row GEMM it
         // shares the grid with (K = d for the second layer's, K = f for the first layer's)
-        int longest = 0;
-        for (int q = 0; q < E; ++q) longest = max(longest, min(L, offsets[q + 1] - offsets[q]));
-        wl[0] = s_t[e]; wl[1] = s_c[e];
-        wl[2] = longest >= 8 * d ? 1 : 0;
-        wl[3] = longest >= 8 * f ? 1 : 0;
+        for (int w = 1; w < 16; ++w) longest = max(longest, s_wave[NQ][w]);
+        wl[WL_TILES256] = s_end[0][E - 1]; wl[WL_TILES128] = s_end[1][E - 1]; wl[WL_ITEMS] = s_end[2][E - 1];
+        wl[WL_ORDER2] = longest >= 8 * d ? 1 : 0;
+        wl[WL_ORDER1] = longest >= 8 * f ? 1 : 0;
     }
 }
 
 // Row-offset table of the gathered token contraction (WGRAD1 reads x[perm[p] / k] for perm
 // position p; ESTMM, App. B Alg. 4, takes its tokens through the re-index vector the same way).
 // Expert e's part starts at entry offsets[e] + 64 e and is cut into blocks of 64 rows (the K-blocks
-// of the contraction; a chunk starts on a block boundary); inside a block, entry 8 j + i belongs
-// to row 8 i + j, the transposed order in which a lane of the staging instructions needs them.
+// of the contraction; a chunk starts on a block boundary); inside a block, entry (64/step) j + i
+// belongs to row step i + j, the transposed order in which a lane of the staging instructions (StageKS,
+// step = its STEP) needs them.
 // An entry is the byte offset of the token's row in x; entries past the segment's end hold `pad`,
 // an offset behind the last row of x, which the buffer range check turns into zeros.
 __global__ __launch_bounds__(256) void build_rowoff(const int32_t* __restrict__ offsets,
                                                     const int32_t* __restrict__ perm, int E, int k,
-                                                    uint32_t row_bytes, uint32_t pad, int total,
+                                                    uint32_t row_bytes, uint32_t pad, int total, int step,
                                                     uint32_t* __restrict__ out) {
     const int g = blockIdx.x * 256 + threadIdx.x;
     if (g >= total) return;
@@ -342,7 +385,8 @@ __global__ __launch_bounds__(256) void build_rowoff(const int32_t* __restrict__ 
     const int b = offsets[lo], n = offsets[lo + 1] - b;
     const int local = g - (b + 64 * lo);
     const int s = local & 63;
-    const int r = (local & ~63) + 8 * (s & 7) + (s >> 3);
+    const int per = 64 / step;
+    const int r = (local & ~63) + step * (s % per) + s / per;
     out[g] = r < n ? (uint32_t)(perm[b + r] / k) * row_bytes : pad;
 }
 
@@ -360,6 +404,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     constexpr bool A_GK = (OP == OP_WGRAD1);   // operand A's k-rows (tokens) are gathered rows of x
     constexpr int SLOT = (BM > BN ? BM : BN) * ROWB;   // bytes of one ring slot (one operand, one block)
     constexpr int SPS = BK / 32;              // k-substeps (one MFMA k = 32 each) per block
+    constexpr int GM = group_rows(BM);
     static_assert(TM % 16 == 0 && TN % 16 == 0, "wave tile must be a multiple of 16x16");
 
     extern __shared__ __align__(1024) uint8_t smem[];   // the slot ring; reused by the epilogue
@@ -375,15 +420,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     int kbeg = 0, kend = 0;           // token contraction: perm rows of this item
     float* tok_out = nullptr;         // token contraction: where the tile goes
     if constexpr (!TOKENS) {
-        const int tm_total = g.worklist[0];
+        const int tm_total = *g.n_row_tiles;
         const int tn = ceil_div(g.N, BN);
         int tile_m, tile_n;
-        {   // groups of kGroupM row tiles x all column tiles are dealt round-robin to the XCDs, so
+        {   // groups of GM row tiles x all column tiles are dealt round-robin to the XCDs, so
             // the 8 XCDs work on neighbouring row tiles (mostly one expert) at any time; the last
             // ngroups % 8 groups are cut in eight instead, every XCD taking an eighth of each, so
             // that no XCD is a whole group behind the others at the end
-            const int per_group = kGroupM * tn;
-            const int ngroups = ceil_div(tm_total, kGroupM);
+            const int per_group = GM * tn;
+            const int ngroups = ceil_div(tm_total, GM);
             const int xcd = item % kXcds, loc = item / kXcds;
             // rounds of eight whole groups; with many groups the last, partial round is dealt whole
             // as well (an XCD's CUs finish their tiles one tile-time apart either way, and whole
@@ -400,18 +445,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
                 const int l2 = loc - whole * per_group;
                 group = whole * kXcds + l2 / per8;
                 if (group >= ngroups) return;
-                const int gtiles = min(kGroupM, tm_total - group * kGroupM) * tn;
+                const int gtiles = min(GM, tm_total - group * GM) * tn;
                 share = ceil_div(gtiles, kXcds);          // this XCD's tiles of the group
                 if (l2 % per8 >= share) return;
                 within = xcd * share + l2 % per8;
             }
-            const int first = group * kGroupM;
-            const int gsz = min(kGroupM, tm_total - first);
+            const int first = group * GM;
+            const int gsz = min(GM, tm_total - first);
             if (within >= gsz * tn) return;
             tile_m = first + within % gsz;
             tile_n = within / gsz;
         }
-        const i32x4 rt = *reinterpret_cast<const i32x4*>(g.worklist + 4 + 4 * tile_m);
+        const i32x4 rt = *reinterpret_cast<const i32x4*>(g.row_tiles + 4 * tile_m);
         e = rt.x; m0 = rt.y; mvalid = rt.z; n0 = tile_n * BN; row_tile = tile_m;
         nk = g.K / BK;
     } else {
@@ -424,10 +469,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         const int xcd = item % kXcds, loc = item / kXcds;
         const int tile = xcd * per + loc % per;
         if (tile >= tmn) return;
-        if (loc / per >= g.worklist[1]) return;
-        const i32x4 it = *reinterpret_cast<const i32x4*>(g.worklist + 4 + 4 * g.rt_cap + 4 * (loc / per));
+        if (loc / per >= *g.n_items) return;
+        const i32x4 it = *reinterpret_cast<const i32x4*>(g.items + 4 * (loc / per));
         int tile_m, tile_n;
-        grouped_tile(tile, tm, tn, tile_m, tile_n);
+        grouped_tile<GM>(tile, tm, tn, tile_m, tile_n);
         e = it.x; m0 = tile_m * BM; n0 = tile_n * BN; mvalid = min(BM, g.M - m0);
         kbeg = it.y; kend = it.z;
         nk = ceil_div(kend - kbeg, BK);
@@ -526,14 +571,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     constexpr int A_RB = BM * 2, B_RB = BN * 2;  // LDS k-row pitch of the K-strided images
     // KC: aoff[sub] = byte offset of this lane's chunk in block row 0.
     // KS: one lane constant a_l0: k-row part | within-chunk byte | (chunk of block 0 ^ key) << 4.
-    // Block q's chunk index differs from block 0's in bits 1..3 only (2q), the bits the key works
-    // on, so its offset is a_l0 ^ (q << 5); the k-row of (substep, half) is an immediate.
+    // Block q's chunk index differs from block 0's in the bits of 2q only (the wave tile's first chunk is a
+    // multiple of the 2 FM or 2 FN chunks of a wave tile), so its offset is a_l0 ^ (q << 5); the k-row of (substep, half) is an immediate.
     uint32_t aoff[SPS], boff[SPS];
     uint32_t a_l0 = 0, b_l0 = 0;
     {
         const int krel = l16 >> 2, pair = (l16 & 3) >> 1, half8 = (l16 & 1) * 8;
         const int key = ks_key(8 * grp + krel);  // the key of every k-row this lane reads
-        static_assert(A_RB % 512 == 0 && B_RB % 512 == 0 && TM % 128 == 0 && TN % 128 == 0, "bit fields of the K-strided fragment offset");
+        static_assert(A_RB % 256 == 0 && B_RB % 256 == 0 && TM % 64 == 0 && TN % 64 == 0 && TM / 8 >= 2 * FM && TN / 8 >= 2 * FN,
+                      "bit fields of the K-strided fragment offset");
         if constexpr (TOKENS) {
             a_l0 = (uint32_t)((8 * grp + krel) * A_RB + half8 + ((((wm * TM) / 8 + pair) ^ key) << 4));
         } else {
@@ -597,20 +643,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // (where the compiler merges its counters), and an LDS read issued just before would be waited
     // for in full.
     constexpr int RSPAN = NM * 3 / 4;
-    static_assert(FM == 8 && FN == 8 && NRD <= RSPAN, "the issue slots are laid out for an 8 x 8 block grid");
+    static_assert((FM == 8 && FN == 8 && NRD <= RSPAN) || (FM == 4 && FN == 4), "issue slots");
     static_assert(SPS == 2, "the schedule below is written for two k-substeps per block");
     constexpr int NIA = SA::NI, NIB = SB::NI;    // staging instructions per wave, operand and block
-    static_assert(NIA == 8 && NIB == 8, "one staging request per eight MFMAs");
+    static_assert(NIA == NIB && NM % NIA == 0 && NM / NIA >= 4, "one staging request per NM / NIA MFMAs");
+    constexpr int SGAP = NM / NIA;               // MFMAs per staging request
     // A 16-cycle MFMA leaves the wave three more issue cycles, so no memory slot may hold more than
     // three instructions: fragment reads are spread evenly over the first three quarters, staging request o sits in the slots
-    // 8 o + 1 (M0 set-up) and 8 o + 3 (load; the MFMA in between is the wait state M0 needs).
+    // SGAP o + 1 (M0 set-up) and SGAP o + 3 (load; the MFMA in between is the wait state M0 needs).
     // Operand A's requests go into substep 0, operand B's follow the block barrier in substep 1:
     // every wave has waited for its own fragment reads of the slot that is refilled (lgkmcnt) before
     // that barrier.
 #define STAGE_AT(m_, PREP_, LOAD_, slot_, kt_)                                                   \
     do {                                                                                         \
-        if ((m_) % 8 == 1) PREP_(slot_, (m_) / 8);                                               \
-        if ((m_) % 8 == 3) LOAD_(kt_, (m_) / 8);                                                 \
+        if ((m_) % SGAP == 1) PREP_(slot_, (m_) / SGAP);                                         \
+        if ((m_) % SGAP == 3) LOAD_(kt_, (m_) / SGAP);                                           \
     } while (0)
     // The MFMA gets the B fragment as its first and the A fragment as its second operand (both
     // have the same lane layout), so each 16x16 block comes out transposed: a lane then holds ONE
@@ -621,7 +668,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // One k-substep: NM MFMAs on fragment set (fa, fb); after MFMA m, memory slot m is issued
     // (at most one fragment read for the next substep or one half of a staging request), so the
     // LDS and vector-memory queues are fed a little at a time while the matrix pipe stays busy:
-    // one wavefront per SIMD has nobody else to hide a burst behind.
+    // one wavefront per SIMD (256x256 tiles) has nobody else to hide a burst behind.
 #define SUBSTEP(fa, fb, READ_, EXTRA_)                                                           \
     do {                                                                                         \
         _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                         \
@@ -642,8 +689,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
 
     // The K loop runs in blocks of BK = 64 (two k-substeps): a row of a K-contiguous operand is
     // then one whole 128-byte line per block, and the texture-address path, which pays per line
-    // touched, moves twice the bytes it would with 32-k stages.  One block of one operand (32 KB)
-    // is a ring slot; the five slots of the 160 KB LDS hold, in request order,
+    // touched, moves twice the bytes it would with 32-k stages.  One block of one operand (32 KB
+    // of a 256-wide tile, 16 KB of a 128-wide one) is a ring slot; the five slots (all or half of the
+    // 160 KB LDS) hold, in request order,
     //     A(j) B(j) | A(j+1) B(j+1) A(j+2)       block j being multiplied | requested ahead
     // i.e. half-block h (A(j): h = 2j, B(j): h = 2j+1) lives in slot h % 5.
     // During block j: substep 0 requests A(j+2) into the slot B(j-1) left; before substep 1 the
@@ -665,22 +713,26 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // staging requests (own counting of vmcnt).  Their results are tied to the wait statement, so
     // nothing can read them in front of it, and they do not live across the loop's back edge, where
     // the compiler would copy them (before they have arrived).
-    uint32_t rcur[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+    constexpr int RO = SA::NI;         // row offsets per lane and block
+    uint32_t rcur[RO] = {};
     const uint32_t* rbase = nullptr;   // this item's first table entry (wave-uniform)
-    const uint32_t rl_off = (uint32_t)(8 * (2 * uwave + (lane >> 5))) * 4u;   // this lane's eight entries of a block
+    uint32_t rl_off = 0;               // this lane's entries of a block
+    if constexpr (A_GK) rl_off = (uint32_t)(RO * (SA::RPI * uwave + lane / SA::CPR)) * 4u;
     auto roff_request = [&](int kt, u32x4& lo, u32x4& hi) __attribute__((always_inline)) {
         const uint32_t* p_ = rbase + (size_t)64 * kt;   // scalar base + lane offset: no vector arithmetic per block
-        asm volatile("global_load_dwordx4 %0, %2, %3\n\tglobal_load_dwordx4 %1, %2, %3 offset:16"
-                     : "=&v"(lo), "=&v"(hi) : "v"(rl_off), "s"(p_) : "memory");
+        if constexpr (RO == 8)
+            asm volatile("global_load_dwordx4 %0, %2, %3\n\tglobal_load_dwordx4 %1, %2, %3 offset:16"
+                         : "=&v"(lo), "=&v"(hi) : "v"(rl_off), "s"(p_) : "memory");
+        else
+            asm volatile("global_load_dwordx4 %0, %1, %2" : "=&v"(lo) : "v"(rl_off), "s"(p_) : "memory");
     };
-#define ROFF_TAKE(lo_, hi_)                                                                       \
+#define ROFF_TAKE(to_, lo_, hi_)                                                                  \
     do {                                                                                          \
-        rcur[0] = (lo_)[0]; rcur[1] = (lo_)[1]; rcur[2] = (lo_)[2]; rcur[3] = (lo_)[3];           \
-        rcur[4] = (hi_)[0]; rcur[5] = (hi_)[1]; rcur[6] = (hi_)[2]; rcur[7] = (hi_)[3];           \
+        _Pragma("unroll") for (int q_ = 0; q_ < RO; ++q_) to_[q_] = q_ < 4 ? (lo_)[q_] : (hi_)[q_ - 4]; \
     } while (0)
     {
         const uint32_t k1 = (uint32_t)min(1, klast);
-        u32x4 r0_lo, r0_hi, r1_lo, r1_hi, r2_lo, r2_hi;
+        u32x4 r0_lo = {}, r0_hi = {}, r1_lo = {}, r1_hi = {}, r2_lo = {}, r2_hi = {};
         if constexpr (A_GK) {
             rbase = g.rowoff + (size_t)kbeg + (size_t)64 * e;
             roff_request(0, r0_lo, r0_hi);
@@ -688,14 +740,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
             roff_request(min(2, klast), r2_lo, r2_hi);
             asm volatile("s_waitcnt vmcnt(0)"
                          : "+v"(r0_lo), "+v"(r0_hi), "+v"(r1_lo), "+v"(r1_hi), "+v"(r2_lo), "+v"(r2_hi) : : "memory");
-            ROFF_TAKE(r0_lo, r0_hi);
+            ROFF_TAKE(rcur, r0_lo, r0_hi);
         }
         _Pragma("unroll") for (int o = 0; o < NIA; ++o) { PREP_A(smem0 + 0 * SLOT, o); asm volatile("s_nop 0"); LOAD_A(0u, o); }
         _Pragma("unroll") for (int o = 0; o < NIB; ++o) { PREP_B(smem0 + 1 * SLOT, o); asm volatile("s_nop 0"); LOAD_B(0u, o); }
-        if constexpr (A_GK) ROFF_TAKE(r1_lo, r1_hi);
+        if constexpr (A_GK) ROFF_TAKE(rcur, r1_lo, r1_hi);
         _Pragma("unroll") for (int o = 0; o < NIA; ++o) { PREP_A(smem0 + 2 * SLOT, o); asm volatile("s_nop 0"); LOAD_A(k1, o); }
         _Pragma("unroll") for (int o = 0; o < NIB; ++o) { PREP_B(smem0 + 3 * SLOT, o); asm volatile("s_nop 0"); LOAD_B(k1, o); }
-        if constexpr (A_GK) ROFF_TAKE(r2_lo, r2_hi);
+        if constexpr (A_GK) ROFF_TAKE(rcur, r2_lo, r2_hi);
     }
     // The accumulators are cleared here, between the first requests and the wait for them: claimed
     // in their accumulation registers by the empty statements (which keep their place among the
@@ -735,7 +787,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
             __syncthreads();   // the barrier in front of the other waves' epilogue
             if constexpr (OP == OP_DGRAD2) {   // this wave's column-sum partials: no rows, zeros
                 const int col = wn * TN + 2 * lane;
-                if (col < nvalid)
+                if (2 * lane < TN && col < nvalid)
                     *reinterpret_cast<float2*>(g.colpart + (size_t)(row_tile * WM + wm) * (size_t)g.N + n0 + col) =
                         make_float2(0.f, 0.f);
             }
@@ -755,15 +807,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         const uint32_t a2 = smem0 + (uint32_t)(sa2 * SLOT);   // A(j+2): the slot of B(j-1)
         const uint32_t b2 = smem0 + (uint32_t)(sa * SLOT);    // B(j+2): the slot of A(j)
         const uint32_t kreq = (uint32_t)min(j + 2, klast);
-        u32x4 rn_lo, rn_hi;
-        uint32_t rnx[8];   // the same eight values once they have arrived
+        u32x4 rn_lo = {}, rn_hi = {};
+        uint32_t rnx[RO];   // the same values once they have arrived
         if constexpr (A_GK) roff_request(min(j + 3, klast), rn_lo, rn_hi);
         FENCE();
         SUBSTEP(fa0, fb0, READ_ONE(fa1, fb1, abase, bbase, 1, r), STAGE_AT(m, PREP_A, LOAD_A, a2, kreq));
         if constexpr (A_GK) {
             asm volatile("s_waitcnt vmcnt(%2)" : "+v"(rn_lo), "+v"(rn_hi) : "n"(NIA) : "memory");
-            rnx[0] = rn_lo[0]; rnx[1] = rn_lo[1]; rnx[2] = rn_lo[2]; rnx[3] = rn_lo[3];
-            rnx[4] = rn_hi[0]; rnx[5] = rn_hi[1]; rnx[6] = rn_hi[2]; rnx[7] = rn_hi[3];
+            ROFF_TAKE(rnx, rn_lo, rn_hi);
         } else {
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIA) : "memory");
         }
@@ -775,8 +826,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
 #define TAKE_AT(m_)                                                                               \
     do {                                                                                          \
         if constexpr (A_GK) {                                                                     \
-            if ((m_) % 8 == 5)                                                                    \
-                asm volatile("v_mov_b32 %0, %1" : "=v"(rcur[(m_) / 8]) : "v"(rnx[(m_) / 8]));     \
+            if ((m_) % SGAP == (SGAP == 8 ? 5 : 2))                                                \
+                asm volatile("v_mov_b32 %0, %1" : "=v"(rcur[(m_) / SGAP]) : "v"(rnx[(m_) / SGAP])); \
         }                                                                                         \
     } while (0)
         SUBSTEP(fa1, fb1, READ_ONE(fa0, fb0, anext, bnext, 0, r), STAGE_AT(m, PREP_B, LOAD_B, b2, kreq); TAKE_AT(m));
@@ -810,41 +861,43 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // ---- epilogue ------------------------------------------------------------------------------
     // In block (i, j) a lane holds row i*16 + l16 and the four columns j*16 + 4*grp + 0..3.  Stored
     // from there, a wave instruction would touch 16 rows with 8 or 16 bytes each.  Instead each
-    // wave turns one 16-row band (i) at a time through its own 32 KB of the (now idle) ring:
+    // wave turns one 16-row band (i) at a time through its own part of the (now idle) ring:
     // vectors are written at [row][chunk ^ row] (16-byte chunks, so both directions are
     // conflict-free), read back with a lane per 16-byte chunk of a row, and leave as full 256- or
     // 512-byte row segments.  DGRAD2's saved activation derivatives come in the same way, staged
     // one band ahead.
     __syncthreads();   // every wave is done reading fragments
     {
-        uint8_t* wreg = smem + uwave * 32768;
+        uint8_t* wreg = smem + uwave * (TN * 256);
         constexpr bool OUT_F32 = TOKENS;   // weight gradients; every activation-like output is 16-bit
         constexpr int ESZ = OUT_F32 ? 4 : 2;
         constexpr int RPB = TN * ESZ;                 // bytes per staged row (TN columns)
         constexpr int CPRO = RPB / 16;                // 16-byte chunks per staged row
         constexpr int BAND = 16;                      // rows per band = rows of an MFMA block
         constexpr int H_OFF = BAND * RPB;             // FC1: second output of a band, behind the first
-        constexpr int G_OFF = 16384, G_BUF = BAND * 256;   // DGRAD2: two bands of saved derivatives
-        static_assert(TN == 128, "epilogue staging is laid out for 128-column wave tiles");
+        constexpr int G_OFF = 2 * BAND * TN * 4, G_BUF = BAND * TN * 2;   // DGRAD2: two bands of saved derivatives
+        static_assert(TN == 128 || TN == 64, "epilogue staging is laid out for 128- and 64-column wave tiles");
+        static_assert(NW * TN * 256 <= NSLOT * SLOT && G_OFF + 2 * G_BUF <= TN * 256, "epilogue staging exceeds the ring");
         const size_t ldo = (size_t)g.N;
         const int wrow0 = wm * TM, wcol0 = wn * TN;
-        // DGRAD2: stage the saved F'(pre)[band][128 cols] (16-bit, 256 B rows, chunk ^ (row & 15))
-        // with direct loads; instruction t covers rows 4t..4t+3
-        constexpr int GI = BAND / 4;                  // staging instructions per band
+        // DGRAD2: stage the saved F'(pre)[band][TN cols] (16-bit, G_CPR chunks a row, chunk ^ (row % G_CPR))
+        // with direct loads; instruction t covers rows G_RPI*t .. G_RPI*t + G_RPI-1
+        constexpr int G_CPR = TN / 8, G_RPI = 64 / G_CPR;
+        constexpr int GI = BAND / G_RPI;              // staging instructions per band
         rsrc_t rp;
         uint32_t pre_voff = 0;
         if constexpr (OP == OP_DGRAD2) {
             rp = make_rsrc(g.pre_in + (size_t)m0 * ldo, (uint32_t)mvalid * (uint32_t)ldo * 2u);
-            pre_voff = (uint32_t)((wrow0 + (lane >> 4)) * (int)ldo + n0 + wcol0) * 2u;
+            pre_voff = (uint32_t)((wrow0 + lane / G_CPR) * (int)ldo + n0 + wcol0) * 2u;
         }
         auto stage_pre = [&](int band, int buf) {
             if constexpr (OP == OP_DGRAD2) {
 #pragma unroll
                 for (int t = 0; t < GI; ++t) {
-                    const int row = 4 * t + (lane >> 4);
-                    const int c = (lane & 15) ^ (row & 15);
+                    const int row = G_RPI * t + lane / G_CPR;
+                    const int c = (lane % G_CPR) ^ (row % G_CPR);
                     dtl16(rp, wreg + G_OFF + buf * G_BUF + t * 1024,
-                          pre_voff + (uint32_t)((band * BAND + 4 * t) * (int)ldo + c * 8) * 2u, 0u);
+                          pre_voff + (uint32_t)((band * BAND + G_RPI * t) * (int)ldo + c * 8) * 2u, 0u);
                 }
             }
         };
@@ -852,7 +905,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         // tile to the end of its last valid row, so stores to rows past the segment are dropped by
         // the range check; a lane whose 16-byte chunk lies past the last valid column gets an
         // offset outside any window.  Instruction t of a band stores rows RPI_O*t + lane/CPRO; the
-        // chunk a lane holds there is (lane % CPRO) ^ row = c0 ^ (RPI_O*t) (row < 16, RPI_O*t has
+        // chunk a lane holds there is (lane % CPRO) ^ (row % CPRO) = c0 ^ (RPI_O*t % CPRO) (RPI_O*t has
         // no bit in common with lane/CPRO), so the per-lane offsets of the NST instructions are the
         // same for every band and the band's row offset is a scalar.
         constexpr int RPI_O = 1024 / RPB;            // rows per store instruction
@@ -867,10 +920,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         const int ldo_b = __builtin_amdgcn_readfirstlane((int)ldo * ESZ);   // bytes per output row
         int ovoff[NST];
         {
-            const int q = lane / CPRO, c0 = (lane % CPRO) ^ q;
+            const int q = lane / CPRO, c0 = (lane % CPRO) ^ (q % CPRO);
 #pragma unroll
             for (int t = 0; t < NST; ++t) {
-                const int c = c0 ^ (RPI_O * t);
+                const int c = c0 ^ (RPI_O * t % CPRO);
                 ovoff[t] = c * 16 < nv_w * ESZ ? q * (int)ldo * ESZ + c * 16 : (int)0x80000000;
             }
         }
@@ -885,7 +938,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         constexpr int BUF_STRIDE = (OP == OP_FC1 ? 2 : 1) * BAND_BYTES;   // FC1 stages two outputs per band
         static_assert(H_OFF == BAND_BYTES && 2 * BUF_STRIDE <= G_OFF, "band buffers overlap");
         u32x4 d0[NST], d1[OP == OP_FC1 ? NST : 1];
-        uint32_t cw[OP == OP_DGRAD2 ? BAND : 1];
+        // DGRAD2: with 128 columns a lane adds up two columns over all rows of a band, with 64 columns the
+        // two half waves take every other row
+        constexpr int CS_STEP = 128 / TN;
+        uint32_t cw[OP == OP_DGRAD2 ? BAND / CS_STEP : 1];
+        const int cs_row = lane / (TN / 2), cs_l = lane % (TN / 2);
         auto band_reads = [&](int buf) __attribute__((always_inline)) {
             uint8_t* wb = wreg + buf * BUF_STRIDE;
 #pragma unroll
@@ -897,9 +954,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
                 // bias-gradient partial: the band holds the rounded dpre values the weight gradient
                 // will read; rows past the segment and columns past N are exact zeros
 #pragma unroll
-                for (int row = 0; row < BAND; ++row)
-                    cw[row] = *reinterpret_cast<const uint32_t*>(
-                        wb + row * RPB + ((((lane >> 2) ^ row)) << 4) + (lane & 3) * 4);
+                for (int q = 0; q < BAND / CS_STEP; ++q) {
+                    const int row = CS_STEP * q + cs_row;
+                    cw[q] = *reinterpret_cast<const uint32_t*>(
+                        wb + row * RPB + (((cs_l >> 2) ^ (row % CPRO)) << 4) + (cs_l & 3) * 4);
+                }
             }
         };
         auto band_store_one = [&](int i, int t) __attribute__((always_inline)) {
@@ -914,9 +973,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
             }
             if constexpr (OP == OP_DGRAD2) {
 #pragma unroll
-                for (int row = 0; row < BAND; ++row) {
+                for (int q = 0; q < BAND / CS_STEP; ++q) {
                     float c0, c1;
-                    unpack2<F16>(cw[row], c0, c1);
+                    unpack2<F16>(cw[q], c0, c1);
                     cs0 += c0; cs1 += c1;
                 }
             }
@@ -953,11 +1012,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
                     // straight from the accumulation registers (an LDS store may take its data from
                     // them; through ordinary registers it is 256 more copies per wave and tile)
                     const int c = col >> 2;
-                    const uint32_t la = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)(wb + l16 * RPB + ((c ^ l16) << 4));
+                    const uint32_t la = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)(wb + l16 * RPB + ((c ^ (l16 % CPRO)) << 4));
                     asm volatile("ds_write_b128 %0, %1" : : "v"(la), "a"(acc[i][j]) : "memory");
                 } else {
                     const int c = col >> 3;
-                    const uint32_t off = (uint32_t)(l16 * RPB + ((c ^ l16) << 4) + (grp & 1) * 8);
+                    const uint32_t off = (uint32_t)(l16 * RPB + ((c ^ (l16 % CPRO)) << 4) + (grp & 1) * 8);
                     if constexpr (OP == OP_FC1) {
                         float hh[4], gg[4];
 #pragma unroll
@@ -996,8 +1055,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         band_reads((FM - 1) & 1);
         band_stores(FM - 1, true);
         if constexpr (OP == OP_DGRAD2) {
-            const int col = wcol0 + 2 * lane;
-            if (col < nvalid)
+            const int col = wcol0 + 2 * cs_l;
+            if constexpr (CS_STEP == 2) { cs0 += __shfl_xor(cs0, 32); cs1 += __shfl_xor(cs1, 32); }
+            if (cs_row == 0 && col < nvalid)
                 *reinterpret_cast<float2*>(g.colpart + (size_t)(row_tile * WM + wm) * ldo + n0 + col) =
                     make_float2(cs0, cs1);
         }
@@ -1005,7 +1065,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
 }
 
 template <int BM, int BN, int WM, int WN, int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
-__global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16(GemmArgs g) {
+__global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16(GemmArgs g) {
     gemm_tile<BM, BN, WM, WN, OP, ACT, F16>(g, (int)blockIdx.x);
 }
 
@@ -1018,10 +1078,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16(GemmArgs g) {
 // than a row-GEMM tile (flag `order` of the work-list header, set by build_worklists; with Zipf
 // routing at C5's shape the largest expert's tiles run 1582 K-blocks against 32 or 128).
 template <int BM, int BN, int WM, int WN, int OPA, int OPB, bool F16 = false>
-__global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_pair(GemmArgs ga, GemmArgs gb, int items_a, int order) {
+__global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pair(GemmArgs ga, GemmArgs gb, int items_a, const int32_t* b_leads) {
     const int item = (int)blockIdx.x;
     const int items_b = (int)gridDim.x - items_a;
-    const bool b_first = ga.worklist[order] != 0;
+    const bool b_first = *b_leads != 0;
     const bool is_b = b_first ? item < items_b : item >= items_a;
     const int local = b_first ? (is_b ? item : item - items_b) : (is_b ? item - items_a : item);
     if (is_b) gemm_tile<BM, BN, WM, WN, OPB, HEXA_ACT_GELU_TANH, F16>(gb, local);
@@ -1071,9 +1131,9 @@ constexpr int kNumCUs = 256;
 
 // Work-item slots of a row GEMM with at most tm_max row tiles and tn column tiles (a multiple of 8):
 // per XCD, enough for either way of dealing the last groups (see gemm_tile).
-inline int row_gemm_slots(int tm_max, int tn) {
-    const int per_group = kGroupM * tn;
-    const int ngroups = ceil_div(tm_max, kGroupM);
+inline int row_gemm_slots(int tm_max, int tn, int GM) {
+    const int per_group = GM * tn;
+    const int ngroups = ceil_div(tm_max, GM);
     const int split = (ngroups / kXcds) * per_group + (kXcds - 1) * ceil_div(per_group, kXcds);
     const int whole = ceil_div(ngroups, kXcds) * per_group;
     return kXcds * (split > whole ? split : whole);
@@ -1085,7 +1145,7 @@ void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char
     auto kern = gemm_bf16<BM, BN, WM, WN, OP, ACT, F16>;
     constexpr int lds = NSLOT * (BM > BN ? BM : BN) * ROWB;
     const int tm_max = D.A / BM + D.E;
-    const int grid = row_gemm_slots(tm_max, ceil_div(g.N, BN));
+    const int grid = row_gemm_slots(tm_max, ceil_div(g.N, BN), group_rows(BM));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds, st, g);
 }
 
@@ -1093,17 +1153,16 @@ void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char
 // split-K finisher of OPB.
 template <int BM, int BN, int WM, int WN, int OPA, int OPB, bool F16 = false>
 void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipStream_t st,
-                 const char* label, const char* label_fin) {
+                 const int32_t* b_leads, const char* label, const char* label_fin) {
     auto kern = gemm_bf16_pair<BM, BN, WM, WN, OPA, OPB, F16>;
     constexpr int lds = NSLOT * (BM > BN ? BM : BN) * ROWB;
     const int tm_max = D.A / BM + D.E;
-    const int items_a = row_gemm_slots(tm_max, ceil_div(ga.N, BN));
+    const int items_a = row_gemm_slots(tm_max, ceil_div(ga.N, BN), group_rows(BM));
     const int tmn = ceil_div(gb.M, BM) * ceil_div(gb.N, BN);
     const int items_b = kXcds * ceil_div(tmn, kXcds) * (D.A / gb.chunk_len + D.E);
     {
         ProfScope ps(st, label);
-        hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a,
-                           OPB == OP_WGRAD2 ? 2 : 3);
+        hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a, b_leads);
     }
     ProfScope ps(st, label_fin);
     const size_t mn = (size_t)gb.M * gb.N;
@@ -1112,36 +1171,91 @@ void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipSt
                        gb.kpart, reinterpret_cast<float*>(gb.out0));
 }
 
-constexpr int TBM = 256, TBN = 256, TWM = 2, TWN = 2;
+// Two tile classes.  256x256: one workgroup per CU (all of LDS, 512 registers per lane), the cheaper one
+// per FLOP (a 128x128 tile fetches and reads twice the bytes per FLOP), which wins once its tiles fill the
+// chip.  128x128: two workgroups per CU (half of LDS, 256 registers), four times as many tiles, so it wins
+// where 256x256 tiles are too few for 256 CUs or mostly padding.
+constexpr int BIG = 256, SMALL = 128;
+
+// Which class a launch takes: the one with the shorter estimated time.  A tile takes a start-up and epilogue
+// time plus a time per 64-k block; a launch takes its tiles' summed time over the slots of the chip plus a
+// share of its longest tile for the uneven end, and never less than its longest tile.  The four numbers of a
+// class are fitted to 120 launches (30 shapes: 256 to 65536 tokens, d 64 to 2048, f 256 to 8192, 4 to 64
+// experts, both classes measured): with them the slower class is picked by 1 % of a launch's time on average
+// and by 14 % at most (a skewed 32768 x 256 x 1024 case); always taking 256x256 tiles costs 16 % on average
+// and up to a factor of 2.2.  Measured on both sides of the line, 256x256 against 128x128, in us:
+// d = 384, f = 1536, 8 experts, top-2: fc2 32.4 / 16.5 at 4096 tokens, 72 / 59 at 16384; d = 768, f = 3072,
+// 16 experts: fc2 78 / 54 at 2048 tokens, 77 / 71 at 4096, 95 / 115 at 8192, 164 / 205 at 16384.
+struct ClassCost { double slots, start_us, block_us, tail; };
+constexpr ClassCost kCostBig{256, 15.1, 1.22, 0.87}, kCostSmall{512, 7.3, 1.31, 0.54};
+
+struct Work { double tiles, blocks; };   // tiles of a contraction, 64-k blocks per tile
+
+inline double launch_us(const ClassCost& c, std::initializer_list<Work> parts) {
+    double sum = 0, longest = 0;
+    for (const Work& w : parts) {
+        const double t = c.start_us + c.block_us * w.blocks;
+        sum += w.tiles * t;
+        longest = std::max(longest, t);
+    }
+    return std::max(longest, sum / c.slots + c.tail * longest);
+}
+
+// Row tiles of height bm the experts' segments are expected to make (the host does not know the routing):
+// rows spread over the experts that can have any, half a tile of padding each.
+inline double expected_row_tiles(const MoeDims& D, int bm) {
+    const double e = D.E < D.A ? D.E : D.A, rows = D.A / e;
+    return rows > bm / 2 ? e * std::max(1.0, rows / bm + 0.5) : e;
+}
+inline Work row_work(const MoeDims& D, int bm, int K, int N) {
+    return {expected_row_tiles(D, bm) * ceil_div(N, bm), K / 64.0};
+}
+inline Work token_work(const MoeDims& D, int bm) {
+    const double rows = D.A / (double)(D.E < D.A ? D.E : D.A), chunk = wgrad_chunk_len(D);
+    return {D.E * std::max(1.0, rows / chunk) * ceil_div(D.d, bm) * ceil_div(D.f, bm), std::min(rows, chunk) / 64.0};
+}
+inline bool small_rows(const MoeDims& D, int K, int N) {
+    return launch_us(kCostSmall, {row_work(D, SMALL, K, N)}) < launch_us(kCostBig, {row_work(D, BIG, K, N)});
+}
+inline bool small_pair(const MoeDims& D, int K, int N) {
+    return launch_us(kCostSmall, {row_work(D, SMALL, K, N), token_work(D, SMALL)}) <
+           launch_us(kCostBig, {row_work(D, BIG, K, N), token_work(D, BIG)});
+}
+inline bool small_fc1(const MoeDims& D) { return small_rows(D, D.d, D.f); }
+inline bool small_fc2(const MoeDims& D) { return small_rows(D, D.f, D.d); }
+inline bool small_bwd2(const MoeDims& D) { return small_pair(D, D.d, D.f); }
+inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 
 }  // namespace
 
-// Every contraction kernel needs the whole 160 KB of LDS as dynamic shared memory, which a kernel
-// may only use after its attribute has been raised, once per device.
-template <typename K>
-static hipError_t allow_full_lds(K kern) {
+// Every contraction kernel needs more dynamic shared memory than a kernel may use before its attribute
+// has been raised, once per device.
+template <int B, typename K>
+static hipError_t allow_lds(K kern) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, NSLOT * TBM * ROWB);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, NSLOT * B * ROWB);
 }
-template <bool F16>
-static hipError_t device_init_dtype() {
-    hipError_t e = allow_full_lds(gemm_bf16<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_GELU_TANH, F16>);
-    if (e == hipSuccess) e = allow_full_lds(gemm_bf16<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_RELU, F16>);
-    if (e == hipSuccess) e = allow_full_lds(gemm_bf16<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_SILU, F16>);
-    if (e == hipSuccess) e = allow_full_lds(gemm_bf16<TBM, TBN, TWM, TWN, OP_FC2, HEXA_ACT_GELU_TANH, F16>);
-    if (e == hipSuccess) e = allow_full_lds(gemm_bf16_pair<TBM, TBN, TWM, TWN, OP_DGRAD2, OP_WGRAD2, F16>);
-    if (e == hipSuccess) e = allow_full_lds(gemm_bf16_pair<TBM, TBN, TWM, TWN, OP_DGRAD1, OP_WGRAD1, F16>);
+template <int B, bool F16>
+static hipError_t device_init_class() {
+    hipError_t e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC1, HEXA_ACT_GELU_TANH, F16>);
+    if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC1, HEXA_ACT_RELU, F16>);
+    if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC1, HEXA_ACT_SILU, F16>);
+    if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>);
+    if (e == hipSuccess) e = allow_lds<B>(gemm_bf16_pair<B, B, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>);
+    if (e == hipSuccess) e = allow_lds<B>(gemm_bf16_pair<B, B, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>);
     return e;
 }
 hipError_t gemm_bf16_device_init() {
-    static_assert(TBM == TBN, "one LDS size for all instantiations");
-    const hipError_t e = device_init_dtype<false>();
-    return e != hipSuccess ? e : device_init_dtype<true>();
+    hipError_t e = device_init_class<BIG, false>();
+    if (e == hipSuccess) e = device_init_class<BIG, true>();
+    if (e == hipSuccess) e = device_init_class<SMALL, false>();
+    if (e == hipSuccess) e = device_init_class<SMALL, true>();
+    return e;
 }
 
 // Row-tile height and partial rows per tile of the DGRAD2 column-sum partials (for the finisher).
-int gemm_row_tile() { return TBM; }
-int gemm_colpart_rows_per_tile() { return TWM; }
+int gemm_dgrad2_row_tile(const MoeDims& D) { return small_bwd2(D) ? SMALL : BIG; }
+int gemm_colpart_rows_per_tile() { return 2; }
 
 // Tokens per split-K chunk of the token contractions: an expert is cut only when its rows alone
 // would give every CU a tile's worth of work for longer than the whole contraction takes on
@@ -1151,7 +1265,7 @@ int gemm_colpart_rows_per_tile() { return TWM; }
 // a quarter of this length made C3 5.6 %, C4 1.9 % and C5 under Zipf routing 0.5 % slower; half
 // as many chunks again made C3 and C4 slower).
 int wgrad_chunk_len(const MoeDims& D) {
-    const long long tmn = (long long)ceil_div(D.d, TBM) * ceil_div(D.f, TBN);
+    const long long tmn = (long long)ceil_div(D.d, BIG) * ceil_div(D.f, BIG);
     long long L = (long long)D.A * tmn / kNumCUs;
     L = (L + 63) / 64 * 64;
     if (L < 1024) L = 1024;
@@ -1162,15 +1276,24 @@ int wgrad_chunk_len(const MoeDims& D) {
 }
 
 // Capacities of the work lists (see build_worklists): row tiles, token-contraction items.
-static int worklist_rt_cap(const MoeDims& D) { return D.A / TBM + D.E; }
-static int worklist_it_cap(const MoeDims& D) { return D.A / wgrad_chunk_len(D) + D.E; }
+static size_t worklist_rt_cap(const MoeDims& D, int bm) { return (size_t)(D.A / bm + D.E); }
+static size_t worklist_it_cap(const MoeDims& D) { return (size_t)(D.A / wgrad_chunk_len(D) + D.E); }
 size_t gemm_worklist_ints(const MoeDims& D) {
-    return 4 + 4 * (size_t)worklist_rt_cap(D) + 4 * (size_t)worklist_it_cap(D);
+    return kWlHeader + 4 * (worklist_rt_cap(D, BIG) + worklist_rt_cap(D, SMALL) + worklist_it_cap(D));
 }
 static void launch_worklists(const MoeDims& D, const hexa_moe_idx& idx, const MoeWorkspace& ws, hipStream_t st) {
     ProfScope ps(st, "worklists");
-    hipLaunchKernelGGL(build_worklists, dim3(1), dim3(1024), 0, st, idx.offsets, D.E, TBM,
-                       wgrad_chunk_len(D), ws.worklist, worklist_rt_cap(D), D.d, D.f);
+    hipLaunchKernelGGL(build_worklists, dim3(1), dim3(1024), 0, st, idx.offsets, D.E,
+                       wgrad_chunk_len(D), ws.worklist, (int)worklist_rt_cap(D, BIG), (int)worklist_rt_cap(D, SMALL), D.d, D.f);
+}
+// Points a contraction's arguments at its part of the work lists.
+static void use_row_tiles(const MoeDims& D, const MoeWorkspace& ws, bool small, GemmArgs& g) {
+    g.row_tiles = ws.worklist + kWlHeader + (small ? 4 * worklist_rt_cap(D, BIG) : 0);
+    g.n_row_tiles = ws.worklist + (small ? WL_TILES128 : WL_TILES256);
+}
+static void use_items(const MoeDims& D, const MoeWorkspace& ws, GemmArgs& g) {
+    g.items = ws.worklist + kWlHeader + 4 * (worklist_rt_cap(D, BIG) + worklist_rt_cap(D, SMALL));
+    g.n_items = ws.worklist + WL_ITEMS;
 }
 
 // Upper bound on split-K slots: only experts with more than one chunk use slots, and
@@ -1179,20 +1302,28 @@ size_t wgrad_max_slots(const MoeDims& D) {
     return 2 * (size_t)(D.A / wgrad_chunk_len(D)) + 2;
 }
 
+template <int B, bool F16>
+static void launch_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
+    if (D.act == HEXA_ACT_RELU) launch_rows<B, B, 2, 2, OP_FC1, HEXA_ACT_RELU, F16>(D, g, st, "fc1");
+    else if (D.act == HEXA_ACT_SILU) launch_rows<B, B, 2, 2, OP_FC1, HEXA_ACT_SILU, F16>(D, g, st, "fc1");
+    else launch_rows<B, B, 2, 2, OP_FC1, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc1");
+}
+
 template <bool F16>
 static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, const bf16_t* b1,
                            const bf16_t* W2, const bf16_t* b2, const hexa_moe_idx& idx,
                            const MoeWorkspace& ws, hipStream_t st) {
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
-    g.worklist = ws.worklist; g.rt_cap = worklist_rt_cap(D);
     launch_worklists(D, idx, ws, st);
     g.A = x; g.a_rows = D.T; g.B = W1; g.bias = b1; g.out0 = ws.pre; g.out1 = ws.h; g.K = D.d; g.N = D.f;
-    if (D.act == HEXA_ACT_RELU) launch_rows<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_RELU, F16>(D, g, st, "fc1");
-    else if (D.act == HEXA_ACT_SILU) launch_rows<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_SILU, F16>(D, g, st, "fc1");
-    else launch_rows<TBM, TBN, TWM, TWN, OP_FC1, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc1");
+    use_row_tiles(D, ws, small_fc1(D), g);
+    if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
+    else launch_fc1<BIG, F16>(D, g, st);
     g.A = (const bf16_t*)ws.h; g.B = W2; g.bias = b2; g.out0 = ws.o; g.out1 = nullptr; g.K = D.f; g.N = D.d;
-    launch_rows<TBM, TBN, TWM, TWN, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+    use_row_tiles(D, ws, small_fc2(D), g);
+    if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+    else launch_rows<BIG, BIG, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     return hipGetLastError();
 }
 
@@ -1200,29 +1331,38 @@ template <bool F16>
 static hipError_t bwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, const bf16_t* W2,
                            const hexa_moe_idx& idx, const MoeWorkspace& ws, float* dW1, float* dW2,
                            hipStream_t st) {
+    const bool small2 = small_bwd2(D), small1 = small_bwd1(D);
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
     g.kpart = ws.kpart; g.chunk_len = wgrad_chunk_len(D);
-    // the work lists are the ones the forward pass built (part of the state it saves in the workspace)
-    g.worklist = ws.worklist; g.rt_cap = worklist_rt_cap(D);
     {   // WGRAD1's row-offset table; entries past a segment's end point behind the last row of x
         ProfScope ps(st, "rowoff");
         const int total = D.A + 64 * D.E;
+        const int step = small1 ? StageKS<SMALL, 4>::STEP : StageKS<BIG, 4>::STEP;
         hipLaunchKernelGGL(build_rowoff, dim3(ceil_div(total, 256)), dim3(256), 0, st, idx.offsets, idx.perm,
-                           D.E, D.k, (uint32_t)D.d * 2u, (uint32_t)D.T * (uint32_t)D.d * 2u, total, ws.rowoff);
+                           D.E, D.k, (uint32_t)D.d * 2u, (uint32_t)D.T * (uint32_t)D.d * 2u, total, step, ws.rowoff);
     }
+    // the work lists are the ones the forward pass built (part of the state it saves in the workspace)
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     GemmArgs r = g, t = g;
     r.A = (const bf16_t*)ws.dout; r.B = W2; r.pre_in = (const bf16_t*)ws.pre; r.out0 = ws.dpre;
     r.colpart = ws.colpart; r.K = D.d; r.N = D.f;
     t.A = (const bf16_t*)ws.h; t.B = (const bf16_t*)ws.dout; t.out0 = dW2; t.M = D.f; t.N = D.d;
-    launch_pair<TBM, TBN, TWM, TWN, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, "bwd_fc2", "wgrad2_finish");
+    use_row_tiles(D, ws, small2, r);
+    use_items(D, ws, t);
+    const int32_t* lead2 = ws.worklist + WL_ORDER2;
+    if (small2) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2", "wgrad2_finish");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2", "wgrad2_finish");
     // 1st linear layer: dxp = dpre W1^T  and  dW1[e] = x[perm/k]^T dpre
     r = g; t = g;
     r.A = (const bf16_t*)ws.dpre; r.B = W1; r.out0 = ws.dxp; r.K = D.f; r.N = D.d;
     t.A = x; t.a_rows = D.T; t.rowoff = ws.rowoff;
     t.B = (const bf16_t*)ws.dpre; t.out0 = dW1; t.M = D.d; t.N = D.f;
-    launch_pair<TBM, TBN, TWM, TWN, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, "bwd_fc1", "wgrad1_finish");
+    use_row_tiles(D, ws, small1, r);
+    use_items(D, ws, t);
+    const int32_t* lead1 = ws.worklist + WL_ORDER1;
+    if (small1) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1", "wgrad1_finish");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1", "wgrad1_finish");
     return hipGetLastError();
 }
 

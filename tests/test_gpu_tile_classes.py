@@ -1,0 +1,32 @@
+"""The two tile classes of the 16-bit contractions (256x256 and 128x128) against the oracle, every element:
+segments of one expert around the edges of a 128-row tile and its 64-row halves, and ragged sizes at which
+the launch rule gives all or some of a step's launches 256x256 tiles (the named workloads C3, C4, C5 are
+covered on samples by test_gpu_full_configs.py)."""
+import pytest
+import torch
+
+from paper_2411_01288_amd.workloads import MoEWorkload, generate
+from test_gpu_parity import full_parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 191, 193, 257])
+def test_row_edges_of_a_128_row_tile(oracle, T):
+    # one expert: a segment of exactly T rows; feature sizes with column tails of both kinds (64 and 192 of 128)
+    w = MoEWorkload("edge", T, 192, 320, 1, 1, "bf16", "topk", 900 + T)
+    data = generate(w, DEV)
+    data["gate"] = 0.5 + torch.rand_like(data["gate"])
+    full_parity(oracle, w, data, label=f"edge T{T}")
+
+
+@pytest.mark.parametrize("T,d,f,E,k,dtype", [
+    (25003, 192, 960, 3, 2, "bf16"),    # all four launches 256x256
+    (17001, 448, 576, 5, 2, "bf16"),    # fc1 128x128, the others 256x256
+    (25003, 384, 448, 1, 2, "f16"),     # fc1 and the second layer's backward 256x256, the others 128x128
+    (25003, 192, 448, 5, 2, "f16"),     # the first layer's backward alone 256x256
+])
+def test_mixed_tile_classes(oracle, T, d, f, E, k, dtype):
+    w = MoEWorkload("mixed", T, d, f, E, min(k, E), dtype, "topk", 77 + T)
+    full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E} k{k}")
