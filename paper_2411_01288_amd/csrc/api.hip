@@ -56,9 +56,10 @@ MoeWorkspace layout(const MoeDims& D, int dtype, void* base) {
     w.dout = take(A * d * es);
     w.dpre = take(A * f * es);
     w.dxp = take(A * d * es);
-    {   // column-sum staging: the prologue's tiles, or (16-bit) the partial rows of the DGRAD2 tiles
+    {   // column-sum staging: the prologue's tiles, or the partial rows of the DGRAD2 tiles
         size_t rows = colsum_partial_rows(D);
-        const size_t rows_gemm = (A / (size_t)gemm_dgrad2_row_tile(D) + (size_t)D.E) * (size_t)gemm_colpart_rows_per_tile();
+        const size_t bm = (size_t)(dtype == HEXA_F32 ? f32_dgrad2_row_tile(D) : gemm_dgrad2_row_tile(D));
+        const size_t rows_gemm = (A / bm + (size_t)D.E) * (size_t)gemm_colpart_rows_per_tile();
         if (rows < rows_gemm) rows = rows_gemm;
         w.colpart = (float*)take(rows * (d > f ? d : f) * 4);
     }
@@ -248,7 +249,7 @@ hexa_status hexa_moe_bwd(const hexa_moe_shape* shape, const void* dY, const void
         if (e == hipSuccess)
             e = launch_f32_bwd(D, (const float*)x, (const float*)W1, (const float*)W2, idx, ws, dW1, dW2, st);
         if (e == hipSuccess)
-            e = launch_segment_colsum<float>(D, (const float*)ws.dpre, D.f, idx.offsets, ws.colpart, db1, st);
+            e = launch_tile_colsum_finish(D, ws.colpart, D.f, f32_dgrad2_row_tile(D), idx.offsets, db1, st);
         if (e == hipSuccess) e = launch_combine_dx<float>(D, (const float*)ws.dxp, idx.inv, (float*)dx, st);
     } else {
         const bool f16 = shape->dtype == HEXA_F16;
@@ -262,7 +263,7 @@ hexa_status hexa_moe_bwd(const hexa_moe_shape* shape, const void* dY, const void
             e = launch_bf16_bwd(D, (const bf16_t*)x, (const bf16_t*)W1, (const bf16_t*)W2, idx, ws,
                                 dW1, dW2, st, f16);
         if (e == hipSuccess)
-            e = launch_tile_colsum_finish(D, ws.colpart, D.f, idx.offsets, db1, st);
+            e = launch_tile_colsum_finish(D, ws.colpart, D.f, gemm_dgrad2_row_tile(D), idx.offsets, db1, st);
         if (e == hipSuccess) {
             if (f16) e = launch_combine_dx<f16_t>(D, (const f16_t*)ws.dxp, idx.inv, (f16_t*)dx, st);
             else e = launch_combine_dx<bf16_t>(D, (const bf16_t*)ws.dxp, idx.inv, (bf16_t*)dx, st);

@@ -81,6 +81,26 @@ __device__ __forceinline__ int seg_tiles_total(const int32_t* __restrict__ offse
     return total;
 }
 
+// The same two look-ups by a whole wavefront (all 64 lanes active), an expert per lane: a scan over the lanes
+// instead of a walk over the experts, whose loads a workgroup would wait for one after the other.
+// Inclusive scan over the 64 lanes with the data-parallel moves of the vector unit (within rows of 16, then
+// lane 15 of rows 0 and 2 into the row behind, then lane 31 into the upper half).
+__device__ __forceinline__ int wave_scan_incl(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return v;
+}
+__device__ __forceinline__ int seg_tiles_total_wave(const int32_t* __restrict__ offsets, int E, int BM) {
+    const int lane = threadIdx.x & 63;
+    int v = 0;
+    for (int e = lane; e < E; e += 64) v += ceil_div(offsets[e + 1] - offsets[e], BM);
+    return __builtin_amdgcn_readlane(wave_scan_incl(v), 63);
+}
+
 // Map tile number `tile` (0-based over all segments, expert-major) to its segment tile.
 // Returns e = -1 when `tile` is past the last one.
 __device__ __forceinline__ SegTile seg_tile_find(const int32_t* __restrict__ offsets, int E, int BM,
@@ -98,6 +118,27 @@ __device__ __forceinline__ SegTile seg_tile_find(const int32_t* __restrict__ off
         acc += nt;
     }
     return s;
+}
+
+__device__ __forceinline__ SegTile seg_tile_find_wave(const int32_t* __restrict__ offsets, int E, int BM,
+                                                      int tile) {
+    const int lane = threadIdx.x & 63;
+    int acc = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        const int e = e0 + lane;
+        const int b = e < E ? offsets[e] : 0, n = e < E ? offsets[e + 1] - b : 0;
+        const int nt = ceil_div(n, BM);
+        const int end = acc + wave_scan_incl(nt);
+        const uint64_t hit = __ballot(end > tile);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int r0 = (tile - (__builtin_amdgcn_readlane(end, src) - __builtin_amdgcn_readlane(nt, src))) * BM;
+            return SegTile{e0 + src, __builtin_amdgcn_readlane(b, src) + r0,
+                           min(BM, __builtin_amdgcn_readlane(n, src) - r0)};
+        }
+        acc = __builtin_amdgcn_readlane(end, 63);
+    }
+    return SegTile{-1, 0, 0};
 }
 
 // ---- optional per-kernel timing (off unless hexa_moe_profile_enable(1); bench_support.hip) ----
@@ -141,6 +182,7 @@ struct MoeWorkspace {
 };
 
 int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path
+int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp32 path
 int gemm_colpart_rows_per_tile();    // DGRAD2 writes this many column-sum partial rows per row tile
 int wgrad_chunk_len(const MoeDims& D);          // tokens per split-K chunk (host policy)
 size_t wgrad_max_slots(const MoeDims& D);
@@ -171,12 +213,12 @@ template <typename T>
 hipError_t launch_segment_colsum(const MoeDims& D, const T* src, int ncols, const int32_t* offsets,
                                  float* partial, float* out, hipStream_t st);
 
-// second stage for column sums the bf16 DGRAD2 kernel left per (row tile, wave row):
+// second stage for column sums a DGRAD2 kernel left per (row tile of row_tile rows, wave row):
 // out[e][c] = sum of the partial rows of the expert's tiles, in tile order
-hipError_t launch_tile_colsum_finish(const MoeDims& D, const float* partial, int ncols,
+hipError_t launch_tile_colsum_finish(const MoeDims& D, const float* partial, int ncols, int row_tile,
                                      const int32_t* offsets, float* out, hipStream_t st);
 
-// fp32 reference-precision path (plain FMA tiles)
+// fp32 path (fp32 matrix instructions)
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,
                           const float* W2, const float* b2, const hexa_moe_idx& idx,
                           const MoeWorkspace& ws, hipStream_t st);

@@ -389,11 +389,11 @@ hipError_t launch_segment_colsum(const MoeDims& D, const T* src, int ncols, cons
     return hipGetLastError();
 }
 
-hipError_t launch_tile_colsum_finish(const MoeDims& D, const float* partial, int ncols,
+hipError_t launch_tile_colsum_finish(const MoeDims& D, const float* partial, int ncols, int row_tile,
                                      const int32_t* offsets, float* out, hipStream_t st) {
     ProfScope ps(st, "colsum_db1");
-    hipLaunchKernelGGL(colsum_finish, dim3(D.E, ceil_div(ncols, 256)), dim3(64 * finish_slices(((size_t)D.A / gemm_dgrad2_row_tile(D) + D.E) * gemm_colpart_rows_per_tile(), D.E)), 0, st, partial, ncols,
-                       D.E, gemm_dgrad2_row_tile(D), gemm_colpart_rows_per_tile(), offsets, out);
+    hipLaunchKernelGGL(colsum_finish, dim3(D.E, ceil_div(ncols, 256)), dim3(64 * finish_slices(((size_t)D.A / row_tile + D.E) * gemm_colpart_rows_per_tile(), D.E)), 0, st, partial, ncols,
+                       D.E, row_tile, gemm_colpart_rows_per_tile(), offsets, out);
     return hipGetLastError();
 }
 
