@@ -98,7 +98,8 @@ def hbm_steps(w, kernels, copy_gbps):
         "combine_y": A * d * es + T * d * es + A * 8,
         # dY (gathered) and o in; dout out (+ perm, gate, dgate)
         "bwd_prologue": A * d * es * 3 + A * 12,
-        "combine_dx": A * d * es + T * d * es + A * 4,
+        # dxp [A,d] and inv in; dx [T,d] out (the bias and split weight gradients of the same launch not counted)
+        "bwd_finish": A * d * es + T * d * es + A * 4,
         "index_scatter": A * 4 + A * 8,
     }
     out = {"copy_GBps": round(copy_gbps, 1)}

@@ -56,17 +56,15 @@ MoeWorkspace layout(const MoeDims& D, int dtype, void* base) {
     w.dout = take(A * d * es);
     w.dpre = take(A * f * es);
     w.dxp = take(A * d * es);
-    {   // column-sum staging: the prologue's tiles, or the partial rows of the DGRAD2 tiles
-        size_t rows = colsum_partial_rows(D);
-        const size_t bm = (size_t)(dtype == HEXA_F32 ? f32_dgrad2_row_tile(D) : gemm_dgrad2_row_tile(D));
-        const size_t rows_gemm = (A / bm + (size_t)D.E) * (size_t)gemm_colpart_rows_per_tile();
-        if (rows < rows_gemm) rows = rows_gemm;
-        w.colpart = (float*)take(rows * (d > f ? d : f) * 4);
-    }
-    if (dtype != HEXA_F32) {
+    const bool f32 = dtype == HEXA_F32;
+    const size_t bm = (size_t)(f32 ? f32_dgrad2_row_tile(D) : gemm_dgrad2_row_tile(D));
+    w.colpart1 = (float*)take((A / bm + (size_t)D.E) * kColpartRows * f * 4);
+    w.colpart2 = (float*)take(prologue_partial_rows(D) * d * 4);
+    const size_t slots = split_slots(D, f32 ? f32_chunk_len(D) : wgrad_chunk_len(D));
+    w.kpart1 = (float*)take(slots * d * f * 4);
+    w.kpart2 = (float*)take(slots * d * f * 4);
+    if (!f32) {
         w.rowoff = (uint32_t*)take((A + 64 * (size_t)D.E) * 4);
-        w.kpart_slots = wgrad_max_slots(D);
-        w.kpart = (float*)take(w.kpart_slots * d * f * 4);
         w.worklist = (int32_t*)take(gemm_worklist_ints(D) * 4);
     }
     w.total_bytes = off;
@@ -244,29 +242,23 @@ hexa_status hexa_moe_bwd(const hexa_moe_shape* shape, const void* dY, const void
     hipError_t e;
     if (shape->dtype != HEXA_F32 && (e = ensure_device_init()) != hipSuccess) return dev(e);
     if (shape->dtype == HEXA_F32) {
-        e = launch_bwd_prologue<float>(D, (const float*)dY, (const float*)ws.o, idx.perm,
-                                       idx.offsets, gate, (float*)ws.dout, dgate, ws.colpart, db2, st);
+        e = launch_bwd_prologue<float>(D, (const float*)dY, gate, idx, ws, dgate, st);
         if (e == hipSuccess)
             e = launch_f32_bwd(D, (const float*)x, (const float*)W1, (const float*)W2, idx, ws, dW1, dW2, st);
         if (e == hipSuccess)
-            e = launch_tile_colsum_finish(D, ws.colpart, D.f, f32_dgrad2_row_tile(D), idx.offsets, db1, st);
-        if (e == hipSuccess) e = launch_combine_dx<float>(D, (const float*)ws.dxp, idx.inv, (float*)dx, st);
+            e = launch_bwd_finish<float>(D, idx, ws, f32_dgrad2_row_tile(D), f32_chunk_len(D), (float*)dx, dW1, db1,
+                                         dW2, db2, st);
     } else {
         const bool f16 = shape->dtype == HEXA_F16;
-        if (f16)
-            e = launch_bwd_prologue<f16_t>(D, (const f16_t*)dY, (const f16_t*)ws.o,
-                                           idx.perm, idx.offsets, gate, (f16_t*)ws.dout, dgate, ws.colpart, db2, st);
-        else
-            e = launch_bwd_prologue<bf16_t>(D, (const bf16_t*)dY, (const bf16_t*)ws.o,
-                                            idx.perm, idx.offsets, gate, (bf16_t*)ws.dout, dgate, ws.colpart, db2, st);
+        if (f16) e = launch_bwd_prologue<f16_t>(D, (const f16_t*)dY, gate, idx, ws, dgate, st);
+        else e = launch_bwd_prologue<bf16_t>(D, (const bf16_t*)dY, gate, idx, ws, dgate, st);
         if (e == hipSuccess)
             e = launch_bf16_bwd(D, (const bf16_t*)x, (const bf16_t*)W1, (const bf16_t*)W2, idx, ws,
                                 dW1, dW2, st, f16);
-        if (e == hipSuccess)
-            e = launch_tile_colsum_finish(D, ws.colpart, D.f, gemm_dgrad2_row_tile(D), idx.offsets, db1, st);
         if (e == hipSuccess) {
-            if (f16) e = launch_combine_dx<f16_t>(D, (const f16_t*)ws.dxp, idx.inv, (f16_t*)dx, st);
-            else e = launch_combine_dx<bf16_t>(D, (const bf16_t*)ws.dxp, idx.inv, (bf16_t*)dx, st);
+            const int bm = gemm_dgrad2_row_tile(D), L = wgrad_chunk_len(D);
+            if (f16) e = launch_bwd_finish<f16_t>(D, idx, ws, bm, L, (f16_t*)dx, dW1, db1, dW2, db2, st);
+            else e = launch_bwd_finish<bf16_t>(D, idx, ws, bm, L, (bf16_t*)dx, dW1, db1, dW2, db2, st);
         }
     }
     return dev(e);

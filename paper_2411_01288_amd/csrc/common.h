@@ -73,16 +73,8 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // to expert `e`, starting at perm position `row0`.
 struct SegTile { int e, row0, rows; };
 
-// Number of BM-row tiles over all expert segments (each segment tiled on its own,
-// so no tile straddles two experts and none is padded to a capacity).
-__device__ __forceinline__ int seg_tiles_total(const int32_t* __restrict__ offsets, int E, int BM) {
-    int total = 0;
-    for (int e = 0; e < E; ++e) total += ceil_div(offsets[e + 1] - offsets[e], BM);
-    return total;
-}
-
-// The same two look-ups by a whole wavefront (all 64 lanes active), an expert per lane: a scan over the lanes
-// instead of a walk over the experts, whose loads a workgroup would wait for one after the other.
+// Look-ups over the expert segments by a whole wavefront (all 64 lanes active), an expert per lane: a scan over
+// the lanes instead of a walk over the experts, whose loads a workgroup would wait for one after the other.
 // Inclusive scan over the 64 lanes with the data-parallel moves of the vector unit (within rows of 16, then
 // lane 15 of rows 0 and 2 into the row behind, then lane 31 into the upper half).
 __device__ __forceinline__ int wave_scan_incl(int v) {
@@ -94,6 +86,8 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
     return v;
 }
+// Number of BM-row tiles over the first E expert segments (each segment tiled on its own, so no tile straddles
+// two experts and none is padded to a capacity).
 __device__ __forceinline__ int seg_tiles_total_wave(const int32_t* __restrict__ offsets, int E, int BM) {
     const int lane = threadIdx.x & 63;
     int v = 0;
@@ -101,25 +95,8 @@ __device__ __forceinline__ int seg_tiles_total_wave(const int32_t* __restrict__ 
     return __builtin_amdgcn_readlane(wave_scan_incl(v), 63);
 }
 
-// Map tile number `tile` (0-based over all segments, expert-major) to its segment tile.
+// Map tile number `tile` (0-based over all segments, expert-major; wave-uniform) to its segment tile.
 // Returns e = -1 when `tile` is past the last one.
-__device__ __forceinline__ SegTile seg_tile_find(const int32_t* __restrict__ offsets, int E, int BM,
-                                                 int tile) {
-    SegTile s{-1, 0, 0};
-    int acc = 0;
-    for (int e = 0; e < E; ++e) {
-        const int b = offsets[e], n = offsets[e + 1] - b;
-        const int nt = ceil_div(n, BM);
-        if (tile < acc + nt) {
-            const int r0 = (tile - acc) * BM;
-            s.e = e; s.row0 = b + r0; s.rows = min(BM, n - r0);
-            return s;
-        }
-        acc += nt;
-    }
-    return s;
-}
-
 __device__ __forceinline__ SegTile seg_tile_find_wave(const int32_t* __restrict__ offsets, int E, int BM,
                                                       int tile) {
     const int lane = threadIdx.x & 63;
@@ -139,6 +116,60 @@ __device__ __forceinline__ SegTile seg_tile_find_wave(const int32_t* __restrict_
         acc = __builtin_amdgcn_readlane(end, 63);
     }
     return SegTile{-1, 0, 0};
+}
+
+// Token-contraction item number `item` (expert-major, then chunks of at most L rows): expert, perm rows
+// [beg, end) and, for an expert of several chunks, the number of its partial-tile buffer (-1 otherwise).
+// e = -1 past the last item; experts without rows have none.
+struct ChunkItem { int e, beg, end, slot; };
+__device__ __forceinline__ ChunkItem chunk_find_wave(const int32_t* __restrict__ offsets, int E, int L, int item) {
+    const int lane = threadIdx.x & 63;
+    int acc = 0, sacc = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        const int e = e0 + lane;
+        const int b = e < E ? offsets[e] : 0, n = e < E ? offsets[e + 1] - b : 0;
+        const int nc = ceil_div(n, L), ns = nc > 1 ? nc : 0;
+        const int end = acc + wave_scan_incl(nc), send = sacc + wave_scan_incl(ns);
+        const uint64_t hit = __ballot(end > item);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int c = item - (__builtin_amdgcn_readlane(end, src) - __builtin_amdgcn_readlane(nc, src));
+            const int beg = __builtin_amdgcn_readlane(b, src), rows = __builtin_amdgcn_readlane(n, src);
+            const int slots = __builtin_amdgcn_readlane(ns, src);
+            return ChunkItem{e0 + src, beg + c * L, beg + min(rows, c * L + L),
+                             slots ? __builtin_amdgcn_readlane(send, src) - slots + c : -1};
+        }
+        acc = __builtin_amdgcn_readlane(end, 63);
+        sacc = __builtin_amdgcn_readlane(send, 63);
+    }
+    return ChunkItem{-1, 0, 0, -1};
+}
+
+// ---- four consecutive floats of a row of any length (dword-aligned) ----
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+// the first `nv` exist (the others read as zero and are not touched)
+__device__ __forceinline__ f32x4 load4(const float* p, int nv) {
+    if (nv >= 4) return *reinterpret_cast<const f32x4u*>(p);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (nv > 0) v[0] = p[0];
+    if (nv > 1) v[1] = p[1];
+    if (nv > 2) v[2] = p[2];
+    return v;
+}
+__device__ __forceinline__ void store4(float* p, f32x4 v, int nv) {
+    if (nv >= 4) { *reinterpret_cast<f32x4u*>(p) = v; return; }
+    if (nv > 0) p[0] = v[0];
+    if (nv > 1) p[1] = v[1];
+    if (nv > 2) p[2] = v[2];
+}
+// sum over the 16 lanes of a DPP row (every lane gets it)
+__device__ __forceinline__ float row_sum16(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));   // row_ror:8
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));
+    return v;
 }
 
 // ---- optional per-kernel timing (off unless hexa_moe_profile_enable(1); bench_support.hip) ----
@@ -174,21 +205,25 @@ struct MoeWorkspace {
     void* dpre;     // [A,f] elem                                       (bwd staging)
     void* dxp;      // [A,d] elem   per-assignment input gradients     (bwd staging)
     uint32_t* rowoff; // [A + 64 E]  byte offsets in x of the token rows, in the order WGRAD1 fetches them (16-bit path; bwd staging)
-    float* colpart; // [rows, max(d,f)] f32 partial column sums          (bwd staging)
-    float* kpart;   // split-K partial weight-gradient tiles           (bwd staging)
-    size_t kpart_slots;
+    float* colpart1; // [rows, f] f32 partial column sums for db1         (bwd staging)
+    float* colpart2; // [rows, d] f32 partial column sums for db2         (bwd staging)
+    float* kpart1;  // [slots, d, f] f32 partial dW1 tiles of experts cut into chunks   (bwd staging)
+    float* kpart2;  // [slots, f, d] f32 partial dW2 tiles
     int32_t* worklist; // row tiles and token-contraction items of the bf16 kernels (saved by fwd, read by bwd)
     size_t total_bytes;
 };
 
 int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path
 int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp32 path
-int gemm_colpart_rows_per_tile();    // DGRAD2 writes this many column-sum partial rows per row tile
-int wgrad_chunk_len(const MoeDims& D);          // tokens per split-K chunk (host policy)
-size_t wgrad_max_slots(const MoeDims& D);
-size_t gemm_worklist_ints(const MoeDims& D);
-int bwd_prologue_tile_rows(const MoeDims& D);   // rows per workgroup of the fused backward prologue
-size_t colsum_partial_rows(const MoeDims& D);   // rows of MoeWorkspace::colpart the column sums need    // int32 entries of MoeWorkspace::worklist
+constexpr int kColpartRows = 2;               // DGRAD2 writes this many column-sum partial rows per row tile
+int wgrad_chunk_len(const MoeDims& D);        // tokens per split-K chunk of the 16-bit path (host policy)
+int f32_chunk_len(const MoeDims& D);          // ... of the fp32 path
+// Upper bound on the partial-tile buffers: only experts with more than one chunk of L rows use them, and the
+// sum over those of ceil(n_e / L) is at most 2 A / L.
+inline size_t split_slots(const MoeDims& D, int L) { return 2 * (size_t)(D.A / L) + 2; }
+size_t gemm_worklist_ints(const MoeDims& D);  // int32 entries of MoeWorkspace::worklist
+int gemm_rowoff_step(const MoeDims& D);       // layout of MoeWorkspace::rowoff that the launch of this shape reads
+size_t prologue_partial_rows(const MoeDims& D);   // rows of MoeWorkspace::colpart2
 
 hipError_t launch_index(const MoeDims& D, const int32_t* topk_idx, hexa_moe_idx out, void* scratch,
                         hipStream_t st);
@@ -199,24 +234,16 @@ hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int bl
 template <typename T>
 hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, const float* gate,
                             T* y, hipStream_t st);
-// dout_p = gate_a dY_t, dgate_a = <dY_t, o_p>, for a = perm[p], and
-// db2[e] = sum over the expert's rows of gate_a dY_t (ESS; `partial` is column-sum staging)
+// dout_p = gate_a dY_t, dgate_a = <dY_t, o_p>, for a = perm[p], and partial column sums of gate_a dY_t for db2
+// (ESS) in ws.colpart2; 16-bit types: also the row-offset table of WGRAD1
 template <typename T>
-hipError_t launch_bwd_prologue(const MoeDims& D, const T* dY, const T* o,
-                               const int32_t* perm, const int32_t* offsets, const float* gate,
-                               T* dout, float* dgate, float* partial, float* db2, hipStream_t st);
+hipError_t launch_bwd_prologue(const MoeDims& D, const T* dY, const float* gate, const hexa_moe_idx& idx,
+                               const MoeWorkspace& ws, float* dgate, hipStream_t st);
+// dx_t = sum over the k slots of dxp; db1, db2 from their partial rows; dW1, dW2 of the experts that were cut into
+// chunks of L rows, and zeros for experts without rows
 template <typename T>
-hipError_t launch_combine_dx(const MoeDims& D, const T* dxp, const int32_t* inv, T* dx,
-                             hipStream_t st);
-// ESS: out[e][c] = sum over the expert's rows of src[p][c]; src is [A, ncols] in perm order
-template <typename T>
-hipError_t launch_segment_colsum(const MoeDims& D, const T* src, int ncols, const int32_t* offsets,
-                                 float* partial, float* out, hipStream_t st);
-
-// second stage for column sums a DGRAD2 kernel left per (row tile of row_tile rows, wave row):
-// out[e][c] = sum of the partial rows of the expert's tiles, in tile order
-hipError_t launch_tile_colsum_finish(const MoeDims& D, const float* partial, int ncols, int row_tile,
-                                     const int32_t* offsets, float* out, hipStream_t st);
+hipError_t launch_bwd_finish(const MoeDims& D, const hexa_moe_idx& idx, const MoeWorkspace& ws, int dgrad2_row_tile,
+                             int L, T* dx, float* dW1, float* db1, float* dW2, float* db2, hipStream_t st);
 
 // fp32 path (fp32 matrix instructions)
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,

@@ -17,9 +17,6 @@
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of odd lengths: dword-aligned
-
 enum Op { F32_FC1 = 0, F32_FC2, F32_DGRAD2, F32_DGRAD1, F32_WGRAD2, F32_WGRAD1 };
 
 struct TileArgs {
@@ -28,11 +25,13 @@ struct TileArgs {
     const float* bias;     // FC1, FC2: [E][N]
     const float* pre_in;   // DGRAD2: saved pre-activations [A][N]
     float* out0;           // row GEMM: [A][N]; token contraction: [E][M][N]
+    float* kpart;          // token contraction: partial tiles [slot][M][N] of experts cut into chunks
     float* out1;           // FC1: h
     float* colpart;        // DGRAD2: column sums of its output per (row tile, wave row)
     const int32_t* perm;
     const int32_t* offsets;
     int K, N, M, E, k, act;
+    int chunk_len;         // token contraction: rows per chunk at most
 };
 
 __device__ __forceinline__ float gelu_f(float u) {
@@ -57,22 +56,6 @@ __device__ __forceinline__ float act_grad_f(float u, int act) {
         return sg * (1.f + u * (1.f - sg));
     }
     return gelu_grad_f(u);
-}
-
-// four floats of which the first `nv` exist (the others read as zero and are not touched)
-__device__ __forceinline__ f32x4 load4(const float* p, int nv) {
-    if (nv >= 4) return *reinterpret_cast<const f32x4u*>(p);
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (nv > 0) v[0] = p[0];
-    if (nv > 1) v[1] = p[1];
-    if (nv > 2) v[2] = p[2];
-    return v;
-}
-__device__ __forceinline__ void store4(float* p, f32x4 v, int nv) {
-    if (nv >= 4) { *reinterpret_cast<f32x4u*>(p) = v; return; }
-    if (nv > 0) p[0] = v[0];
-    if (nv > 1) p[1] = v[1];
-    if (nv > 2) p[2] = v[2];
 }
 
 // One operand's share of a K-block: R rows (or columns) x BK contraction elements, 256 threads, NC chunks of
@@ -104,15 +87,6 @@ struct Operand {
     }
 };
 
-// sum over the 16 lanes of a DPP row (every lane gets it)
-__device__ __forceinline__ float row_sum16(float v) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));   // row_ror:8
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));
-    return v;
-}
-
 constexpr int kXcds = 8;   // workgroup i is dispatched to XCD i % 8
 
 // LDS of a tile class: two buffers (one multiplied, one filled) of both operands.
@@ -138,10 +112,11 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
     const int l16 = lane & 15, grp = lane >> 4;
 
     // ---- which tile: an XCD takes a contiguous eighth of the row GEMM's tiles (column tiles fastest), or an
-    // eighth of every expert's tiles of a token contraction, so that its L2 holds what they share
+    // eighth of every chunk's tiles of a token contraction, so that its L2 holds what they share
     const int xcd = item % kXcds, loc = item / kXcds;
     const int tn = ceil_div(a.N, BM);
     int e, m0, n0, rows, K, kbeg = 0, row_tile = 0;
+    float* tok_out = nullptr;
     if constexpr (!TOKENS) {
         const int tiles = seg_tiles_total_wave(a.offsets, a.E, BM) * tn;
         const int per = ceil_div(tiles, kXcds);
@@ -152,11 +127,13 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
         e = s.e; m0 = s.row0; rows = s.rows; n0 = (t - row_tile * tn) * BM; K = a.K;
     } else {
         const int tmn = ceil_div(a.M, BM) * tn, per = ceil_div(tmn, kXcds);
-        e = loc / per;
         const int t = xcd * per + loc % per;
-        if (t >= tmn || e >= a.E) return;
+        if (t >= tmn) return;
+        const ChunkItem c = chunk_find_wave(a.offsets, a.E, a.chunk_len, loc / per);
+        if (c.e < 0) return;
+        e = c.e; kbeg = c.beg; K = c.end - c.beg;
         m0 = (t / tn) * BM; n0 = (t % tn) * BM; rows = min(BM, a.M - m0);
-        kbeg = a.offsets[e]; K = a.offsets[e + 1] - kbeg;
+        tok_out = c.slot >= 0 ? a.kpart + (size_t)c.slot * a.M * a.N : a.out0 + (size_t)e * a.M * a.N;
     }
     const int nk = ceil_div(K, BK);
 
@@ -272,7 +249,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
     }
 
     // ---- epilogue
-    const size_t orow0 = TOKENS ? (size_t)e * a.M + m0 : (size_t)m0;
+    float* out = TOKENS ? tok_out : a.out0;
 #pragma unroll
     for (int jj = 0; jj < FM; ++jj) {
         const int n = n0 + 16 * (wn * FM + jj) + 4 * grp, nv = a.N - n;
@@ -282,7 +259,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
         for (int i = 0; i < FM; ++i) {
             const int m = 16 * (wm * FM + i) + l16;
             if (m < rows && nv > 0) {
-                const size_t oi = (orow0 + m) * a.N + n;
+                const size_t oi = (size_t)(m0 + m) * a.N + n;
                 f32x4 v = acc[i][jj] + bias;
                 if constexpr (OP == F32_DGRAD2) {
                     const f32x4 u = load4(a.pre_in + oi, nv);
@@ -290,7 +267,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
                     for (int r = 0; r < 4; ++r) v[r] *= act_grad_f(u[r], a.act);
                     cs += v;
                 }
-                store4(a.out0 + oi, v, nv);
+                store4(out + oi, v, nv);
                 if constexpr (OP == F32_FC1) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) v[r] = act_f(v[r], a.act);
@@ -326,7 +303,7 @@ int row_items(const MoeDims& D, int bm, int N) {
     return kXcds * ceil_div((D.A / bm + D.E) * ceil_div(N, bm), kXcds);
 }
 int token_items(const MoeDims& D, int bm) {
-    return kXcds * ceil_div(ceil_div(D.d, bm) * ceil_div(D.f, bm), kXcds) * D.E;
+    return kXcds * ceil_div(ceil_div(D.d, bm) * ceil_div(D.f, bm), kXcds) * (D.A / f32_chunk_len(D) + D.E);
 }
 
 // Which class a launch takes: 64x64 tiles fetch half as much per FLOP, 32x32 tiles are four times as many and
@@ -352,6 +329,14 @@ void pair_launch(const MoeDims& D, const TileArgs& ra, const TileArgs& rb, hipSt
 
 }  // namespace
 
+// Rows per chunk of the token contractions: what makes four workgroups per CU of chunks and tiles, at least 256 (a
+// chunk costs a partial d x f tile written and read back).
+int f32_chunk_len(const MoeDims& D) {
+    const long long tiles = (long long)ceil_div(D.d, 64) * ceil_div(D.f, 64);
+    long long L = ((long long)D.A * tiles / 1024 + 63) / 64 * 64;
+    if (L < 256) L = 256;
+    return (int)(L < 0x7fffffc0 ? L : 0x7fffffc0);
+}
 int f32_dgrad2_row_tile(const MoeDims& D) { return small_rows(D, D.f) ? 32 : 64; }
 
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,
@@ -374,18 +359,18 @@ hipError_t launch_f32_bwd(const MoeDims& D, const float* x, const float* W1, con
                           const hexa_moe_idx& idx, const MoeWorkspace& ws, float* dW1, float* dW2,
                           hipStream_t st) {
     TileArgs g{};
-    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act;
+    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act; g.chunk_len = f32_chunk_len(D);
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     TileArgs r = g, t = g;
     r.A = (const float*)ws.dout; r.B = W2; r.pre_in = (const float*)ws.pre; r.out0 = (float*)ws.dpre;
-    r.colpart = ws.colpart; r.K = D.d; r.N = D.f;
-    t.A = (const float*)ws.h; t.B = (const float*)ws.dout; t.out0 = dW2; t.M = D.f; t.N = D.d;
+    r.colpart = ws.colpart1; r.K = D.d; r.N = D.f;
+    t.A = (const float*)ws.h; t.B = (const float*)ws.dout; t.out0 = dW2; t.kpart = ws.kpart2; t.M = D.f; t.N = D.d;
     if (small_rows(D, r.N)) pair_launch<1, 64, F32_DGRAD2, F32_WGRAD2>(D, r, t, st, "bwd_fc2");
     else pair_launch<2, 32, F32_DGRAD2, F32_WGRAD2>(D, r, t, st, "bwd_fc2");
     // 1st linear layer: dxp = dpre W1^T  and  dW1[e] = x[perm/k]^T dpre
     r = g; t = g;
     r.A = (const float*)ws.dpre; r.B = W1; r.out0 = (float*)ws.dxp; r.K = D.f; r.N = D.d;
-    t.A = x; t.B = (const float*)ws.dpre; t.out0 = dW1; t.M = D.d; t.N = D.f;
+    t.A = x; t.B = (const float*)ws.dpre; t.out0 = dW1; t.kpart = ws.kpart1; t.M = D.d; t.N = D.f;
     if (small_rows(D, r.N)) pair_launch<1, 64, F32_DGRAD1, F32_WGRAD1>(D, r, t, st, "bwd_fc1");
     else pair_launch<2, 32, F32_DGRAD1, F32_WGRAD1>(D, r, t, st, "bwd_fc1");
     return hipGetLastError();

@@ -49,7 +49,7 @@ struct GemmArgs {
                           // token contraction: [A][M] perm order
     const bf16_t* B;      // row GEMM: weights [E][..]; token contraction: [A][N] perm order
     const int32_t* perm;  // FC1 gather
-    const uint32_t* rowoff;  // WGRAD1 gather: byte offsets of the token rows, see build_rowoff
+    const uint32_t* rowoff;  // WGRAD1 gather: byte offsets of the token rows, written by the backward prologue
     const int32_t* offsets;
     const bf16_t* bias;   // [E][N] or NULL
     const bf16_t* pre_in; // DGRAD2: the saved GELU'(pre)
@@ -361,33 +361,6 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
         wl[WL_ORDER2] = longest >= 8 * d ? 1 : 0;
         wl[WL_ORDER1] = longest >= 8 * f ? 1 : 0;
     }
-}
-
-// Row-offset table of the gathered token contraction (WGRAD1 reads x[perm[p] / k] for perm
-// position p; ESTMM, App. B Alg. 4, takes its tokens through the re-index vector the same way).
-// Expert e's part starts at entry offsets[e] + 64 e and is cut into blocks of 64 rows (the K-blocks
-// of the contraction; a chunk starts on a block boundary); inside a block, entry (64/step) j + i
-// belongs to row step i + j, the transposed order in which a lane of the staging instructions (StageKS,
-// step = its STEP) needs them.
-// An entry is the byte offset of the token's row in x; entries past the segment's end hold `pad`,
-// an offset behind the last row of x, which the buffer range check turns into zeros.
-__global__ __launch_bounds__(256) void build_rowoff(const int32_t* __restrict__ offsets,
-                                                    const int32_t* __restrict__ perm, int E, int k,
-                                                    uint32_t row_bytes, uint32_t pad, int total, int step,
-                                                    uint32_t* __restrict__ out) {
-    const int g = blockIdx.x * 256 + threadIdx.x;
-    if (g >= total) return;
-    int lo = 0, hi = E - 1;                       // the last expert whose part starts at or before g
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offsets[mid] + 64 * mid <= g) lo = mid; else hi = mid - 1;
-    }
-    const int b = offsets[lo], n = offsets[lo + 1] - b;
-    const int local = g - (b + 64 * lo);
-    const int s = local & 63;
-    const int per = 64 / step;
-    const int r = (local & ~63) + step * (s % per) + s / per;
-    out[g] = r < n ? (uint32_t)(perm[b + r] / k) * row_bytes : pad;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1088,45 +1061,6 @@ __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pai
     else gemm_tile<BM, BN, WM, WN, OPA, HEXA_ACT_GELU_TANH, F16>(ga, local);
 }
 
-// Second stage of the split token contraction, plus exact zeros for experts without tokens.
-// out[e] = sum_c kpart[slot_e + c] in chunk order when the expert was split; untouched when it
-// had exactly one chunk (the GEMM wrote it directly).
-__global__ __launch_bounds__(256) void wgrad_finish(const int32_t* __restrict__ offsets, int E, int L,
-                                                    size_t mn, const float* __restrict__ kpart,
-                                                    float* __restrict__ out) {
-    const int e = blockIdx.y;
-    const int n = offsets[e + 1] - offsets[e];
-    const int nch = ceil_div(n, L);
-    if (nch == 1) return;
-    int slot = 0;
-    for (int q = 0; q < e; ++q) {
-        const int c = ceil_div(offsets[q + 1] - offsets[q], L);
-        if (c > 1) slot += c;
-    }
-    float4* dst = reinterpret_cast<float4*>(out + (size_t)e * mn);
-    const size_t n4 = mn / 4;
-    const size_t stride = (size_t)gridDim.x * 256;
-    // four elements per thread and pass, their loads issued together (one at a time, the few
-    // workgroups of a split expert are a chain of memory latencies)
-    for (size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x; i0 < n4; i0 += 4 * stride) {
-        float4 s[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) s[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int c = 0; c < nch; ++c) {
-            const float4* src = reinterpret_cast<const float4*>(kpart + (size_t)(slot + c) * mn);
-            float4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                v[u] = i0 + u * stride < n4 ? src[i0 + u * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { s[u].x += v[u].x; s[u].y += v[u].y; s[u].z += v[u].z; s[u].w += v[u].w; }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (i0 + u * stride < n4) dst[i0 + u * stride] = s[u];
-    }
-}
-
 constexpr int kNumCUs = 256;
 
 // Work-item slots of a row GEMM with at most tm_max row tiles and tn column tiles (a multiple of 8):
@@ -1149,26 +1083,18 @@ void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds, st, g);
 }
 
-// Row GEMM OPA and token contraction OPB of one linear layer's backward in one grid, then the
-// split-K finisher of OPB.
+// Row GEMM OPA and token contraction OPB of one linear layer's backward in one grid.
 template <int BM, int BN, int WM, int WN, int OPA, int OPB, bool F16 = false>
 void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipStream_t st,
-                 const int32_t* b_leads, const char* label, const char* label_fin) {
+                 const int32_t* b_leads, const char* label) {
     auto kern = gemm_bf16_pair<BM, BN, WM, WN, OPA, OPB, F16>;
     constexpr int lds = NSLOT * (BM > BN ? BM : BN) * ROWB;
     const int tm_max = D.A / BM + D.E;
     const int items_a = row_gemm_slots(tm_max, ceil_div(ga.N, BN), group_rows(BM));
     const int tmn = ceil_div(gb.M, BM) * ceil_div(gb.N, BN);
     const int items_b = kXcds * ceil_div(tmn, kXcds) * (D.A / gb.chunk_len + D.E);
-    {
-        ProfScope ps(st, label);
-        hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a, b_leads);
-    }
-    ProfScope ps(st, label_fin);
-    const size_t mn = (size_t)gb.M * gb.N;
-    const int gx = (int)((mn / 4 + 255) / 256 < 1024 ? (mn / 4 + 255) / 256 : 1024);
-    hipLaunchKernelGGL(wgrad_finish, dim3(gx, D.E), dim3(256), 0, st, gb.offsets, D.E, gb.chunk_len, mn,
-                       gb.kpart, reinterpret_cast<float*>(gb.out0));
+    ProfScope ps(st, label);
+    hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a, b_leads);
 }
 
 // Two tile classes.  256x256: one workgroup per CU (all of LDS, 512 registers per lane), the cheaper one
@@ -1253,9 +1179,9 @@ hipError_t gemm_bf16_device_init() {
     return e;
 }
 
-// Row-tile height and partial rows per tile of the DGRAD2 column-sum partials (for the finisher).
+// Row-tile height of the DGRAD2 column-sum partials (for the finisher).
 int gemm_dgrad2_row_tile(const MoeDims& D) { return small_bwd2(D) ? SMALL : BIG; }
-int gemm_colpart_rows_per_tile() { return 2; }
+int gemm_rowoff_step(const MoeDims& D) { return small_bwd1(D) ? StageKS<SMALL, 4>::STEP : StageKS<BIG, 4>::STEP; }
 
 // Tokens per split-K chunk of the token contractions: an expert is cut only when its rows alone
 // would give every CU a tile's worth of work for longer than the whole contraction takes on
@@ -1296,12 +1222,6 @@ static void use_items(const MoeDims& D, const MoeWorkspace& ws, GemmArgs& g) {
     g.n_items = ws.worklist + WL_ITEMS;
 }
 
-// Upper bound on split-K slots: only experts with more than one chunk use slots, and
-// sum over those of ceil(n_e / L) <= 2 A / L.
-size_t wgrad_max_slots(const MoeDims& D) {
-    return 2 * (size_t)(D.A / wgrad_chunk_len(D)) + 2;
-}
-
 template <int B, bool F16>
 static void launch_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
     if (D.act == HEXA_ACT_RELU) launch_rows<B, B, 2, 2, OP_FC1, HEXA_ACT_RELU, F16>(D, g, st, "fc1");
@@ -1334,35 +1254,28 @@ static hipError_t bwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
     const bool small2 = small_bwd2(D), small1 = small_bwd1(D);
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
-    g.kpart = ws.kpart; g.chunk_len = wgrad_chunk_len(D);
-    {   // WGRAD1's row-offset table; entries past a segment's end point behind the last row of x
-        ProfScope ps(st, "rowoff");
-        const int total = D.A + 64 * D.E;
-        const int step = small1 ? StageKS<SMALL, 4>::STEP : StageKS<BIG, 4>::STEP;
-        hipLaunchKernelGGL(build_rowoff, dim3(ceil_div(total, 256)), dim3(256), 0, st, idx.offsets, idx.perm,
-                           D.E, D.k, (uint32_t)D.d * 2u, (uint32_t)D.T * (uint32_t)D.d * 2u, total, step, ws.rowoff);
-    }
+    g.chunk_len = wgrad_chunk_len(D);
     // the work lists are the ones the forward pass built (part of the state it saves in the workspace)
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     GemmArgs r = g, t = g;
     r.A = (const bf16_t*)ws.dout; r.B = W2; r.pre_in = (const bf16_t*)ws.pre; r.out0 = ws.dpre;
-    r.colpart = ws.colpart; r.K = D.d; r.N = D.f;
-    t.A = (const bf16_t*)ws.h; t.B = (const bf16_t*)ws.dout; t.out0 = dW2; t.M = D.f; t.N = D.d;
+    r.colpart = ws.colpart1; r.K = D.d; r.N = D.f;
+    t.A = (const bf16_t*)ws.h; t.B = (const bf16_t*)ws.dout; t.out0 = dW2; t.kpart = ws.kpart2; t.M = D.f; t.N = D.d;
     use_row_tiles(D, ws, small2, r);
     use_items(D, ws, t);
     const int32_t* lead2 = ws.worklist + WL_ORDER2;
-    if (small2) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2", "wgrad2_finish");
-    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2", "wgrad2_finish");
+    if (small2) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2");
     // 1st linear layer: dxp = dpre W1^T  and  dW1[e] = x[perm/k]^T dpre
     r = g; t = g;
     r.A = (const bf16_t*)ws.dpre; r.B = W1; r.out0 = ws.dxp; r.K = D.f; r.N = D.d;
     t.A = x; t.a_rows = D.T; t.rowoff = ws.rowoff;
-    t.B = (const bf16_t*)ws.dpre; t.out0 = dW1; t.M = D.d; t.N = D.f;
+    t.B = (const bf16_t*)ws.dpre; t.out0 = dW1; t.kpart = ws.kpart1; t.M = D.d; t.N = D.f;
     use_row_tiles(D, ws, small1, r);
     use_items(D, ws, t);
     const int32_t* lead1 = ws.worklist + WL_ORDER1;
-    if (small1) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1", "wgrad1_finish");
-    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1", "wgrad1_finish");
+    if (small1) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1");
     return hipGetLastError();
 }
 
