@@ -252,8 +252,8 @@ def main():
     achieved = rates[dom]
     counts = idx["counts"].cpu().numpy()
     ksum = lambda names: sum(kernels[k]["ms"] * kernels[k]["launches"] for k in names if k in kernels) / args.steps
-    idx_ms = ksum(["index_count", "index_scan", "index_scatter"])
-    fwd_ms = ksum(["fc1", "fc2", "combine_y"]) + 0.5 * ksum(["worklists"])
+    idx_ms = ksum(["index_count", "index_scatter"])
+    fwd_ms = ksum(["worklists", "fc1", "fc2", "combine_y"])
     all_ms = ksum(list(kernels))
     out = {
         "metric": METRIC, "value": tflops, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,

@@ -209,7 +209,7 @@ struct MoeWorkspace {
     float* colpart2; // [rows, d] f32 partial column sums for db2         (bwd staging)
     float* kpart1;  // [slots, d, f] f32 partial dW1 tiles of experts cut into chunks   (bwd staging)
     float* kpart2;  // [slots, f, d] f32 partial dW2 tiles
-    int32_t* worklist; // row tiles and token-contraction items of the bf16 kernels (saved by fwd, read by bwd)
+    int32_t* worklist; // tiles and items of the 256x256 contraction kernels (saved by fwd, read by bwd)
     size_t total_bytes;
 };
 

@@ -60,10 +60,8 @@ struct GemmArgs {
     int topk, E, K, N, M;
     int a_rows;           // FC1: rows of the gathered operand (tokens T)
     int chunk_len;        // token contraction: max tokens per work item
-    const int32_t* row_tiles; // row GEMM: its row tiles and their number (see build_worklists)
-    const int32_t* n_row_tiles;
-    const int32_t* items;     // token contraction: its items and their number
-    const int32_t* n_items;
+    const int32_t* lists; // 256x256 tiles: the work lists (see build_worklists)
+    int rt_cap;           // their capacity in row tiles
 };
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -272,26 +270,23 @@ __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& til
     tile_n = in / gsz;
 }
 
-// Work lists, built once per forward call from the segment offsets (the backward pass reads the same
-// lists: they are part of what the forward pass leaves in the workspace), so that a
-// workgroup finds its tile with two scalar loads instead of a walk over all experts (which cost a
-// 256x256 tile of a d = 2048 contraction about a tenth of its time, with the CU idle meanwhile).
-//   header (kWlHeader ints): number of 256-row tiles, of 128-row tiles, of token-contraction items;
-//       then 1 or 0: the fused backward grid of the second / first linear layer starts with its
-//       token contraction (see gemm_bf16_pair)
-//   row tiles of 256 rows, of 128 rows, four ints each:  expert, first perm row, rows, unused
-//   items, four ints each:                               expert, first perm row, end perm row, split-K slot
-// Row tiles are numbered expert-major (tiles never straddle experts; experts without rows have
-// none).  Items are numbered expert-major then chunk: item i covers at most L rows of one expert;
-// slot >= 0 numbers the partial tile buffer of an expert that was cut into several chunks, -1
-// means the expert is one chunk and its tile goes straight to the output.
-enum WlHeader { WL_TILES256 = 0, WL_TILES128, WL_ITEMS, WL_ORDER2, WL_ORDER1 };
+// Which tile a workgroup works on follows from the segment offsets alone.  Rows are cut into tiles numbered
+// expert-major (tiles never straddle experts; experts without rows have none); the items of a token contraction
+// are numbered expert-major, then chunk: at most L rows of one expert each, with the number of the partial-tile
+// buffer of an expert that was cut into several chunks (-1: one chunk, its tile goes straight to the output).
+//
+// 256x256 tiles take theirs from work lists: with one workgroup per CU nothing hides the look-up, two scalar
+// loads are the shortest, and the launch that builds the lists (once per forward call; the backward pass reads the same
+// ones, they are part of what the forward pass leaves in the workspace) is small beside theirs.
+//   header (kWlHeader ints): number of row tiles, of token-contraction items; then 1 or 0: the fused backward
+//       grid of the second / first linear layer starts with its token contraction (see gemm_bf16_pair)
+//   row tiles, then items, four ints each:  expert, first perm row, end perm row, partial buffer
+enum WlHeader { WL_TILES = 0, WL_ITEMS, WL_ORDER2, WL_ORDER1 };
 constexpr int kWlHeader = 8;
 
 __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restrict__ offsets, int E,
-                                                        int L, int32_t* __restrict__ wl,
-                                                        int rt_cap256, int rt_cap128, int d, int f) {
-    constexpr int NQ = 4;                      // 256-row tiles, 128-row tiles, items, split-K slots
+                                                        int L, int32_t* __restrict__ wl, int rt_cap, int d, int f) {
+    constexpr int NQ = 3;                      // row tiles, items, partial buffers
     __shared__ int s_end[NQ][1024];            // inclusive sums over the experts
     __shared__ int s_off[1025];
     __shared__ int s_wave[NQ + 1][16];
@@ -299,20 +294,12 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
     int n = 0, b = 0;
     if (e < E) { b = offsets[e]; n = offsets[e + 1] - b; }
     const int nc = ceil_div(n, L);
-    int v[NQ] = {ceil_div(n, 256), ceil_div(n, 128), nc, nc > 1 ? nc : 0};
+    int v[NQ] = {wave_scan_incl(ceil_div(n, 256)), wave_scan_incl(nc), wave_scan_incl(nc > 1 ? nc : 0)};
     int longest = min(L, n);
     s_off[e] = b;
     if (e == E - 1) s_off[E] = b + n;
-    // inclusive scans: inside each wavefront by shuffles, the wavefronts' sums through LDS
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int u = __shfl_up(v[q], off);
-            if (lane >= off) v[q] += u;
-        }
-        longest = max(longest, __shfl_xor(longest, off));
-    }
+    for (int off = 1; off < 64; off <<= 1) longest = max(longest, __shfl_xor(longest, off));
     if (lane == 63) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) s_wave[q][wave] = v[q];
@@ -334,22 +321,17 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
         }
         return lo;
     };
-    int4* tiles256 = reinterpret_cast<int4*>(wl + kWlHeader);
-    int4* tiles128 = tiles256 + rt_cap256;
-    int4* items = tiles128 + rt_cap128;
-    for (int q = 0; q < 2; ++q) {
-        const int bm = q == 0 ? 256 : 128;
-        int4* dst = q == 0 ? tiles256 : tiles128;
-        for (int i = e; i < s_end[q][E - 1]; i += 1024) {
-            const int x = find(q, i);
-            const int r0 = (i - (x > 0 ? s_end[q][x - 1] : 0)) * bm;
-            dst[i] = make_int4(x, s_off[x] + r0, min(bm, s_off[x + 1] - s_off[x] - r0), 0);
-        }
+    int4* tiles = reinterpret_cast<int4*>(wl + kWlHeader);
+    int4* items = tiles + rt_cap;
+    for (int i = e; i < s_end[0][E - 1]; i += 1024) {
+        const int x = find(0, i);
+        const int r0 = s_off[x] + (i - (x > 0 ? s_end[0][x - 1] : 0)) * 256;
+        tiles[i] = make_int4(x, r0, min(s_off[x + 1], r0 + 256), -1);
     }
-    for (int i = e; i < s_end[2][E - 1]; i += 1024) {
-        const int x = find(2, i);
-        const int first = x > 0 ? s_end[2][x - 1] : 0, c = i - first;
-        const int slot = s_end[2][x] - first > 1 ? (x > 0 ? s_end[3][x - 1] : 0) + c : -1;
+    for (int i = e; i < s_end[1][E - 1]; i += 1024) {
+        const int x = find(1, i);
+        const int first = x > 0 ? s_end[1][x - 1] : 0, c = i - first;
+        const int slot = s_end[1][x] - first > 1 ? (x > 0 ? s_end[2][x - 1] : 0) + c : -1;
         items[i] = make_int4(x, s_off[x] + c * L, min(s_off[x + 1], s_off[x] + c * L + L), slot);
     }
     if (e == 0) {
@@ -357,10 +339,117 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
         // contraction when that item runs at least eight times as long as a tile of the row GEMM it
         // shares the grid with (K = d for the second layer's, K = f for the first layer's)
         for (int w = 1; w < 16; ++w) longest = max(longest, s_wave[NQ][w]);
-        wl[WL_TILES256] = s_end[0][E - 1]; wl[WL_TILES128] = s_end[1][E - 1]; wl[WL_ITEMS] = s_end[2][E - 1];
+        wl[WL_TILES] = s_end[0][E - 1]; wl[WL_ITEMS] = s_end[1][E - 1];
         wl[WL_ORDER2] = longest >= 8 * d ? 1 : 0;
         wl[WL_ORDER1] = longest >= 8 * f ? 1 : 0;
     }
+}
+
+// 128x128 tiles are found by every wavefront for itself: a lane takes EPL consecutive experts, a scan over the
+// lanes numbers their tiles, and all offsets arrive in one memory latency.  It costs a workgroup a few hundred
+// instructions that the CU's second workgroup hides, and saves the launch that would build a list (5 us of a
+// 70 us decode step; used for 256x256 tiles too it cost their contractions 1 to 3 %).
+template <int EPL>
+struct ExpertLanes {
+    int b[EPL + 1];                            // segment starts of this lane's experts, and the end of the last
+    __device__ __forceinline__ ExpertLanes(const int32_t* __restrict__ offsets, int E) {
+        const int e0 = (int)(threadIdx.x & 63) * EPL;
+#pragma unroll
+        for (int q = 0; q <= EPL; ++q) b[q] = offsets[min(e0 + q, E)];
+    }
+    // number of pieces of at most `len` rows: inclusive scan over the lanes
+    __device__ __forceinline__ int pieces(int len, int& mine) const {
+        mine = 0;
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) mine += ceil_div(b[q + 1] - b[q], len);
+        return wave_scan_incl(mine);
+    }
+    // piece number i (wave-uniform, below the total): expert, first row, end row, and the number of partial
+    // buffers of the experts in front that have several pieces plus the piece's own (-1: the expert's only one)
+    __device__ __forceinline__ ChunkItem find(int i, int len, int incl, int mine) const {
+        int slots = 0;
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) {
+            const int n = ceil_div(b[q + 1] - b[q], len);
+            slots += n > 1 ? n : 0;
+        }
+        int at = incl - mine, slot = wave_scan_incl(slots) - slots;
+        ChunkItem r{0, 0, 0, -1};
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) {
+            const int n = ceil_div(b[q + 1] - b[q], len), c = i - at;
+            if (c >= 0 && c < n) {
+                r.e = (int)(threadIdx.x & 63) * EPL + q;
+                r.beg = b[q] + c * len;
+                r.end = min(b[q + 1], r.beg + len);
+                r.slot = n > 1 ? slot + c : -1;
+            }
+            at += n;
+            slot += n > 1 ? n : 0;
+        }
+        const int src = __ffsll((long long)__ballot(incl > i)) - 1;
+        return ChunkItem{__builtin_amdgcn_readlane(r.e, src), __builtin_amdgcn_readlane(r.beg, src),
+                         __builtin_amdgcn_readlane(r.end, src), __builtin_amdgcn_readlane(r.slot, src)};
+    }
+};
+
+// Item `item` of a row GEMM (slot i is dispatched to XCD i % 8): groups of GM row tiles x all column tiles are
+// dealt round-robin to the XCDs, so the 8 XCDs work on neighbouring row tiles (mostly one expert) at any time;
+// the last ngroups % 8 groups are cut in eight instead, every XCD taking an eighth of each, so that no XCD is a
+// whole group behind the others at the end.  False: no tile.
+template <int GM>
+__device__ __forceinline__ bool row_tile_of(int item, int tm_total, int tn, int& tile_m, int& tile_n) {
+    const int per_group = GM * tn;
+    const int ngroups = ceil_div(tm_total, GM);
+    const int xcd = item % kXcds, loc = item / kXcds;
+    // rounds of eight whole groups; with many groups the last, partial round is dealt whole
+    // as well (an XCD's CUs finish their tiles one tile-time apart either way, and whole
+    // groups keep their L2 locality), with few the balance matters more
+    const int whole = ngroups >= kSplitBelow ? ceil_div(ngroups, kXcds) : ngroups / kXcds;
+    int group, within;
+    if (loc < whole * per_group) {
+        group = (loc / per_group) * kXcds + xcd;
+        if (group >= ngroups) return false;
+        within = loc % per_group;
+    } else {
+        const int per8 = ceil_div(per_group, kXcds);
+        const int l2 = loc - whole * per_group;
+        group = whole * kXcds + l2 / per8;
+        if (group >= ngroups) return false;
+        const int gtiles = min(GM, tm_total - group * GM) * tn;
+        const int share = ceil_div(gtiles, kXcds);    // this XCD's tiles of the group
+        if (l2 % per8 >= share) return false;
+        within = xcd * share + l2 % per8;
+    }
+    const int first = group * GM;
+    const int gsz = min(GM, tm_total - first);
+    if (within >= gsz * tn) return false;
+    tile_m = first + within % gsz;
+    tile_n = within / gsz;
+    return true;
+}
+
+__device__ __forceinline__ ChunkItem list_entry(const int32_t* p) {
+    const i32x4 v = *reinterpret_cast<const i32x4*>(p);
+    return ChunkItem{v.x, v.y, v.z, v.w};
+}
+template <int EPL, int BM>
+__device__ __forceinline__ bool pick_row_tile(const GemmArgs& g, int item, int tn, ChunkItem& it, int& tile_m, int& tile_n) {
+    const ExpertLanes<EPL> x(g.offsets, g.E);
+    int mine;
+    const int incl = x.pieces(BM, mine);
+    if (!row_tile_of<group_rows(BM)>(item, __builtin_amdgcn_readlane(incl, 63), tn, tile_m, tile_n)) return false;
+    it = x.find(tile_m, BM, incl, mine);
+    return true;
+}
+template <int EPL>
+__device__ __forceinline__ bool pick_chunk(const GemmArgs& g, int i, ChunkItem& it) {
+    const ExpertLanes<EPL> x(g.offsets, g.E);
+    int mine;
+    const int incl = x.pieces(g.chunk_len, mine);
+    if (i >= __builtin_amdgcn_readlane(incl, 63)) return false;
+    it = x.find(i, g.chunk_len, incl, mine);
+    return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -393,44 +482,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     int kbeg = 0, kend = 0;           // token contraction: perm rows of this item
     float* tok_out = nullptr;         // token contraction: where the tile goes
     if constexpr (!TOKENS) {
-        const int tm_total = *g.n_row_tiles;
         const int tn = ceil_div(g.N, BN);
         int tile_m, tile_n;
-        {   // groups of GM row tiles x all column tiles are dealt round-robin to the XCDs, so
-            // the 8 XCDs work on neighbouring row tiles (mostly one expert) at any time; the last
-            // ngroups % 8 groups are cut in eight instead, every XCD taking an eighth of each, so
-            // that no XCD is a whole group behind the others at the end
-            const int per_group = GM * tn;
-            const int ngroups = ceil_div(tm_total, GM);
-            const int xcd = item % kXcds, loc = item / kXcds;
-            // rounds of eight whole groups; with many groups the last, partial round is dealt whole
-            // as well (an XCD's CUs finish their tiles one tile-time apart either way, and whole
-            // groups keep their L2 locality), with few the balance matters more
-            const int whole = ngroups >= kSplitBelow ? ceil_div(ngroups, kXcds) : ngroups / kXcds;
-            int group, within, share;
-            if (loc < whole * per_group) {
-                group = (loc / per_group) * kXcds + xcd;
-                if (group >= ngroups) return;
-                within = loc % per_group;
-                share = per_group;
-            } else {
-                const int per8 = ceil_div(per_group, kXcds);
-                const int l2 = loc - whole * per_group;
-                group = whole * kXcds + l2 / per8;
-                if (group >= ngroups) return;
-                const int gtiles = min(GM, tm_total - group * GM) * tn;
-                share = ceil_div(gtiles, kXcds);          // this XCD's tiles of the group
-                if (l2 % per8 >= share) return;
-                within = xcd * share + l2 % per8;
-            }
-            const int first = group * GM;
-            const int gsz = min(GM, tm_total - first);
-            if (within >= gsz * tn) return;
-            tile_m = first + within % gsz;
-            tile_n = within / gsz;
+        ChunkItem it;
+        if constexpr (BM == 256) {
+            if (!row_tile_of<GM>(item, g.lists[WL_TILES], tn, tile_m, tile_n)) return;
+            it = list_entry(g.lists + kWlHeader + 4 * tile_m);
+        } else {
+            if (!(g.E <= 64 ? pick_row_tile<1, BM>(g, item, tn, it, tile_m, tile_n)
+                  : g.E <= 256 ? pick_row_tile<4, BM>(g, item, tn, it, tile_m, tile_n)
+                               : pick_row_tile<16, BM>(g, item, tn, it, tile_m, tile_n))) return;
         }
-        const i32x4 rt = *reinterpret_cast<const i32x4*>(g.row_tiles + 4 * tile_m);
-        e = rt.x; m0 = rt.y; mvalid = rt.z; n0 = tile_n * BN; row_tile = tile_m;
+        e = it.e; m0 = it.beg; mvalid = it.end - it.beg; n0 = tile_n * BN; row_tile = tile_m;
         nk = g.K / BK;
     } else {
         // every (expert, chunk) item is a set of tm*tn tiles over the same tokens; each XCD takes
@@ -442,15 +505,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         const int xcd = item % kXcds, loc = item / kXcds;
         const int tile = xcd * per + loc % per;
         if (tile >= tmn) return;
-        if (loc / per >= *g.n_items) return;
-        const i32x4 it = *reinterpret_cast<const i32x4*>(g.items + 4 * (loc / per));
+        ChunkItem it;
+        if constexpr (BM == 256) {
+            if (loc / per >= g.lists[WL_ITEMS]) return;
+            it = list_entry(g.lists + kWlHeader + 4 * (g.rt_cap + loc / per));
+        } else {
+            if (!(g.E <= 64 ? pick_chunk<1>(g, loc / per, it)
+                  : g.E <= 256 ? pick_chunk<4>(g, loc / per, it) : pick_chunk<16>(g, loc / per, it))) return;
+        }
         int tile_m, tile_n;
         grouped_tile<GM>(tile, tm, tn, tile_m, tile_n);
-        e = it.x; m0 = tile_m * BM; n0 = tile_n * BN; mvalid = min(BM, g.M - m0);
-        kbeg = it.y; kend = it.z;
+        e = it.e; m0 = tile_m * BM; n0 = tile_n * BN; mvalid = min(BM, g.M - m0);
+        kbeg = it.beg; kend = it.end;
         nk = ceil_div(kend - kbeg, BK);
-        tok_out = (it.w >= 0) ? g.kpart + (size_t)it.w * g.M * g.N
-                              : reinterpret_cast<float*>(g.out0) + (size_t)e * g.M * g.N;
+        tok_out = (it.slot >= 0) ? g.kpart + (size_t)it.slot * g.M * g.N
+                                 : reinterpret_cast<float*>(g.out0) + (size_t)e * g.M * g.N;
     }
     const int nvalid = min(BN, g.N - n0);
 
@@ -1048,13 +1117,20 @@ __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16(Gem
 // are multiples of 8 (XCD mapping).  Workgroups start roughly in slot order, so the contraction
 // with the longer tiles should come first: normally the row GEMM OPA (slots [0, items_a)), but the
 // token contraction OPB when routing is so skewed that one expert's chunk runs many times longer
-// than a row-GEMM tile (flag `order` of the work-list header, set by build_worklists; with Zipf
-// routing at C5's shape the largest expert's tiles run 1582 K-blocks against 32 or 128).
+// than a row-GEMM tile, eight times or more (with Zipf routing at C5's shape the largest expert's tiles run
+// 1582 K-blocks against 32 or 128).
 template <int BM, int BN, int WM, int WN, int OPA, int OPB, bool F16 = false>
-__global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pair(GemmArgs ga, GemmArgs gb, int items_a, const int32_t* b_leads) {
+__global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pair(GemmArgs ga, GemmArgs gb, int items_a) {
     const int item = (int)blockIdx.x;
     const int items_b = (int)gridDim.x - items_a;
-    const bool b_first = *b_leads != 0;
+    bool b_first = false;
+    if constexpr (BM == 256) {
+        b_first = ga.lists[OPA == OP_DGRAD2 ? WL_ORDER2 : WL_ORDER1] != 0;
+    } else {
+        int longest = 0;                        // rows of the longest token-contraction item
+        for (int e = (int)(threadIdx.x & 63); e < gb.E; e += 64) longest = max(longest, gb.offsets[e + 1] - gb.offsets[e]);
+        b_first = __any(min(longest, gb.chunk_len) >= 8 * ga.K) != 0;
+    }
     const bool is_b = b_first ? item < items_b : item >= items_a;
     const int local = b_first ? (is_b ? item : item - items_b) : (is_b ? item - items_a : item);
     if (is_b) gemm_tile<BM, BN, WM, WN, OPB, HEXA_ACT_GELU_TANH, F16>(gb, local);
@@ -1085,8 +1161,7 @@ void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char
 
 // Row GEMM OPA and token contraction OPB of one linear layer's backward in one grid.
 template <int BM, int BN, int WM, int WN, int OPA, int OPB, bool F16 = false>
-void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipStream_t st,
-                 const int32_t* b_leads, const char* label) {
+void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipStream_t st, const char* label) {
     auto kern = gemm_bf16_pair<BM, BN, WM, WN, OPA, OPB, F16>;
     constexpr int lds = NSLOT * (BM > BN ? BM : BN) * ROWB;
     const int tm_max = D.A / BM + D.E;
@@ -1094,7 +1169,7 @@ void launch_pair(const MoeDims& D, const GemmArgs& ga, const GemmArgs& gb, hipSt
     const int tmn = ceil_div(gb.M, BM) * ceil_div(gb.N, BN);
     const int items_b = kXcds * ceil_div(tmn, kXcds) * (D.A / gb.chunk_len + D.E);
     ProfScope ps(st, label);
-    hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a, b_leads);
+    hipLaunchKernelGGL(kern, dim3(items_a + items_b), dim3(WM * WN * 64), lds, st, ga, gb, items_a);
 }
 
 // Two tile classes.  256x256: one workgroup per CU (all of LDS, 512 registers per lane), the cheaper one
@@ -1201,25 +1276,14 @@ int wgrad_chunk_len(const MoeDims& D) {
     return (int)L;
 }
 
-// Capacities of the work lists (see build_worklists): row tiles, token-contraction items.
-static size_t worklist_rt_cap(const MoeDims& D, int bm) { return (size_t)(D.A / bm + D.E); }
-static size_t worklist_it_cap(const MoeDims& D) { return (size_t)(D.A / wgrad_chunk_len(D) + D.E); }
+// Capacity of the work lists: row tiles, token-contraction items.
+static size_t worklist_rt_cap(const MoeDims& D) { return (size_t)(D.A / BIG + D.E); }
 size_t gemm_worklist_ints(const MoeDims& D) {
-    return kWlHeader + 4 * (worklist_rt_cap(D, BIG) + worklist_rt_cap(D, SMALL) + worklist_it_cap(D));
+    return kWlHeader + 4 * (worklist_rt_cap(D) + (size_t)(D.A / wgrad_chunk_len(D) + D.E));
 }
-static void launch_worklists(const MoeDims& D, const hexa_moe_idx& idx, const MoeWorkspace& ws, hipStream_t st) {
-    ProfScope ps(st, "worklists");
-    hipLaunchKernelGGL(build_worklists, dim3(1), dim3(1024), 0, st, idx.offsets, D.E,
-                       wgrad_chunk_len(D), ws.worklist, (int)worklist_rt_cap(D, BIG), (int)worklist_rt_cap(D, SMALL), D.d, D.f);
-}
-// Points a contraction's arguments at its part of the work lists.
-static void use_row_tiles(const MoeDims& D, const MoeWorkspace& ws, bool small, GemmArgs& g) {
-    g.row_tiles = ws.worklist + kWlHeader + (small ? 4 * worklist_rt_cap(D, BIG) : 0);
-    g.n_row_tiles = ws.worklist + (small ? WL_TILES128 : WL_TILES256);
-}
-static void use_items(const MoeDims& D, const MoeWorkspace& ws, GemmArgs& g) {
-    g.items = ws.worklist + kWlHeader + 4 * (worklist_rt_cap(D, BIG) + worklist_rt_cap(D, SMALL));
-    g.n_items = ws.worklist + WL_ITEMS;
+static void use_lists(const MoeDims& D, const MoeWorkspace& ws, GemmArgs& g) {
+    g.lists = ws.worklist;
+    g.rt_cap = (int)worklist_rt_cap(D);
 }
 
 template <int B, bool F16>
@@ -1235,13 +1299,17 @@ static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
                            const MoeWorkspace& ws, hipStream_t st) {
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
-    launch_worklists(D, idx, ws, st);
+    use_lists(D, ws, g);
+    // the backward pass that may follow reads the lists too
+    if (!(small_fc1(D) && small_fc2(D) && small_bwd2(D) && small_bwd1(D))) {
+        ProfScope ps(st, "worklists");
+        hipLaunchKernelGGL(build_worklists, dim3(1), dim3(1024), 0, st, idx.offsets, D.E, wgrad_chunk_len(D),
+                           ws.worklist, g.rt_cap, D.d, D.f);
+    }
     g.A = x; g.a_rows = D.T; g.B = W1; g.bias = b1; g.out0 = ws.pre; g.out1 = ws.h; g.K = D.d; g.N = D.f;
-    use_row_tiles(D, ws, small_fc1(D), g);
     if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
     else launch_fc1<BIG, F16>(D, g, st);
     g.A = (const bf16_t*)ws.h; g.B = W2; g.bias = b2; g.out0 = ws.o; g.out1 = nullptr; g.K = D.f; g.N = D.d;
-    use_row_tiles(D, ws, small_fc2(D), g);
     if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     else launch_rows<BIG, BIG, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     return hipGetLastError();
@@ -1254,28 +1322,22 @@ static hipError_t bwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
     const bool small2 = small_bwd2(D), small1 = small_bwd1(D);
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
+    use_lists(D, ws, g);
     g.chunk_len = wgrad_chunk_len(D);
-    // the work lists are the ones the forward pass built (part of the state it saves in the workspace)
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     GemmArgs r = g, t = g;
     r.A = (const bf16_t*)ws.dout; r.B = W2; r.pre_in = (const bf16_t*)ws.pre; r.out0 = ws.dpre;
     r.colpart = ws.colpart1; r.K = D.d; r.N = D.f;
     t.A = (const bf16_t*)ws.h; t.B = (const bf16_t*)ws.dout; t.out0 = dW2; t.kpart = ws.kpart2; t.M = D.f; t.N = D.d;
-    use_row_tiles(D, ws, small2, r);
-    use_items(D, ws, t);
-    const int32_t* lead2 = ws.worklist + WL_ORDER2;
-    if (small2) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2");
-    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, lead2, "bwd_fc2");
+    if (small2) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, "bwd_fc2");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>(D, r, t, st, "bwd_fc2");
     // 1st linear layer: dxp = dpre W1^T  and  dW1[e] = x[perm/k]^T dpre
     r = g; t = g;
     r.A = (const bf16_t*)ws.dpre; r.B = W1; r.out0 = ws.dxp; r.K = D.f; r.N = D.d;
     t.A = x; t.a_rows = D.T; t.rowoff = ws.rowoff;
     t.B = (const bf16_t*)ws.dpre; t.out0 = dW1; t.kpart = ws.kpart1; t.M = D.d; t.N = D.f;
-    use_row_tiles(D, ws, small1, r);
-    use_items(D, ws, t);
-    const int32_t* lead1 = ws.worklist + WL_ORDER1;
-    if (small1) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1");
-    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, lead1, "bwd_fc1");
+    if (small1) launch_pair<SMALL, SMALL, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, "bwd_fc1");
+    else launch_pair<BIG, BIG, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>(D, r, t, st, "bwd_fc1");
     return hipGetLastError();
 }
 

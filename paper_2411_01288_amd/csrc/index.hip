@@ -3,16 +3,19 @@
 // The paper scatters token ids with one global atomicAdd per token, which makes
 // the order inside an expert's segment depend on scheduling.  Here the result is
 // the unique stable counting sort of the flat assignment ids, built without any
-// order-dependent atomic:
-//   1. index_count   each wavefront owns a contiguous run of ids and histograms
-//                    it in LDS (integer adds commute, so the counts are exact);
-//   2. index_scan    one workgroup turns the [chunk][expert] histogram into
-//                    counts, offsets and, per chunk and expert, the first output
-//                    position (expert-major, chunk-minor exclusive scan);
-//   3. index_scatter each wavefront re-reads its run 64 ids at a time; the rank
-//                    of an id among equal experts in its row comes from
-//                    ballot + popcount of the lower lanes, rows are chained
-//                    through a per-wave LDS cursor.
+// order-dependent atomic.  A workgroup owns a contiguous chunk of ids, each of its
+// wavefronts a contiguous run of the chunk:
+//   1. index_count    (more than one chunk) histograms a chunk (integer adds
+//                     commute, so the counts are exact);
+//   2. index_scatter  every workgroup adds up the chunks' histograms for itself:
+//                     totals (-> offsets) and the share in front of its own chunk;
+//                     it counts its wavefronts' runs, which gives each wavefront
+//                     its first output position per expert, and re-reads its ids
+//                     64 at a time: the rank of an id among equal experts in its
+//                     row comes from one ballot per bit of the expert id, rows are
+//                     chained through a per-wavefront LDS cursor.
+// Bound by launches and by the chain of latencies inside them, not by bytes (3 MB at
+// 262144 ids), hence as few launches as possible.
 // Segments carry no padding: tiles are cut per segment by the consumers.
 #include "common.h"
 
@@ -20,156 +23,159 @@
 
 namespace {
 
-constexpr int kWavesPerWg = 4;
-constexpr int kMaxChunks = 1024;
+// Chunks: one up to kOneChunk ids (a single workgroup, a single launch), else at most kMaxChunks.
+constexpr int kOneChunk = 8192;
+constexpr int kMaxChunks = 128;
 
-struct IndexPlan { int rows_per_wave, nchunks; };
+struct IndexPlan { int waves, chunk, nchunks; };   // wavefronts per workgroup, ids per chunk
 
-IndexPlan plan_for(int A) {
+IndexPlan plan_for(const MoeDims& D) {
     IndexPlan p;
-    p.rows_per_wave = (A + 64 * kMaxChunks - 1) / (64 * kMaxChunks);
-    if (p.rows_per_wave < 1) p.rows_per_wave = 1;
-    p.nchunks = (A + 64 * p.rows_per_wave - 1) / (64 * p.rows_per_wave);
+    p.waves = D.E <= 512 ? 16 : 8;   // (a wavefront's histogram is E words of LDS)
+    const long long unit = 64 * p.waves;
+    const long long want = D.A <= kOneChunk ? D.A : (D.A + kMaxChunks - 1) / kMaxChunks;
+    const long long chunk = (want + unit - 1) / unit * unit;
+    p.chunk = (int)chunk;
+    p.nchunks = (int)((D.A + chunk - 1) / chunk);
     return p;
 }
 
-__global__ __launch_bounds__(256) void index_count(const int32_t* __restrict__ idx, int A, int E,
-                                                   int R, int nchunks, int32_t* __restrict__ hist) {
-    extern __shared__ int32_t lh[];  // [4][E]
-    for (int i = threadIdx.x; i < kWavesPerWg * E; i += 256) lh[i] = 0;
+__global__ __launch_bounds__(1024) void index_count(const int32_t* __restrict__ idx, int A, int E,
+                                                    int chunk, int32_t* __restrict__ hist) {
+    extern __shared__ int32_t lh[];  // [E]
+    for (int i = threadIdx.x; i < E; i += blockDim.x) lh[i] = 0;
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int chunk = blockIdx.x * kWavesPerWg + wave;
-    if (chunk < nchunks) {
-        const int a0 = chunk * 64 * R;
-        for (int r = 0; r < R; ++r) {
-            const int a = a0 + r * 64 + lane;
-            if (a < A) {
-                const int e = idx[a];
-                if ((unsigned)e < (unsigned)E) atomicAdd(&lh[wave * E + e], 1);
-            }
-        }
+    const long long a0 = (long long)blockIdx.x * chunk;
+    for (int i = threadIdx.x; i < chunk; i += blockDim.x) {
+        const long long a = a0 + i;
+        const int e = a < A ? idx[a] : -1;
+        if ((unsigned)e < (unsigned)E) atomicAdd(&lh[e], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kWavesPerWg * E; i += 256) {
-        const int c = blockIdx.x * kWavesPerWg + i / E;
-        if (c < nchunks) hist[(size_t)c * E + i % E] = lh[i];
-    }
+    for (int i = threadIdx.x; i < E; i += blockDim.x) hist[(size_t)blockIdx.x * E + i] = lh[i];
 }
 
-// hist[c][e] (counts) -> hist[c][e] (first output position of chunk c's ids of expert e)
-__global__ __launch_bounds__(1024) void index_scan(int32_t* __restrict__ hist, int E, int nchunks,
-                                                   int32_t* __restrict__ counts,
-                                                   int32_t* __restrict__ offsets) {
-    __shared__ int32_t gs[1024];   // [G][E] group sums, then exclusive group bases
-    __shared__ int32_t cnt[1024];  // counts, then offsets
-    const int G = max(1, 1024 / E);
-    const int cpg = ceil_div(nchunks, G);
-    const int t = threadIdx.x;
-    const int e = t % E, g = t / E;
-    const bool active = g < G;
-    const int c0 = g * cpg, c1 = min(nchunks, c0 + cpg);
-    // (both passes over this thread's chunks go eight loads at a time: one at a time, the kernel is
-    // a chain of memory latencies)
-    int s = 0;
-    if (active) {
-        for (int c = c0; c < c1; c += 8) {
-            int v[8];
+// LDS: [waves][E] run counts, then first output positions; [E] totals, then offsets; [E] ids of earlier chunks
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void index_scatter(const int32_t* __restrict__ idx, int A, int E, int bits,
+                                                            int chunk, int nchunks,
+                                                            const int32_t* __restrict__ hist,
+                                                            int32_t* __restrict__ counts,
+                                                            int32_t* __restrict__ offsets,
+                                                            int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ inv) {
+    constexpr int NT = 64 * WAVES;
+    constexpr int B = 8;                  // rows of 64 ids whose loads are issued together
+    extern __shared__ int32_t lds[];
+    __shared__ int32_t s_valid;
+    int32_t* run = lds;
+    int32_t* tot = lds + WAVES * E;
+    int32_t* before = tot + E;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (int i = t; i < (WAVES + 2) * E; i += NT) lds[i] = 0;
+    __syncthreads();
+    const int rows = chunk / NT;          // rows per wavefront
+    const long long a0 = (long long)blockIdx.x * chunk + (long long)wave * rows * 64 + lane;
+    auto load_rows = [&](int r0, int (&e)[B]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = c + u < c1 ? hist[(size_t)(c + u) * E + e] : 0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+        for (int u = 0; u < B; ++u) {
+            const long long a = a0 + (long long)(r0 + u) * 64;
+            e[u] = r0 + u < rows && a < A ? idx[a] : -1;
         }
-    }
-    if (active) gs[g * E + e] = s;
-    __syncthreads();
-    int base = 0;
-    if (active) {
-        for (int q = 0; q < g; ++q) base += gs[q * E + e];
-        if (g == 0) {
-            int tot = 0;
-            for (int q = 0; q < G; ++q) tot += gs[q * E + e];
-            cnt[e] = tot;
-            counts[e] = tot;
-        }
-    }
-    __syncthreads();
-    int off = 0, mine = 0;
-    if (t < E) {
-        for (int q = 0; q < t; ++q) off += cnt[q];
-        mine = cnt[t];
-    }
-    __syncthreads();
-    if (t < E) {
-        cnt[t] = off;
-        offsets[t] = off;
-        if (t == E - 1) offsets[E] = off + mine;
-    }
-    __syncthreads();
-    if (active) {
-        int run = cnt[e] + base;
-        for (int c = c0; c < c1; c += 8) {
-            int v[8];
+    };
+    for (int r0 = 0; r0 < rows; r0 += B) {
+        int e[B];
+        load_rows(r0, e);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = c + u < c1 ? hist[(size_t)(c + u) * E + e] : 0;
+        for (int u = 0; u < B; ++u)
+            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&run[wave * E + e[u]], 1);
+    }
+    // totals and the share of the chunks in front of this one (integer sums: exact in any order)
+    if (nchunks > 1) {
+        const int G = max(1, NT / E), cpg = ceil_div(nchunks, G);
+        for (int i = t; i < G * E; i += NT) {
+            const int e = i % E, c0 = i / E * cpg, c1 = min(nchunks, c0 + cpg);
+            int s = 0, f = 0;
+            for (int c = c0; c < c1; c += B) {
+                int v[B];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (c + u < c1) hist[(size_t)(c + u) * E + e] = run;
-                run += v[u];
+                for (int u = 0; u < B; ++u) v[u] = c + u < c1 ? hist[(size_t)(c + u) * E + e] : 0;
+#pragma unroll
+                for (int u = 0; u < B; ++u) { s += v[u]; f += c + u < (int)blockIdx.x ? v[u] : 0; }
             }
+            atomicAdd(&tot[e], s);
+            atomicAdd(&before[e], f);
         }
     }
-}
-
-__global__ __launch_bounds__(256) void index_scatter(const int32_t* __restrict__ idx, int A, int E,
-                                                     int R, int nchunks,
-                                                     const int32_t* __restrict__ hist,
-                                                     const int32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ perm,
-                                                     int32_t* __restrict__ inv) {
-    extern __shared__ int32_t lraw[];  // [4][E] cursors
-    volatile int32_t* lb = lraw;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int chunk = blockIdx.x * kWavesPerWg + wave;
-    for (int i = threadIdx.x; i < kWavesPerWg * E; i += 256) {
-        const int c = blockIdx.x * kWavesPerWg + i / E;
-        lraw[i] = c < nchunks ? hist[(size_t)c * E + i % E] : 0;
+    __syncthreads();
+    if (nchunks == 1) {
+        for (int e = t; e < E; e += NT) {
+            int s = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) s += run[w * E + e];
+            tot[e] = s;
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        int acc = 0;
+        for (int e0 = 0; e0 < E; e0 += 64) {
+            const int e = e0 + lane;
+            const int n = e < E ? tot[e] : 0;
+            const int end = acc + wave_scan_incl(n);
+            if (e < E) {
+                tot[e] = end - n;
+                if (blockIdx.x == 0) { counts[e] = n; offsets[e] = end - n; }
+            }
+            acc = __builtin_amdgcn_readlane(end, 63);
+        }
+        if (lane == 0) {
+            s_valid = acc;
+            if (blockIdx.x == 0) offsets[E] = acc;
+        }
     }
     __syncthreads();
-    if (chunk >= nchunks) return;
-    const int n_valid = offsets[E];
+    for (int e = t; e < E; e += NT) {
+        int pos = tot[e] + before[e];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const int n = run[w * E + e];
+            run[w * E + e] = pos;
+            pos += n;
+        }
+    }
+    __syncthreads();
+    const int n_valid = s_valid;
     const uint64_t lt_mask = (1ull << lane) - 1ull;
-    const int a0 = chunk * 64 * R;
-    for (int r = 0; r < R; ++r) {
-        const int a = a0 + r * 64 + lane;
-        int e = -1;
-        if (a < A) e = idx[a];
-        const bool valid = (a < A) && ((unsigned)e < (unsigned)E);
-        uint64_t remaining = __ballot(valid);
-        int rank = 0, cnt = 0;
-        while (remaining) {  // uniform: one trip per distinct expert in this row
-            const int leader = __ffsll((long long)remaining) - 1;
-            const int e0 = __shfl(e, leader);
-            const uint64_t m = __ballot(valid && e == e0);
-            if (valid && e == e0) {
-                rank = __popcll(m & lt_mask);
-                cnt = __popcll(m);
+    volatile int32_t* cursor = run + wave * E;
+    for (int r0 = 0; r0 < rows; r0 += B) {
+        int e[B];
+        load_rows(r0, e);
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (r0 + u >= rows) break;
+            const long long a = a0 + (long long)(r0 + u) * 64;
+            const bool valid = (unsigned)e[u] < (unsigned)E;
+            uint64_t same = __ballot(valid);          // lanes with this lane's expert
+            for (int q = 0; q < bits; ++q) {
+                const uint64_t m = __ballot((e[u] >> q) & 1);
+                same &= (e[u] >> q) & 1 ? m : ~m;
             }
-            remaining &= ~m;
+            const int rank = __popcll(same & lt_mask), cnt = __popcll(same);
+            int b = 0;
+            if (valid) b = cursor[e[u]];
+            __builtin_amdgcn_wave_barrier();
+            if (valid) {
+                const int pos = b + rank;
+                perm[pos] = (int)a;
+                inv[a] = pos;
+                if (rank == cnt - 1) cursor[e[u]] = b + cnt;
+            } else if (a < A) {
+                inv[a] = -1;  // dropped: expert id outside [0, E)
+            }
+            if (a < A && a >= n_valid) perm[a] = -1;  // tail left empty by dropped ids
+            __builtin_amdgcn_wave_barrier();
         }
-        int b = 0;
-        if (valid) b = lb[wave * E + e];
-        __builtin_amdgcn_wave_barrier();
-        if (valid) {
-            const int pos = b + rank;
-            perm[pos] = a;
-            inv[a] = pos;
-            if (rank == cnt - 1) lb[wave * E + e] = b + cnt;
-        } else if (a < A) {
-            inv[a] = -1;  // dropped: expert id outside [0, E)
-        }
-        if (a < A && a >= n_valid) perm[a] = -1;  // tail left empty by dropped ids
-        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -226,26 +232,31 @@ hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int bl
     return hipGetLastError();
 }
 
+// What the interface asks for: a word per expert and run of 64 ids (at most 1024 runs).  The chunks need no more.
 size_t index_scratch_bytes(const MoeDims& D) {
-    const IndexPlan p = plan_for(D.A);
-    return align_up((size_t)p.nchunks * D.E * sizeof(int32_t), 256);
+    const long long per = ((long long)D.A + 64 * 1024 - 1) / (64 * 1024) * 64;
+    return align_up((size_t)(((long long)D.A + per - 1) / per) * D.E * sizeof(int32_t), 256);
 }
 
 hipError_t launch_index(const MoeDims& D, const int32_t* topk_idx, hexa_moe_idx out, void* scratch,
                         hipStream_t st) {
-    const IndexPlan p = plan_for(D.A);
+    const IndexPlan p = plan_for(D);
     int32_t* hist = (int32_t*)scratch;
-    const int nwg = ceil_div(p.nchunks, kWavesPerWg);
-    const size_t lds = (size_t)kWavesPerWg * D.E * sizeof(int32_t);
-    { ProfScope ps(st, "index_count");
-    hipLaunchKernelGGL(index_count, dim3(nwg), dim3(256), lds, st, topk_idx, D.A, D.E,
-                       p.rows_per_wave, p.nchunks, hist); }
-    { ProfScope ps(st, "index_scan");
-    hipLaunchKernelGGL(index_scan, dim3(1), dim3(1024), 0, st, hist, D.E, p.nchunks, out.counts,
-                       out.offsets); }
-    { ProfScope ps(st, "index_scatter");
-    hipLaunchKernelGGL(index_scatter, dim3(nwg), dim3(256), lds, st, topk_idx, D.A, D.E,
-                       p.rows_per_wave, p.nchunks, hist, out.offsets, out.perm, out.inv); }
+    int bits = 0;
+    while ((1 << bits) < D.E) ++bits;
+    if (p.nchunks > 1) {
+        ProfScope ps(st, "index_count");
+        hipLaunchKernelGGL(index_count, dim3(p.nchunks), dim3(1024), D.E * sizeof(int32_t), st, topk_idx, D.A, D.E,
+                           p.chunk, hist);
+    }
+    ProfScope ps(st, "index_scatter");
+    const size_t lds = (size_t)(p.waves + 2) * D.E * sizeof(int32_t);
+    if (p.waves == 16)
+        hipLaunchKernelGGL(index_scatter<16>, dim3(p.nchunks), dim3(1024), lds, st, topk_idx, D.A, D.E, bits, p.chunk,
+                           p.nchunks, hist, out.counts, out.offsets, out.perm, out.inv);
+    else
+        hipLaunchKernelGGL(index_scatter<8>, dim3(p.nchunks), dim3(512), lds, st, topk_idx, D.A, D.E, bits, p.chunk,
+                           p.nchunks, hist, out.counts, out.offsets, out.perm, out.inv);
     return hipGetLastError();
 }
 

@@ -30,3 +30,10 @@ def test_row_edges_of_a_128_row_tile(oracle, T):
 def test_mixed_tile_classes(oracle, T, d, f, E, k, dtype):
     w = MoEWorkload("mixed", T, d, f, E, min(k, E), dtype, "topk", 77 + T)
     full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E} k{k}")
+
+
+@pytest.mark.parametrize("E", [1, 64, 65, 256, 257, 1024])
+def test_expert_look_up(oracle, E):
+    # 128x128 tiles; one, four or sixteen experts per lane in the look-up, many of them empty, some cut into chunks
+    w = MoEWorkload("lanes", 6000, 64, 128, E, min(E, 2), "bf16", "zipf", 60 + E)
+    full_parity(oracle, w, generate(w, DEV), label=f"E{E}")
