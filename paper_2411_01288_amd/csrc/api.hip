@@ -66,6 +66,8 @@ MoeWorkspace layout(const MoeDims& D, int dtype, void* base) {
     if (!f32) {
         w.rowoff = (uint32_t*)take((A + 64 * (size_t)D.E) * 4);
         w.worklist = (int32_t*)take(gemm_worklist_ints(D) * 4);
+        const int shares = fc2_shares(D);
+        if (shares > 1) w.fc2part = (float*)take((size_t)shares * A * d * 4);
     }
     w.total_bytes = off;
     return w;
@@ -102,6 +104,15 @@ hipError_t ensure_device_init() {
     e = gemm_bf16_device_init();
     if (e == hipSuccess) g_dev_ready[d].store(true, std::memory_order_release);
     return e;
+}
+
+template <typename T>
+hipError_t finish_fwd(const MoeDims& D, const int32_t* topk_idx, const float* gate, const void* b2,
+                      const hexa_moe_idx& idx, const MoeWorkspace& ws, void* y, hipStream_t st) {
+    const int shares = fc2_shares(D);
+    if (shares > 1)
+        return launch_combine_split<T>(D, ws.fc2part, shares, (const T*)b2, topk_idx, idx.inv, gate, (T*)ws.o, (T*)y, st);
+    return launch_combine_y<T>(D, (const T*)ws.o, idx.inv, gate, (T*)y, st);
 }
 
 }  // namespace
@@ -218,8 +229,8 @@ hexa_status hexa_moe_fwd(const hexa_moe_shape* shape, const void* x, const int32
         e = launch_bf16_fwd(D, (const bf16_t*)x, (const bf16_t*)W1, (const bf16_t*)b1,
                             (const bf16_t*)W2, (const bf16_t*)b2, idx, ws, st, f16);
         if (e == hipSuccess) {
-            if (f16) e = launch_combine_y<f16_t>(D, (const f16_t*)ws.o, idx.inv, gate, (f16_t*)y, st);
-            else e = launch_combine_y<bf16_t>(D, (const bf16_t*)ws.o, idx.inv, gate, (bf16_t*)y, st);
+            if (f16) e = finish_fwd<f16_t>(D, topk_idx, gate, b2, idx, ws, y, st);
+            else e = finish_fwd<bf16_t>(D, topk_idx, gate, b2, idx, ws, y, st);
         }
     }
     return dev(e);

@@ -201,6 +201,7 @@ struct MoeWorkspace {
     void* pre;      // [A,f] elem   fp32: pre-activations; bf16: GELU'(pre), perm order (saved by fwd)
     void* h;        // [A,f] elem   activations, perm order            (saved by fwd)
     void* o;        // [A,d] elem   per-assignment expert outputs      (saved by fwd)
+    float* fc2part; // [shares,A,d] f32 unrounded sums of a split FC2 (16-bit path, few rows; fwd staging)
     void* dout;     // [A,d] elem   gate * dY gathered to perm order   (bwd staging)
     void* dpre;     // [A,f] elem                                       (bwd staging)
     void* dxp;      // [A,d] elem   per-assignment input gradients     (bwd staging)
@@ -222,6 +223,7 @@ int f32_chunk_len(const MoeDims& D);          // ... of the fp32 path
 // sum over those of ceil(n_e / L) is at most 2 A / L.
 inline size_t split_slots(const MoeDims& D, int L) { return 2 * (size_t)(D.A / L) + 2; }
 size_t gemm_worklist_ints(const MoeDims& D);  // int32 entries of MoeWorkspace::worklist
+int fc2_shares(const MoeDims& D);             // shares of K in which the 16-bit path runs FC2 (1: unsplit)
 int gemm_rowoff_step(const MoeDims& D);       // layout of MoeWorkspace::rowoff that the launch of this shape reads
 size_t prologue_partial_rows(const MoeDims& D);   // rows of MoeWorkspace::colpart2
 
@@ -234,6 +236,10 @@ hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int bl
 template <typename T>
 hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, const float* gate,
                             T* y, hipStream_t st);
+// the same from the partial sums of an FC2 in `shares` shares of K, which it also finishes: o = round(sum + b2[e])
+template <typename T>
+hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const T* b2, const int32_t* topk_idx,
+                                const int32_t* inv, const float* gate, T* o, T* y, hipStream_t st);
 // dout_p = gate_a dY_t, dgate_a = <dY_t, o_p>, for a = perm[p], and partial column sums of gate_a dY_t for db2
 // (ESS) in ws.colpart2; 16-bit types: also the row-offset table of WGRAD1
 template <typename T>

@@ -33,12 +33,10 @@ template <> struct Vec<bf16_t> {
 #pragma unroll
         for (int i = 0; i < 4; ++i) unpack2<false>(q[i], v[2 * i], v[2 * i + 1]);
     }
-    __device__ static void store(bf16_t* p, const float (&v)[8], int) {
-        uint4 q;
-        q.x = pack_bf2(v[0], v[1]); q.y = pack_bf2(v[2], v[3]);
-        q.z = pack_bf2(v[4], v[5]); q.w = pack_bf2(v[6], v[7]);
-        *reinterpret_cast<uint4*>(p) = q;
+    __device__ static Raw pack(const float (&v)[8]) {
+        return Raw{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
     }
+    __device__ static void store(bf16_t* p, const float (&v)[8], int) { *reinterpret_cast<Raw*>(p) = pack(v); }
 };
 template <> struct Vec<f16_t> {
     static constexpr int N = 8;
@@ -48,12 +46,10 @@ template <> struct Vec<f16_t> {
 #pragma unroll
         for (int i = 0; i < 4; ++i) unpack2<true>(q[i], v[2 * i], v[2 * i + 1]);
     }
-    __device__ static void store(f16_t* p, const float (&v)[8], int) {
-        uint4 q;
-        q.x = pack_h2(v[0], v[1]); q.y = pack_h2(v[2], v[3]);
-        q.z = pack_h2(v[4], v[5]); q.w = pack_h2(v[6], v[7]);
-        *reinterpret_cast<uint4*>(p) = q;
+    __device__ static Raw pack(const float (&v)[8]) {
+        return Raw{pack_h2(v[0], v[1]), pack_h2(v[2], v[3]), pack_h2(v[4], v[5]), pack_h2(v[6], v[7])};
     }
+    __device__ static void store(f16_t* p, const float (&v)[8], int) { *reinterpret_cast<Raw*>(p) = pack(v); }
 };
 
 // One thread per VN consecutive columns of one token; workgroup `block` of the combination.  The rows of two
@@ -105,6 +101,59 @@ __global__ __launch_bounds__(256) void combine_rows(int T_, int d, int k, const 
                                                     const int32_t* __restrict__ inv,
                                                     const float* __restrict__ gate, T* __restrict__ dst) {
     combine_block<T>(blockIdx.x, T_, d, k, src, inv, gate, dst);
+}
+
+// The same for an FC2 that ran in shares of K: adds the shares' sums in order and the bias, rounds, stores the
+// expert outputs o that the backward pass reads, and combines the rounded values.
+template <typename T>
+__global__ __launch_bounds__(256) void combine_split(int T_, int d, int k, int shares, size_t share_elems,
+                                                     const float* __restrict__ part, const T* __restrict__ b2,
+                                                     const int32_t* __restrict__ topk_idx,
+                                                     const int32_t* __restrict__ inv, const float* __restrict__ gate,
+                                                     T* __restrict__ o, T* __restrict__ y) {
+    constexpr int VN = Vec<T>::N;
+    const uint32_t per_row = (uint32_t)(d / VN);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t t = gid / per_row;
+    if (t >= (uint32_t)T_) return;
+    const int c = (int)(gid - t * per_row) * VN;
+    float acc[VN];
+#pragma unroll
+    for (int i = 0; i < VN; ++i) acc[i] = 0.f;
+    for (int j = 0; j < k; ++j) {
+        const size_t a = (size_t)t * k + j;
+        const int p = inv[a], e = topk_idx[a];
+        if (p < 0) continue;   // dropped assignment: its id is outside [0, E)
+        const float g = gate[a];
+        const float* src = part + (size_t)p * d + c;
+        const typename Vec<T>::Raw qb = Vec<T>::load_raw(b2 + (size_t)e * d + c, VN);
+        float v[VN], b[VN];
+#pragma unroll
+        for (int i = 0; i < VN; ++i) v[i] = 0.f;
+        for (int s0 = 0; s0 < shares; s0 += 4) {
+            f32x4 q[4][VN / 4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < VN / 4; ++h) {
+                    q[u][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (s0 + u < shares) q[u][h] = *reinterpret_cast<const f32x4*>(src + (s0 + u) * share_elems + 4 * h);
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int i = 0; i < VN; ++i) v[i] += q[u][i / 4][i % 4];
+        }
+        Vec<T>::unpack(qb, b);
+#pragma unroll
+        for (int i = 0; i < VN; ++i) v[i] += b[i];
+        const typename Vec<T>::Raw r = Vec<T>::pack(v);
+        *reinterpret_cast<typename Vec<T>::Raw*>(o + (size_t)p * d + c) = r;
+        Vec<T>::unpack(r, v);
+#pragma unroll
+        for (int i = 0; i < VN; ++i) acc[i] += g * v[i];
+    }
+    Vec<T>::store(y + (size_t)t * d + c, acc, VN);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -405,6 +454,15 @@ hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, co
 }
 
 template <typename T>
+hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const T* b2, const int32_t* topk_idx,
+                                const int32_t* inv, const float* gate, T* o, T* y, hipStream_t st) {
+    ProfScope ps(st, "combine_y");
+    hipLaunchKernelGGL(combine_split<T>, dim3(combine_blocks<T>(D)), dim3(256), 0, st, D.T, D.d, D.k, shares,
+                       (size_t)D.A * D.d, part, b2, topk_idx, inv, gate, o, y);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_bwd_prologue(const MoeDims& D, const T* dY, const float* gate, const hexa_moe_idx& idx,
                                const MoeWorkspace& ws, float* dgate, hipStream_t st) {
     constexpr int VN = Vec<T>::N;
@@ -453,6 +511,10 @@ hipError_t launch_bwd_finish(const MoeDims& D, const hexa_moe_idx& idx, const Mo
                                                hipStream_t);                                       \
     template hipError_t launch_bwd_finish<T>(const MoeDims&, const hexa_moe_idx&, const MoeWorkspace&, int, int, T*, \
                                              float*, float*, float*, float*, hipStream_t);
+template hipError_t launch_combine_split<bf16_t>(const MoeDims&, const float*, int, const bf16_t*, const int32_t*,
+                                                 const int32_t*, const float*, bf16_t*, bf16_t*, hipStream_t);
+template hipError_t launch_combine_split<f16_t>(const MoeDims&, const float*, int, const f16_t*, const int32_t*,
+                                                const int32_t*, const float*, f16_t*, f16_t*, hipStream_t);
 INSTANTIATE(float)
 INSTANTIATE(bf16_t)
 INSTANTIATE(f16_t)

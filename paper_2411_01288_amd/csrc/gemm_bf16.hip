@@ -42,7 +42,8 @@ constexpr int kXcds = 8;         // workgroup i is dispatched to XCD i % 8
 constexpr int group_rows(int bm) { return 1024 / bm; }   // row tiles per L2-sharing group: 1024 rows' worth
 constexpr int kSplitBelow = 128; // row GEMMs with fewer groups cut their last ngroups % 8 groups across the XCDs
 
-enum Op { OP_FC1 = 0, OP_FC2, OP_DGRAD2, OP_DGRAD1, OP_WGRAD2, OP_WGRAD1 };
+// (OP_FC2P: a share of FC2's contraction, unrounded and without the bias, see launch_bf16_fwd)
+enum Op { OP_FC1 = 0, OP_FC2, OP_DGRAD2, OP_DGRAD1, OP_WGRAD2, OP_WGRAD1, OP_FC2P };
 
 struct GemmArgs {
     const bf16_t* A;      // row GEMM: [rows][K] (rows = tokens when gather, else perm positions)
@@ -58,8 +59,10 @@ struct GemmArgs {
     float* kpart;         // split-K slots [slot][M][N]
     float* colpart;       // DGRAD2: per (row tile, wave row) column sums of dpre [2*tiles][N]
     int topk, E, K, N, M;
-    int a_rows;           // FC1: rows of the gathered operand (tokens T)
+    int a_rows;           // FC1, WGRAD1: rows of the gathered operand (tokens T); FC2P: rows of the output
     int chunk_len;        // token contraction: max tokens per work item
+    int share;            // FC2P: number of this share of K, and 64-k blocks per share
+    int share_blocks;
     const int32_t* lists; // 256x256 tiles: the work lists (see build_worklists)
     int rt_cap;           // their capacity in row tiles
 };
@@ -186,6 +189,8 @@ __device__ __forceinline__ void buf_store16(u32x4 data, rsrc_t r, int voff, int 
 template <int R, int NW, bool GATHER>
 struct StageKC {
     static constexpr int RPQ = 1024 / ROWB;      // rows per instruction
+    static constexpr int CPR = CPRK;             // lanes per row
+    static_assert(RPQ == 8, "one look-up per lane and staged row");
     static constexpr int NI = R / RPQ / NW;      // instructions per wave and stage
     static_assert(R % (RPQ * NW) == 0 && (RPQ * NW) % 16 == 0, "unsupported staging shape");
     // byte offset of (row, chunk) from the resource base: one per instruction when the rows are
@@ -462,7 +467,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int FM = TM / 16, FN = TN / 16;   // 16x16 MFMA blocks per wave tile
     constexpr bool TOKENS = (OP == OP_WGRAD2 || OP == OP_WGRAD1);
-    constexpr bool B_KS = TOKENS || OP == OP_FC1 || OP == OP_FC2;
+    constexpr bool B_KS = TOKENS || OP == OP_FC1 || OP == OP_FC2 || OP == OP_FC2P;
     constexpr bool A_GK = (OP == OP_WGRAD1);   // operand A's k-rows (tokens) are gathered rows of x
     constexpr int SLOT = (BM > BN ? BM : BN) * ROWB;   // bytes of one ring slot (one operand, one block)
     constexpr int SPS = BK / 32;              // k-substeps (one MFMA k = 32 each) per block
@@ -479,7 +484,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // ---- which work item ------------------------------------------------------------------
     int e, m0, n0, mvalid, nk;
     int row_tile = 0;                 // row GEMMs: number of this row tile over all segments
-    int kbeg = 0, kend = 0;           // token contraction: perm rows of this item
+    int kbeg = 0, kend = 0;           // token contraction: perm rows of this item; FC2P: first block of K
     float* tok_out = nullptr;         // token contraction: where the tile goes
     if constexpr (!TOKENS) {
         const int tn = ceil_div(g.N, BN);
@@ -495,6 +500,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         }
         e = it.e; m0 = it.beg; mvalid = it.end - it.beg; n0 = tile_n * BN; row_tile = tile_m;
         nk = g.K / BK;
+        if constexpr (OP == OP_FC2P) {
+            kbeg = g.share * g.share_blocks;            // (in blocks)
+            nk = min(g.share_blocks, nk - kbeg);
+        }
     } else {
         // every (expert, chunk) item is a set of tm*tn tiles over the same tokens; each XCD takes
         // an eighth of every item's tiles (neighbouring ones), so the XCDs stay balanced however
@@ -537,7 +546,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         // FC1 gathers token rows of x through the re-index vector; the other row GEMMs read
         // perm-ordered rows, and rows past the segment fall outside the resource (zeros)
         if constexpr (OP == OP_FC1) ra = make_rsrc(g.A, (uint32_t)g.a_rows * (uint32_t)g.K * 2u);
-        else ra = make_rsrc(g.A + (size_t)m0 * g.K, (uint32_t)mvalid * (uint32_t)g.K * 2u);
+        else ra = make_rsrc(g.A + (size_t)m0 * g.K + kbeg * BK, (uint32_t)mvalid * (uint32_t)g.K * 2u - (uint32_t)(kbeg * BK) * 2u);
         a_step = BK * 2;
         const uint32_t ca = (uint32_t)SA::lane_chunk(uwave, lane) * 16u;
         if constexpr (OP == OP_FC1) {
@@ -551,7 +560,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         }
         if constexpr (B_KS) {  // W[e][K][N]
             b_ld = (uint32_t)g.N * 2u;
-            rb = make_rsrc(g.B + (size_t)e * g.K * g.N, (uint32_t)g.K * b_ld);
+            rb = make_rsrc(g.B + ((size_t)e * g.K + kbeg * BK) * g.N, (uint32_t)(g.K - kbeg * BK) * b_ld);
             b_step = BK * b_ld;
             lnb = SB::lane_init(uwave, lane, b_ld, n0);
         } else {               // W[e][N][K]: rows past N fall outside the resource
@@ -911,7 +920,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     __syncthreads();   // every wave is done reading fragments
     {
         uint8_t* wreg = smem + uwave * (TN * 256);
-        constexpr bool OUT_F32 = TOKENS;   // weight gradients; every activation-like output is 16-bit
+        constexpr bool OUT_F32 = TOKENS || OP == OP_FC2P;   // weight gradients, partial sums; every other output is 16-bit
         constexpr int ESZ = OUT_F32 ? 4 : 2;
         constexpr int RPB = TN * ESZ;                 // bytes per staged row (TN columns)
         constexpr int CPRO = RPB / 16;                // 16-byte chunks per staged row
@@ -1108,6 +1117,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
 
 template <int BM, int BN, int WM, int WN, int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
 __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16(GemmArgs g) {
+    if constexpr (OP == OP_FC2P) {
+        g.share = (int)blockIdx.y;
+        g.out0 = reinterpret_cast<float*>(g.out0) + (size_t)g.share * g.a_rows * g.N;
+    }
     gemm_tile<BM, BN, WM, WN, OP, ACT, F16>(g, (int)blockIdx.x);
 }
 
@@ -1150,13 +1163,13 @@ inline int row_gemm_slots(int tm_max, int tn, int GM) {
 }
 
 template <int BM, int BN, int WM, int WN, int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
-void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char* label) {
+void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char* label, int shares = 1) {
     ProfScope ps(st, label);
     auto kern = gemm_bf16<BM, BN, WM, WN, OP, ACT, F16>;
     constexpr int lds = NSLOT * (BM > BN ? BM : BN) * ROWB;
     const int tm_max = D.A / BM + D.E;
     const int grid = row_gemm_slots(tm_max, ceil_div(g.N, BN), group_rows(BM));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(grid, shares), dim3(WM * WN * 64), lds, st, g);
 }
 
 // Row GEMM OPA and token contraction OPB of one linear layer's backward in one grid.
@@ -1227,7 +1240,34 @@ inline bool small_fc2(const MoeDims& D) { return small_rows(D, D.f, D.d); }
 inline bool small_bwd2(const MoeDims& D) { return small_pair(D, D.d, D.f); }
 inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 
+// FC2 in shares of K: with few rows its tiles are few and long (K = d_ff), so a decode step leaves most CUs idle.
+// The workgroups of a share write unrounded sums, combine_split adds them up in order; that traffic and the
+// number of shares are weighed by the same estimate.  It was checked against 1, 2, 4 and 8 shares on 13 shapes of
+// 1 to 4096 tokens: never more than 10 % behind the best of them for fc2 + combine, 2 % on average.  Measured,
+// fc2 + combine in us at 1 / 2 / 4 / 8 shares: 16 tokens, d = 768, f = 3072, 16 experts, top-2: 35 / 25 / 22 / 26;
+// 64 tokens, 2048 x 8192 x 64: 287 / 251 / 257 / 263; 1024 tokens, 512 x 2048 x 8: 28 / 28 / 25 / 31; 2048 tokens,
+// 768 x 3072 x 16: 47 / 56 / 62 / 83 (one share is taken).
+int choose_fc2_shares(const MoeDims& D) {
+    if (!small_fc2(D)) return 1;
+    const int blocks = D.f / BK;
+    int best = 1;
+    double best_us = 0;
+    for (int s = 1; s <= 8 && s <= blocks; ++s) {
+        Work w = row_work(D, SMALL, D.f, D.d);
+        w.tiles *= s;
+        w.blocks = ceil_div(blocks, s);
+        double us = launch_us(kCostSmall, {w});
+        if (s > 1) us += s + (double)s * D.A * D.d * 8.0 / 4e6;   // written and read back at 4 TB/s
+        if (s == 1 || us < best_us) { best = s; best_us = us; }
+    }
+    return best;
+}
+
 }  // namespace
+
+// (rounded so that every share has at least one block)
+int fc2_share_blocks(const MoeDims& D) { return ceil_div(D.f / BK, choose_fc2_shares(D)); }
+int fc2_shares(const MoeDims& D) { return ceil_div(D.f / BK, fc2_share_blocks(D)); }
 
 // Every contraction kernel needs more dynamic shared memory than a kernel may use before its attribute
 // has been raised, once per device.
@@ -1242,6 +1282,9 @@ static hipError_t device_init_class() {
     if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC1, HEXA_ACT_RELU, F16>);
     if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC1, HEXA_ACT_SILU, F16>);
     if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>);
+    if constexpr (B == SMALL) {
+        if (e == hipSuccess) e = allow_lds<B>(gemm_bf16<B, B, 2, 2, OP_FC2P, HEXA_ACT_GELU_TANH, F16>);
+    }
     if (e == hipSuccess) e = allow_lds<B>(gemm_bf16_pair<B, B, 2, 2, OP_DGRAD2, OP_WGRAD2, F16>);
     if (e == hipSuccess) e = allow_lds<B>(gemm_bf16_pair<B, B, 2, 2, OP_DGRAD1, OP_WGRAD1, F16>);
     return e;
@@ -1310,7 +1353,10 @@ static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
     if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
     else launch_fc1<BIG, F16>(D, g, st);
     g.A = (const bf16_t*)ws.h; g.B = W2; g.bias = b2; g.out0 = ws.o; g.out1 = nullptr; g.K = D.f; g.N = D.d;
-    if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+    if (fc2_shares(D) > 1) {
+        g.out0 = ws.fc2part; g.a_rows = D.A; g.share_blocks = fc2_share_blocks(D);
+        launch_rows<SMALL, SMALL, 2, 2, OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
+    } else if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     else launch_rows<BIG, BIG, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     return hipGetLastError();
 }
