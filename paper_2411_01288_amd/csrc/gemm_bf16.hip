@@ -550,11 +550,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         a_step = BK * 2;
         const uint32_t ca = (uint32_t)SA::lane_chunk(uwave, lane) * 16u;
         if constexpr (OP == OP_FC1) {
+            // a wavefront stages 8 NI rows: each lane looks up one (an eight-fold look-up with as many divisions
+            // sits in front of every tile's first request) and hands it to the eight lanes that fetch it
+            const int mine = SA::lane_row(uwave, lane % 8 * SA::CPR, lane / 8 % SA::NI);
+            const uint32_t row = (uint32_t)(g.perm[m0 + (mine < mvalid ? mine : 0)] / g.topk) * (uint32_t)g.K * 2u;
 #pragma unroll
-            for (int i = 0; i < SA::NI; ++i) {
-                const int r = SA::lane_row(uwave, lane, i);
-                lna.voff[i] = (uint32_t)(g.perm[m0 + (r < mvalid ? r : 0)] / g.topk) * (uint32_t)g.K * 2u + ca;
-            }
+            for (int i = 0; i < SA::NI; ++i) lna.voff[i] = (uint32_t)__shfl((int)row, 8 * i + lane / SA::CPR) + ca;
         } else {
             lna.voff[0] = (uint32_t)SA::lane_row(uwave, lane, 0) * (uint32_t)g.K * 2u + ca;
         }
