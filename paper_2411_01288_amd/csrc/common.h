@@ -118,7 +118,18 @@ __device__ __forceinline__ SegTile seg_tile_find_wave(const int32_t* __restrict_
     return SegTile{-1, 0, 0};
 }
 
-// Token-contraction item number `item` (expert-major, then chunks of at most L rows): expert, perm rows
+// How a token contraction cuts an expert's n rows: into as many chunks as keep them below 9/8 L (a second chunk
+// for a few rows would cost two partial tiles written and read back), equal up to the 64-row blocks they start on.
+// Measured, backward launches in us with equal chunks below L / 9/8 L / 3/2 L: 4096 x 384 x 1536 top-2 of 8 experts (1024
+// rows each, L = 1024) 93.9 / 83.9 / 83.9; 3001 x 320 x 448 top-3 of 17 under Zipf routing 50.4 / 50.3 / 53.3; 32768 x 768 x
+// 3072 under Zipf routing the same within 0.3 %.
+__device__ __forceinline__ int chunk_count(int n, int L) { return n > 0 ? max(1, (n - L / 8 - 1) / L + 1) : 0; }
+__device__ __forceinline__ int chunk_start(int n, int nc, int c) {
+    const int q = n / nc;
+    return c >= nc ? n : (c * q + min(c, n - nc * q)) & ~63;
+}
+
+// Token-contraction item number `item` (expert-major, then chunks): expert, perm rows
 // [beg, end) and, for an expert of several chunks, the number of its partial-tile buffer (-1 otherwise).
 // e = -1 past the last item; experts without rows have none.
 struct ChunkItem { int e, beg, end, slot; };
@@ -128,21 +139,37 @@ __device__ __forceinline__ ChunkItem chunk_find_wave(const int32_t* __restrict__
     for (int e0 = 0; e0 < E; e0 += 64) {
         const int e = e0 + lane;
         const int b = e < E ? offsets[e] : 0, n = e < E ? offsets[e + 1] - b : 0;
-        const int nc = ceil_div(n, L), ns = nc > 1 ? nc : 0;
+        const int nc = chunk_count(n, L), ns = nc > 1 ? nc : 0;
         const int end = acc + wave_scan_incl(nc), send = sacc + wave_scan_incl(ns);
         const uint64_t hit = __ballot(end > item);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
-            const int c = item - (__builtin_amdgcn_readlane(end, src) - __builtin_amdgcn_readlane(nc, src));
+            const int chunks = __builtin_amdgcn_readlane(nc, src);
+            const int c = item - (__builtin_amdgcn_readlane(end, src) - chunks);
             const int beg = __builtin_amdgcn_readlane(b, src), rows = __builtin_amdgcn_readlane(n, src);
             const int slots = __builtin_amdgcn_readlane(ns, src);
-            return ChunkItem{e0 + src, beg + c * L, beg + min(rows, c * L + L),
+            return ChunkItem{e0 + src, beg + chunk_start(rows, chunks, c), beg + chunk_start(rows, chunks, c + 1),
                              slots ? __builtin_amdgcn_readlane(send, src) - slots + c : -1};
         }
         acc = __builtin_amdgcn_readlane(end, 63);
         sacc = __builtin_amdgcn_readlane(send, 63);
     }
     return ChunkItem{-1, 0, 0, -1};
+}
+
+constexpr int kXcds = 8;   // workgroup i is dispatched to XCD i % 8
+
+// Slot `slot` of a token contraction whose items have `tiles` output tiles each: the item, and the tile, one of an
+// eighth of the item's tiles (neighbouring ones) per XCD; -1: none.  Where the tiles are no multiple of eight, which XCDs
+// take one more goes round from item to item (36 tiles as 5 5 5 5 5 5 5 1 for every item left the last XCD idle: the
+// backward contractions of 32768 x 768 x 3072 under Zipf routing 632 + 548 -> 615 + 529 us).
+__device__ __forceinline__ int token_item_of(int slot, int tiles, int& tile) {
+    const int per = ceil_div(tiles, kXcds), loc = slot / kXcds;
+    const int item = loc / per;
+    const int x = (slot + item) % kXcds;
+    const int first = x * tiles / kXcds, end = (x + 1) * tiles / kXcds;
+    tile = first + loc - item * per;
+    return tile < end ? item : -1;
 }
 
 // ---- four consecutive floats of a row of any length (dword-aligned) ----
@@ -219,8 +246,8 @@ int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp
 constexpr int kColpartRows = 2;               // DGRAD2 writes this many column-sum partial rows per row tile
 int wgrad_chunk_len(const MoeDims& D);        // tokens per split-K chunk of the 16-bit path (host policy)
 int f32_chunk_len(const MoeDims& D);          // ... of the fp32 path
-// Upper bound on the partial-tile buffers: only experts with more than one chunk of L rows use them, and the
-// sum over those of ceil(n_e / L) is at most 2 A / L.
+// Upper bound on the partial-tile buffers: only experts with more than one chunk use them (n_e > 9/8 L), and the
+// sum of their chunk counts is at most 16/9 A / L.
 inline size_t split_slots(const MoeDims& D, int L) { return 2 * (size_t)(D.A / L) + 2; }
 size_t gemm_worklist_ints(const MoeDims& D);  // int32 entries of MoeWorkspace::worklist
 int fc2_shares(const MoeDims& D);             // shares of K in which the 16-bit path runs FC2 (1: unsplit)

@@ -364,7 +364,7 @@ __device__ __forceinline__ void colsum_block(const ColsumJob& j, uint32_t block,
 }
 
 // Second stage of the split token contraction, plus exact zeros for experts without tokens:
-// out[e] = sum_c kpart[slot_e + c] in chunk order when the expert was cut into several chunks of L rows; untouched
+// out[e] = sum_c kpart[slot_e + c] in chunk order when the expert was cut into several chunks (see chunk_count); untouched
 // when it had exactly one (the contraction wrote it directly).  The work is cut into pieces of 4096 elements,
 // which the workgroups of this job take in turn.
 __device__ __forceinline__ void split_block(const SplitJob& j, uint32_t block, uint32_t nblocks,
@@ -377,7 +377,7 @@ __device__ __forceinline__ void split_block(const SplitJob& j, uint32_t block, u
     for (int e0 = 0; e0 < E; e0 += 64) {
         const int e = e0 + lane;
         const int n = e < E ? offsets[e + 1] - offsets[e] : 0;
-        const int nc = ceil_div(n, L), ns = nc > 1 ? nc : 0;
+        const int nc = chunk_count(n, L), ns = nc > 1 ? nc : 0;
         const int send = wave_scan_incl(ns);
         uint64_t todo = __ballot(e < E && nc != 1);
         for (; todo; todo &= todo - 1, ++before) {

@@ -31,7 +31,7 @@ struct TileArgs {
     const int32_t* perm;
     const int32_t* offsets;
     int K, N, M, E, k, act;
-    int chunk_len;         // token contraction: rows per chunk at most
+    int chunk_len;         // token contraction: rows per chunk that are aimed at (see chunk_count)
 };
 
 __device__ __forceinline__ float gelu_f(float u) {
@@ -87,8 +87,6 @@ struct Operand {
     }
 };
 
-constexpr int kXcds = 8;   // workgroup i is dispatched to XCD i % 8
-
 // LDS of a tile class: two buffers (one multiplied, one filled) of both operands.
 template <int FM, int BK>
 constexpr int tile_floats() {
@@ -113,23 +111,22 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, floa
 
     // ---- which tile: an XCD takes a contiguous eighth of the row GEMM's tiles (column tiles fastest), or an
     // eighth of every chunk's tiles of a token contraction, so that its L2 holds what they share
-    const int xcd = item % kXcds, loc = item / kXcds;
     const int tn = ceil_div(a.N, BM);
     int e, m0, n0, rows, K, kbeg = 0, row_tile = 0;
     float* tok_out = nullptr;
     if constexpr (!TOKENS) {
         const int tiles = seg_tiles_total_wave(a.offsets, a.E, BM) * tn;
-        const int per = ceil_div(tiles, kXcds);
-        const int t = xcd * per + loc;
+        const int per = ceil_div(tiles, kXcds), loc = item / kXcds;
+        const int t = item % kXcds * per + loc;
         if (loc >= per || t >= tiles) return;
         row_tile = t / tn;
         const SegTile s = seg_tile_find_wave(a.offsets, a.E, BM, row_tile);
         e = s.e; m0 = s.row0; rows = s.rows; n0 = (t - row_tile * tn) * BM; K = a.K;
     } else {
-        const int tmn = ceil_div(a.M, BM) * tn, per = ceil_div(tmn, kXcds);
-        const int t = xcd * per + loc % per;
-        if (t >= tmn) return;
-        const ChunkItem c = chunk_find_wave(a.offsets, a.E, a.chunk_len, loc / per);
+        int t;
+        const int i = token_item_of(item, ceil_div(a.M, BM) * tn, t);
+        if (i < 0) return;
+        const ChunkItem c = chunk_find_wave(a.offsets, a.E, a.chunk_len, i);
         if (c.e < 0) return;
         e = c.e; kbeg = c.beg; K = c.end - c.beg;
         m0 = (t / tn) * BM; n0 = (t % tn) * BM; rows = min(BM, a.M - m0);

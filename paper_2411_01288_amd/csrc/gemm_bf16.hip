@@ -38,7 +38,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BK = 64;            // contraction elements per block of the K loop (one 128-byte line per row)
 constexpr int NSLOT = 5;          // LDS ring: five slots, each holds one operand's share of a block
-constexpr int kXcds = 8;         // workgroup i is dispatched to XCD i % 8
 constexpr int group_rows(int bm) { return 1024 / bm; }   // row tiles per L2-sharing group: 1024 rows' worth
 constexpr int kSplitBelow = 128; // row GEMMs with fewer groups cut their last ngroups % 8 groups across the XCDs
 
@@ -60,7 +59,7 @@ struct GemmArgs {
     float* colpart;       // DGRAD2: per (row tile, wave row) column sums of dpre [2*tiles][N]
     int topk, E, K, N, M;
     int a_rows;           // FC1, WGRAD1: rows of the gathered operand (tokens T); FC2P: rows of the output
-    int chunk_len;        // token contraction: max tokens per work item
+    int chunk_len;        // token contraction: tokens per work item that are aimed at (see chunk_count)
     int share;            // FC2P: number of this share of K, and 64-k blocks per share
     int share_blocks;
     const int32_t* lists; // 256x256 tiles: the work lists (see build_worklists)
@@ -277,7 +276,7 @@ __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& til
 
 // Which tile a workgroup works on follows from the segment offsets alone.  Rows are cut into tiles numbered
 // expert-major (tiles never straddle experts; experts without rows have none); the items of a token contraction
-// are numbered expert-major, then chunk: at most L rows of one expert each, with the number of the partial-tile
+// are numbered expert-major, then chunk (see chunk_count), with the number of the partial-tile
 // buffer of an expert that was cut into several chunks (-1: one chunk, its tile goes straight to the output).
 //
 // 256x256 tiles take theirs from work lists: with one workgroup per CU nothing hides the look-up, two scalar
@@ -298,9 +297,9 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
     const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
     int n = 0, b = 0;
     if (e < E) { b = offsets[e]; n = offsets[e + 1] - b; }
-    const int nc = ceil_div(n, L);
+    const int nc = chunk_count(n, L);
     int v[NQ] = {wave_scan_incl(ceil_div(n, 256)), wave_scan_incl(nc), wave_scan_incl(nc > 1 ? nc : 0)};
-    int longest = min(L, n);
+    int longest = n / max(nc, 1);
     s_off[e] = b;
     if (e == E - 1) s_off[E] = b + n;
 #pragma unroll
@@ -336,8 +335,9 @@ __global__ __launch_bounds__(1024) void build_worklists(const int32_t* __restric
     for (int i = e; i < s_end[1][E - 1]; i += 1024) {
         const int x = find(1, i);
         const int first = x > 0 ? s_end[1][x - 1] : 0, c = i - first;
-        const int slot = s_end[1][x] - first > 1 ? (x > 0 ? s_end[2][x - 1] : 0) + c : -1;
-        items[i] = make_int4(x, s_off[x] + c * L, min(s_off[x + 1], s_off[x] + c * L + L), slot);
+        const int chunks = s_end[1][x] - first, rows = s_off[x + 1] - s_off[x];
+        const int slot = chunks > 1 ? (x > 0 ? s_end[2][x - 1] : 0) + c : -1;
+        items[i] = make_int4(x, s_off[x] + chunk_start(rows, chunks, c), s_off[x] + chunk_start(rows, chunks, c + 1), slot);
     }
     if (e == 0) {
         // the longest token-contraction item, in rows; a fused backward grid starts with the token
@@ -362,31 +362,39 @@ struct ExpertLanes {
 #pragma unroll
         for (int q = 0; q <= EPL; ++q) b[q] = offsets[min(e0 + q, E)];
     }
-    // number of pieces of at most `len` rows: inclusive scan over the lanes
+    // pieces of an expert of n rows: row tiles of `len` rows, or (CHUNKS) token-contraction items
+    template <bool CHUNKS>
+    __device__ static __forceinline__ int count(int n, int len) { return CHUNKS ? chunk_count(n, len) : ceil_div(n, len); }
+    // their number: inclusive scan over the lanes
+    template <bool CHUNKS>
     __device__ __forceinline__ int pieces(int len, int& mine) const {
         mine = 0;
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) mine += ceil_div(b[q + 1] - b[q], len);
+        for (int q = 0; q < EPL; ++q) mine += count<CHUNKS>(b[q + 1] - b[q], len);
         return wave_scan_incl(mine);
     }
-    // piece number i (wave-uniform, below the total): expert, first row, end row, and the number of partial
+    // piece number i (wave-uniform, below the total): expert, first row, end row, and (CHUNKS) the number of partial
     // buffers of the experts in front that have several pieces plus the piece's own (-1: the expert's only one)
+    template <bool CHUNKS>
     __device__ __forceinline__ ChunkItem find(int i, int len, int incl, int mine) const {
-        int slots = 0;
+        int slots = 0, slot = 0;
+        if constexpr (CHUNKS) {
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) {
-            const int n = ceil_div(b[q + 1] - b[q], len);
-            slots += n > 1 ? n : 0;
+            for (int q = 0; q < EPL; ++q) {
+                const int n = count<true>(b[q + 1] - b[q], len);
+                slots += n > 1 ? n : 0;
+            }
+            slot = wave_scan_incl(slots) - slots;
         }
-        int at = incl - mine, slot = wave_scan_incl(slots) - slots;
+        int at = incl - mine;
         ChunkItem r{0, 0, 0, -1};
 #pragma unroll
         for (int q = 0; q < EPL; ++q) {
-            const int n = ceil_div(b[q + 1] - b[q], len), c = i - at;
+            const int rows = b[q + 1] - b[q], n = count<CHUNKS>(rows, len), c = i - at;
             if (c >= 0 && c < n) {
                 r.e = (int)(threadIdx.x & 63) * EPL + q;
-                r.beg = b[q] + c * len;
-                r.end = min(b[q + 1], r.beg + len);
+                r.beg = b[q] + (CHUNKS ? chunk_start(rows, n, c) : c * len);
+                r.end = CHUNKS ? b[q] + chunk_start(rows, n, c + 1) : min(b[q + 1], r.beg + len);
                 r.slot = n > 1 ? slot + c : -1;
             }
             at += n;
@@ -442,18 +450,18 @@ template <int EPL, int BM>
 __device__ __forceinline__ bool pick_row_tile(const GemmArgs& g, int item, int tn, ChunkItem& it, int& tile_m, int& tile_n) {
     const ExpertLanes<EPL> x(g.offsets, g.E);
     int mine;
-    const int incl = x.pieces(BM, mine);
+    const int incl = x.template pieces<false>(BM, mine);
     if (!row_tile_of<group_rows(BM)>(item, __builtin_amdgcn_readlane(incl, 63), tn, tile_m, tile_n)) return false;
-    it = x.find(tile_m, BM, incl, mine);
+    it = x.template find<false>(tile_m, BM, incl, mine);
     return true;
 }
 template <int EPL>
 __device__ __forceinline__ bool pick_chunk(const GemmArgs& g, int i, ChunkItem& it) {
     const ExpertLanes<EPL> x(g.offsets, g.E);
     int mine;
-    const int incl = x.pieces(g.chunk_len, mine);
+    const int incl = x.template pieces<true>(g.chunk_len, mine);
     if (i >= __builtin_amdgcn_readlane(incl, 63)) return false;
-    it = x.find(i, g.chunk_len, incl, mine);
+    it = x.template find<true>(i, g.chunk_len, incl, mine);
     return true;
 }
 
@@ -509,18 +517,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         // an eighth of every item's tiles (neighbouring ones), so the XCDs stay balanced however
         // uneven the experts are, and the whole chip streams the same token rows at a time
         const int tm = ceil_div(g.M, BM), tn = ceil_div(g.N, BN);
-        const int tmn = tm * tn;
-        const int per = ceil_div(tmn, kXcds);
-        const int xcd = item % kXcds, loc = item / kXcds;
-        const int tile = xcd * per + loc % per;
-        if (tile >= tmn) return;
+        int tile;
+        const int i = token_item_of(item, tm * tn, tile);
+        if (i < 0) return;
         ChunkItem it;
         if constexpr (BM == 256) {
-            if (loc / per >= g.lists[WL_ITEMS]) return;
-            it = list_entry(g.lists + kWlHeader + 4 * (g.rt_cap + loc / per));
+            if (i >= g.lists[WL_ITEMS]) return;
+            it = list_entry(g.lists + kWlHeader + 4 * (g.rt_cap + i));
         } else {
-            if (!(g.E <= 64 ? pick_chunk<1>(g, loc / per, it)
-                  : g.E <= 256 ? pick_chunk<4>(g, loc / per, it) : pick_chunk<16>(g, loc / per, it))) return;
+            if (!(g.E <= 64 ? pick_chunk<1>(g, i, it)
+                  : g.E <= 256 ? pick_chunk<4>(g, i, it) : pick_chunk<16>(g, i, it))) return;
         }
         int tile_m, tile_n;
         grouped_tile<GM>(tile, tm, tn, tile_m, tile_n);
@@ -1142,8 +1148,11 @@ __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pai
         b_first = ga.lists[OPA == OP_DGRAD2 ? WL_ORDER2 : WL_ORDER1] != 0;
     } else {
         int longest = 0;                        // rows of the longest token-contraction item
-        for (int e = (int)(threadIdx.x & 63); e < gb.E; e += 64) longest = max(longest, gb.offsets[e + 1] - gb.offsets[e]);
-        b_first = __any(min(longest, gb.chunk_len) >= 8 * ga.K) != 0;
+        for (int e = (int)(threadIdx.x & 63); e < gb.E; e += 64) {
+            const int n = gb.offsets[e + 1] - gb.offsets[e];
+            longest = max(longest, n / max(chunk_count(n, gb.chunk_len), 1));
+        }
+        b_first = __any(longest >= 8 * ga.K) != 0;
     }
     const bool is_b = b_first ? item < items_b : item >= items_a;
     const int local = b_first ? (is_b ? item : item - items_b) : (is_b ? item - items_a : item);
@@ -1314,8 +1323,8 @@ int wgrad_chunk_len(const MoeDims& D) {
     long long L = (long long)D.A * tmn / kNumCUs;
     L = (L + 63) / 64 * 64;
     if (L < 1024) L = 1024;
-    // one item's rows are addressed with 32-bit byte offsets: L * max(d, f) * 2 < 2^32
-    const long long cap = (0xffffffffLL / (2LL * (D.d > D.f ? D.d : D.f))) / 64 * 64;
+    // one item's rows (less than 2 L) are addressed with 32-bit byte offsets: 2 L * max(d, f) * 2 < 2^32
+    const long long cap = (0xffffffffLL / (4LL * (D.d > D.f ? D.d : D.f))) / 64 * 64;
     if (L > cap) L = cap;
     return (int)L;
 }

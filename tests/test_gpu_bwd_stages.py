@@ -29,3 +29,11 @@ def test_row_lengths(oracle, dtype, d):
 def test_split_experts(oracle, T, d, f, E, k, dtype, routing):
     w = MoEWorkload("split", T, d, f, E, k, dtype, routing, 40 + T)
     full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E}")
+
+
+@pytest.mark.parametrize("T,dtype", [(287, "f32"), (288, "f32"), (289, "f32"), (545, "f32"), (1919, "f32"),
+                                     (1152, "bf16"), (1153, "bf16"), (2177, "f16"), (7000, "bf16")])
+def test_chunk_counts(oracle, T, dtype):
+    # one expert around the row counts at which it is cut into one more chunk (of about 256 and 1024 rows)
+    w = MoEWorkload("cut", T, 64, 64, 1, 1, dtype, "topk", 80 + T)
+    full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T}")

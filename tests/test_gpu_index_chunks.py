@@ -14,6 +14,7 @@ DEV = "cuda:0"
     (1, 1, 1, False), (63, 1, 2, True), (65, 1, 64, False), (1023, 1, 65, True), (1025, 1, 3, False),
     (8192, 1, 64, False), (8191, 1, 512, True), (8193, 1, 64, False), (4097, 2, 17, True), (8192, 1, 513, False),
     (16400, 1, 1024, True), (131072, 1, 5, False), (131073, 2, 33, True), (400000, 1, 600, False),
+    (1200000, 1, 40, True), (600000, 2, 1, False),      # more rows than a wavefront keeps in registers
 ])
 def test_index_plans(oracle, T, k, E, drop):
     rng = np.random.default_rng(T + E)
