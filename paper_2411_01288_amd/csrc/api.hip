@@ -107,11 +107,11 @@ hipError_t ensure_device_init() {
 }
 
 template <typename T>
-hipError_t finish_fwd(const MoeDims& D, const int32_t* topk_idx, const float* gate, const void* b2,
-                      const hexa_moe_idx& idx, const MoeWorkspace& ws, void* y, hipStream_t st) {
+hipError_t finish_fwd(const MoeDims& D, const float* gate, const hexa_moe_idx& idx, const MoeWorkspace& ws, void* y,
+                      hipStream_t st) {
     const int shares = fc2_shares(D);
     if (shares > 1)
-        return launch_combine_split<T>(D, ws.fc2part, shares, (const T*)b2, topk_idx, idx.inv, gate, (T*)ws.o, (T*)y, st);
+        return launch_combine_split<T>(D, ws.fc2part, shares, idx.inv, gate, (T*)ws.o, (T*)y, st);
     return launch_combine_y<T>(D, (const T*)ws.o, idx.inv, gate, (T*)y, st);
 }
 
@@ -229,8 +229,8 @@ hexa_status hexa_moe_fwd(const hexa_moe_shape* shape, const void* x, const int32
         e = launch_bf16_fwd(D, (const bf16_t*)x, (const bf16_t*)W1, (const bf16_t*)b1,
                             (const bf16_t*)W2, (const bf16_t*)b2, idx, ws, st, f16);
         if (e == hipSuccess) {
-            if (f16) e = finish_fwd<f16_t>(D, topk_idx, gate, b2, idx, ws, y, st);
-            else e = finish_fwd<bf16_t>(D, topk_idx, gate, b2, idx, ws, y, st);
+            if (f16) e = finish_fwd<f16_t>(D, gate, idx, ws, y, st);
+            else e = finish_fwd<bf16_t>(D, gate, idx, ws, y, st);
         }
     }
     return dev(e);

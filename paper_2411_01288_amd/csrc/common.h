@@ -263,10 +263,10 @@ hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int bl
 template <typename T>
 hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, const float* gate,
                             T* y, hipStream_t st);
-// the same from the partial sums of an FC2 in `shares` shares of K, which it also finishes: o = round(sum + b2[e])
+// the same from the partial sums of an FC2 in `shares` shares of K, which it also finishes: o = round(sum)
 template <typename T>
-hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const T* b2, const int32_t* topk_idx,
-                                const int32_t* inv, const float* gate, T* o, T* y, hipStream_t st);
+hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const int32_t* inv,
+                                const float* gate, T* o, T* y, hipStream_t st);
 // dout_p = gate_a dY_t, dgate_a = <dY_t, o_p>, for a = perm[p], and partial column sums of gate_a dY_t for db2
 // (ESS) in ws.colpart2; 16-bit types: also the row-offset table of WGRAD1
 template <typename T>

@@ -103,12 +103,11 @@ __global__ __launch_bounds__(256) void combine_rows(int T_, int d, int k, const 
     combine_block<T>(blockIdx.x, T_, d, k, src, inv, gate, dst);
 }
 
-// The same for an FC2 that ran in shares of K: adds the shares' sums in order and the bias, rounds, stores the
-// expert outputs o that the backward pass reads, and combines the rounded values.
+// The same for an FC2 that ran in shares of K: adds the shares' sums in order, rounds, stores the expert outputs o
+// that the backward pass reads, and combines the rounded values.
 template <typename T>
 __global__ __launch_bounds__(256) void combine_split(int T_, int d, int k, int shares, size_t share_elems,
-                                                     const float* __restrict__ part, const T* __restrict__ b2,
-                                                     const int32_t* __restrict__ topk_idx,
+                                                     const float* __restrict__ part,
                                                      const int32_t* __restrict__ inv, const float* __restrict__ gate,
                                                      T* __restrict__ o, T* __restrict__ y) {
     constexpr int VN = Vec<T>::N;
@@ -122,12 +121,11 @@ __global__ __launch_bounds__(256) void combine_split(int T_, int d, int k, int s
     for (int i = 0; i < VN; ++i) acc[i] = 0.f;
     for (int j = 0; j < k; ++j) {
         const size_t a = (size_t)t * k + j;
-        const int p = inv[a], e = topk_idx[a];
-        if (p < 0) continue;   // dropped assignment: its id is outside [0, E)
+        const int p = inv[a];
+        if (p < 0) continue;   // dropped assignment
         const float g = gate[a];
         const float* src = part + (size_t)p * d + c;
-        const typename Vec<T>::Raw qb = Vec<T>::load_raw(b2 + (size_t)e * d + c, VN);
-        float v[VN], b[VN];
+        float v[VN];
 #pragma unroll
         for (int i = 0; i < VN; ++i) v[i] = 0.f;
         for (int s0 = 0; s0 < shares; s0 += 4) {
@@ -144,9 +142,6 @@ __global__ __launch_bounds__(256) void combine_split(int T_, int d, int k, int s
 #pragma unroll
                 for (int i = 0; i < VN; ++i) v[i] += q[u][i / 4][i % 4];
         }
-        Vec<T>::unpack(qb, b);
-#pragma unroll
-        for (int i = 0; i < VN; ++i) v[i] += b[i];
         const typename Vec<T>::Raw r = Vec<T>::pack(v);
         *reinterpret_cast<typename Vec<T>::Raw*>(o + (size_t)p * d + c) = r;
         Vec<T>::unpack(r, v);
@@ -454,11 +449,11 @@ hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, co
 }
 
 template <typename T>
-hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const T* b2, const int32_t* topk_idx,
-                                const int32_t* inv, const float* gate, T* o, T* y, hipStream_t st) {
+hipError_t launch_combine_split(const MoeDims& D, const float* part, int shares, const int32_t* inv,
+                                const float* gate, T* o, T* y, hipStream_t st) {
     ProfScope ps(st, "combine_y");
     hipLaunchKernelGGL(combine_split<T>, dim3(combine_blocks<T>(D)), dim3(256), 0, st, D.T, D.d, D.k, shares,
-                       (size_t)D.A * D.d, part, b2, topk_idx, inv, gate, o, y);
+                       (size_t)D.A * D.d, part, inv, gate, o, y);
     return hipGetLastError();
 }
 
@@ -511,10 +506,10 @@ hipError_t launch_bwd_finish(const MoeDims& D, const hexa_moe_idx& idx, const Mo
                                                hipStream_t);                                       \
     template hipError_t launch_bwd_finish<T>(const MoeDims&, const hexa_moe_idx&, const MoeWorkspace&, int, int, T*, \
                                              float*, float*, float*, float*, hipStream_t);
-template hipError_t launch_combine_split<bf16_t>(const MoeDims&, const float*, int, const bf16_t*, const int32_t*,
-                                                 const int32_t*, const float*, bf16_t*, bf16_t*, hipStream_t);
-template hipError_t launch_combine_split<f16_t>(const MoeDims&, const float*, int, const f16_t*, const int32_t*,
-                                                const int32_t*, const float*, f16_t*, f16_t*, hipStream_t);
+template hipError_t launch_combine_split<bf16_t>(const MoeDims&, const float*, int, const int32_t*, const float*, bf16_t*, bf16_t*,
+                                                 hipStream_t);
+template hipError_t launch_combine_split<f16_t>(const MoeDims&, const float*, int, const int32_t*, const float*, f16_t*, f16_t*,
+                                                 hipStream_t);
 INSTANTIATE(float)
 INSTANTIATE(bf16_t)
 INSTANTIATE(f16_t)

@@ -41,7 +41,7 @@ constexpr int NSLOT = 5;          // LDS ring: five slots, each holds one operan
 constexpr int group_rows(int bm) { return 1024 / bm; }   // row tiles per L2-sharing group: 1024 rows' worth
 constexpr int kSplitBelow = 128; // row GEMMs with fewer groups cut their last ngroups % 8 groups across the XCDs
 
-// (OP_FC2P: a share of FC2's contraction, unrounded and without the bias, see launch_bf16_fwd)
+// (OP_FC2P: a share of FC2's contraction, unrounded, the first one with the bias; see choose_fc2_shares)
 enum Op { OP_FC1 = 0, OP_FC2, OP_DGRAD2, OP_DGRAD1, OP_WGRAD2, OP_WGRAD1, OP_FC2P };
 
 struct GemmArgs {
@@ -51,7 +51,7 @@ struct GemmArgs {
     const int32_t* perm;  // FC1 gather
     const uint32_t* rowoff;  // WGRAD1 gather: byte offsets of the token rows, written by the backward prologue
     const int32_t* offsets;
-    const bf16_t* bias;   // [E][N] or NULL
+    const bf16_t* bias;   // [E][N] (FC1, FC2, FC2P)
     const bf16_t* pre_in; // DGRAD2: the saved GELU'(pre)
     void* out0;
     void* out1;
@@ -610,11 +610,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // memory latency and nothing to hide it behind.  These plain loads are older than every staging
     // request, so the staging waits, which count from the youngest request back, cover them.
     u32x2 biasv[FN];
-    if constexpr (OP == OP_FC1 || OP == OP_FC2) {
+    if constexpr (OP == OP_FC1 || OP == OP_FC2 || OP == OP_FC2P) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
             const int gc = min(n0 + wn * TN + j * 16 + 4 * grp, g.N - 4);   // masked columns read a valid bias
             biasv[j] = *reinterpret_cast<const u32x2*>(g.bias + (size_t)e * g.N + gc);
+            if (OP == OP_FC2P && g.share > 0) biasv[j] = u32x2{0, 0};
         }
     }
 
@@ -1060,13 +1061,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
             for (int j = 0; j < FN; ++j) {
                 const int col = j * 16 + 4 * grp;                  // column inside the wave tile
                 f32x4 v = acc[i][j];
-                if constexpr (OP == OP_FC1 || OP == OP_FC2) {
+                if constexpr (OP == OP_FC1 || OP == OP_FC2 || OP == OP_FC2P) {
                     const u32x2 bb = biasv[j];
                     float b0, b1, b2, b3;
                     unpack2<F16>(bb.x, b0, b1); unpack2<F16>(bb.y, b2, b3);
                     v[0] += b0; v[1] += b1; v[2] += b2; v[3] += b3;
                 }
-                if constexpr (OUT_F32) {
+                if constexpr (OP == OP_FC2P) {
+                    const int c = col >> 2;
+                    *reinterpret_cast<f32x4*>(wb + l16 * RPB + ((c ^ (l16 % CPRO)) << 4)) = v;
+                } else if constexpr (OUT_F32) {
                     // straight from the accumulation registers (an LDS store may take its data from
                     // them; through ordinary registers it is 256 more copies per wave and tile)
                     const int c = col >> 2;
