@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/hexa_moe.h"
+#include "segments.h"
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 
@@ -62,7 +63,6 @@ template <> struct Elem<f16_t> {
     __device__ static void st(f16_t* p, float v) { *p = (f16_t)v; }
 };
 
-__host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // GELU, tanh form (the activation F between the two MLPs; App. B Table 5 rows 2, 7).
@@ -116,17 +116,6 @@ __device__ __forceinline__ SegTile seg_tile_find_wave(const int32_t* __restrict_
         acc = __builtin_amdgcn_readlane(end, 63);
     }
     return SegTile{-1, 0, 0};
-}
-
-// How a token contraction cuts an expert's n rows: into as many chunks as keep them below 9/8 L (a second chunk
-// for a few rows would cost two partial tiles written and read back), equal up to the 64-row blocks they start on.
-// Measured, backward launches in us with equal chunks below L / 9/8 L / 3/2 L: 4096 x 384 x 1536 top-2 of 8 experts (1024
-// rows each, L = 1024) 93.9 / 83.9 / 83.9; 3001 x 320 x 448 top-3 of 17 under Zipf routing 50.4 / 50.3 / 53.3; 32768 x 768 x
-// 3072 under Zipf routing the same within 0.3 %.
-__device__ __forceinline__ int chunk_count(int n, int L) { return n > 0 ? max(1, (n - L / 8 - 1) / L + 1) : 0; }
-__device__ __forceinline__ int chunk_start(int n, int nc, int c) {
-    const int q = n / nc;
-    return c >= nc ? n : (c * q + min(c, n - nc * q)) & ~63;
 }
 
 // Token-contraction item number `item` (expert-major, then chunks): expert, perm rows
