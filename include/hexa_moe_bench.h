@@ -32,6 +32,19 @@ HEXA_API int hexa_moe_profile_read(int i, const char **label, float *ms_total, i
 HEXA_API hexa_status hexa_moe_mfma_probe(int32_t variant, int32_t workgroups, int32_t iters, float *sink,
                                 void *stream, double *flop);
 
+/* How the launches of a shape are cut (host only; depends on the shape alone).  Tests use it to see that a
+ * shape takes the kernels they are about. */
+typedef struct {
+    int32_t fc1_tile, fc2_tile, bwd_fc2_tile, bwd_fc1_tile; /* rows and columns of an output tile of each
+                                  contraction launch (bwd_fc2 / bwd_fc1: both contractions of the layer) */
+    int32_t fc2_shares;        /* shares of K in which FC2 runs (1: unsplit) */
+    int32_t chunk_rows;        /* rows per chunk that the token contractions aim at */
+    int64_t partial_buffers;   /* partial weight gradients the workspace has room for, per weight matrix */
+    int64_t index_chunk_ids, index_chunks;   /* index build: ids per workgroup, workgroups */
+    int64_t prologue_blocks;   /* workgroups of the backward prologue (with dgate) */
+} hexa_moe_plan;
+HEXA_API hexa_status hexa_moe_launch_plan(const hexa_moe_shape *shape, hexa_moe_plan *plan);
+
 #ifdef __cplusplus
 }
 #endif

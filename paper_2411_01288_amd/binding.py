@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libhexa_moe_asan.so" if os.environ.get("HEXA_MOE
 HEXA_F32, HEXA_BF16, HEXA_F16 = 0, 1, 2
 EXPORTS = ("hexa_moe_index_scratch_bytes", "hexa_moe_workspace_bytes", "hexa_moe_status_string",
            "hexa_moe_index", "hexa_moe_index_static", "hexa_moe_fwd", "hexa_moe_bwd", "hexa_moe_profile_enable",
-           "hexa_moe_profile_read", "hexa_moe_mfma_probe", "hexa_moe_route",
+           "hexa_moe_profile_read", "hexa_moe_launch_plan", "hexa_moe_mfma_probe", "hexa_moe_route",
            "hexa_moe_allocate", "hexa_moe_padded_capacity", "hexa_moe_padded_index")
 
 
@@ -35,6 +35,12 @@ class Shape(ctypes.Structure):
 class Idx(ctypes.Structure):
     _fields_ = [("counts", ctypes.c_void_p), ("offsets", ctypes.c_void_p),
                 ("perm", ctypes.c_void_p), ("inv", ctypes.c_void_p)]
+
+
+class Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("fc1_tile", "fc2_tile", "bwd_fc2_tile", "bwd_fc1_tile", "fc2_shares",
+                                              "chunk_rows")] + \
+               [(n, ctypes.c_int64) for n in ("partial_buffers", "index_chunk_ids", "index_chunks", "prologue_blocks")]
 
 
 def _load():
@@ -68,6 +74,8 @@ def _load():
     lib.hexa_moe_allocate.restype = ctypes.c_int
     lib.hexa_moe_allocate.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_double), ctypes.c_int64,
                                       ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    lib.hexa_moe_launch_plan.restype = ctypes.c_int
+    lib.hexa_moe_launch_plan.argtypes = [ctypes.POINTER(Shape), ctypes.POINTER(Plan)]
     lib.hexa_moe_profile_enable.restype = None
     lib.hexa_moe_profile_enable.argtypes = [ctypes.c_int]
     lib.hexa_moe_profile_read.restype = ctypes.c_int
@@ -238,6 +246,13 @@ def profile_read() -> Dict[str, Tuple[float, int]]:
         out[label.value.decode()] = (ms.value, n.value)
         i += 1
     return out
+
+
+def launch_plan(shape: Shape) -> Dict[str, int]:
+    """How the launches of this shape are cut (host only): tile sizes, shares, chunks."""
+    p = Plan()
+    _check(lib.hexa_moe_launch_plan(ctypes.byref(shape), ctypes.byref(p)))
+    return {n: getattr(p, n) for n, _ in Plan._fields_}
 
 
 def mfma_probe(workgroups: int, iters: int, sink: "torch.Tensor", variant: int = 0) -> float:

@@ -69,4 +69,23 @@ int hexa_moe_profile_read(int i, const char** label, float* ms_total, int* launc
     return 1;
 }
 
+hexa_status hexa_moe_launch_plan(const hexa_moe_shape* shape, hexa_moe_plan* plan) {
+    MoeDims D;
+    const hexa_status s = hexa_check_shape(shape, &D);
+    if (s != HEXA_OK) return s;
+    if (!plan) return HEXA_ERR_NULL;
+    const bool f32 = shape->dtype == HEXA_F32;
+    int tile[4];
+    if (f32) f32_tile_classes(D, tile);
+    else gemm_tile_classes(D, tile);
+    *plan = hexa_moe_plan{};
+    plan->fc1_tile = tile[0]; plan->fc2_tile = tile[1]; plan->bwd_fc2_tile = tile[2]; plan->bwd_fc1_tile = tile[3];
+    plan->fc2_shares = f32 ? 1 : fc2_shares(D);
+    plan->chunk_rows = f32 ? f32_chunk_len(D) : wgrad_chunk_len(D);
+    plan->partial_buffers = (int64_t)split_slots(D, plan->chunk_rows);
+    index_chunks(D, &plan->index_chunk_ids, &plan->index_chunks);
+    plan->prologue_blocks = prologue_blocks(D, !f32, true);
+    return HEXA_OK;
+}
+
 }  // extern "C"

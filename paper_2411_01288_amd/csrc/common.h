@@ -230,6 +230,9 @@ struct MoeWorkspace {
     size_t total_bytes;
 };
 
+// tile sizes of the launches fc1, fc2, bwd_fc2, bwd_fc1
+void gemm_tile_classes(const MoeDims& D, int (&tile)[4]);
+void f32_tile_classes(const MoeDims& D, int (&tile)[4]);
 int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path
 int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp32 path
 constexpr int kColpartRows = 2;               // DGRAD2 writes this many column-sum partial rows per row tile
@@ -242,10 +245,12 @@ size_t gemm_worklist_ints(const MoeDims& D);  // int32 entries of MoeWorkspace::
 int fc2_shares(const MoeDims& D);             // shares of K in which the 16-bit path runs FC2 (1: unsplit)
 int gemm_rowoff_step(const MoeDims& D);       // layout of MoeWorkspace::rowoff that the launch of this shape reads
 size_t prologue_partial_rows(const MoeDims& D);   // rows of MoeWorkspace::colpart2
+int64_t prologue_blocks(const MoeDims& D, bool rowoff, bool dgate);   // workgroups: tiles, then side jobs
 
 hipError_t launch_index(const MoeDims& D, const int32_t* topk_idx, hexa_moe_idx out, void* scratch,
                         hipStream_t st);
 size_t index_scratch_bytes(const MoeDims& D);
+void index_chunks(const MoeDims& D, int64_t* ids, int64_t* chunks);   // ids per workgroup, workgroups
 hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int blk, long long cap,
                                int32_t* v, int32_t* idx_, hipStream_t st);
 

@@ -439,6 +439,9 @@ void prologue_launch(const PrologueArgs& a, int blocks, hipStream_t st) {
 }  // namespace
 
 size_t prologue_partial_rows(const MoeDims& D) { return (size_t)(D.A / prologue_tile_rows(D) + D.E + 1); }
+int64_t prologue_blocks(const MoeDims& D, bool rowoff, bool dgate) {
+    return (int64_t)prologue_partial_rows(D) + ceil_div(rowoff ? D.A + 64 * D.E : dgate ? D.A : 0, 256);
+}
 
 template <typename T>
 hipError_t launch_combine_y(const MoeDims& D, const T* o, const int32_t* inv, const float* gate,
@@ -469,7 +472,7 @@ hipError_t launch_bwd_prologue(const MoeDims& D, const T* dY, const float* gate,
     a.tile_rows = prologue_tile_rows(D);
     a.tile_blocks = (int)prologue_partial_rows(D);
     a.step = a.rowoff ? gemm_rowoff_step(D) : 64;
-    const int blocks = a.tile_blocks + ceil_div(a.rowoff ? D.A + 64 * D.E : dgate ? D.A : 0, 256);
+    const int blocks = (int)prologue_blocks(D, a.rowoff != nullptr, dgate != nullptr);
     ProfScope ps(st, "bwd_prologue");
     if (D.d <= 16 * VN) prologue_launch<T, 1, 16>(a, blocks, st);
     else if (D.d <= 64 * VN) prologue_launch<T, 1, 64>(a, blocks, st);

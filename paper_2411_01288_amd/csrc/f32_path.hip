@@ -334,6 +334,10 @@ int f32_chunk_len(const MoeDims& D) {
     if (L < 256) L = 256;
     return (int)(L < 0x7fffffc0 ? L : 0x7fffffc0);
 }
+void f32_tile_classes(const MoeDims& D, int (&tile)[4]) {
+    tile[0] = tile[2] = small_rows(D, D.f) ? 32 : 64;
+    tile[1] = tile[3] = small_rows(D, D.d) ? 32 : 64;
+}
 int f32_dgrad2_row_tile(const MoeDims& D) { return small_rows(D, D.f) ? 32 : 64; }
 
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,

@@ -1243,6 +1243,11 @@ hipError_t gemm_bf16_device_init() {
     return e;
 }
 
+void gemm_tile_classes(const MoeDims& D, int (&tile)[4]) {
+    const bool small[4] = {small_fc1(D), small_fc2(D), small_bwd2(D), small_bwd1(D)};
+    for (int i = 0; i < 4; ++i) tile[i] = small[i] ? SMALL : BIG;
+}
+
 // Row-tile height of the DGRAD2 column-sum partials (for the finisher).
 int gemm_dgrad2_row_tile(const MoeDims& D) { return small_bwd2(D) ? SMALL : BIG; }
 int gemm_rowoff_step(const MoeDims& D) { return small_bwd1(D) ? StageKS<SMALL, 4>::STEP : StageKS<BIG, 4>::STEP; }

@@ -232,6 +232,11 @@ hipError_t launch_padded_index(const MoeDims& D, const hexa_moe_idx& idx, int bl
     return hipGetLastError();
 }
 
+void index_chunks(const MoeDims& D, int64_t* ids, int64_t* chunks) {
+    const IndexPlan p = plan_for(D);
+    *ids = p.chunk; *chunks = p.nchunks;
+}
+
 // What the interface asks for: a word per expert and run of 64 ids (at most 1024 runs).  The chunks need no more.
 size_t index_scratch_bytes(const MoeDims& D) {
     const long long per = ((long long)D.A + 64 * 1024 - 1) / (64 * 1024) * 64;

@@ -52,6 +52,20 @@ def test_size_queries_and_shape_validation(B):
         assert B.workspace_bytes(bad) == 0 and B.index_scratch_bytes(bad) == 0
 
 
+def test_launch_plan_query(B):
+    assert B.lib.hexa_moe_launch_plan(None, ctypes.byref(B.Plan())) == 1
+    assert B.lib.hexa_moe_launch_plan(ctypes.byref(B.make_shape(8, 64, 64, 4, 1, "bf16")), None) == 1
+    with pytest.raises(B.HexaError):
+        B.launch_plan(B.make_shape(8, 60, 64, 4, 1, "bf16"))
+    tiles = ("fc1_tile", "fc2_tile", "bwd_fc2_tile", "bwd_fc1_tile")
+    plan = lambda *a: [B.launch_plan(B.make_shape(*a))[n] for n in (*tiles, "fc2_shares")]
+    assert plan(131072, 2048, 8192, 64, 2, "bf16") == [256] * 4 + [1]     # rows enough to fill the chip
+    assert plan(600, 128, 256, 6, 2, "f16")[:4] == [128] * 4
+    assert plan(16, 768, 3072, 16, 2, "bf16")[4] > 1                      # few rows, long contraction
+    assert plan(4096, 384, 1536, 8, 2, "f32") == [64] * 4 + [1]
+    assert plan(256, 64, 256, 4, 1, "f32") == [32] * 4 + [1]
+
+
 def test_error_codes_without_touching_a_gpu(B):
     lib = B.lib
     ok = B.make_shape(8, 64, 64, 4, 1, "bf16")
