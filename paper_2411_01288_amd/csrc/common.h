@@ -238,9 +238,14 @@ int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp
 constexpr int kColpartRows = 2;               // DGRAD2 writes this many column-sum partial rows per row tile
 int wgrad_chunk_len(const MoeDims& D);        // tokens per split-K chunk of the 16-bit path (host policy)
 int f32_chunk_len(const MoeDims& D);          // ... of the fp32 path
-// Upper bound on the partial-tile buffers: only experts with more than one chunk use them (n_e > 9/8 L), and the
-// sum of their chunk counts is at most 16/9 A / L.
-inline size_t split_slots(const MoeDims& D, int L) { return 2 * (size_t)(D.A / L) + 2; }
+// The most partial-tile buffers that any routing needs.  An expert of L + L/8 + 1 rows is the smallest that is cut, into
+// two chunks, and every L rows more are one chunk more (see chunk_count): as many experts as possible that are just
+// cut, and the rows left over on one of them.
+inline size_t split_slots(const MoeDims& D, int L) {
+    const long long cut = (long long)L + L / 8 + 1;
+    const long long n = D.A / cut < D.E ? D.A / cut : D.E;
+    return n > 0 ? (size_t)(2 * n + (D.A - n * cut) / L) : 0;
+}
 size_t gemm_worklist_ints(const MoeDims& D);  // int32 entries of MoeWorkspace::worklist
 int fc2_shares(const MoeDims& D);             // shares of K in which the 16-bit path runs FC2 (1: unsplit)
 int gemm_rowoff_step(const MoeDims& D);       // layout of MoeWorkspace::rowoff that the launch of this shape reads

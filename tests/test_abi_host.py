@@ -66,6 +66,29 @@ def test_launch_plan_query(B):
     assert plan(256, 64, 256, 4, 1, "f32") == [32] * 4 + [1]
 
 
+@pytest.mark.parametrize("T,E", [(1, 1), (288, 1), (289, 1), (545, 2), (577, 2), (578, 2), (579, 1), (1100, 3), (1500, 8)])
+def test_partial_buffers_are_what_the_worst_routing_needs(B, T, E):
+    """The workspace holds as many partial weight gradients as the chunks of any routing of T rows to E experts can
+    need, and no more: none where no expert can be cut."""
+    import numpy as np
+    plan = B.launch_plan(B.make_shape(T, 64, 64, E, 1, "f32"))
+    L = plan["chunk_rows"]
+    assert L == 256
+    n = np.arange(T + 1)
+    chunks = np.where(n > 0, np.maximum(0, n - L // 8 - 1) // L + 1, 0)   # of an expert of n rows
+    need = np.where(chunks > 1, chunks, 0)
+    best = need.copy()                         # best[a]: the most that a rows over the experts so far can need
+    for _ in range(E - 1):
+        best = np.array([np.max(best[:a + 1] + need[a::-1]) for a in n])
+    assert plan["partial_buffers"] == best.max()
+
+
+def test_workspace_has_no_partial_buffers_for_experts_that_are_never_cut(B):
+    # 128 rows in all, one chunk each, beside weights of 2 x 268 MB per expert
+    assert B.workspace_bytes(B.make_shape(64, 8192, 8192, 8, 2, "f32")) < 64 << 20
+    assert B.workspace_bytes(B.make_shape(64, 2048, 8192, 64, 2, "bf16")) < 64 << 20
+
+
 def test_error_codes_without_touching_a_gpu(B):
     lib = B.lib
     ok = B.make_shape(8, 64, 64, 4, 1, "bf16")
