@@ -177,16 +177,16 @@ struct PrologueArgs {
 // entries past the segment's end hold an offset behind the last row of x, which the buffer range check turns
 // into zeros.
 __device__ __forceinline__ void prologue_side_jobs(const PrologueArgs& a, int block) {
-    const int g = block * 256 + (int)threadIdx.x;
-    if (a.dgate && g < a.A && a.inv[g] < 0) a.dgate[g] = 0.f;
-    if (!a.rowoff || g >= a.A + 64 * a.E) return;
+    const uint32_t g = (uint32_t)block * 256u + threadIdx.x;   // (A + 64 E may pass 2^31)
+    if (a.dgate && g < (uint32_t)a.A && a.inv[g] < 0) a.dgate[g] = 0.f;
+    if (!a.rowoff || g >= (uint32_t)a.A + 64u * (uint32_t)a.E) return;
     int lo = 0, hi = a.E - 1;                       // the last expert whose part starts at or before g
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (a.offsets[mid] + 64 * mid <= g) lo = mid; else hi = mid - 1;
+        if ((uint32_t)a.offsets[mid] + 64u * (uint32_t)mid <= g) lo = mid; else hi = mid - 1;
     }
     const int b = a.offsets[lo], n = a.offsets[lo + 1] - b;
-    const int local = g - (b + 64 * lo);
+    const int local = (int)(g - ((uint32_t)b + 64u * (uint32_t)lo));
     const int s = local & 63;
     const int per = 64 / a.step;
     const int r = (local & ~63) + a.step * (s % per) + s / per;
@@ -440,7 +440,8 @@ void prologue_launch(const PrologueArgs& a, int blocks, hipStream_t st) {
 
 size_t prologue_partial_rows(const MoeDims& D) { return (size_t)(D.A / prologue_tile_rows(D) + D.E + 1); }
 int64_t prologue_blocks(const MoeDims& D, bool rowoff, bool dgate) {
-    return (int64_t)prologue_partial_rows(D) + ceil_div(rowoff ? D.A + 64 * D.E : dgate ? D.A : 0, 256);
+    const int64_t side = rowoff ? (int64_t)D.A + 64 * D.E : dgate ? D.A : 0;
+    return (int64_t)prologue_partial_rows(D) + (side + 255) / 256;
 }
 
 template <typename T>

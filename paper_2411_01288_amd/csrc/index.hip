@@ -33,7 +33,7 @@ IndexPlan plan_for(const MoeDims& D) {
     IndexPlan p;
     p.waves = D.E <= 512 ? 16 : 8;   // (a wavefront's histogram is E words of LDS)
     const long long unit = 64 * p.waves;
-    const long long want = D.A <= kOneChunk ? D.A : (D.A + kMaxChunks - 1) / kMaxChunks;
+    const long long want = D.A <= kOneChunk ? D.A : ((long long)D.A + kMaxChunks - 1) / kMaxChunks;
     const long long chunk = (want + unit - 1) / unit * unit;
     p.chunk = (int)chunk;
     p.nchunks = (int)((D.A + chunk - 1) / chunk);

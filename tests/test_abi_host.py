@@ -89,6 +89,19 @@ def test_workspace_has_no_partial_buffers_for_experts_that_are_never_cut(B):
     assert B.workspace_bytes(B.make_shape(64, 2048, 8192, 64, 2, "bf16")) < 64 << 20
 
 
+@pytest.mark.parametrize("T,k,E,dtype", [(2**31 - 1, 1, 1, "f32"), (2**31 - 1, 1, 1024, "f32"), (2**31 - 127, 1, 600, "f32"),
+                                         (2**31 - 128, 1, 8, "f32"), (2**25 - 2, 64, 1024, "bf16")])
+def test_launch_sizes_at_the_largest_assignment_counts(B, T, k, E, dtype):
+    """T*k up to 2^31 - 1 is accepted: the sizes derived from it must not wrap."""
+    A = T * k
+    assert A <= 2**31 - 1
+    plan = B.launch_plan(B.make_shape(T, 64, 64, E, k, dtype))
+    ids, chunks = plan["index_chunk_ids"], plan["index_chunks"]
+    assert 1 <= chunks <= 128 and ids % 64 == 0 and (chunks - 1) * ids < A <= chunks * ids
+    side = A + (64 * E if dtype != "f32" else 0)      # gate gradients of dropped assignments; row-offset entries
+    assert plan["prologue_blocks"] == A // 128 + E + 1 + -(-side // 256)
+
+
 def test_error_codes_without_touching_a_gpu(B):
     lib = B.lib
     ok = B.make_shape(8, 64, 64, 4, 1, "bf16")
