@@ -131,9 +131,18 @@ def _ptr(t: Optional[torch.Tensor], dims, dtype, name: str):
     return t.data_ptr()
 
 
+def _raw_stream_getter(torch_c):
+    """device -> handle of its current stream: without a stream object where this torch offers that (it is no public
+    interface), else through torch.cuda.current_stream()."""
+    get = getattr(torch_c, "_cuda_getCurrentRawStream", None)
+    return get if get is not None else lambda device: torch.cuda.current_stream(device).cuda_stream
+
+
+_raw_stream = _raw_stream_getter(torch._C)
+
+
 def _stream():
-    # the handle of torch.cuda.current_stream()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def index_scratch_bytes(shape: Shape) -> int:

@@ -166,6 +166,14 @@ def test_binding_checks_tensor_shapes_on_the_host(B):
     assert ei.value.code == 3
 
 
+def test_stream_handle_without_the_private_torch_call(B, monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    assert B._raw_stream_getter(SimpleNamespace(_cuda_getCurrentRawStream=lambda device: 40 + device))(2) == 42
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: SimpleNamespace(cuda_stream=70 + device))
+    assert B._raw_stream_getter(SimpleNamespace())(3) == 73
+
+
 def test_heterogeneous_allocation_against_the_oracle(B):
     """hexa_moe_allocate (Sec. 3.4 Eq. 1 / Eq. 2, largest-remainder rounding) against the exact
     rational oracle: hand cases, seeded random cases, and its error returns."""
