@@ -12,14 +12,21 @@ def poisoned(shape, dtype, device):
     return torch.full(shape, float("nan"), dtype=dtype, device=device)
 
 
-def run_hip_layer(w, data, want_dgate=True):
+def assert_tiles(w, tiles):
+    """The launch rule gives fc1, fc2, bwd_fc2 and bwd_fc1 of this workload tiles of these sizes."""
+    from paper_2411_01288_amd import binding as B
+    p = B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))
+    assert [p[n] for n in ("fc1_tile", "fc2_tile", "bwd_fc2_tile", "bwd_fc1_tile")] == tiles
+
+
+def run_hip_layer(w, data, want_dgate=True, activation=0):
     """data: dict of device tensors from workloads.generate.  Returns (idx, y, grads) on device.
 
     Every output tensor and the whole workspace start out as NaN bit patterns (0xFF bytes are a
     NaN in fp32, bf16 and fp16 alike), the index outputs as -7: whatever the library does not
     write, or reads without having written, shows up in the results."""
     from paper_2411_01288_amd import binding as B
-    shape = B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype)
+    shape = B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype, activation)
     dev = data["x"].device
     dt = data["x"].dtype
     T, d, f, E, k = w.T, w.d_model, w.d_ff, w.E, w.k

@@ -5,15 +5,17 @@ import pytest
 import torch
 
 from paper_2411_01288_amd.workloads import MoEWorkload, generate, workload
-from gpu_util import TOL, host32, host_inputs, nrm_err, run_hip_layer
+from gpu_util import TOL, assert_tiles, host32, host_inputs, nrm_err, run_hip_layer
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def test_bitwise_reproducible_and_bwd_can_repeat():
+@pytest.mark.parametrize("T,d,f,E,tile", [(3000, 256, 512, 7, 128), (80000, 256, 256, 64, 256)])
+def test_bitwise_reproducible_and_bwd_can_repeat(T, d, f, E, tile):
     from paper_2411_01288_amd import binding as B
-    w = MoEWorkload("rep", 3000, 256, 512, 7, 2, "bf16", "zipf", 5)
+    w = MoEWorkload("rep", T, d, f, E, 2, "bf16", "zipf", 5)
+    assert_tiles(w, [tile] * 4)
     data = generate(w, DEV)
     shape = B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype)
     outs = []

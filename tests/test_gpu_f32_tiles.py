@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2411_01288_amd.workloads import MoEWorkload, generate
+from gpu_util import assert_tiles
 from test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -21,12 +22,13 @@ def test_edges_of_a_tile(oracle, T, d, f):
     full_parity(oracle, w, data, label=f"edge T{T} d{d} f{f}")
 
 
-@pytest.mark.parametrize("T,d,f,E,k,routing", [
-    (4001, 190, 771, 3, 2, "topk"),     # fc1 and the second layer's backward 64x64, the others 32x32
-    (9001, 509, 66, 2, 1, "topk"),      # fc2 and the first layer's backward 64x64, the others 32x32
-    (3001, 258, 1027, 70, 3, "zipf"),   # all 64x64, more experts than lanes
-    (500, 40, 50, 200, 2, "zipf"),      # all 32x32, most experts empty
+@pytest.mark.parametrize("T,d,f,E,k,routing,tiles", [
+    (4001, 190, 771, 3, 2, "topk", [64, 32, 64, 32]),
+    (9001, 509, 66, 2, 1, "topk", [32, 64, 32, 64]),
+    (3001, 258, 1027, 70, 3, "zipf", [64, 64, 64, 64]),   # more experts than lanes
+    (500, 40, 50, 200, 2, "zipf", [32, 32, 32, 32]),      # most experts empty
 ])
-def test_mixed_tile_classes(oracle, T, d, f, E, k, routing):
+def test_mixed_tile_classes(oracle, T, d, f, E, k, routing, tiles):
     w = MoEWorkload("mixed", T, d, f, E, k, "f32", routing, 33 + T)
+    assert_tiles(w, tiles)
     full_parity(oracle, w, generate(w, DEV), label=f"f32 T{T} d{d} f{f} E{E} k{k}")

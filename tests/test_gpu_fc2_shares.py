@@ -7,7 +7,7 @@ import torch
 
 from paper_2411_01288_amd import binding as B
 from paper_2411_01288_amd.workloads import MoEWorkload, generate
-from gpu_util import TOL, host32, host_inputs, nrm_err, poisoned
+from gpu_util import TOL, host32, host_inputs, nrm_err, run_hip_layer
 from test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -20,6 +20,7 @@ DEV = "cuda:0"
 ])
 def test_split_fc2(oracle, T, d, f, E, k, dtype):
     w = MoEWorkload("shares", T, d, f, E, k, dtype, "topk", 210 + T)
+    assert B.launch_plan(B.make_shape(T, d, f, E, k, dtype))["fc2_shares"] > 1
     full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E} k{k}")
 
 
@@ -27,13 +28,15 @@ def test_split_fc2_drops_out_of_range_ids(oracle):
     w = MoEWorkload("shares", 20, 128, 2048, 6, 2, "bf16", "topk", 4)
     data = generate(w, DEV)
     data["topk_idx"][:, 1] = torch.tensor([6, -1] * 10, device=DEV, dtype=torch.int32)
-    shape = B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype)
-    idx = B.hexa_moe_index(shape, data["topk_idx"])
-    ws = B.alloc_workspace(shape, torch.device(DEV))
-    ws.fill_(0xFF)
-    y = B.hexa_moe_fwd(shape, data["x"], data["topk_idx"], data["gate"], data["W1"], data["b1"], data["W2"], data["b2"],
-                       idx, ws, poisoned((w.T, w.d_model), data["x"].dtype, DEV))
+    assert B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))["fc2_shares"] > 1
+    _, y, g = run_hip_layer(w, data)     # the backward reads the expert outputs that this path stores
     c = host_inputs(data)
-    ref = oracle.fwd(c["x"], np.ascontiguousarray(c["topk_idx"][:, :1]), np.ascontiguousarray(c["gate"][:, :1]),
-                     c["W1"], c["b1"], c["W2"], c["b2"])
-    assert nrm_err(host32(y), ref) <= TOL["bf16"]
+    kept = lambda a: np.ascontiguousarray(a[:, :1])
+    args = (c["x"], kept(c["topk_idx"]), kept(c["gate"]), c["W1"], c["b1"], c["W2"])
+    dx, dgate = oracle.bwd_tokens(*args, c["b2"], c["dY"])
+    dW1, db1, dW2, db2 = oracle.bwd_experts(*args, c["dY"])
+    for name, got, ref in (("y", y, oracle.fwd(*args, c["b2"])), ("dx", g["dx"], dx), ("dgate", g["dgate"][:, :1], dgate),
+                           ("dW1", g["dW1"], dW1), ("db1", g["db1"], db1), ("dW2", g["dW2"], dW2),
+                           ("db2", g["db2"], db2)):
+        assert nrm_err(host32(got), ref) <= TOL["bf16"], name
+    assert not g["dgate"][:, 1].any()

@@ -1,19 +1,25 @@
 """The whole step (index, forward, backward) recorded into a HIP graph and replayed: the library
 allocates nothing, synchronises nothing and issues no memset nodes, so a capture of its launches
-must reproduce the eager results bit for bit on every replay (launch-latency regime, workload C2)."""
+must reproduce the eager results bit for bit on every replay (launch-latency regime, workload C2;
+and a shape whose contractions read work lists)."""
 import pytest
 import torch
 
-from paper_2411_01288_amd.workloads import generate, workload
+from paper_2411_01288_amd.workloads import MoEWorkload, generate, workload
+from gpu_util import assert_tiles
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("name", ["C1", "C2"])
+@pytest.mark.parametrize("name", ["C1", "C2", "lists"])
 def test_graph_replays_equal_eager(name):
     from paper_2411_01288_amd import binding as B
-    w = workload(name)
+    if name == "lists":                      # 256x256 contractions, which read work lists
+        w = MoEWorkload("lists", 80000, 256, 256, 64, 2, "bf16", "zipf", 3)
+        assert_tiles(w, [256, 256, 256, 256])
+    else:
+        w = workload(name)
     data = generate(w, DEV)
     shape = B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype)
     idx = B.alloc_idx(shape, DEV)

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2411_01288_amd.workloads import MoEWorkload, generate, workload
-from gpu_util import TOL, host32, host_inputs, nrm_err, run_hip_layer
+from gpu_util import TOL, assert_tiles, host32, host_inputs, nrm_err, run_hip_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -29,8 +29,8 @@ def check_index(oracle, w, data, idx):
     return counts
 
 
-def full_parity(oracle, w, data, label=""):
-    idx, y, g = run_hip_layer(w, data)
+def full_parity(oracle, w, data, label="", activation=0):
+    idx, y, g = run_hip_layer(w, data, activation=activation)
     counts = check_index(oracle, w, data, idx)
     c = host_inputs(data)
     tol = TOL[w.dtype]
@@ -77,18 +77,20 @@ def test_bf16_small_shapes(oracle, dev, T, d, f, E, k, routing):
 
 
 @pytest.mark.parametrize("T,d,f,E,k,routing", [
-    (70000, 64, 512, 8, 2, "zipf"),       # 140 000 rows = ~550 row tiles = ~138 groups of four
+    (70000, 64, 512, 8, 2, "zipf"),       # 140 000 rows = ~1100 row tiles = ~138 groups of eight
     (70000, 64, 256, 64, 2, "bias"),      # the same with 64 experts (C5's count): many segment tails
 ])
 def test_bf16_many_row_tiles_full(oracle, dev, T, d, f, E, k, routing):
-    """Row GEMMs deal their 256-row tiles to the eight XCDs in groups of four, and once there are
+    """Row GEMMs deal their row tiles to the eight XCDs in groups of 1024 rows' worth, and once there are
     128 groups or more (only C5-sized problems otherwise) the last, partial round of groups is
     dealt whole instead of being cut in eight.  Small feature sizes let the oracle check every
-    element of such a problem."""
+    element of such a problem (128x128 tiles, groups of eight; with 256x256 tiles the row-edge case of
+    test_gpu_big_tiles.py takes this branch)."""
     w = MoEWorkload("many-tiles", T, d, f, E, k, "bf16", routing, 4242 + E)
+    assert_tiles(w, [128, 128, 128, 128])
     data = generate(w, dev)
     counts = np.bincount(data["topk_idx"].cpu().numpy().ravel(), minlength=E)
-    assert sum(-(-int(n) // 256) for n in counts) >= 4 * 128
+    assert sum(-(-int(n) // 128) for n in counts) >= 8 * 128
     full_parity(oracle, w, data, label=f"bf16 T{T} d{d} f{f} E{E} k{k} {routing}")
 
 

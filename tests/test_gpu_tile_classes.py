@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2411_01288_amd.workloads import MoEWorkload, generate
+from gpu_util import assert_tiles
 from test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -16,19 +17,22 @@ DEV = "cuda:0"
 def test_row_edges_of_a_128_row_tile(oracle, T):
     # one expert: a segment of exactly T rows; feature sizes with column tails of both kinds (64 and 192 of 128)
     w = MoEWorkload("edge", T, 192, 320, 1, 1, "bf16", "topk", 900 + T)
+    assert_tiles(w, [128, 128, 128, 128])
     data = generate(w, DEV)
     data["gate"] = 0.5 + torch.rand_like(data["gate"])
     full_parity(oracle, w, data, label=f"edge T{T}")
 
 
-@pytest.mark.parametrize("T,d,f,E,k,dtype", [
-    (25003, 192, 960, 3, 2, "bf16"),    # all four launches 256x256
-    (17001, 448, 576, 5, 2, "bf16"),    # fc1 128x128, the others 256x256
-    (25003, 384, 448, 1, 2, "f16"),     # fc1 and the second layer's backward 256x256, the others 128x128
-    (25003, 192, 448, 5, 2, "f16"),     # the first layer's backward alone 256x256
+@pytest.mark.parametrize("T,d,f,E,k,dtype,tiles", [
+    (25003, 192, 960, 3, 2, "bf16", [256, 256, 256, 256]),
+    (17001, 448, 576, 5, 2, "bf16", [128, 256, 256, 256]),
+    (25003, 384, 448, 1, 2, "f16", [128, 128, 128, 128]),    # (top-1: there is one expert)
+    (56250, 320, 192, 9, 2, "f16", [256, 128, 256, 128]),    # the second layer's backward reads the lists, the first's does not
+    (25003, 192, 448, 5, 2, "f16", [128, 128, 128, 256]),
 ])
-def test_mixed_tile_classes(oracle, T, d, f, E, k, dtype):
+def test_mixed_tile_classes(oracle, T, d, f, E, k, dtype, tiles):
     w = MoEWorkload("mixed", T, d, f, E, min(k, E), dtype, "topk", 77 + T)
+    assert_tiles(w, tiles)
     full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E} k{k}")
 
 
@@ -36,4 +40,5 @@ def test_mixed_tile_classes(oracle, T, d, f, E, k, dtype):
 def test_expert_look_up(oracle, E):
     # 128x128 tiles; one, four or sixteen experts per lane in the look-up, many of them empty, some cut into chunks
     w = MoEWorkload("lanes", 6000, 64, 128, E, min(E, 2), "bf16", "zipf", 60 + E)
+    assert_tiles(w, [128, 128, 128, 128])
     full_parity(oracle, w, generate(w, DEV), label=f"E{E}")
