@@ -10,11 +10,6 @@
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 
-__device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
-// round-to-nearest-even; gfx950 lowers this cast to v_cvt_pk_bf16_f32
-__device__ __forceinline__ bf16_t f2bf(float f) {
-    return __builtin_bit_cast(bf16_t, (__bf16)f);
-}
 // two floats -> two bf16 (round to nearest even) in one word: a single v_cvt_pk_bf16_f32
 __device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) {
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -48,20 +43,6 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
     if constexpr (F16) return pack_h2(lo, hi);
     else return pack_bf2(lo, hi);
 }
-
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    __device__ static float ld(const float* p) { return *p; }
-    __device__ static void st(float* p, float v) { *p = v; }
-};
-template <> struct Elem<bf16_t> {
-    __device__ static float ld(const bf16_t* p) { return bf2f(*p); }
-    __device__ static void st(bf16_t* p, float v) { *p = f2bf(v); }
-};
-template <> struct Elem<f16_t> {
-    __device__ static float ld(const f16_t* p) { return (float)*p; }
-    __device__ static void st(f16_t* p, float v) { *p = (f16_t)v; }
-};
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -208,7 +189,7 @@ hexa_status hexa_check_shape(const hexa_moe_shape* s, MoeDims* D);
 
 constexpr int kMaxDevices = 64;   // per-device state of the library is kept in arrays of this length
 
-// Sets the launch attributes of every contraction kernel (160 KB of dynamic LDS) on the current
+// Sets the launch attributes of every contraction kernel (160 or 80 KB of dynamic LDS) on the current
 // device.  Called once per device by the entry points, outside any stream capture.
 hipError_t gemm_bf16_device_init();
 

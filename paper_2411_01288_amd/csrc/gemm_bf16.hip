@@ -695,9 +695,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     // one row.  The K loop is bottom-tested for that reason: with a zero-trip path the accumulators
     // of the two paths meet behind the loop, and the register allocator shuffles them there.
     const int klast = nk - 1;
-    // WGRAD1: the byte offsets in x of the eight token rows this lane fetches per K-block (instruction
-    // i of a wave covers the block's rows 8 i + 2 wave + lane / 32; the table stores a block's 64
-    // offsets transposed, so those eight are 32 consecutive bytes).  rcur holds the offsets of the
+    // WGRAD1: the byte offsets in x of the RO token rows this lane fetches per K-block, eight with 256x256
+    // tiles, four with 128x128 (instruction i of a wave covers the block's rows STEP i + RPI wave + lane / CPR
+    // of StageKS; the table stores a block's 64 offsets transposed, so those RO are consecutive).  rcur holds the offsets of the
     // block requested next (block j + 2 during block j); those of the block after it are loaded at
     // the head of block j and taken over at the wait in its middle, which covers them because they
     // are older than operand A's requests of that block.  The loads are inline assembly like the
@@ -742,7 +742,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     }
     // The accumulators are cleared here, between the first requests and the wait for them: claimed
     // in their accumulation registers by the empty statements (which keep their place among the
-    // other volatile statements), the 256 writes run while the first block is on its way instead of
+    // other volatile statements), the writes run while the first block is on its way instead of
     // after it has arrived.
     f32x4 acc[FM][FN];
 #pragma unroll
@@ -757,8 +757,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
     int sa = 0, sb = 1;                           // slots of A(j), B(j)
     int j = 0;
     if constexpr (!TOKENS) {
-        // A wave whose 128 rows all lie past the segment's end (the lower half of a tail tile with
-        // at most 128 rows) has nothing to multiply: it keeps its share of the staging requests and
+        // A wave whose rows all lie past the segment's end (the lower half of a tail tile with
+        // at most BM / 2 rows) has nothing to multiply: it keeps its share of the staging requests and
         // the barriers, and skips the fragment reads, the MFMAs and the epilogue.  The time of the
         // tile is the other waves'; what is saved is energy, which is what this part runs short of.
         if (__builtin_amdgcn_readfirstlane(mvalid - wm * TM) <= 0) {
@@ -812,7 +812,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int item) {
         __syncthreads();
         FENCE();
         // (WGRAD1 takes the new row offsets over one register per eighth of the substep, each copy in
-        // an issue slot of its own: left to the compiler, the eight copies sit in a row at the
+        // an issue slot of its own: left to the compiler, the copies sit in a row at the
         // loop's back edge, two MFMAs' worth of issue cycles)
 #define TAKE_AT(m_)                                                                               \
     do {                                                                                          \
@@ -1143,7 +1143,9 @@ constexpr int BIG = 256, SMALL = 128;
 // class are fitted to 120 launches (30 shapes: 256 to 65536 tokens, d 64 to 2048, f 256 to 8192, 4 to 64
 // experts, both classes measured): with them the slower class is picked by 1 % of a launch's time on average
 // and by 14 % at most (a skewed 32768 x 256 x 1024 case); always taking 256x256 tiles costs 16 % on average
-// and up to a factor of 2.2.  Measured on both sides of the line, 256x256 against 128x128, in us:
+// and up to a factor of 2.2.  As a prediction of a launch's time it is rough, and it knows no whole rounds of tiles: of 30
+// traced launches (profiles/pass_kernel_times.md) it gives the 256x256 ones 0.90 to 1.06 of their time, the 128x128
+// ones 1.1 to 2.3 (block_us is that of two workgroups side by side on a CU, and a small grid leaves one).  Measured on both sides of the line, 256x256 against 128x128, in us:
 // d = 384, f = 1536, 8 experts, top-2: fc2 32.4 / 16.5 at 4096 tokens, 72 / 59 at 16384; d = 768, f = 3072,
 // 16 experts: fc2 78 / 54 at 2048 tokens, 77 / 71 at 4096, 95 / 115 at 8192, 164 / 205 at 16384.
 struct ClassCost { double slots, start_us, block_us, tail; };

@@ -266,7 +266,7 @@ hipError_t launch_index(const MoeDims& D, const int32_t* topk_idx, hexa_moe_idx 
 }
 
 // ---------------------------------------------------------------------------------------------
-// hexa_moe_index_static: the same three kernels with the chunk histogram in a fixed array of
+// hexa_moe_index_static: the same one or two launches with the chunk histogram in a fixed array of
 // device memory that belongs to the library, for callers that cannot allocate (no hipMalloc under
 // stream capture, tight serving loops).  Nothing here allocates or frees.
 // ---------------------------------------------------------------------------------------------
@@ -308,7 +308,7 @@ extern "C" hexa_status hexa_moe_index_static(const hexa_moe_shape* shape, const 
     if (index_scratch_bytes(D) > (size_t)HEXA_INDEX_STATIC_SCRATCH_BYTES) return HEXA_ERR_WORKSPACE;
     void* ptr = nullptr;
     if (static_scratch(&ptr) != hipSuccess) return HEXA_ERR_DEVICE;
-    // index_count overwrites every histogram entry the later kernels read, so what an earlier
-    // call left in the array needs no clearing
+    // index_count overwrites every histogram entry that index_scatter reads (a single chunk reads none), so what an
+    // earlier call left in the array needs no clearing
     return launch_index(D, topk_idx, out, ptr, (hipStream_t)stream) == hipSuccess ? HEXA_OK : HEXA_ERR_DEVICE;
 }
