@@ -27,6 +27,8 @@ namespace {
 constexpr int kOneChunk = 8192;
 constexpr int kMaxChunks = 128;
 
+constexpr int kLongChunk = 4096;   // ids from which on the kernels for long chunks are used
+
 struct IndexPlan { int waves, chunk, nchunks; };   // wavefronts per workgroup, ids per chunk
 
 IndexPlan plan_for(const MoeDims& D) {
@@ -40,23 +42,62 @@ IndexPlan plan_for(const MoeDims& D) {
     return p;
 }
 
+constexpr int kRows = 8;   // rows of 64 ids that a wavefront loads together
+
+// Counts a wavefront's next n rows (at most kRows; ids of -1: none) in an LDS histogram.  Additions to one address are
+// made one after the other, so rows of equal ids, the usual ones where routing has collapsed or there is one expert,
+// are a single addition.  Only where chunks are long (LONG): index build in us, 2000000 ids on one of 16 experts
+// 44 -> 21, 8000000 on one of 64 308 -> 132, one expert 144 -> 52, spread evenly over 64 170 -> 143 (loads of eight rows
+// at once in index_count); with a row or two per wavefront the longer code costs more than it saves (9003 ids: 1 us).
+__device__ __forceinline__ void count_rows(int32_t* hist, const int (&e)[kRows], int n, int E) {
+    const int e0 = __builtin_amdgcn_readfirstlane(e[0]);
+    if (__all(e[0] == e0)) {
+        bool same = true;
+#pragma unroll
+        for (int u = 1; u < kRows; ++u) same = same && (u >= n || e[u] == e0);
+        if (__all(same)) {
+            if ((unsigned)e0 < (unsigned)E && (threadIdx.x & 63) == 0) atomicAdd(&hist[e0], 64 * min(n, kRows));
+            return;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+        if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[e[u]], 1);
+}
+
+template <bool LONG>
 __global__ __launch_bounds__(1024) void index_count(const int32_t* __restrict__ idx, int A, int E,
                                                     int chunk, int32_t* __restrict__ hist) {
     extern __shared__ int32_t lh[];  // [E]
     for (int i = threadIdx.x; i < E; i += blockDim.x) lh[i] = 0;
     __syncthreads();
     const long long a0 = (long long)blockIdx.x * chunk;
-    for (int i = threadIdx.x; i < chunk; i += blockDim.x) {
-        const long long a = a0 + i;
-        const int e = a < A ? idx[a] : -1;
-        if ((unsigned)e < (unsigned)E) atomicAdd(&lh[e], 1);
+    if constexpr (LONG) {
+        const int rows = chunk / 64, waves = blockDim.x / 64, lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+        for (int r0 = wave; r0 < rows; r0 += kRows * waves) {   // rows go round over the wavefronts
+            int e[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int r = r0 + u * waves;
+                const long long a = a0 + (long long)r * 64 + lane;
+                e[u] = r < rows && a < A ? idx[a] : -1;
+            }
+            count_rows(lh, e, ceil_div(rows - r0, waves), E);
+        }
+    } else {
+        for (int i = threadIdx.x; i < chunk; i += blockDim.x) {
+            const long long a = a0 + i;
+            const int e = a < A ? idx[a] : -1;
+            if ((unsigned)e < (unsigned)E) atomicAdd(&lh[e], 1);
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < E; i += blockDim.x) hist[(size_t)blockIdx.x * E + i] = lh[i];
 }
 
 // LDS: [waves][E] run counts, then first output positions; [E] totals, then offsets; [E] ids of earlier chunks
-template <int WAVES>
+template <int WAVES, bool LONG>
 __global__ __launch_bounds__(64 * WAVES) void index_scatter(const int32_t* __restrict__ idx, int A, int E, int bits,
                                                             int chunk, int nchunks,
                                                             const int32_t* __restrict__ hist,
@@ -65,7 +106,7 @@ __global__ __launch_bounds__(64 * WAVES) void index_scatter(const int32_t* __res
                                                             int32_t* __restrict__ perm,
                                                             int32_t* __restrict__ inv) {
     constexpr int NT = 64 * WAVES;
-    constexpr int B = 8;                  // rows of 64 ids whose loads are issued together
+    constexpr int B = kRows;              // rows of 64 ids whose loads are issued together
     extern __shared__ int32_t lds[];
     __shared__ int32_t s_valid;
     int32_t* run = lds;
@@ -86,9 +127,13 @@ __global__ __launch_bounds__(64 * WAVES) void index_scatter(const int32_t* __res
     for (int r0 = 0; r0 < rows; r0 += B) {
         int e[B];
         load_rows(r0, e);
+        if constexpr (LONG) {
+            count_rows(run + wave * E, e, rows - r0, E);
+        } else {
 #pragma unroll
-        for (int u = 0; u < B; ++u)
-            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&run[wave * E + e[u]], 1);
+            for (int u = 0; u < B; ++u)
+                if ((unsigned)e[u] < (unsigned)E) atomicAdd(&run[wave * E + e[u]], 1);
+        }
     }
     // totals and the share of the chunks in front of this one (integer sums: exact in any order)
     if (nchunks > 1) {
@@ -249,19 +294,18 @@ hipError_t launch_index(const MoeDims& D, const int32_t* topk_idx, hexa_moe_idx 
     int32_t* hist = (int32_t*)scratch;
     int bits = 0;
     while ((1 << bits) < D.E) ++bits;
+    const bool lng = p.nchunks > 1 && p.chunk >= kLongChunk;
     if (p.nchunks > 1) {
         ProfScope ps(st, "index_count");
-        hipLaunchKernelGGL(index_count, dim3(p.nchunks), dim3(1024), D.E * sizeof(int32_t), st, topk_idx, D.A, D.E,
-                           p.chunk, hist);
+        hipLaunchKernelGGL(lng ? index_count<true> : index_count<false>, dim3(p.nchunks), dim3(1024),
+                           D.E * sizeof(int32_t), st, topk_idx, D.A, D.E, p.chunk, hist);
     }
     ProfScope ps(st, "index_scatter");
     const size_t lds = (size_t)(p.waves + 2) * D.E * sizeof(int32_t);
-    if (p.waves == 16)
-        hipLaunchKernelGGL(index_scatter<16>, dim3(p.nchunks), dim3(1024), lds, st, topk_idx, D.A, D.E, bits, p.chunk,
-                           p.nchunks, hist, out.counts, out.offsets, out.perm, out.inv);
-    else
-        hipLaunchKernelGGL(index_scatter<8>, dim3(p.nchunks), dim3(512), lds, st, topk_idx, D.A, D.E, bits, p.chunk,
-                           p.nchunks, hist, out.counts, out.offsets, out.perm, out.inv);
+    const auto kern = p.waves == 16 ? (lng ? index_scatter<16, true> : index_scatter<16, false>)
+                                    : (lng ? index_scatter<8, true> : index_scatter<8, false>);
+    hipLaunchKernelGGL(kern, dim3(p.nchunks), dim3(64 * p.waves), lds, st, topk_idx, D.A, D.E, bits, p.chunk,
+                       p.nchunks, hist, out.counts, out.offsets, out.perm, out.inv);
     return hipGetLastError();
 }
 

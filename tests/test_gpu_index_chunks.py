@@ -23,6 +23,22 @@ def test_index_plans(oracle, T, k, E, drop):
     if drop:
         ids[rng.random(T * k) < 0.1] = E
         ids[rng.random(T * k) < 0.1] = -1
+    check(oracle, ids, T, k, E, drop)
+
+
+@pytest.mark.parametrize("T,E", [(1, 3), (64, 1), (65, 7), (511, 1), (512, 600), (8192, 64), (8193, 64), (70001, 2), (393216, 5), (393217, 5),
+                                 (400000, 1024), (1100000, 16)])
+@pytest.mark.parametrize("ids_of", ["last", "stray", "dropped"])
+def test_collapsed_routing(oracle, T, E, ids_of):
+    # rows of equal ids are counted in one addition: all on the last expert; all but a few; none in range
+    ids = np.full(T, E if ids_of == "dropped" else E - 1, np.int32)
+    if ids_of == "stray":
+        ids[np.random.default_rng(T).integers(0, T, 1 + T // 3000)] = 0
+        ids[-1] = -1
+    check(oracle, ids, T, 1, E, ids_of != "last")
+
+
+def check(oracle, ids, T, k, E, drop):
     shape = B.make_shape(T, 64, 64, E, k, "f32")
     got = B.alloc_idx(shape, torch.device(DEV))
     for t in got.values():
