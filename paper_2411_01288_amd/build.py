@@ -174,16 +174,18 @@ def sanitizer_runtime() -> str:
 
 def build_sanitized_library(jobs: int = 7) -> str:
     """libhexa_moe_asan.so: the same sources with AddressSanitizer and UndefinedBehaviorSanitizer on the
-    host code (argument checks, workspace layout, launch set-up).  tests/test_sanitizers.py runs the
-    host-only ABI tests against it; GPU sanitizers are not used."""
+    host code (argument checks, workspace layout, launch set-up), and the binding's marshalling (as always).
+    tests/test_sanitizers.py runs the host-only ABI tests against it; GPU sanitizers are not used."""
     def one(src: str) -> str:
         obj = os.path.join(CSRC, src.replace(".hip", ".asan.o"))
         flags = [f for f in FLAGS if f != "-O3"] + ["-O1", "-g", "-fno-omit-frame-pointer"]
         subprocess.check_call(["hipcc", *flags, *SAN_HOST, "-c", os.path.join(CSRC, src), "-o", obj])
         return obj
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(one, SOURCES))
-    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fsanitize=address,undefined",
+        marshal.result()
+    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fsanitize=address,undefined", "-fno-gpu-sanitize",
                            "-shared-libsan", "-o", SAN_LIB, *objs])
     return SAN_LIB
 

@@ -12,7 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 @pytest.fixture(scope="module")
 def B():
     from paper_2411_01288_amd import build as bld
-    if not os.path.exists(bld.LIB):
+    if not (os.path.exists(bld.LIB) and os.path.exists(bld.MARSHAL)):
         bld.build_library()
     from paper_2411_01288_amd import binding
     return binding

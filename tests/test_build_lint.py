@@ -1,6 +1,7 @@
 """The wait-state lint of the build (paper_2411_01288_amd/build.py: lint_asm_hazards) on small listings."""
 import pytest
 
+from paper_2411_01288_amd import build
 from paper_2411_01288_amd.build import lint_asm_hazards
 
 STORE = "\tbuffer_store_dwordx4 v[4:7], v2, s[0:3], s16 offen\n"
@@ -20,3 +21,13 @@ STORE = "\tbuffer_store_dwordx4 v[4:7], v2, s[0:3], s16 offen\n"
 ])
 def test_lint_finds_the_hazards_the_compiler_leaves(text, hits):
     assert len(lint_asm_hazards(text)) == hits
+
+
+def test_both_builds_make_all_that_the_binding_loads(monkeypatch):
+    for name, library in (("build_library", build.LIB), ("build_sanitized_library", build.SAN_LIB)):
+        made = set()
+        monkeypatch.setattr(build.subprocess, "check_call", lambda cmd, **kw: made.add(cmd[cmd.index("-o") + 1]))
+        monkeypatch.setattr(build, "_compile", lambda src: src)
+        monkeypatch.setattr(build, "lint_staging_hazards", lambda *a: None)
+        getattr(build, name)()
+        assert {library, build.MARSHAL} <= made
