@@ -95,8 +95,11 @@ struct Operand {
 // a = a1 + a2 + a3: the upper half of a, of what is left, and of what is left then: 8 + 8 + 8 bits of mantissa, so exactly a but
 // for bits below 2^-133, the smallest number of bf16 (that is, for |a| >= 2^-109).  a b is the six products a1 b1, a1 b2, a2 b1,
 // a2 b2, a1 b3, a3 b1; the other three are 2^-23 of it at most, 2^-24 on average.  Products of bf16 are exact, sums are fp32.
+// `lost` collects what is left for the third plane: a tile in which a bit of any operand has no place (the lower half of that is not zero)
+// is multiplied again on the fp32 instruction.  Sums of 512 products with operands of 1e-36 are off by 4e-7 that way, by 5e-5 in planes.  The
+// collecting takes 1 % (a step of 4096 x 384 x 1536 of 8 520 -> 527 us).
 struct Planes { uint32_t w[3]; };   // of two values
-__device__ __forceinline__ Planes split2(float a, float b) {
+__device__ __forceinline__ Planes split2(float a, float b, uint32_t& lost) {
     Planes p;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -106,6 +109,8 @@ __device__ __forceinline__ Planes split2(float a, float b) {
             b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
         }
     }
+    // (in assembly: the compiler would keep all remainders of a step and combine them at its end)
+    asm("v_or3_b32 %0, %0, %1, %2" : "+v"(lost) : "v"(a), "v"(b));
     return p;
 }
 
@@ -128,7 +133,7 @@ struct SplitOperand {
     __device__ static __forceinline__ int col() { return KS ? 4 * ((int)threadIdx.x / GROUPS) : 4 * group(); }
     // stores the planes of v, or of -v
     template <bool NEG>
-    __device__ static __forceinline__ void put(uint8_t* s, const f32x4 (&v_)[NC]) {
+    __device__ static __forceinline__ void put(uint8_t* s, const f32x4 (&v_)[NC], uint32_t& lost) {
         f32x4 v[NC];
 #pragma unroll
         for (int i = 0; i < NC; ++i) v[i] = NEG ? -v_[i] : v_[i];
@@ -137,14 +142,14 @@ struct SplitOperand {
         if constexpr (KS) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const Planes p = split2(v[0][i], v[1][i]);
+                const Planes p = split2(v[0][i], v[1][i], lost);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) *reinterpret_cast<uint32_t*>(at(col() + i) + q * PLANE) = p.w[q];
             }
         } else {
 #pragma unroll
             for (int i = 0; i < NC; ++i) {
-                const Planes lo = split2(v[i][0], v[i][1]), hi = split2(v[i][2], v[i][3]);
+                const Planes lo = split2(v[i][0], v[i][1], lost), hi = split2(v[i][2], v[i][3], lost);
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     *reinterpret_cast<uint2*>(at(row() + STEP * i) + q * PLANE) = make_uint2(lo.w[q], hi.w[q]);
@@ -304,11 +309,11 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 // against 4.7e-7 of the fp32 instruction at 8000 x 500 x 1000).  So every other step multiplies by -A and is subtracted:
 // the errors of two steps cancel on average (2.0e-7), and every other row tile begins that way (of a contraction of one step or an odd
 // number, the last has no partner; db1 at 4498 x 28 x 1298 5.1e-7 -> 1.7e-7, 1.9e-7 on the fp32 instruction).  And a step's products are added up from zero and then to the accumulator, a rounding per
-// step instead of six.
+// step instead of six.  lost: see split2.
 template <int FM>
 constexpr int split_bytes() { return 3 * 64 * 64 * FM; }
 template <int FM, int OP>
-__device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlace& t, uint8_t* smem, f32x4 (&acc)[FM][FM]) {
+__device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlace& t, uint8_t* smem, f32x4 (&acc)[FM][FM], uint32_t& lost) {
     constexpr int BM = 32 * FM, BK = 32;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
@@ -328,8 +333,8 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
     }
     auto step = [&](auto whole, auto odd, int j) __attribute__((always_inline)) {
         constexpr bool WHOLE = decltype(whole)::value, ODD = decltype(odd)::value;
-        OA::template put<ODD>(smem, va);
-        OB::template put<false>(sb, vb);
+        OA::template put<ODD>(smem, va, lost);
+        OB::template put<false>(sb, vb, lost);
         __syncthreads();
         if (WHOLE || j + 1 < nk) in.template load<WHOLE>((j + 1) * BK, va, vb);
         __builtin_amdgcn_sched_barrier(0);   // (the compiler would put the loads behind the products)
@@ -438,9 +443,10 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
     clear();
     bool plain = !SPLIT;
     if constexpr (SPLIT) {
-        multiply_split<FM, OP>(a, t, smem, acc);
+        uint32_t lost = 0;
+        multiply_split<FM, OP>(a, t, smem, acc, lost);
         // An infinity has no planes (inf - inf is NaN): a tile whose sums are not all finite is multiplied again on the fp32
-        // instruction, which gives what it gave before.
+        // instruction, too.
         float z = 0.f;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -448,7 +454,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
             for (int j = 0; j < FM; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z = fmaf(acc[i][j][r], 0.f, z);
-        plain = __syncthreads_or(z != z) != 0;
+        plain = __syncthreads_or(z != z || (lost & 0xffffu) != 0) != 0;
         if (plain) clear();
     }
     if (plain) multiply_f32<FM, BK, OP>(a, t, reinterpret_cast<float*>(smem), acc);

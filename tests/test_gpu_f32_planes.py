@@ -62,6 +62,34 @@ def test_ends_of_the_range(oracle, big, weight):
     assert nrm_err(host32(y[100]), ref[100]) <= TOL["f32"]
 
 
+def rounding(got, ref, mag):
+    """Errors of sums of products as (largest, root mean square), relative to the sums of the products' sizes `mag`."""
+    e = ((got.double() - ref).abs() / mag).flatten()
+    return float(e.max()), float(e.square().mean().sqrt())
+
+
+# bits below 2^-133 have no place in the planes
+@pytest.mark.parametrize("scale", [1e-34, 1e-36, 1e-38])
+def test_tiny_operands(scale):
+    w = MoEWorkload("tiny", 5000, 640, 704, 1, 1, "f32", "topk", 6)
+    assert_tiles(w, [64, 64, 64, 64])
+    data = generate(w, DEV)
+    data["W1"].zero_()
+    data["b1"] = data["b1"].abs() + 100.0                                  # h = b1, exactly
+    data["W2"] *= 1e4                                                      # (products stay in the normal range)
+    data["dY"] *= scale
+    data["gate"].fill_(1.0)
+    _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    x, dY, W2 = data["x"].double(), data["dY"].double(), data["W2"][0].double()
+    h = data["b1"].double().expand(w.T, -1)
+    # K roundings of 2^-24 of a sum on the way make about sqrt(K) of them, K <= 5000, so these are far from bounds for fp32 sums
+    for name, got, ref, mag in (("dW2", g["dW2"][0], h.t() @ dY, h.t() @ dY.abs()),
+                                ("db1", g["db1"][0], (dY @ W2.t()).sum(0), (dY.abs() @ W2.abs().t()).sum(0)),
+                                ("dW1", g["dW1"][0], x.t() @ (dY @ W2.t()), x.abs().t() @ (dY.abs() @ W2.abs().t()))):
+        top, rms = rounding(got, ref, mag)
+        assert top <= 16 * 2.0 ** -24 and rms <= 2 * 2.0 ** -24, (name, top, rms)
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
 def test_not_finite(value):
     w, data = workload()
