@@ -310,6 +310,10 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 // the errors of two steps cancel on average (2.0e-7), and every other row tile begins that way (of a contraction of one step or an odd
 // number, the last has no partner; db1 at 4498 x 28 x 1298 5.1e-7 -> 1.7e-7, 1.9e-7 on the fp32 instruction).  And a step's products are added up from zero and then to the accumulator, a rounding per
 // step instead of six.  lost: see split2.
+// Contractions of one K-step run on the fp32 instruction: the planes gain them nothing (fc1 at 8192 tokens x 8, 16, 24, 32 x 2048 of 8,
+// top-2, us: 77, 80, 86, 87 that way, 83, 87, 86, 88 in planes; a step of 200000 x 4 x 4 of 4 284 -> 275), and the dropped products show
+// where few are summed (rms error of 1, 2, 4, 8 products 2.5e-8, 2.6e-8, 2.7e-8, 2.7e-8 of their sizes' sum, 6.9e-8, 5.7e-8, 4.5e-8, 3.4e-8 in planes).
+constexpr int kSplitFrom = 33;
 template <int FM>
 constexpr int split_bytes() { return 3 * 64 * 64 * FM; }
 template <int FM, int OP>
@@ -441,8 +445,8 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
             for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     clear();
-    bool plain = !SPLIT;
-    if constexpr (SPLIT) {
+    bool plain = true;
+    if constexpr (SPLIT) if (t.K >= kSplitFrom) {
         uint32_t lost = 0;
         multiply_split<FM, OP>(a, t, smem, acc, lost);
         // An infinity has no planes (inf - inf is NaN): a tile whose sums are not all finite is multiplied again on the fp32

@@ -90,6 +90,59 @@ def test_tiny_operands(scale):
         assert top <= 16 * 2.0 ** -24 and rms <= 2 * 2.0 ** -24, (name, top, rms)
 
 
+def make(T, d, f, E, seed, tiles):
+    w = MoEWorkload("made", T, d, f, E, 1, "f32", "topk", seed)
+    assert_tiles(w, tiles)
+    data = generate(w, DEV)
+    data["gate"].fill_(1.0)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    randn = lambda *s: torch.randn(s, generator=gen, device=DEV)
+    return w, data, randn
+
+
+# A sum of K products is off by at most K roundings of 2^-24 of the products' sizes, and a rounding is about half of that in the root mean
+# square; the later ones are as large as the partial sums, which grow slower than the sizes add up.
+# 32 is the longest contraction that is not split, 64 and 65 are two steps and the first row of a third.
+@pytest.mark.parametrize("rows", [1, 2, 3, 4, 8, 31, 32, 33, 64, 65])
+def test_short_token_contractions(rows):
+    w, data, _ = make(64 * rows, 704, 704, 64, rows, [64, 64, 64, 64])
+    data["topk_idx"] = (torch.arange(w.T, device=DEV, dtype=torch.int32) % 64).view(w.T, 1).contiguous()
+    data["W1"].zero_()
+    data["b1"] = data["b1"].abs() + 0.5                                     # h = b1, exactly
+    data["W2"].copy_(torch.eye(704, device=DEV))                            # dpre = dY, exactly
+    _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    x, dY = (data[n].double().view(rows, 64, 704) for n in ("x", "dY"))
+    h = data["b1"].double()[:, :, None]
+    for name, ref, mag in (("dW1", torch.matmul(x.permute(1, 2, 0).contiguous(), dY.permute(1, 0, 2).contiguous()),
+                            torch.matmul(x.abs().permute(1, 2, 0).contiguous(), dY.abs().permute(1, 0, 2).contiguous())),
+                           ("dW2", h * dY.sum(0)[:, None, :], h * dY.abs().sum(0)[:, None, :])):
+        top, rms = rounding(g[name], ref, mag)
+        assert top <= rows * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, (name, top, rms)
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 8, 31, 32, 33, 64, 65])
+def test_short_row_contractions(K):
+    w, data, randn = make(4096, K, 1024, 1, K, [64, 32, 64, 32])
+    pick = torch.randperm(1024, device=DEV)[:K]
+    one_hot = torch.zeros(K, 1024, device=DEV)
+    one_hot[torch.arange(K, device=DEV), pick] = 1.0
+    # y: some columns of relu(x W1)
+    data["W1"], data["W2"] = randn(1, K, 1024), one_hot.t().contiguous()[None]
+    data["b1"].zero_(), data["b2"].zero_()
+    _, y, _ = run_hip_layer(w, data, activation=B.ACT_RELU)
+    x, W1 = data["x"].double(), data["W1"][0][:, pick].double()
+    on = x @ W1 > 0
+    top, rms = rounding(y[on], (x @ W1)[on], (x.abs() @ W1.abs())[on])
+    assert top <= K * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, ("fc1", top, rms)
+    # dx: some columns of dY W2^T
+    data["W1"], data["W2"] = one_hot[None].contiguous(), randn(1, 1024, K)
+    data["b1"].fill_(100.0)
+    _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    dY, W2 = data["dY"].double(), data["W2"][0][pick].double().t()
+    top, rms = rounding(g["dx"], dY @ W2, dY.abs() @ W2.abs())
+    assert top <= K * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, ("dgrad2", top, rms)
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
 def test_not_finite(value):
     w, data = workload()
