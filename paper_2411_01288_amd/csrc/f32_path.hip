@@ -92,23 +92,31 @@ struct Operand {
 };
 
 // ---- three bf16 planes ----
-// a = a1 + a2 + a3: the upper half of a, of what is left, and of what is left then: 8 + 8 + 8 bits of mantissa, so exactly a but
+// a = a1 + a2 + a3: a rounded to bf16, what is left rounded to bf16, and what is left then: 8 + 8 + 8 bits of mantissa, so exactly a but
 // for bits below 2^-133, the smallest number of bf16 (that is, for |a| >= 2^-109).  a b is the six products a1 b1, a1 b2, a2 b1,
-// a2 b2, a1 b3, a3 b1; the other three are 2^-23 of it at most, 2^-24 on average.  Products of bf16 are exact, sums are fp32.
+// a2 b2, a1 b3, a3 b1; the other three are 2^-24 of it at most (a2 is 2^-8 of a at most, a3 2^-17), 7e-9 in the root mean square, and of
+// either sign.  (Planes cut off instead of rounded: 2^-21 and always towards zero; sums of a single product were off by 4.2e-7 at
+// most and 6.9e-8 in the root mean square, now 9.7e-8 and 2.6e-8, the fp32 instruction 6.0e-8 and 2.5e-8.)  Products of bf16 are exact, sums are fp32.
 // `lost` collects what is left for the third plane: a tile in which a bit of any operand has no place (the lower half of that is not zero)
 // is multiplied again on the fp32 instruction.  Sums of 512 products with operands of 1e-36 are off by 4e-7 that way, by 5e-5 in planes.  The
 // collecting takes 1 % (a step of 4096 x 384 x 1536 of 8 520 -> 527 us).
-struct Planes { uint32_t w[3]; };   // of two values
+struct Planes { uint32_t w[3]; };   // of two values, or of their negatives
+template <bool NEG>
 __device__ __forceinline__ Planes split2(float a, float b, uint32_t& lost) {
     Planes p;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        p.w[q] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // the upper halves
-        if (q < 2) {
-            a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
-            b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
-        }
+    if constexpr (NEG) {
+        asm("v_cvt_pk_bf16_f32 %0, -%1, -%2" : "=v"(p.w[0]) : "v"(a), "v"(b));   // (the compiler negates in instructions of their own)
+        a = -a;
+        b = -b;
+    } else {
+        p.w[0] = pack_bf2(a, b);
     }
+    a -= __uint_as_float(p.w[0] << 16);
+    b -= __uint_as_float(p.w[0] & 0xffff0000u);
+    p.w[1] = pack_bf2(a, b);
+    a -= __uint_as_float(p.w[1] << 16);
+    b -= __uint_as_float(p.w[1] & 0xffff0000u);
+    p.w[2] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // the upper halves
     // (in assembly: the compiler would keep all remainders of a step and combine them at its end)
     asm("v_or3_b32 %0, %0, %1, %2" : "+v"(lost) : "v"(a), "v"(b));
     return p;
@@ -133,23 +141,20 @@ struct SplitOperand {
     __device__ static __forceinline__ int col() { return KS ? 4 * ((int)threadIdx.x / GROUPS) : 4 * group(); }
     // stores the planes of v, or of -v
     template <bool NEG>
-    __device__ static __forceinline__ void put(uint8_t* s, const f32x4 (&v_)[NC], uint32_t& lost) {
-        f32x4 v[NC];
-#pragma unroll
-        for (int i = 0; i < NC; ++i) v[i] = NEG ? -v_[i] : v_[i];
+    __device__ static __forceinline__ void put(uint8_t* s, const f32x4 (&v)[NC], uint32_t& lost) {
         const int k = KT * group(), chunk = k / 8, byte = k % 8 * 2;
         auto at = [&](int r) __attribute__((always_inline)) { return s + (chunk * R + (r ^ chunk)) * 16 + byte; };
         if constexpr (KS) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const Planes p = split2(v[0][i], v[1][i], lost);
+                const Planes p = split2<NEG>(v[0][i], v[1][i], lost);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) *reinterpret_cast<uint32_t*>(at(col() + i) + q * PLANE) = p.w[q];
             }
         } else {
 #pragma unroll
             for (int i = 0; i < NC; ++i) {
-                const Planes lo = split2(v[i][0], v[i][1], lost), hi = split2(v[i][2], v[i][3], lost);
+                const Planes lo = split2<NEG>(v[i][0], v[i][1], lost), hi = split2<NEG>(v[i][2], v[i][3], lost);
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     *reinterpret_cast<uint2*>(at(row() + STEP * i) + q * PLANE) = make_uint2(lo.w[q], hi.w[q]);
@@ -308,8 +313,11 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 // The matrix instruction cuts what lies below its largest product off downwards, which shows in sums over many results (db1: 2.1e-6
 // against 4.7e-7 of the fp32 instruction at 8000 x 500 x 1000).  So every other step multiplies by -A and is subtracted:
 // the errors of two steps cancel on average (2.0e-7), and every other row tile begins that way (of a contraction of one step or an odd
-// number, the last has no partner; db1 at 4498 x 28 x 1298 5.1e-7 -> 1.7e-7, 1.9e-7 on the fp32 instruction).  And a step's products are added up from zero and then to the accumulator, a rounding per
-// step instead of six.  lost: see split2.
+// number, the last has no partner).  And a step's products are added up from zero, those of the first planes apart from the small ones, so that
+// both sums are rounded where they meet and not cut off, and then to the accumulator: two roundings per step.  lost: see split2.
+// Errors are below the fp32 instruction's but for the fewest products: sums of two in a long contraction 3.1e-8 of their sizes (2.6e-8 there), of
+// 16 2.5e-8 (2.8e-8).  (All but a3 b3 of the nine products: a step of 4096 x 384 x 1536 of 8 540 -> 577 us; the small ones added up apart
+// over all steps, which brings those two to 2.2e-8 and 1.3e-8: 561.)
 // Contractions of one K-step run on the fp32 instruction: the planes gain them nothing (fc1 at 8192 tokens x 8, 16, 24, 32 x 2048 of 8,
 // top-2, us: 77, 80, 86, 87 that way, 83, 87, 86, 88 in planes; a step of 200000 x 4 x 4 of 4 284 -> 275), and the dropped products show
 // where few are summed (rms error of 1, 2, 4, 8 products 2.5e-8, 2.6e-8, 2.7e-8, 2.7e-8 of their sizes' sum, 6.9e-8, 5.7e-8, 4.5e-8, 3.4e-8 in planes).
@@ -343,7 +351,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         if (WHOLE || j + 1 < nk) in.template load<WHOLE>((j + 1) * BK, va, vb);
         __builtin_amdgcn_sched_barrier(0);   // (the compiler would put the loads behind the products)
         bf16x8 a1[FM], b1[FM], a2[FM], b2[FM], a3[FM], b3[FM];
-        f32x4 part[FM][FM];
+        f32x4 lo[FM][FM];
         auto read_a = [&](int q, bf16x8 (&f)[FM]) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < FM; ++i) f[i] = OA::frag(smem, q, 16 * (wm * FM + i), l16, grp);
@@ -358,29 +366,33 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
             for (int jj = 0; jj < FM; ++jj)
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    part[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[jj], fa[i], first ? f32x4{0.f, 0.f, 0.f, 0.f} : part[i][jj],
-                                                                          0, 0, 0);
+                    lo[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[jj], fa[i], first ? f32x4{0.f, 0.f, 0.f, 0.f} : lo[i][jj],
+                                                                        0, 0, 0);
         };
-        // small products first; planes are read as they are needed (all at once they take the registers of a fourth
-        // workgroup on the CU)
+        // planes are read as they are needed (all at once they take the registers of a fourth workgroup on the CU)
         read_a(2, a3); read_b(0, b1);
         __builtin_amdgcn_sched_barrier(0);
-        product(true, a3, b1);
-        read_a(0, a1); read_b(2, b3);
-        __builtin_amdgcn_sched_barrier(0);
         read_a(1, a2);
-        product(false, a1, b3);
+        product(true, a3, b1);
         __builtin_amdgcn_sched_barrier(0);
         read_b(1, b2);
         product(false, a2, b1);
         __builtin_amdgcn_sched_barrier(0);
+        read_a(0, a1);
         product(false, a2, b2);
+        __builtin_amdgcn_sched_barrier(0);
+        read_b(2, b3);
         product(false, a1, b2);
-        product(false, a1, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        product(false, a1, b3);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int jj = 0; jj < FM; ++jj)
 #pragma unroll
-            for (int jj = 0; jj < FM; ++jj) acc[i][jj] = ODD ? acc[i][jj] - part[i][jj] : acc[i][jj] + part[i][jj];
+            for (int i = 0; i < FM; ++i) {
+                const f32x4 hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1[jj], a1[i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                const f32x4 part = hi + lo[i][jj];
+                acc[i][jj] = ODD ? acc[i][jj] - part : acc[i][jj] + part;
+            }
         __syncthreads();
     };
     constexpr std::true_type YES;

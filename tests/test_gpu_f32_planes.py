@@ -90,18 +90,21 @@ def test_tiny_operands(scale):
         assert top <= 16 * 2.0 ** -24 and rms <= 2 * 2.0 ** -24, (name, top, rms)
 
 
+def randn(gen, *shape):
+    return torch.randn(shape, generator=gen, device=DEV)
+
+
 def make(T, d, f, E, seed, tiles):
     w = MoEWorkload("made", T, d, f, E, 1, "f32", "topk", seed)
     assert_tiles(w, tiles)
     data = generate(w, DEV)
     data["gate"].fill_(1.0)
     gen = torch.Generator(device=DEV).manual_seed(seed)
-    randn = lambda *s: torch.randn(s, generator=gen, device=DEV)
-    return w, data, randn
+    return w, data, gen
 
 
-# A sum of K products is off by at most K roundings of 2^-24 of the products' sizes, and a rounding is about half of that in the root mean
-# square; the later ones are as large as the partial sums, which grow slower than the sizes add up.
+# A sum of K products is off by at most K roundings of 2^-24 of the products' sizes.  A rounding is at most 2^-24 / sqrt(3) in the root mean
+# square, and all K together make no more: the partial sums that are rounded grow like a square root, the sizes add up.
 # 32 is the longest contraction that is not split, 64 and 65 are two steps and the first row of a third.
 @pytest.mark.parametrize("rows", [1, 2, 3, 4, 8, 31, 32, 33, 64, 65])
 def test_short_token_contractions(rows):
@@ -117,30 +120,57 @@ def test_short_token_contractions(rows):
                             torch.matmul(x.abs().permute(1, 2, 0).contiguous(), dY.abs().permute(1, 0, 2).contiguous())),
                            ("dW2", h * dY.sum(0)[:, None, :], h * dY.abs().sum(0)[:, None, :])):
         top, rms = rounding(g[name], ref, mag)
-        assert top <= rows * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, (name, top, rms)
+        assert top <= rows * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, (name, top, rms)
 
 
 @pytest.mark.parametrize("K", [1, 2, 3, 4, 8, 31, 32, 33, 64, 65])
 def test_short_row_contractions(K):
-    w, data, randn = make(4096, K, 1024, 1, K, [64, 32, 64, 32])
-    pick = torch.randperm(1024, device=DEV)[:K]
+    w, data, gen = make(4096, K, 1024, 1, K, [64, 32, 64, 32])
+    pick = torch.randperm(1024, generator=gen, device=DEV)[:K]
     one_hot = torch.zeros(K, 1024, device=DEV)
     one_hot[torch.arange(K, device=DEV), pick] = 1.0
     # y: some columns of relu(x W1)
-    data["W1"], data["W2"] = randn(1, K, 1024), one_hot.t().contiguous()[None]
+    data["W1"], data["W2"] = randn(gen, 1, K, 1024), one_hot.t().contiguous()[None]
     data["b1"].zero_(), data["b2"].zero_()
     _, y, _ = run_hip_layer(w, data, activation=B.ACT_RELU)
     x, W1 = data["x"].double(), data["W1"][0][:, pick].double()
     on = x @ W1 > 0
     top, rms = rounding(y[on], (x @ W1)[on], (x.abs() @ W1.abs())[on])
-    assert top <= K * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, ("fc1", top, rms)
+    assert top <= K * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, ("fc1", top, rms)
     # dx: some columns of dY W2^T
-    data["W1"], data["W2"] = one_hot[None].contiguous(), randn(1, 1024, K)
+    data["W1"], data["W2"] = one_hot[None].contiguous(), randn(gen, 1, 1024, K)
     data["b1"].fill_(100.0)
     _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
     dY, W2 = data["dY"].double(), data["W2"][0][pick].double().t()
     top, rms = rounding(g["dx"], dY @ W2, dY.abs() @ W2.abs())
-    assert top <= K * 2.0 ** -24 and rms <= 0.5 * 2.0 ** -24, ("dgrad2", top, rms)
+    assert top <= K * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, ("dgrad2", top, rms)
+
+
+# Few products in a long contraction: three roundings of 2^-24 for each (first planes with the others, and to the sum) and as much again
+# for the dropped products (2^-24 at most).  Features of 1 + 2^-7 - 2^-23 have the most in the dropped planes if these are cut off.
+@pytest.mark.parametrize("count,value", [(1, None), (1, 1 + 2.0 ** -7 - 2.0 ** -23), (2, None), (4, None), (16, None)])
+def test_sparse_rows(count, value):
+    w, data, gen = make(4096, 512, 1024, 1, 50 + count, [64, 32, 64, 32])
+    x = torch.zeros(w.T, 512, device=DEV)
+    for _ in range(count):
+        at = torch.randint(0, 512, (w.T,), generator=gen, device=DEV)
+        x[torch.arange(w.T, device=DEV), at] = randn(gen, w.T) if value is None else torch.full((w.T,), value, device=DEV)
+    data["x"] = x
+    pick = torch.randperm(1024, generator=gen, device=DEV)[:512]
+    data["W1"] = randn(gen, 1, 512, 1024)
+    if value is not None:
+        data["W1"].copy_(torch.where(data["W1"] > 0, value, 0.5 * value))
+    data["W2"] = torch.zeros(1, 1024, 512, device=DEV)
+    data["W2"][0, pick, torch.arange(512, device=DEV)] = 1.0
+    data["b1"].zero_(), data["b2"].zero_()
+    _, y, _ = run_hip_layer(w, data, activation=B.ACT_RELU)
+    W1 = data["W1"][0][:, pick].double()
+    ref, mag = x.double() @ W1, x.double().abs() @ W1.abs()
+    on = ref > 0
+    top, rms = rounding(y[on], ref[on], mag[on])
+    assert top <= (2 if count == 1 else 4 * count) * 2.0 ** -24 and rms <= 0.6 * 2.0 ** -24, (top, rms)
+    if value is None:                                                      # no side is preferred
+        assert abs(float((y[on].double() - ref[on]).sum() / mag[on].sum())) <= 0.05 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
