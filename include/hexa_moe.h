@@ -36,6 +36,14 @@
  *     weight matrix and inside one 256-row tile of an activation or gradient
  *     matrix);
  *     HEXA_F32 takes any positive sizes.  E <= 1024.
+ *   - HEXA_F32: the contractions are fp32 sums of products of fp32 operands over
+ *     the whole range of fp32.  Launches of many output tiles multiply operands
+ *     as sums of three bf16 numbers (contractions of more than 32 terms); their
+ *     errors are those of fp32 sums or less, and tiles that such a sum cannot
+ *     represent (infinities, NaN, bits below 2^-133) take the fp32 instruction.
+ *     Same sizes, same bits: a row's result does not depend on its place in the
+ *     batch, only on the sizes of the call and, in its last bits, on whether such
+ *     a value stands in the same tile of rows or weights.
  *   - The first hexa_moe_workspace_bytes, hexa_moe_fwd or hexa_moe_bwd call for a
  *     16-bit shape on a device raises the shared-memory limit of the contraction
  *     kernels there (once per device, thread-safe).  That set-up call must not

@@ -310,11 +310,11 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 }
 
 // The same on v_mfma_f32_16x16x32_bf16 with both operands in three planes; one LDS buffer, the next K-step in registers.
-// The matrix instruction cuts what lies below its largest product off downwards, which shows in sums over many results (db1: 2.1e-6
-// against 4.7e-7 of the fp32 instruction at 8000 x 500 x 1000).  So every other step multiplies by -A and is subtracted:
-// the errors of two steps cancel on average (2.0e-7), and every other row tile begins that way (of a contraction of one step or an odd
-// number, the last has no partner).  And a step's products are added up from zero, those of the first planes apart from the small ones, so that
-// both sums are rounded where they meet and not cut off, and then to the accumulator: two roundings per step.  lost: see split2.
+// A step's products are added up from zero, those of the first planes apart from the small ones, so that both sums are rounded where they
+// meet, and then to the accumulator: two roundings per step.  The matrix instruction itself cuts what lies below its largest product off
+// downwards, which is little of that but adds up in sums over very many results, so every other step multiplies by -A and is subtracted (db1
+// over 300000 rows of 512 products: off by 5.1e-7, 3.0e-7 of it to one side -> 4.1e-7 and 0.6e-7; 6.5e-7 on the fp32 instruction).
+// Steps and signs are the same in every tile: a row's result does not depend on its place in the batch.  lost: see split2.
 // Errors are below the fp32 instruction's but for the fewest products: sums of two in a long contraction 3.1e-8 of their sizes (2.6e-8 there), of
 // 16 2.5e-8 (2.8e-8).  (All but a3 b3 of the nine products: a step of 4096 x 384 x 1536 of 8 540 -> 577 us; the small ones added up apart
 // over all steps, which brings those two to 2.2e-8 and 1.3e-8: 561.)
@@ -398,7 +398,6 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
     constexpr std::true_type YES;
     constexpr std::false_type NO;
     int j = 0;
-    if (t.row_tile & 1) step(NO, YES, j++);
     for (; j + 2 < in.nwhole; j += 2) {
         step(YES, NO, j);
         step(YES, YES, j + 1);

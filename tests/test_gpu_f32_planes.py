@@ -173,6 +173,27 @@ def test_sparse_rows(count, value):
         assert abs(float((y[on].double() - ref[on]).sum() / mag[on].sum())) <= 0.05 * 2.0 ** -24
 
 
+def test_results_do_not_depend_on_the_place_in_the_batch():
+    w, data, _ = make(5000, 608, 704, 1, 9, [64, 64, 64, 64])               # 19 and 22 steps
+    data["x"], data["dY"] = (data[n][:1].expand(w.T, -1).contiguous() for n in ("x", "dY"))
+    _, y, g = run_hip_layer(w, data)
+    assert torch.equal(y, y[:1].expand_as(y)) and torch.equal(g["dx"], g["dx"][:1].expand_as(g["dx"]))
+
+
+def test_column_sums_over_many_rows():
+    """db1 as a sum over 300000 results: what is cut off to one side in each of them adds up in it."""
+    w, data, _ = make(300000, 512, 256, 1, 10, [64, 64, 64, 64])
+    data["W1"].zero_(), data["b1"].fill_(1.0)                               # dpre = dY W2^T
+    _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    ref = sum(c.double().sum(0) for c in data["dY"].split(50000)) @ data["W2"][0].double().t()
+    err = g["db1"][0].double() - ref
+    # A result is off by about 2^-23 of its size at random (errors of fp32 sums of 512 products); so is their sum, and adding up 300000 is
+    # good for three times that.  The mean over 256 columns is a sixteenth of one column's, four times which is allowed.
+    rms = float(ref.square().mean().sqrt())
+    assert float(err.square().mean().sqrt()) <= 5 * 2.0 ** -23 * rms
+    assert abs(float(err.mean())) <= 1.25 * 2.0 ** -23 * rms
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
 def test_not_finite(value):
     w, data = workload()
