@@ -213,3 +213,31 @@ def test_not_finite(value):
     assert float((y[rest] - y0[rest]).abs().max()) <= 2e-6 * float(y0.abs().max())
     others = [i for i in range(w.E) if i != e]
     assert torch.equal(g["dW1"][others], g0["dW1"][others]) and torch.isfinite(g["dx"][rest]).all()
+
+
+@pytest.mark.parametrize("name,at,value", [("x", (1234, 56), float("inf")), ("x", (4999, 639), float("nan")), ("dY", (1234, 5), float("-inf")),
+                                           ("dY", (64, 639), float("nan")), ("W1", (0, 56, 17), float("inf")), ("W2", (0, 703, 5), float("-inf"))])
+def test_not_finite_in_every_contraction(name, at, value):
+    """All four launches on 64x64 tiles: what is infinite, of which sign, and what is NaN in every output, and the rest as accurate
+    as ever.  Columns of one sign in W2 keep infinities of y from meeting their opposites."""
+    w, data, _ = make(5000, 640, 704, 1, 12, [64, 64, 64, 64])
+    data["W2"][0, :, 0].abs_(), data["W2"][0, :, 1].abs_().neg_()
+    data[name][at] = value
+    _, y, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    x, W1, b1, W2, b2, dY = (data[n].double() if n in ("x", "dY") else data[n][0].double() for n in ("x", "W1", "b1", "W2", "b2", "dY"))
+    pre = x @ W1 + b1
+    on = pre > 0                                                           # (NaN: off)
+    h = torch.where(on, pre, torch.zeros_like(pre))
+    dpre = (dY @ W2.t()) * on
+    ref = {"y": h @ W2 + b2, "dx": dpre @ W1.t(), "dW1": x.t() @ dpre, "db1": dpre.sum(0), "dW2": h.t() @ dY, "db2": dY.sum(0)}
+    reached = set()
+    for n, r in ref.items():
+        got = (y if n == "y" else g[n]).double().view_as(r)
+        for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(kind(got), kind(r)), (n, kind)
+        fine = torch.isfinite(r)
+        if not fine.all():
+            reached.add(n)
+        if fine.any():
+            assert nrm_err(got[fine].cpu().numpy(), r[fine].cpu().numpy()) <= TOL["f32"], n
+    assert reached >= {"x": {"dW1"}, "dY": {"dx", "dW1", "db1", "dW2", "db2"}, "W1": {"y", "dx", "dW2"}, "W2": {"y", "dx", "dW1", "db1"}}[name]
