@@ -144,11 +144,14 @@ def _stream():
 
 
 def _load_marshal():
+    rebuild = "build it with `python -m paper_2411_01288_amd.build`"
     try:
         from . import _marshal as m
     except ImportError as e:
-        raise ImportError(f"{_HERE}/_marshal.so is missing or does not load: build it with "
-                          "`python -m paper_2411_01288_amd.build`") from e
+        raise ImportError(f"{_HERE}/_marshal.*.so is missing or does not load: {rebuild}") from e
+    built_for = getattr(m, "torch", "another version")
+    if built_for != str(torch.__version__):
+        raise ImportError(f"{m.__file__} was built for torch {built_for}, this is {torch.__version__}: {rebuild}")
     address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     m.bind(tuple(map(address, (lib.hexa_moe_route, lib.hexa_moe_index, lib.hexa_moe_fwd, lib.hexa_moe_bwd))),
            Shape, _ptr, (torch.float32, torch.bfloat16, torch.float16, torch.int32))

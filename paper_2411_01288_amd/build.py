@@ -129,16 +129,17 @@ def lint_staging_hazards(src: str = "gemm_bf16.hip") -> None:
         raise RuntimeError(f"{src}: wait-state hazards: {bad[:5]}")
 
 
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))   # (another Python does not look for it)
 
 
 def build_marshal() -> str:
-    """_marshal.so: the argument marshalling of binding.py (host code, against the installed torch)."""
+    """_marshal.*.so: the argument marshalling of binding.py (host code, against the installed torch, whose version it keeps)."""
     import torch
     from torch.utils.cpp_extension import include_paths
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden",
                            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           f'-DBUILT_FOR_TORCH="{torch.__version__}"',
                            *(f"-isystem{d}" for d in [*include_paths(), sysconfig.get_paths()["include"]]),
                            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
                            f"-L{lib}", f"-Wl,-rpath,{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10"])

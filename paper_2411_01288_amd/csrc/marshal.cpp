@@ -230,4 +230,12 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, kMethods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&kModule); }
+// torch: the version this was built for (it reads tensors as laid out there; the binding compares)
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject* m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "torch", BUILT_FOR_TORCH) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

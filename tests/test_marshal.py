@@ -1,6 +1,7 @@
 """The argument checks of a pass's calls (csrc/marshal.cpp): what was refused stays refused, with _ptr's errors, and what was
 taken (tensor subclasses, an active function mode, None for an optional output) stays taken."""
 import ctypes
+import sysconfig
 
 import pytest
 import torch
@@ -34,6 +35,14 @@ def test_none_reaches_the_library():
     shape = B.make_shape(T, D, F, E, K, "bf16")
     none = {n: None for n in ("counts", "offsets", "perm", "inv")}
     assert B._marshal.index(shape, None, none, torch.zeros(4), 0) == 1
+
+
+def test_a_module_for_another_torch_or_python_is_refused(monkeypatch):
+    assert B._marshal.torch == torch.__version__
+    assert B._marshal.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(torch, "__version__", "1.0")
+    with pytest.raises(ImportError, match="was built for torch .* build it with"):
+        B._load_marshal()
 
 
 def layer(dev="cuda:0"):
