@@ -63,7 +63,7 @@ struct GemmArgs {
     int chunk_len;        // token contraction: tokens per work item that are aimed at (see chunk_count)
     int share;            // FC2P: number of this share of K, and 64-k blocks per share
     int share_blocks;
-    int streamed;         // 128x128 tiles: large weights, less than a tile of rows per expert (see RowTiles)
+    int streamed;         // 128x128 tiles of a forward pass: large weights, less than a tile of rows per expert (see RowTiles)
     int token_first;      // 256x256 tiles of a backward grid: see token_first()
     const int32_t* lists; // 256x256 tiles: the work lists (see build_worklists)
     int rt_cap;           // their capacity in row tiles
@@ -391,7 +391,7 @@ __device__ __forceinline__ int pick_pair_wave(const GemmArgs& ga, const GemmArgs
     const ExpertLanes<EPL> s(ga.offsets, ga.E);
     int rmine, cmine;
     const int rincl = s.template pieces<false>(BM, rmine), cincl = s.template pieces<true>(gb.chunk_len, cmine);
-    const RowTiles<BM> rows(__builtin_amdgcn_readlane(rincl, 63), ceil_div(ga.N, BM), ga.streamed != 0);
+    const RowTiles<BM> rows(__builtin_amdgcn_readlane(rincl, 63), ceil_div(ga.N, BM), false);
     const int tm = ceil_div(gb.M, BM), tn = ceil_div(gb.N, BM);
     const TokenTiles tok{tm * tn};
     const int items = __builtin_amdgcn_readlane(cincl, 63);
@@ -1188,7 +1188,10 @@ inline bool token_first(const MoeDims& D, int K, int N) {
     const double tr = kCostBig.start_us + kCostBig.block_us * r.blocks, tt = kCostBig.start_us + kCostBig.block_us * t.blocks;
     return tt > tr && r.tiles * tr + t.tiles * tt < 4.0 * kCostBig.slots * tt;
 }
-// Weights that are read once and do not fit the Infinity Cache (256 MB): see RowTiles.
+// Weights that are read once and do not fit the Infinity Cache (256 MB): see RowTiles.  For the forward pass (fc1 / fc2 in us, an eighth
+// of all tiles per XCD -> streamed: 64 tokens, 2048 x 8192 of 64 350 / 248 -> 327 / 243; 1000, 1024 x 4096 of 64 195 / 108 -> 166 / 115; 2000, 2048 x 2048
+// of 64 191 / 132 -> 159 / 107; 300, 1536 x 6144 of 24 155 / 100 -> 153 / 101).  In the backward pass the weight gradients, which share the
+// grid, lose to it where there are few rows: bwd_fc2 of the first 796 -> 842, of 8 tokens at 2048 x 8192 of 16 218 -> 228, of the second 326 -> 318.
 inline bool streamed(const MoeDims& D) {
     return (long long)D.A < (long long)SMALL * D.E && (double)D.E * D.d * D.f * 2.0 > 256e6;
 }
@@ -1331,7 +1334,6 @@ static hipError_t bwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
     const bool small2 = small_bwd2(D), small1 = small_bwd1(D);
     GemmArgs g{};
     g.offsets = idx.offsets; g.perm = idx.perm; g.topk = D.k; g.E = D.E;
-    g.streamed = streamed(D);
     use_lists(D, ws, g);
     g.chunk_len = wgrad_chunk_len(D);
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do

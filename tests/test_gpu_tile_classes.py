@@ -42,3 +42,14 @@ def test_expert_look_up(oracle, E):
     w = MoEWorkload("lanes", 6000, 64, 128, E, min(E, 2), "bf16", "zipf", 60 + E)
     assert_tiles(w, [128, 128, 128, 128])
     full_parity(oracle, w, generate(w, DEV), label=f"E{E}")
+
+
+# more than 256 MB of weights and fewer than 128 rows per expert: the forward pass deals groups of tiles in eighths.  Column tiles
+# with a tail, groups of row tiles with a rest, empty experts
+@pytest.mark.parametrize("T,d,f,E,k,dtype,routing", [(300, 1024, 2112, 62, 2, "bf16", "zipf"), (9, 2048, 3264, 20, 1, "f16", "topk"),
+                                                     (1200, 704, 3136, 61, 1, "bf16", "bias")])
+def test_streamed_weights(oracle, T, d, f, E, k, dtype, routing):
+    w = MoEWorkload("streamed", T, d, f, E, k, dtype, routing, 31 + T)
+    assert w.A < 128 * E and 2 * E * d * f > 256e6
+    assert_tiles(w, [128, 128, 128, 128])
+    full_parity(oracle, w, generate(w, DEV), label=f"streamed T{T}")
