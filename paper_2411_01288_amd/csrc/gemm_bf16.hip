@@ -276,41 +276,59 @@ struct StageKS {
 // lanes numbers their tiles, and all offsets arrive in one memory latency.  It costs a workgroup a few hundred
 // instructions that the CU's second workgroup hides, and saves the launch that would build a list (5 us of a
 // 70 us decode step; used for 256x256 tiles too it cost their contractions 1 to 3 %).
+// What takes a division per expert (into how many chunks one is cut, and how long they are) is only asked where some expert is cut
+// or long enough: with 16 experts per lane the divisions took every workgroup, also those without a tile, several us (bwd_fc2 of 49
+// tokens, 64 x 3392 of 292, top-2: 217 -> 94 us; of 5261 tokens, 768 x 2496 of 126 342 -> 300).  With one expert per lane a division costs
+// no more than the question whether it is needed.
 template <int EPL>
 struct ExpertLanes {
     int b[EPL + 1];                            // segment starts of this lane's experts, and the end of the last
+    int most = 0;                              // rows of the largest of them
     __device__ __forceinline__ ExpertLanes(const int32_t* __restrict__ offsets, int E) {
         const int e0 = (int)(threadIdx.x & 63) * EPL;
 #pragma unroll
         for (int q = 0; q <= EPL; ++q) b[q] = offsets[min(e0 + q, E)];
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) most = max(most, b[q + 1] - b[q]);
     }
+    __device__ __forceinline__ int total() const { return __builtin_amdgcn_readlane(b[EPL], 63); }   // rows of all experts
+    // whether any expert makes several chunks (see chunk_count)
+    __device__ __forceinline__ bool any_cut(int len) const { return __any(most - len / 8 > len) != 0; }
     // pieces of an expert of n rows: row tiles of `len` rows, or (CHUNKS) token-contraction items
     template <bool CHUNKS>
-    __device__ static __forceinline__ int count(int n, int len) { return CHUNKS ? chunk_count(n, len) : ceil_div(n, len); }
+    __device__ static __forceinline__ int count(int n, int len, bool cut) {
+        return CHUNKS ? cut ? chunk_count(n, len) : n > 0 : ceil_div(n, len);
+    }
     // their number: inclusive scan over the lanes
     template <bool CHUNKS>
-    __device__ __forceinline__ int pieces(int len, int& mine) const {
+    __device__ __forceinline__ int pieces(int len, bool cut, int& mine) const {
         mine = 0;
+        if (EPL > 1 && CHUNKS && !cut) {
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) mine += count<CHUNKS>(b[q + 1] - b[q], len);
+            for (int q = 0; q < EPL; ++q) mine += count<CHUNKS>(b[q + 1] - b[q], len, false);
+        } else {
+#pragma unroll
+            for (int q = 0; q < EPL; ++q) mine += count<CHUNKS>(b[q + 1] - b[q], len, true);
+        }
         return wave_scan_incl(mine);
     }
-    // rows of the longest token-contraction item of this lane's experts
-    __device__ __forceinline__ int longest(int len) const {
-        int rows = 0;
+    // whether the longest token-contraction item has `rows` rows or more
+    __device__ __forceinline__ bool any_long(int len, bool cut, int rows) const {
+        if (EPL > 1 ? __any(most >= rows) == 0 || !cut : !cut) return __any(most >= rows) != 0;
+        int longest = 0;
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) rows = max(rows, (b[q + 1] - b[q]) / max(chunk_count(b[q + 1] - b[q], len), 1));
-        return rows;
+        for (int q = 0; q < EPL; ++q) longest = max(longest, (b[q + 1] - b[q]) / max(chunk_count(b[q + 1] - b[q], len), 1));
+        return __any(longest >= rows) != 0;
     }
     // piece number i (wave-uniform, below the total): expert, first row, end row, and (CHUNKS) the number of partial
     // buffers of the experts in front that have several pieces plus the piece's own (-1: the expert's only one)
-    template <bool CHUNKS>
+    template <bool CHUNKS, bool CUT>
     __device__ __forceinline__ ChunkItem find(int i, int len, int incl, int mine) const {
         int slots = 0, slot = 0;
-        if constexpr (CHUNKS) {
+        if constexpr (CHUNKS && CUT) {
 #pragma unroll
             for (int q = 0; q < EPL; ++q) {
-                const int n = count<true>(b[q + 1] - b[q], len);
+                const int n = count<true>(b[q + 1] - b[q], len, true);
                 slots += n > 1 ? n : 0;
             }
             slot = wave_scan_incl(slots) - slots;
@@ -319,12 +337,17 @@ struct ExpertLanes {
         ChunkItem r{0, 0, 0, -1};
 #pragma unroll
         for (int q = 0; q < EPL; ++q) {
-            const int rows = b[q + 1] - b[q], n = count<CHUNKS>(rows, len), c = i - at;
+            const int rows = b[q + 1] - b[q], n = count<CHUNKS>(rows, len, CUT), c = i - at;
             if (c >= 0 && c < n) {
                 r.e = (int)(threadIdx.x & 63) * EPL + q;
-                r.beg = b[q] + (CHUNKS ? chunk_start(rows, n, c) : c * len);
-                r.end = CHUNKS ? b[q] + chunk_start(rows, n, c + 1) : min(b[q + 1], r.beg + len);
-                r.slot = n > 1 ? slot + c : -1;
+                if constexpr (CHUNKS && !CUT) {
+                    r.beg = b[q];
+                    r.end = b[q + 1];
+                } else {
+                    r.beg = b[q] + (CHUNKS ? chunk_start(rows, n, c) : c * len);
+                    r.end = CHUNKS ? b[q] + chunk_start(rows, n, c + 1) : min(b[q + 1], r.beg + len);
+                    r.slot = n > 1 ? slot + c : -1;
+                }
             }
             at += n;
             slot += n > 1 ? n : 0;
@@ -349,11 +372,11 @@ template <int EPL, int BM>
 __device__ __forceinline__ bool pick_rows_wave(const GemmArgs& g, int x, int loc, Tile& t) {
     const ExpertLanes<EPL> s(g.offsets, g.E);
     int mine;
-    const int incl = s.template pieces<false>(BM, mine);
+    const int incl = s.template pieces<false>(BM, false, mine);
     const RowTiles<BM> rows(__builtin_amdgcn_readlane(incl, 63), ceil_div(g.N, BM), g.streamed != 0);
     if (loc >= rows.count(x)) return false;
     rows.tile(x, loc, t.tile_m, t.tile_n);
-    t.it = s.template find<false>(t.tile_m, BM, incl, mine);
+    t.it = s.template find<false, false>(t.tile_m, BM, incl, mine);
     return true;
 }
 template <int BM>
@@ -376,11 +399,7 @@ __device__ __forceinline__ bool pick_rows_big(const GemmArgs& g, int x, int loc,
 // few rounds (token_first()).  128x128 tiles, of which a launch has a round or two: whichever has the longer ones on average, but the
 // token contraction where its longest are twice as long (4096 x 384 x 1536 of 8, bwd_fc2: 38 -> 33 us; 3001 x 320 x 448 of 17 under
 // Zipf routing, the step: 81.0 -> 80.1; by the longest item alone, 1146 x 576 x 2304 of 20 under Zipf routing, bwd_fc2: 48 -> 53).
-template <int BM>
-__device__ __forceinline__ int pair_order(const RowTiles<BM>& rows, const TokenTiles& tok, int items, bool b_first, int x,
-                                          int& loc) {
-    const int na = rows.count(x), nb = tok.count(x, items);
-    if (loc >= na + nb) return 0;
+__device__ __forceinline__ int pair_order(int na, int nb, bool b_first, int& loc) {
     const bool is_b = b_first ? loc < nb : loc >= na;
     if (is_b && !b_first) loc -= na;
     if (!is_b && b_first) loc -= nb;
@@ -389,20 +408,25 @@ __device__ __forceinline__ int pair_order(const RowTiles<BM>& rows, const TokenT
 template <int EPL, int BM>
 __device__ __forceinline__ int pick_pair_wave(const GemmArgs& ga, const GemmArgs& gb, int x, int loc, Tile& t) {
     const ExpertLanes<EPL> s(ga.offsets, ga.E);
+    const bool cut = s.any_cut(gb.chunk_len);
     int rmine, cmine;
-    const int rincl = s.template pieces<false>(BM, rmine), cincl = s.template pieces<true>(gb.chunk_len, cmine);
+    const int rincl = s.template pieces<false>(BM, false, rmine), cincl = s.template pieces<true>(gb.chunk_len, cut, cmine);
     const RowTiles<BM> rows(__builtin_amdgcn_readlane(rincl, 63), ceil_div(ga.N, BM), false);
     const int tm = ceil_div(gb.M, BM), tn = ceil_div(gb.N, BM);
     const TokenTiles tok{tm * tn};
     const int items = __builtin_amdgcn_readlane(cincl, 63);
-    const bool b_first = __any(s.longest(gb.chunk_len) >= 2 * ga.K) != 0 || (items > 0 && ga.offsets[ga.E] / items > ga.K);
-    const int which = pair_order<BM>(rows, tok, items, b_first, x, loc);
+    // (the second: more than K rows on average, rounded down)
+    const bool b_first = s.any_long(gb.chunk_len, cut, 2 * ga.K) || (long long)s.total() >= (ga.K + 1LL) * items;
+    const int na = rows.count(x), nb = tok.count(x, items);
+    if (loc >= na + nb) return 0;
+    const int which = pair_order(na, nb, b_first, loc);
     if (which == 1) {
         rows.tile(x, loc, t.tile_m, t.tile_n);
-        t.it = s.template find<false>(t.tile_m, BM, rincl, rmine);
-    } else if (which == 2) {
+        t.it = s.template find<false, false>(t.tile_m, BM, rincl, rmine);
+    } else {
         int tile;
-        t.it = s.template find<true>(tok.find(x, loc, tile), gb.chunk_len, cincl, cmine);
+        const int i = tok.find(x, loc, tile);
+        t.it = cut ? s.template find<true, true>(i, gb.chunk_len, cincl, cmine) : s.template find<true, false>(i, gb.chunk_len, cincl, cmine);
         grouped_tile<group_rows(BM)>(tile, tm, tn, t.tile_m, t.tile_n);
     }
     return which;
@@ -413,11 +437,13 @@ __device__ __forceinline__ int pick_pair(const GemmArgs& ga, const GemmArgs& gb,
         const RowTiles<BM> rows(ga.lists[WL_TILES], ceil_div(ga.N, BM), false);
         const int tm = ceil_div(gb.M, BM), tn = ceil_div(gb.N, BM);
         const TokenTiles tok{tm * tn};
-        const int which = pair_order<BM>(rows, tok, ga.lists[WL_ITEMS], ga.lists[order] != 0 || ga.token_first != 0, x, loc);
+        const int na = rows.count(x), nb = tok.count(x, ga.lists[WL_ITEMS]);
+        if (loc >= na + nb) return 0;
+        const int which = pair_order(na, nb, ga.lists[order] != 0 || ga.token_first != 0, loc);
         if (which == 1) {
             rows.tile(x, loc, t.tile_m, t.tile_n);
             t.it = list_entry(ga.lists + kWlHeader + 4 * t.tile_m);
-        } else if (which == 2) {
+        } else {
             int tile;
             t.it = list_entry(ga.lists + kWlHeader + 4 * (ga.rt_cap + tok.find(x, loc, tile)));
             grouped_tile<group_rows(BM)>(tile, tm, tn, t.tile_m, t.tile_n);

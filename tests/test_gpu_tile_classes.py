@@ -5,6 +5,7 @@ covered on samples by test_gpu_full_configs.py)."""
 import pytest
 import torch
 
+from paper_2411_01288_amd import binding as B
 from paper_2411_01288_amd.workloads import MoEWorkload, generate
 from gpu_util import assert_tiles
 from test_gpu_parity import full_parity
@@ -53,3 +54,21 @@ def test_streamed_weights(oracle, T, d, f, E, k, dtype, routing):
     assert w.A < 128 * E and 2 * E * d * f > 256e6
     assert_tiles(w, [128, 128, 128, 128])
     full_parity(oracle, w, generate(w, DEV), label=f"streamed T{T}")
+
+
+# the look-up divides only where an expert is cut into chunks, which is from L + L / 8 + 1 rows on: the last size without, the first with,
+# few rows on many experts (none near it); one, four and sixteen experts per lane
+@pytest.mark.parametrize("E", [40, 130, 300])
+@pytest.mark.parametrize("over", [0, 1, None])
+def test_look_up_with_and_without_cut_experts(oracle, E, over):
+    w = MoEWorkload("cut", 3000 if over is not None else 2 * E // 3, 64, 192, E, 1, "bf16", "topk", E)
+    assert_tiles(w, [128, 128, 128, 128])
+    data = generate(w, DEV)
+    if over is not None:
+        L = B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, E, 1, w.dtype))["chunk_rows"]
+        n = L + L // 8 + over
+        assert n < w.T
+        at = torch.randperm(w.T, device=DEV)
+        data["topk_idx"][at[:n]] = E - 3
+        data["topk_idx"][at[n:]] = (torch.arange(w.T - n, device=DEV, dtype=torch.int32) % (E - 3)).view(-1, 1)
+    full_parity(oracle, w, data, label=f"cut E{E} {over}")
