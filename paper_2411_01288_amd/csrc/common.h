@@ -129,8 +129,7 @@ __device__ __forceinline__ ChunkItem chunk_find_wave(const int32_t* __restrict__
 
 // Slot `slot` of a token contraction whose items have `tiles` output tiles each: the item, and the tile, one of an
 // eighth of the item's tiles (neighbouring ones) per XCD; -1: none.  Where the tiles are no multiple of eight, which XCDs
-// take one more goes round from item to item (36 tiles as 5 5 5 5 5 5 5 1 for every item left the last XCD idle: the
-// backward contractions of 32768 x 768 x 3072 under Zipf routing 632 + 548 -> 615 + 529 us).
+// take one more goes round from item to item.  (The fp32 path's deal; the 16-bit path's, in deal.h, leaves no slots without a tile.)
 __device__ __forceinline__ int token_item_of(int slot, int tiles, int& tile) {
     const int per = ceil_div(tiles, kXcds), loc = slot / kXcds;
     const int item = loc / per;
@@ -256,7 +255,7 @@ template <typename T>
 hipError_t launch_bwd_finish(const MoeDims& D, const hexa_moe_idx& idx, const MoeWorkspace& ws, int dgrad2_row_tile,
                              int L, T* dx, float* dW1, float* db1, float* dW2, float* db2, hipStream_t st);
 
-// fp32 path (fp32 matrix instructions)
+// fp32 path (fp32 matrix instructions, or bf16 ones on operands in three parts)
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,
                           const float* W2, const float* b2, const hexa_moe_idx& idx,
                           const MoeWorkspace& ws, hipStream_t st);

@@ -21,7 +21,7 @@ __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& til
 // Workgroup i runs on XCD i % 8, as number i / 8 of that XCD, and the XCDs fill up in this order: so an XCD's
 // tiles are numbered without gaps, and workgroups without a tile (the grid is sized for the worst routing) come last.
 // With such workgroups in between, the ones behind them find places taken: 492 tiles of two per CU took two rounds
-// instead of one (bwd_fc1 at 4096 x 384 x 1536 of 8 experts, 31 -> 21 us).
+// instead of one (bwd_fc1 at 4096 x 384 x 1536 of 8 experts, 33 -> 26 us).
 
 // The tiles of a row GEMM, tm x tn.  256x256 tiles: groups dealt round-robin to the XCDs, so the 8 XCDs work on
 // neighbouring row tiles (mostly one expert) at any time; what is left after rounds of eight groups is shared out tile by tile,
@@ -80,8 +80,9 @@ struct RowTiles {
 
 // The last round of 256x256 tiles, one per CU, leaves most of an XCD's 32 CUs idle for a whole tile where few are left:
 // up to kQuartersUpTo of them are cut into four 128x128 tiles each, which have the CU to themselves too and take 0.33 to 0.4
-// of the time.  Two full rounds of quarters do not win (16 tiles per XCD, 3720 tokens, 960 x 3840 of 4, fc2: 86 -> 91 us).  fc1 + fc2 of a serving pass of 8192 tokens, 1024 x 4096 of 32 (324 and
-// 1296 tiles of 256 per round): 214 + 179 -> 202 + 168 us; fc2 at 16384 x 1024 x 4096 of 32 310 -> 249, 32768 x 768 x 3072 of 16 324 -> 287.
+// of the time.  Two full rounds of quarters do not win (16 tiles per XCD, 3720 tokens, 960 x 3840 of 4, fc2: 86 -> 91 us).  fc2 of a serving
+// pass of 8192 tokens, 1024 x 4096 of 32 (324 tiles, 256 a round): 184 -> 151 us; in a step at 16384 x 1024 x 4096 of 32 279 -> 267, 32768 x 768 x 3072
+// of 16 303 -> 283, 65536 x 1024 x 4096 of 32 462 -> 423.
 constexpr int kCusPerXcd = 32, kQuartersUpTo = 12;
 
 // What workgroup number loc of XCD x works on: tile number loc of the XCD (changed to it), all of it (quarter -1) or the quarter

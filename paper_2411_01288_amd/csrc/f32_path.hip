@@ -4,15 +4,15 @@
 // 32x32 where those are too few for 256 CUs) and several workgroups share a CU and hide each other's latencies.
 //
 // 32x32 tiles run on v_mfma_f32_16x16x4_f32: 256 FLOP per clock and CU (157 TFLOP/s on the chip), a sixteenth of the bf16
-// rate.  64x64 tiles run on the bf16 instruction with every operand split into three bf16 numbers that add up to it (see split2):
-// six products instead of one, at sixteen times the rate.  What bounds them is no longer the matrix pipe (28 % busy) but
-// everything around it in turn: splitting (35 % of the vector pipe), LDS (34 %), two barriers a step.
+// rate.  64x64 tiles run on the bf16 instruction with every operand split into three bf16 numbers that add up to it (see split2;
+// the method of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
+// 2019): six products instead of one, at sixteen times the rate.  What bounds them is no longer the matrix pipe (27 to 31 % busy) but
+// everything around it in turn: splitting, LDS (33 to 39 %), two barriers a step.
 // Measured at 8192 rows, d = 384, f = 1536, 8 experts (9.7 GFLOP a contraction), against the fp32 instruction on the same tiles:
-// fc1 121 -> 105 us, fc2 120 -> 101, the two backward layers 219 -> 192 and 213 -> 185; at 8192 rows, 512 x 1024, 3 experts 96 -> 86,
-// 94 -> 85, 170 -> 157, 172 -> 159.  Errors against fp64, that shape's step: y 8.1e-7 -> 2.0e-7, dx 8.0e-7 -> 2.0e-7, dW1 6.9e-7 -> 1.9e-7, db1
-// 4.0e-7 -> 1.6e-7.  Tried and not kept: planes by rounding (cvt_pk; errors 1.7e-7, 3 % slower), all fragments read at once (three
-// workgroups per CU, 12 % slower), two LDS buffers with the split between the products (12 % slower), 64x128 tiles (fc2
-// 3 % faster, fc1 20 % slower).
+// fc1 110 -> 95 us, fc2 108 -> 93, the two backward layers 199 -> 171 and 194 -> 168.  Errors against fp64, that shape's step: y 8.0e-7 ->
+// 1.7e-7, dx 8.0e-7 -> 1.7e-7, dW1 6.8e-7 -> 1.5e-7, db1 3.8e-7 -> 1.4e-7; at other lengths see split2, multiply_split and kSplitFrom.  Tried
+// and not kept: all fragments read at once (three workgroups per CU, 12 % slower), two LDS buffers with the split between the products
+// (12 % slower), 64x128 tiles (fc2 3 % faster, fc1 20 % slower).
 #include <type_traits>
 
 #include "common.h"
@@ -99,7 +99,7 @@ struct Operand {
 // most and 6.9e-8 in the root mean square, now 9.7e-8 and 2.6e-8, the fp32 instruction 6.0e-8 and 2.5e-8.)  Products of bf16 are exact, sums are fp32.
 // `lost` collects what is left for the third plane: a tile in which a bit of any operand has no place (the lower half of that is not zero)
 // is multiplied again on the fp32 instruction.  Sums of 512 products with operands of 1e-36 are off by 4e-7 that way, by 5e-5 in planes.  The
-// collecting takes 1 % (a step of 4096 x 384 x 1536 of 8 520 -> 527 us).
+// collecting takes 1 % (a step of 4096 x 384 x 1536 of 8 520 -> 527 us); a launch of such tiles only takes both times (bwd_fc2 there 172 -> 322).
 struct Planes { uint32_t w[3]; };   // of two values, or of their negatives
 template <bool NEG>
 __device__ __forceinline__ Planes split2(float a, float b, uint32_t& lost) {
@@ -533,11 +533,12 @@ int token_items(const MoeDims& D, int bm) {
     return kXcds * ceil_div(ceil_div(D.d, bm) * ceil_div(D.f, bm), kXcds) * (D.A / f32_chunk_len(D) + D.E);
 }
 
-// Which class a launch takes: 64x64 tiles fetch half as much per FLOP, 32x32 tiles are four times as many and
+// Which class a launch takes: 64x64 tiles fetch half as much per FLOP and multiply in planes, 32x32 tiles are four times as many and
 // waste less at the ends of segments.  The line is where a row GEMM has 700 of the larger tiles, not quite three
-// per CU; measured on both sides (us, 64x64 / 32x32), d = 384, f = 1536, 8 experts, top-2: fc1 113 / 142 at
-// 4096 tokens (3264 tiles), 46 / 45 at 1024 (960 tiles); fc2 at 1024 tokens (240 tiles) 46 / 43; d = 64,
-// f = 256, 4 experts at 256 tokens (32 tiles): fc1 9.6 / 6.5.
+// per CU; measured on both sides (us, 64x64 / 32x32), d = 384, f = 1536, 8 experts, top-2: fc1 91 / 107 at 4096 tokens
+// (3264 tiles), 34 / 34 at 1024 (960), 24 / 23 at 512 (576), 23 / 17 at 256 (384); fc2 89 / 97 at 4096 (816), 54 / 56 at 2048 (432),
+// 43 / 35 at 1024 (240).  A backward grid takes its row GEMM's class; by itself it would take 64x64 tiles earlier (bwd_fc1 at 2048
+// tokens 91 / 106) and for the narrowest layers not at all (bwd_fc2 at 100000 x 4 x 4 of 4, 1566 tiles, 36 / 24).
 bool small_rows(const MoeDims& D, int N) {
     return (long long)(D.A / 64 + D.E) * ceil_div(N, 64) < 700;
 }
