@@ -310,14 +310,15 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 }
 
 // The same on v_mfma_f32_16x16x32_bf16 with both operands in three planes; one LDS buffer, the next K-step in registers.
-// A step's products are added up from zero, those of the first planes apart from the small ones, so that both sums are rounded where they
-// meet, and then to the accumulator: two roundings per step.  The matrix instruction itself cuts what lies below its largest product off
-// downwards, which is little of that but adds up in sums over very many results, so every other step multiplies by -A and is subtracted (db1
-// over 300000 rows of 512 products: off by 5.1e-7, 3.0e-7 of it to one side -> 4.1e-7 and 0.6e-7; 6.5e-7 on the fp32 instruction).
+// The products of the first planes are added up from zero in every step and then to the accumulator, so that a step rounds once where the
+// sums meet; the small ones are added up apart over all steps, and to the accumulator at the end.  The matrix instruction itself
+// cuts what lies below its largest product off downwards, which is little of that but adds up in sums over very many results, so every other
+// step multiplies by -A and is subtracted (db1 over 300000 rows of 512 products: 3.0e-7 to one side -> 0.5e-7; errors of 4.8e-7, of 6.5e-7
+// on the fp32 instruction).
 // Steps and signs are the same in every tile: a row's result does not depend on its place in the batch.  lost: see split2.
-// Errors are below the fp32 instruction's but for the fewest products: sums of two in a long contraction 3.1e-8 of their sizes (2.6e-8 there), of
-// 16 2.5e-8 (2.8e-8).  (All but a3 b3 of the nine products: a step of 4096 x 384 x 1536 of 8 540 -> 577 us; the small ones added up apart
-// over all steps, which brings those two to 2.2e-8 and 1.3e-8: 561.)
+// Errors are below the fp32 instruction's but where a long contraction has a single product that is not zero (2.6e-8 against 2.5e-8 in the
+// root mean square; of two 2.2e-8 against 2.6e-8, of 16 1.3e-8 against 2.8e-8 of their sizes).  (All but a3 b3 of the nine products: a step of
+// 4096 x 384 x 1536 of 8 540 -> 577 us.  The small products added up with the large ones in every step: the same time, of two 3.1e-8.)
 // Contractions of one K-step run on the fp32 instruction: the planes gain them nothing (fc1 at 8192 tokens x 8, 16, 24, 32 x 2048 of 8,
 // top-2, us: 77, 80, 86, 87 that way, 83, 87, 86, 88 in planes; a step of 200000 x 4 x 4 of 4 284 -> 275), and the dropped products show
 // where few are summed (rms error of 1, 2, 4, 8 products 2.5e-8, 2.6e-8, 2.7e-8, 2.7e-8 of their sizes' sum, 6.9e-8, 5.7e-8, 4.5e-8, 3.4e-8 in planes).
@@ -343,6 +344,11 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         in.load_perm(0);
         in.template load<false>(0, va, vb);
     }
+    f32x4 low[FM][FM];    // the small products of all steps
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < FM; ++jj) low[i][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto step = [&](auto whole, auto odd, int j) __attribute__((always_inline)) {
         constexpr bool WHOLE = decltype(whole)::value, ODD = decltype(odd)::value;
         OA::template put<ODD>(smem, va, lost);
@@ -350,8 +356,13 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         __syncthreads();
         if (WHOLE || j + 1 < nk) in.template load<WHOLE>((j + 1) * BK, va, vb);
         __builtin_amdgcn_sched_barrier(0);   // (the compiler would put the loads behind the products)
+        if (j > 0) {     // the small products have the sign of the step's.  (As a branch: spills none of the step's registers)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int jj = 0; jj < FM; ++jj) low[i][jj] = -low[i][jj];
+        }
         bf16x8 a1[FM], b1[FM], a2[FM], b2[FM], a3[FM], b3[FM];
-        f32x4 lo[FM][FM];
         auto read_a = [&](int q, bf16x8 (&f)[FM]) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < FM; ++i) f[i] = OA::frag(smem, q, 16 * (wm * FM + i), l16, grp);
@@ -361,37 +372,35 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
             for (int i = 0; i < FM; ++i) f[i] = OB::frag(sb, q, 16 * (wn * FM + i), l16, grp);
         };
         // B first: the block comes out transposed, a lane holds row l16 and four consecutive columns
-        auto product = [&](bool first, const bf16x8 (&fa)[FM], const bf16x8 (&fb)[FM]) __attribute__((always_inline)) {
+        auto product = [&](const bf16x8 (&fa)[FM], const bf16x8 (&fb)[FM]) __attribute__((always_inline)) {
 #pragma unroll
             for (int jj = 0; jj < FM; ++jj)
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
-                    lo[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[jj], fa[i], first ? f32x4{0.f, 0.f, 0.f, 0.f} : lo[i][jj],
-                                                                        0, 0, 0);
+                for (int i = 0; i < FM; ++i) low[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[jj], fa[i], low[i][jj], 0, 0, 0);
         };
         // planes are read as they are needed (all at once they take the registers of a fourth workgroup on the CU)
         read_a(2, a3); read_b(0, b1);
         __builtin_amdgcn_sched_barrier(0);
         read_a(1, a2);
-        product(true, a3, b1);
+        product(a3, b1);
         __builtin_amdgcn_sched_barrier(0);
         read_b(1, b2);
-        product(false, a2, b1);
+        product(a2, b1);
         __builtin_amdgcn_sched_barrier(0);
         read_a(0, a1);
-        product(false, a2, b2);
+        product(a2, b2);
         __builtin_amdgcn_sched_barrier(0);
         read_b(2, b3);
-        product(false, a1, b2);
+        product(a1, b2);
         __builtin_amdgcn_sched_barrier(0);
-        product(false, a1, b3);
+        product(a1, b3);
 #pragma unroll
         for (int jj = 0; jj < FM; ++jj)
 #pragma unroll
             for (int i = 0; i < FM; ++i) {
+                if (i == 0) __builtin_amdgcn_sched_barrier(0);   // (two at a time: registers)
                 const f32x4 hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1[jj], a1[i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                const f32x4 part = hi + lo[i][jj];
-                acc[i][jj] = ODD ? acc[i][jj] - part : acc[i][jj] + part;
+                acc[i][jj] = ODD ? acc[i][jj] - hi : acc[i][jj] + hi;
             }
         __syncthreads();
     };
@@ -406,6 +415,11 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         step(NO, NO, j);
         if (j + 1 < nk) step(NO, YES, j + 1);
     }
+    // low has the sign of the last step
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < FM; ++jj) acc[i][jj] = nk & 1 ? acc[i][jj] + low[i][jj] : acc[i][jj] - low[i][jj];
 }
 
 // One tile of contraction OP: 32 FM x 32 FM outputs, four wavefronts as 2 x 2.  ESMM (Sec. 3.1 item 1; App. B Alg. 2) for

@@ -146,7 +146,7 @@ def test_short_row_contractions(K):
     assert top <= K * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, ("dgrad2", top, rms)
 
 
-# Few products in a long contraction: three roundings of 2^-24 for each (first planes with the others, and to the sum) and as much again
+# Few products in a long contraction: a rounding of 2^-24 for each where the large products meet the sum and one for the small ones, and as much again
 # for the dropped products (2^-24 at most).  Features of 1 + 2^-7 - 2^-23 have the most in the dropped planes if these are cut off.
 @pytest.mark.parametrize("count,value", [(1, None), (1, 1 + 2.0 ** -7 - 2.0 ** -23), (2, None), (4, None), (16, None)])
 def test_sparse_rows(count, value):
@@ -168,7 +168,7 @@ def test_sparse_rows(count, value):
     ref, mag = x.double() @ W1, x.double().abs() @ W1.abs()
     on = ref > 0
     top, rms = rounding(y[on], ref[on], mag[on])
-    assert top <= (2 if count == 1 else 4 * count) * 2.0 ** -24 and rms <= 0.6 * 2.0 ** -24, (top, rms)
+    assert top <= 2 * count * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, (top, rms)
     if value is None:                                                      # no side is preferred
         assert abs(float((y[on].double() - ref[on]).sum() / mag[on].sum())) <= 0.05 * 2.0 ** -24
 
@@ -222,6 +222,10 @@ def test_not_finite_in_every_contraction(name, at, value):
     as ever.  Columns of one sign in W2 keep infinities of y from meeting their opposites."""
     w, data, _ = make(5000, 640, 704, 1, 12, [64, 64, 64, 64])
     data["W2"][0, :, 0].abs_(), data["W2"][0, :, 1].abs_().neg_()
+    # pre-activations are odd multiples of 2^-12, so that no rounding decides which hidden units are on
+    data["x"] = torch.round(data["x"] * 8) / 8
+    data["W1"] = torch.round(data["W1"] * 256) / 256
+    data["b1"] = torch.round(data["b1"] * 2048) / 2048 + 2.0 ** -12
     data[name][at] = value
     _, y, g = run_hip_layer(w, data, activation=B.ACT_RELU)
     x, W1, b1, W2, b2, dY = (data[n].double() if n in ("x", "dY") else data[n][0].double() for n in ("x", "W1", "b1", "W2", "b2", "dY"))
