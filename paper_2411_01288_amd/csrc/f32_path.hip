@@ -9,7 +9,7 @@
 // 2019): six products instead of one, at sixteen times the rate.  What bounds them is no longer the matrix pipe (27 to 31 % busy) but
 // everything around it in turn: splitting, LDS (33 to 39 %), two barriers a step.
 // Measured at 8192 rows, d = 384, f = 1536, 8 experts (9.7 GFLOP a contraction), against the fp32 instruction on the same tiles:
-// fc1 110 -> 95 us, fc2 108 -> 93, the two backward layers 199 -> 171 and 194 -> 168.  Errors against fp64, that shape's step: y 8.0e-7 ->
+// fc1 110 -> 94 us, fc2 108 -> 91, the two backward layers 199 -> 167 and 192 -> 163.  Errors against fp64, that shape's step: y 8.0e-7 ->
 // 1.7e-7, dx 8.0e-7 -> 1.7e-7, dW1 6.8e-7 -> 1.5e-7, db1 3.8e-7 -> 1.4e-7; at other lengths see split2, multiply_split and kSplitFrom.  Tried
 // and not kept: all fragments read at once (three workgroups per CU, 12 % slower), two LDS buffers with the split between the products
 // (12 % slower), 64x128 tiles (fc2 3 % faster, fc1 20 % slower).
@@ -318,7 +318,7 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 // Steps and signs are the same in every tile: a row's result does not depend on its place in the batch.  lost: see split2.
 // Errors are below the fp32 instruction's but where a long contraction has a single product that is not zero (2.6e-8 against 2.5e-8 in the
 // root mean square; of two 2.2e-8 against 2.6e-8, of 16 1.3e-8 against 2.8e-8 of their sizes).  (All but a3 b3 of the nine products: a step of
-// 4096 x 384 x 1536 of 8 540 -> 577 us.  The small products added up with the large ones in every step: the same time, of two 3.1e-8.)
+// 4096 x 384 x 1536 of 8 541 -> 584 us.  The small products added up with the large ones in every step: the same time, of two 3.1e-8.)
 // Contractions of one K-step run on the fp32 instruction: the planes gain them nothing (fc1 at 8192 tokens x 8, 16, 24, 32 x 2048 of 8,
 // top-2, us: 77, 80, 86, 87 that way, 83, 87, 86, 88 in planes; a step of 200000 x 4 x 4 of 4 284 -> 275), and the dropped products show
 // where few are summed (rms error of 1, 2, 4, 8 products 2.5e-8, 2.6e-8, 2.7e-8, 2.7e-8 of their sizes' sum, 6.9e-8, 5.7e-8, 4.5e-8, 3.4e-8 in planes).
