@@ -192,7 +192,7 @@ hipError_t gemm_bf16_device_init();
 
 // saved + staging regions inside the caller's workspace (device pointers)
 struct MoeWorkspace {
-    void* pre;      // [A,f] elem   fp32: pre-activations; bf16: GELU'(pre), perm order (saved by fwd)
+    void* pre;      // [A,f] elem   F'(pre), perm order                 (saved by fwd)
     void* h;        // [A,f] elem   activations, perm order            (saved by fwd)
     void* o;        // [A,d] elem   per-assignment expert outputs      (saved by fwd)
     float* fc2part; // [shares,A,d] f32 unrounded sums of a split FC2 (16-bit path, few rows; fwd staging)

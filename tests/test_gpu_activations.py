@@ -52,3 +52,25 @@ def test_activation_parity(oracle_act, kind, dtype, T, d, f, E, k):
                         data["W2"], data["b2"], idx, ws)
     torch.cuda.synchronize()
     assert nrm_err(host32(y0), y_ref) > 2.5 * tol
+
+
+@pytest.mark.parametrize("lo,hi", [(-0.1, 0.1), (-1, 1), (-6, -1), (1, 6), (-40, 40)])
+def test_f32_gelu_and_its_derivative(lo, hi):
+    """One feature, one hidden unit, weights of one: y is F(x) and dx is F'(x), against fp64."""
+    from paper_2411_01288_amd import binding as B
+    T = 20001
+    x = torch.empty(T, 1, device=DEV).uniform_(lo, hi, generator=torch.Generator(device=DEV).manual_seed(3))
+    shape = B.make_shape(T, 1, 1, 1, 1, "f32")
+    ones, zeros = torch.ones(T, 1, device=DEV), torch.zeros(1, 1, device=DEV)
+    ids, W = torch.zeros(T, 1, dtype=torch.int32, device=DEV), ones[:1].view(1, 1, 1)
+    idx, ws = B.hexa_moe_index(shape, ids), B.alloc_workspace(shape, DEV)
+    y = B.hexa_moe_fwd(shape, x, ids, ones, W, zeros, W, zeros, idx, ws)
+    g = B.hexa_moe_bwd(shape, ones, x, ids, ones, W, W, idx, ws)["dx"]
+    u = x.double()
+    t = 2 * (2 / np.pi) ** 0.5 * (u + 0.044715 * u ** 3)
+    s, s1 = torch.sigmoid(t), torch.sigmoid(-t)
+    q = 2 * (2 / np.pi) ** 0.5 * (1 + 3 * 0.044715 * u ** 2)
+    # the smaller of s and 1 - s is off by 4 roundings of 2^-24 (instructions of 1 ulp) and by those of t, |t| of them; then one or two more
+    off = (4 + t.abs()) * torch.minimum(s, s1) + torch.maximum(s, s1)
+    assert ((y.double() - u * s).abs() <= 2.0 ** -24 * u.abs() * (off + s) + 1e-26).all()
+    assert ((g.double() - (s + u * s * s1 * q)).abs() <= 2.0 ** -24 * (off + u.abs() * q * (off * s + (off + 3 * s) * s1) + 1) + 1e-26).all()
