@@ -102,8 +102,17 @@ hipError_t ensure_device_init() {
     std::lock_guard<std::mutex> lk(g_dev_mu);
     if (g_dev_ready[d].load(std::memory_order_relaxed)) return hipSuccess;
     e = gemm_bf16_device_init();
+    if (e == hipSuccess) e = f32_device_init();
     if (e == hipSuccess) g_dev_ready[d].store(true, std::memory_order_release);
     return e;
+}
+
+// Whether a launch of this shape asks for more than 64 KB of LDS.
+bool needs_device_init(const MoeDims& D, int dtype) {
+    if (dtype != HEXA_F32) return true;
+    bool wide[4];
+    f32_wide(D, wide);
+    return wide[0] || wide[1];
 }
 
 template <typename T>
@@ -178,7 +187,7 @@ size_t hexa_moe_index_scratch_bytes(const hexa_moe_shape* shape) {
 size_t hexa_moe_workspace_bytes(const hexa_moe_shape* shape) {
     MoeDims D;
     if (check_shape(shape, &D) != HEXA_OK) return 0;
-    if (shape->dtype != HEXA_F32) (void)ensure_device_init();   // no device here: the entry points will report it
+    if (needs_device_init(D, shape->dtype)) (void)ensure_device_init();   // no device here: the entry points will report it
     return layout(D, shape->dtype, nullptr).total_bytes;
 }
 
@@ -219,7 +228,7 @@ hexa_status hexa_moe_fwd(const hexa_moe_shape* shape, const void* x, const int32
     if (misaligned({x, W1, b1, W2, b2, y}, 16)) return HEXA_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (shape->dtype != HEXA_F32 && (e = ensure_device_init()) != hipSuccess) return dev(e);
+    if (needs_device_init(D, shape->dtype) && (e = ensure_device_init()) != hipSuccess) return dev(e);
     if (shape->dtype == HEXA_F32) {
         e = launch_f32_fwd(D, (const float*)x, (const float*)W1, (const float*)b1, (const float*)W2,
                            (const float*)b2, idx, ws, st);
@@ -251,7 +260,7 @@ hexa_status hexa_moe_bwd(const hexa_moe_shape* shape, const void* dY, const void
     if (misaligned({dY, x, W1, W2, dx, dW1, db1, dW2, db2}, 16)) return HEXA_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (shape->dtype != HEXA_F32 && (e = ensure_device_init()) != hipSuccess) return dev(e);
+    if (needs_device_init(D, shape->dtype) && (e = ensure_device_init()) != hipSuccess) return dev(e);
     if (shape->dtype == HEXA_F32) {
         e = launch_bwd_prologue<float>(D, (const float*)dY, gate, idx, ws, dgate, st);
         if (e == hipSuccess)

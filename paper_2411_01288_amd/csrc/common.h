@@ -189,6 +189,7 @@ constexpr int kMaxDevices = 64;   // per-device state of the library is kept in 
 // Sets the launch attributes of every contraction kernel (160 or 80 KB of dynamic LDS) on the current
 // device.  Called once per device by the entry points, outside any stream capture.
 hipError_t gemm_bf16_device_init();
+hipError_t f32_device_init();   // 72 KB
 
 // saved + staging regions inside the caller's workspace (device pointers)
 struct MoeWorkspace {
@@ -211,6 +212,7 @@ struct MoeWorkspace {
 // tile sizes of the launches fc1, fc2, bwd_fc2, bwd_fc1
 void gemm_tile_classes(const MoeDims& D, int (&tile)[4]);
 void f32_tile_classes(const MoeDims& D, int (&tile)[4]);
+void f32_wide(const MoeDims& D, bool (&wide)[4]);   // which of them take 128x64 tiles
 int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path
 int f32_dgrad2_row_tile(const MoeDims& D);    // rows of a DGRAD2 tile of the fp32 path
 constexpr int kColpartRows = 2;               // DGRAD2 writes this many column-sum partial rows per row tile

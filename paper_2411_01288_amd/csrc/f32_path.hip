@@ -1,10 +1,10 @@
 // fp32 path: the same dataflow as the 16-bit MFMA path (App. B Table 5 rows 1-10 on the re-index
 // vector), for workloads whose products and sums must be fp32.  Any size and any (dword) alignment of rows is taken:
-// 16-byte loads where a block is whole, element by element where a tile meets an edge; tiles are small (64x64, or
-// 32x32 where those are too few for 256 CUs) and several workgroups share a CU and hide each other's latencies.
+// 16-byte loads where a block is whole, element by element where a tile meets an edge; tiles are small (64x64, 128x64 for long
+// contractions, or 32x32 where those are too few for 256 CUs) and several workgroups share a CU and hide each other's latencies.
 //
 // 32x32 tiles run on v_mfma_f32_16x16x4_f32: 256 FLOP per clock and CU (157 TFLOP/s on the chip), a sixteenth of the bf16
-// rate.  64x64 tiles run on the bf16 instruction with every operand split into three bf16 numbers that add up to it (see split2;
+// rate.  Larger tiles run on the bf16 instruction with every operand split into three bf16 numbers that add up to it (see split2;
 // the method of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
 // 2019): six products instead of one, at sixteen times the rate.  What bounds them is no longer the matrix pipe (27 to 31 % busy) but
 // everything around it in turn: splitting, LDS (33 to 39 %), two barriers a step.
@@ -14,6 +14,7 @@
 // and not kept: all fragments read at once (three workgroups per CU, 12 % slower), two LDS buffers with the split between the products
 // (12 % slower), 64x128 tiles (fc2 3 % faster, fc1 20 % slower).
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -35,6 +36,7 @@ struct TileArgs {
     const int32_t* perm;
     const int32_t* offsets;
     int K, N, M, E, k, act;
+    int T;                 // rows of x
     int chunk_len;         // token contraction: rows per chunk that are aimed at (see chunk_count)
 };
 
@@ -179,7 +181,7 @@ struct TilePlace { int e, m0, n0, rows, K, kbeg, row_tile; };
 
 // What both ways of multiplying share: the loads of K-block k0 (a thread's NC chunks of four floats per operand; OA, OB:
 // Operand or SplitOperand), masked where the block is not whole.
-template <int BM, int BK, int OP, typename OA, typename OB>
+template <int BM, int BN, int BK, int OP, typename OA, typename OB>
 struct BlockLoader {
     static constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     static constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
@@ -209,7 +211,7 @@ struct BlockLoader {
             for (int i = 0; i < OB::NC; ++i)
                 bp[i] = a.B + ((size_t)t.e * a.N + min(t.n0 + br + OB::STEP * i, a.N - 1)) * a.K + bc;
         }
-        const bool inner = (!TOKENS || t.m0 + BM <= a.M) && (!B_KS || t.n0 + BM <= a.N);
+        const bool inner = (!TOKENS || t.m0 + BM <= a.M) && (!B_KS || t.n0 + BN <= a.N);
         nwhole = inner ? t.K / BK : 0;
     }
     __device__ __forceinline__ void load_perm(int k0) {
@@ -244,26 +246,27 @@ struct BlockLoader {
     }
 };
 
-// acc += the tile's contraction on v_mfma_f32_16x16x4_f32: four wavefronts as 2 x 2, FM x FM blocks each; two LDS buffers
-// of both operands, one multiplied, one filled.
+// A tile is 32 FM x 32 FN, four wavefronts as 2 x 2, FM x FN blocks each: 32x32, 64x64, 128x64.
+constexpr int frag_cols(int fm) { return fm == 4 ? 2 : fm; }
+
+// acc += the tile's contraction on v_mfma_f32_16x16x4_f32; two LDS buffers of both operands, one multiplied, one filled.
+template <int R, int BK>
+constexpr int f32_image() { return Operand<false, R, BK>::FLOATS > Operand<true, R, BK>::FLOATS ? Operand<false, R, BK>::FLOATS : Operand<true, R, BK>::FLOATS; }
 template <int FM, int BK>
-constexpr int f32_floats() {
-    constexpr int kc = Operand<false, 32 * FM, BK>::FLOATS, ks = Operand<true, 32 * FM, BK>::FLOATS;
-    return 4 * (kc > ks ? kc : ks);
-}
+constexpr int f32_floats() { return 2 * (f32_image<32 * FM, BK>() + f32_image<32 * frag_cols(FM), BK>()); }
 template <int FM, int BK, int OP>
-__device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace& t, float* smem, f32x4 (&acc)[FM][FM]) {
-    constexpr int BM = 32 * FM;
+__device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace& t, float* smem, f32x4 (&acc)[FM][frag_cols(FM)]) {
+    constexpr int BM = 32 * FM, FN = frag_cols(FM), BN = 32 * FN;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
     using OA = Operand<TOKENS, BM, BK>;
-    using OB = Operand<B_KS, BM, BK>;
+    using OB = Operand<B_KS, BN, BK>;
     constexpr int A_BUF = OA::FLOATS, PAIR = OA::FLOATS + OB::FLOATS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, grp = lane >> 4;
     const int nk = ceil_div(t.K, BK);
-    BlockLoader<BM, BK, OP, OA, OB> in(a, t);
+    BlockLoader<BM, BN, BK, OP, OA, OB> in(a, t);
     // Block j + 2 is on its way to registers and block j + 1 already there while block j is multiplied.
     f32x4 va0[OA::NC], vb0[OB::NC], va1[OA::NC], vb1[OB::NC];
     if (nk > 0) {
@@ -283,9 +286,9 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
         if (WHOLE || j + 2 < nk) in.template load<WHOLE>((j + 2) * BK, vaf, vbf);
 #pragma unroll
         for (int h = 0; h < BK / 16; ++h) {
-            f32x4 fa[FM], fb[FM];
+            f32x4 fa[FM], fb[FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i) fb[i] = OB::frag(sb, 16 * (wn * FM + i), h, l16, grp);
+            for (int i = 0; i < FN; ++i) fb[i] = OB::frag(sb, 16 * (wn * FN + i), h, l16, grp);
 #pragma unroll
             for (int i = 0; i < FM; ++i) fa[i] = OA::frag(sa, 16 * (wm * FM + i), h, l16, grp);
             // B first: the block comes out transposed, a lane holds row l16 and four consecutive columns
@@ -294,7 +297,7 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
 #pragma unroll
-                    for (int jj = 0; jj < FM; ++jj)
+                    for (int jj = 0; jj < FN; ++jj)
                         acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[jj][q], fa[i][q], acc[i][jj], 0, 0, 0);
         }
         if (WHOLE || j + 1 < nk) {
@@ -343,7 +346,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
     const int l16 = lane & 15, grp = lane >> 4;
     uint8_t* const sb = smem + 3 * OA::PLANE;
     const int nk = ceil_div(t.K, BK);
-    BlockLoader<BM, BK, OP, OA, OB> in(a, t);
+    BlockLoader<BM, BM, BK, OP, OA, OB> in(a, t);
     // Block j + 1 is on its way to registers while block j is multiplied.
     f32x4 va[OA::NC], vb[OB::NC];
     if (nk > 0) {
@@ -428,17 +431,295 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         for (int jj = 0; jj < FM; ++jj) acc[i][jj] = nk & 1 ? acc[i][jj] + low[i][jj] : acc[i][jj] - low[i][jj];
 }
 
-// One tile of contraction OP: 32 FM x 32 FM outputs, four wavefronts as 2 x 2.  ESMM (Sec. 3.1 item 1; App. B Alg. 2) for
+// ---- 128x64 tiles ----
+// The same products and sums on 128x64 tiles, 64x32 outputs per wavefront, two workgroups per CU: three quarters of the splitting, of the fragment
+// reads and of the loads per product.  The work of a K-step is laid out by hand: behind each of a wavefront's 48 matrix instructions stand
+// a fragment read of this step, a piece of the splitting of the next step's operands, the stores of its planes, a load, the additions of the large
+// products.  Two LDS buffers, one barrier a step, two steps of operands on their way to registers.
+// What bounds a step is the issue of vector instructions: with matrix instructions between them, one in 4.3 cycles and SIMD, matrix instructions
+// counted, 96 + 2 * 176 a step of both workgroups, 0.95 us, against 0.71 us of the matrix pipe.  (v_dot2_f32_bf16 would take a plane off in one
+// instruction instead of two, but waits for the matrix pipe: two of them behind a matrix instruction take as long as four.)  Tried and not
+// kept: 128x128 tiles, one workgroup per CU (fc1 at 8192 rows, 384 x 1536 of 8 experts, 94 -> 116 us: nothing runs under a tile's start and
+// epilogue, 13 us; with four wavefronts of 64x64, 142).
+// (a, b), or their negatives, as a bf16 pair; what is left of them, or of their negatives, is left in a and b.
+template <bool NEG>
+__device__ __forceinline__ uint32_t split_off(float& a, float& b) {
+    uint32_t w;
+    if constexpr (NEG) {
+        asm("v_cvt_pk_bf16_f32 %0, -%1, -%2" : "=v"(w) : "v"(a), "v"(b));
+        a = -a;
+        b = -b;
+    } else {
+        w = pack_bf2(a, b);
+    }
+    a -= __uint_as_float(w << 16);
+    b -= __uint_as_float(w & 0xffff0000u);
+    return w;
+}
+
+// One operand's share of a K-step, R rows (or columns) x 32 contraction elements, 256 threads: a thread has N = R / 32 times four consecutive k, of
+// rows row, row + 32, ... (K contiguous: N loads of four floats), or of N consecutive columns (K strided: four loads of N floats).  Neighbouring
+// threads have rows or columns four apart, which spreads their 64-bit stores over all banks.  All loads are range-checked by the buffer resource:
+// k-rows past the end are zeros, columns past the edge are another row's and their results not stored; at most three floats past the end of a row
+// are read.  LDS holds the planes as in SplitOperand, twice.  (A key of more than two bits would put rows that are read in the same cycle, of
+// different chunks, on the same banks: fragment reads took twice as long.)
+template <bool KS, bool GATHER, int R>
+struct WideOperand {
+    static constexpr int N = R / 32, NL = KS ? 4 : N, W = KS ? N : 4;
+    static constexpr int PLANE = R * 64, BUFFER = 3 * PLANE;
+    static constexpr int PIECES = 7 * N;
+    typedef float load_t __attribute__((ext_vector_type(W)));
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t voff[KS && !GATHER ? 1 : NL];
+    uint32_t pitch = 0;         // bytes of a k-row
+    uint8_t* put_at[KS ? N : 1];
+    const uint8_t* frag_at;
+    load_t v[2][NL];            // blocks j + 1 and j + 2
+
+    static __device__ __forceinline__ int group() { return (int)threadIdx.x & 7; }
+    static __device__ __forceinline__ int line() { return (int)threadIdx.x >> 3; }
+    static __device__ __forceinline__ int row() { return (line() & 3) << 2 | (line() >> 2 & 3) | (line() & 16); }
+    // a thread's columns of a K-strided operand, the last ones at the edge
+    static __device__ __forceinline__ uint32_t column(int n0, int n) { return (uint32_t)(n0 + min(W * line(), (n - n0 - 1) / W * W)) * 4u; }
+    __device__ __forceinline__ void resource(const float* p, size_t floats) {
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(uint32_t)(floats * 4), 0x00020000);
+    }
+    // base: first row or column of the wavefront's fragments
+    __device__ __forceinline__ void place(uint8_t* s, int base) {
+        const int chunk = group() >> 1, l16 = (int)threadIdx.x & 15, grp = (int)threadIdx.x >> 4 & 3;
+#pragma unroll
+        for (int i = 0; i < (KS ? N : 1); ++i)
+            put_at[i] = s + (chunk * R + ((KS ? N * line() + i : row()) ^ chunk)) * 16 + (group() & 1) * 8;
+        frag_at = s + (grp * R + base + (l16 ^ grp)) * 16;
+    }
+    __device__ __forceinline__ bf16x8 frag(int buf, int q, int i) const {
+        return *reinterpret_cast<const bf16x8*>(frag_at + buf * BUFFER + q * PLANE + i * 256);
+    }
+    __device__ __forceinline__ void load(int set, int i, int k0) {
+        const uint32_t o = KS && !GATHER ? voff[0] : voff[i];
+        const uint32_t s = KS ? GATHER ? 0u : (uint32_t)(k0 + i) * pitch : (uint32_t)k0 * 4u;
+        if constexpr (W == 4) v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, (int)s, 0));
+        else v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)o, (int)s, 0));
+    }
+    // zeros for k >= K of block k0 (K contiguous)
+    __device__ __forceinline__ void mask(int set, int k0, int K) {
+        if constexpr (!KS) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (k0 + 4 * group() + q >= K) v[set][i][q] = 0.f;
+        }
+    }
+    // Piece P of splitting a set into the planes of buffer `set`: P / 7 is the row (K contiguous) or column (K strided), whose
+    // four values are two pairs, taken in turn.
+    float x[4];
+    uint32_t w[2][3];
+    template <bool NEG, int set, int P>
+    __device__ __forceinline__ void piece(uint32_t& lost) {
+        constexpr int i = P / 7, s = P % 7, h = s % 2;
+        if constexpr (s < 4) {
+            if constexpr (s < 2) {
+                x[2 * h] = v[set][KS ? 2 * h : i][KS ? i : 2 * h];
+                x[2 * h + 1] = v[set][KS ? 2 * h + 1 : i][KS ? i : 2 * h + 1];
+            }
+            w[h][s / 2] = split_off<NEG && s < 2>(x[2 * h], x[2 * h + 1]);
+        } else if constexpr (s < 6) {
+            w[h][2] = __builtin_amdgcn_perm(__float_as_uint(x[2 * h + 1]), __float_as_uint(x[2 * h]), 0x07060302u);
+            lost |= __float_as_uint(x[2 * h]) | __float_as_uint(x[2 * h + 1]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<uint2*>(put_at[KS ? i : 0] + set * BUFFER + q * PLANE + (KS ? 0 : i * 512)) = make_uint2(w[0][q], w[1][q]);
+        }
+    }
+};
+
+// p / k for 0 <= p < 2^31 by a product: with 2^(s-1) < k <= 2^s and m = floor(2^(31+s) / k) + 1 it is 2 p m / 2^(32+s), as m k exceeds 2^(31+s)
+// by 2^s at most.
+struct DivideBy {
+    uint32_t m, s;
+    __device__ __forceinline__ explicit DivideBy(uint32_t k) : s(k > 1 ? 32 - __builtin_clz(k - 1) : 0) { m = (uint32_t)((1ull << (31 + s)) / k + 1); }
+    __device__ __forceinline__ uint32_t operator()(uint32_t p) const { return __umulhi(2 * p, m) >> s; }
+};
+
+// f(0), f(1), ... as compile-time constants
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+// (in assembly: the compiler would move sums between register files)
+__device__ __forceinline__ void small_product(f32x4& c, bf16x8 fb, bf16x8 fa) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(fb), "v"(fa));
+}
+// (its user leaves four matrix instructions between)
+__device__ __forceinline__ void large_product(f32x4& c, bf16x8 fb, bf16x8 fa) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(fb), "v"(fa));
+}
+
+constexpr int kWideLds = 2 * 3 * 64 * (128 + 64);   // two buffers of three planes of both operands
+template <int OP>
+__device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace& t, uint8_t* smem, f32x4 (&acc)[4][2], uint32_t& lost) {
+    constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1, GATHER = OP == F32_WGRAD1;
+    constexpr bool A_KS = TOKENS, B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
+    const int wave = (int)threadIdx.x >> 6, nk = ceil_div(t.K, 32);    // at least two steps
+    WideOperand<A_KS, GATHER, 128> oa;
+    WideOperand<B_KS, false, 64> ob;
+    oa.place(smem, (wave >> 1) * 64);
+    ob.place(smem + 2 * oa.BUFFER, (wave & 1) * 32);
+    const int group = oa.group(), row = oa.row();
+    const DivideBy token((uint32_t)a.k);
+    // WGRAD1: perm entries of the block whose offsets are computed next (past the end: zeros, whose rows meet zeros of the other operand)
+    __amdgpu_buffer_rsrc_t perm_rsrc;
+    if constexpr (GATHER) perm_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.perm + t.kbeg), 0, t.K * 4, 0x00020000);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 pv;
+    const uint32_t col = oa.column(t.m0, a.M);
+    auto perm_load = [&](int kb) __attribute__((always_inline)) {
+        if constexpr (GATHER) pv = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(perm_rsrc, 16 * group, 128 * min(kb, nk - 1), 0));
+    };
+    auto perm_take = [&](int i) __attribute__((always_inline)) {
+        if constexpr (GATHER) oa.voff[i] = token(pv[i]) * oa.pitch + col;
+    };
+    if constexpr (B_KS) {
+        ob.pitch = (uint32_t)a.N * 4u;
+        if constexpr (TOKENS) ob.resource(a.B + (size_t)t.kbeg * a.N, (size_t)t.K * a.N);
+        else ob.resource(a.B + (size_t)t.e * a.K * a.N, (size_t)a.K * a.N);
+        ob.voff[0] = (uint32_t)(4 * group) * ob.pitch + ob.column(t.n0, a.N);
+    } else {
+        ob.resource(a.B + (size_t)t.e * a.K * a.N, (size_t)a.K * a.N);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ob.voff[i] = (uint32_t)min(t.n0 + row + 32 * i, a.N - 1) * (uint32_t)a.K * 4u + 16u * group;
+    }
+    if constexpr (TOKENS) {
+        oa.pitch = (uint32_t)a.M * 4u;
+        if constexpr (GATHER) {
+            oa.resource(a.A, (size_t)a.T * a.M);
+        } else {
+            oa.resource(a.A + (size_t)t.kbeg * a.M, (size_t)t.K * a.M);
+            oa.voff[0] = (uint32_t)(4 * group) * oa.pitch + col;
+        }
+    } else {
+        if constexpr (OP == F32_FC1) oa.resource(a.A, (size_t)a.T * a.K);
+        else oa.resource(a.A + (size_t)t.m0 * a.K, (size_t)t.rows * a.K);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {    // rows past the segment repeat its last one (their results are not stored)
+            const int r = min(row + 32 * i, t.rows - 1);
+            oa.voff[i] = (OP == F32_FC1 ? token((uint32_t)a.perm[t.m0 + r]) : (uint32_t)r) * (uint32_t)a.K * 4u + 16u * group;
+        }
+    }
+    auto take_and_load = [&](int set, int kb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < ob.NL; ++i) ob.load(set, i, 32 * min(kb, nk - 1));
+#pragma unroll
+        for (int i = 0; i < oa.NL; ++i) { perm_take(i); oa.load(set, i, 32 * min(kb, nk - 1)); }
+        perm_load(kb + 1);
+    };
+    perm_load(0);
+    take_and_load(0, 0);
+    take_and_load(1, 1);
+    for_each_of([&](auto p) __attribute__((always_inline)) { oa.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, oa.PIECES>{});
+    for_each_of([&](auto p) __attribute__((always_inline)) { ob.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, ob.PIECES>{});
+    take_and_load(0, 2);
+    __syncthreads();
+    bf16x8 a1[4], a2[4], a3[4], b1[2], b2[2], b3[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a3[i] = oa.frag(0, 2, i);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) b1[i] = ob.frag(0, 0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) perm_take(i);
+    perm_load(4);
+    f32x4 low[2][4][2];    // the small products of the even and of the odd steps, which have signs of their own
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) low[p][i][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // multiplies block j, splits block j + 1, loads block j + 3
+    auto step = [&](auto odd, int j) __attribute__((always_inline)) {
+        constexpr bool ODD = decltype(odd)::value;
+        constexpr int cur = ODD, nxt = !ODD;
+        const int kb = min(j + 3, nk - 1);
+        if constexpr (!A_KS && !B_KS) {   // the other contractions have zeros there in their K-strided operand
+            if (j + 2 == nk && 32 * nk > t.K) oa.mask(nxt, 32 * (j + 1), t.K);
+        }
+        f32x4 hi[6];
+        __builtin_amdgcn_sched_barrier(0);
+        for_each_of([&](auto slot) __attribute__((always_inline)) {
+            constexpr int m = decltype(slot)::value, prod = m / 8, r = m % 8, jj = r / 4, i = jj % 2 ? 3 - r % 4 : r % 4;
+            if constexpr (prod == 0) small_product(low[cur][i][jj], b1[jj], a3[i]);
+            else if constexpr (prod == 1) small_product(low[cur][i][jj], b1[jj], a2[i]);
+            else if constexpr (prod == 2) small_product(low[cur][i][jj], b2[jj], a2[i]);
+            else if constexpr (prod == 3) small_product(low[cur][i][jj], b2[jj], a1[i]);
+            else if constexpr (prod == 4) large_product(hi[r % 6], b1[jj], a1[i]);
+            else small_product(low[cur][i][jj], b3[jj], a1[i]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (m < 4) a2[m] = oa.frag(cur, 1, m);
+            else if constexpr (m >= 6 && m < 10 && m % 2 == 0) b2[(m - 6) / 2] = ob.frag(cur, 1, (m - 6) / 2);
+            else if constexpr (m >= 10 && m < 18 && m % 2 == 0) a1[(m - 10) / 2] = oa.frag(cur, 0, (m - 10) / 2);
+            else if constexpr (m >= 18 && m < 22 && m % 2 == 0) b3[(m - 18) / 2] = ob.frag(cur, 2, (m - 18) / 2);
+            if constexpr (m < oa.PIECES) oa.template piece<!ODD, nxt, m>(lost);
+            else if constexpr (m < oa.PIECES + ob.PIECES) ob.template piece<false, nxt, m - oa.PIECES>(lost);
+            // the loads of block j + 3, one at a time, into what has been split: a row of them fills the address queue, and the wavefront waits
+            constexpr int la = A_KS ? m - 28 : m % 7 == 3 ? m / 7 : -1, lb = B_KS ? m - 42 : m == 31 ? 0 : m == 38 ? 1 : -1;
+            if constexpr (la >= 0 && la < oa.NL) oa.load(nxt, la, 32 * kb);
+            if constexpr (lb >= 0 && lb < ob.NL) ob.load(nxt, lb, 32 * kb);
+            if constexpr (m >= 37 && m < 45) {     // the large products of five instructions ago
+                constexpr int r5 = m - 37, j5 = r5 / 4, i5 = j5 % 2 ? 3 - r5 % 4 : r5 % 4;
+                acc[i5][j5] = ODD ? acc[i5][j5] - hi[r5 % 6] : acc[i5][j5] + hi[r5 % 6];
+            }
+            if constexpr (GATHER) {
+                if constexpr (m >= 34 && m < 38) perm_take(m - 34);
+                if constexpr (m == 38) perm_load(j + 5);
+            }
+            if constexpr (m == 41) __syncthreads();
+            if constexpr (m >= 42 && m < 46) a3[m - 42] = oa.frag(nxt, 2, m - 42);
+            if constexpr (m == 42 || m == 45) b1[(m - 42) / 3] = ob.frag(nxt, 0, (m - 42) / 3);
+            __builtin_amdgcn_sched_barrier(0);
+        }, std::make_integer_sequence<int, 48>{});
+    };
+    int j = 0;
+    for (;;) {
+        step(std::false_type{}, j);
+        if (++j >= nk) break;
+        step(std::true_type{}, j);
+        if (++j >= nk) break;
+    }
+    // (the compiler does not count the wait states that the results of the assembly's instructions need)
+    asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+            asm volatile("" : "+v"(low[0][i][jj]), "+v"(low[1][i][jj]));
+            acc[i][jj] += low[0][i][jj] - low[1][i][jj];
+        }
+}
+
+// One tile of contraction OP: 32 FM x 32 frag_cols(FM) outputs.  ESMM (Sec. 3.1 item 1; App. B Alg. 2) for
 // the row GEMMs, whose rows are one expert's segment; ESTMM (item 3; Alg. 4) for the token contractions.
 // BK: K-block of the fp32 instructions.
 template <int FM, int BK, bool SPLIT>
 constexpr int tile_bytes() {
-    constexpr int f = 4 * f32_floats<FM, BK>(), s = SPLIT ? split_bytes<FM>() : 0;
+    constexpr int f = 4 * f32_floats<FM, BK>(), s = FM == 4 ? kWideLds : SPLIT ? split_bytes<FM>() : 0;
     return f > s ? f : s;
 }
+// (what exceeds 64 KB is the launch's to ask for)
+template <int FM, int BK, bool SPLIT>
+__device__ __forceinline__ uint8_t* tile_lds() {
+    if constexpr (tile_bytes<FM, BK, SPLIT>() > 65536) {
+        extern __shared__ __align__(16) uint8_t dynamic_lds[];
+        return dynamic_lds;
+    } else {
+        __shared__ __align__(16) uint8_t lds[tile_bytes<FM, BK, SPLIT>()];
+        return lds;
+    }
+}
+template <int FM, int BK, bool SPLIT>
+constexpr int dynamic_bytes() { return tile_bytes<FM, BK, SPLIT>() > 65536 ? tile_bytes<FM, BK, SPLIT>() : 0; }
 template <int FM, int BK, bool SPLIT, int OP>
 __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint8_t* smem) {
-    constexpr int BM = 32 * FM;
+    constexpr int BM = 32 * FM, FN = frag_cols(FM), BN = 32 * FN;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -446,7 +727,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
 
     // ---- which tile: an XCD takes a contiguous eighth of the row GEMM's tiles (column tiles fastest), or an
     // eighth of every chunk's tiles of a token contraction, so that its L2 holds what they share
-    const int tn = ceil_div(a.N, BM);
+    const int tn = ceil_div(a.N, BN);
     TilePlace t{};
     float* tok_out = nullptr;
     if constexpr (!TOKENS) {
@@ -456,7 +737,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
         if (loc >= per || i >= tiles) return;
         t.row_tile = i / tn;
         const SegTile s = seg_tile_find_wave(a.offsets, a.E, BM, t.row_tile);
-        t.e = s.e; t.m0 = s.row0; t.rows = s.rows; t.n0 = (i - t.row_tile * tn) * BM; t.K = a.K;
+        t.e = s.e; t.m0 = s.row0; t.rows = s.rows; t.n0 = (i - t.row_tile * tn) * BN; t.K = a.K;
     } else {
         int tile;
         const int i = token_item_of(item, ceil_div(a.M, BM) * tn, tile);
@@ -464,29 +745,30 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
         const ChunkItem c = chunk_find_wave(a.offsets, a.E, a.chunk_len, i);
         if (c.e < 0) return;
         t.e = c.e; t.kbeg = c.beg; t.K = c.end - c.beg;
-        t.m0 = (tile / tn) * BM; t.n0 = (tile % tn) * BM; t.rows = min(BM, a.M - t.m0);
+        t.m0 = (tile / tn) * BM; t.n0 = (tile % tn) * BN; t.rows = min(BM, a.M - t.m0);
         tok_out = c.slot >= 0 ? a.kpart + (size_t)c.slot * a.M * a.N : a.out0 + (size_t)t.e * a.M * a.N;
     }
 
-    f32x4 acc[FM][FM];
+    f32x4 acc[FM][FN];
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     clear();
     bool plain = true;
     if constexpr (SPLIT) if (t.K >= kSplitFrom) {
         uint32_t lost = 0;
-        multiply_split<FM, OP>(a, t, smem, acc, lost);
+        if constexpr (FM == 4) multiply_wide<OP>(a, t, smem, acc, lost);
+        else multiply_split<FM, OP>(a, t, smem, acc, lost);
         // An infinity has no planes (inf - inf is NaN): a tile whose sums are not all finite is multiplied again on the fp32
         // instruction, too.
         float z = 0.f;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FM; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z = fmaf(acc[i][j][r], 0.f, z);
         plain = __syncthreads_or(z != z || (lost & 0xffffu) != 0) != 0;
@@ -497,8 +779,8 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
     // ---- epilogue
     float* out = TOKENS ? tok_out : a.out0;
 #pragma unroll
-    for (int jj = 0; jj < FM; ++jj) {
-        const int n = t.n0 + 16 * (wn * FM + jj) + 4 * grp, nv = a.N - n;
+    for (int jj = 0; jj < FN; ++jj) {
+        const int n = t.n0 + 16 * (wn * FN + jj) + 4 * grp, nv = a.N - n;
         f32x4 bias = {0.f, 0.f, 0.f, 0.f}, cs = {0.f, 0.f, 0.f, 0.f};
         if constexpr (OP == F32_FC1 || OP == F32_FC2) bias = load4(a.bias + (size_t)t.e * a.N + n, nv);
 #pragma unroll
@@ -535,8 +817,8 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
 }
 
 template <int FM, int BK, bool SPLIT, int OP>
-__global__ __launch_bounds__(256, SPLIT ? 4 : 1) void f32_gemm(TileArgs a) {
-    __shared__ __align__(16) uint8_t smem[tile_bytes<FM, BK, SPLIT>()];
+__global__ __launch_bounds__(256, FM == 4 ? 2 : SPLIT ? 4 : 1) void f32_gemm(TileArgs a) {
+    uint8_t* const smem = tile_lds<FM, BK, SPLIT>();
     f32_tile<FM, BK, SPLIT, OP>(a, (int)blockIdx.x, smem);
 }
 
@@ -544,18 +826,20 @@ __global__ __launch_bounds__(256, SPLIT ? 4 : 1) void f32_gemm(TileArgs a) {
 // the tail of one fills with tiles of the other.  Workgroups start in order; the one with the longer tiles comes first
 // (b_first: OPB in slots [0, items), else OPA).
 template <int FM, int BK, bool SPLIT, int OPA, int OPB>
-__global__ __launch_bounds__(256, SPLIT ? 4 : 1) void f32_gemm_pair(TileArgs ra, TileArgs rb, int items, int b_first) {
-    __shared__ __align__(16) uint8_t smem[tile_bytes<FM, BK, SPLIT>()];
+__global__ __launch_bounds__(256, FM == 4 ? 2 : SPLIT ? 4 : 1) void f32_gemm_pair(TileArgs ra, TileArgs rb, int items, int b_first) {
+    uint8_t* const smem = tile_lds<FM, BK, SPLIT>();
     const int item = (int)blockIdx.x, local = item < items ? item : item - items;
     if ((item < items) != (b_first != 0)) f32_tile<FM, BK, SPLIT, OPA>(ra, local, smem);
     else f32_tile<FM, BK, SPLIT, OPB>(rb, local, smem);
 }
 
+int tile_cols(int bm) { return bm < 64 ? bm : 64; }
 int row_items(const MoeDims& D, int bm, int N) {
-    return kXcds * ceil_div((D.A / bm + D.E) * ceil_div(N, bm), kXcds);
+    return kXcds * ceil_div((D.A / bm + D.E) * ceil_div(N, tile_cols(bm)), kXcds);
 }
-int token_items(const MoeDims& D, int bm) {
-    return kXcds * ceil_div(ceil_div(D.d, bm) * ceil_div(D.f, bm), kXcds) * (D.A / f32_chunk_len(D) + D.E);
+// M x N: an expert's weight gradient
+int token_items(const MoeDims& D, int bm, int M, int N) {
+    return kXcds * ceil_div(ceil_div(M, bm) * ceil_div(N, tile_cols(bm)), kXcds) * (D.A / f32_chunk_len(D) + D.E);
 }
 
 // Which class a launch takes: 64x64 tiles fetch half as much per FLOP and multiply in planes, 32x32 tiles are four times as many and
@@ -573,26 +857,62 @@ bool small_rows(const MoeDims& D, int N) {
 // x 512 x 2048 of 16 110 / 85, fc2 at 8192 x 256 x 301 of 2 (2064) 25.7 / 22.8; fc2 at 1024 x 384 x 1536 of 8 (864) 38.5 / 39.5.
 bool short_blocks(int tiles) { return tiles > 4 * 256; }
 
+// Planes on 128x64 tiles, two workgroups per CU, or on 64x64, four: a tile's start and epilogue are better hidden under three others' K loops, so
+// the line is the contraction's length.  Measured on both sides, us, 64x64 / 128x64: fc2 at 8192 rows, 384 x 1536 of 8 experts (K = 1536) 91 / 81,
+// at 10000 rows, 450 x 600 of 9 (600) 64.7 / 54.7, at 16384 rows, 512 x 300 of 4 (300) 52 / 55; fc1 at the first (384) 94 / 108, at 9000 rows, 512 x
+// 1000 of 16 (512) 92 / 95; bwd_fc1 at the first (1536) 166 / 147, bwd_fc2 (384, with token contractions of 1024 rows) 158 / 156.  fc2 of 2048 rows
+// at that layer, 144 tiles, 37.7 / 36.7.
+constexpr int kWideFrom = 576;
+bool wide_rows(const MoeDims& D, int K) {
+    constexpr long long most = 0xffff0000LL;   // bytes that an operand's 32-bit offsets reach
+    const long long chunk = 9LL * f32_chunk_len(D) / 8 + 256, wider = D.d > D.f ? D.d : D.f;
+    return K >= kWideFrom && 4LL * D.T * D.d <= most && 4LL * D.d * D.f <= most && 4 * chunk * wider <= most;
+}
+// 32: fp32 instruction, 64: planes, 128: planes on wide tiles
+int rows_class(const MoeDims& D, int K, int N) { return small_rows(D, N) ? 32 : wide_rows(D, K) ? 128 : 64; }
+
+template <int FM, int BK, bool SPLIT, int OP>
+void rows_launch_as(int grid, const TileArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((f32_gemm<FM, BK, SPLIT, OP>), dim3(grid), dim3(256), (dynamic_bytes<FM, BK, SPLIT>()), st, a);
+}
 template <int OP>
 void rows_launch(const MoeDims& D, const TileArgs& a, hipStream_t st, const char* label) {
-    const bool small = small_rows(D, a.N);
-    const int grid = row_items(D, small ? 32 : 64, a.N);
-    const auto kern = !small ? f32_gemm<2, 16, true, OP> : short_blocks(grid) ? f32_gemm<1, 32, false, OP> : f32_gemm<1, 64, false, OP>;
+    const int c = rows_class(D, a.K, a.N), grid = row_items(D, c, a.N);
     ProfScope ps(st, label);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, a);
+    if (c == 128) rows_launch_as<4, 16, true, OP>(grid, a, st);
+    else if (c == 64) rows_launch_as<2, 16, true, OP>(grid, a, st);
+    else if (short_blocks(grid)) rows_launch_as<1, 32, false, OP>(grid, a, st);
+    else rows_launch_as<1, 64, false, OP>(grid, a, st);
+}
+template <int FM, int BK, bool SPLIT, int OPA, int OPB>
+void pair_launch_as(int grid, const TileArgs& ra, const TileArgs& rb, int items, bool b_first, hipStream_t st) {
+    hipLaunchKernelGGL((f32_gemm_pair<FM, BK, SPLIT, OPA, OPB>), dim3(grid), dim3(256), (dynamic_bytes<FM, BK, SPLIT>()), st, ra, rb, items,
+                       (int)b_first);
 }
 template <int OPA, int OPB>
 void pair_launch(const MoeDims& D, const TileArgs& ra, const TileArgs& rb, hipStream_t st, const char* label) {
-    const bool small = small_rows(D, ra.N);
-    const int items_a = row_items(D, small ? 32 : 64, ra.N), items_b = token_items(D, small ? 32 : 64), grid = items_a + items_b;
+    const int c = rows_class(D, ra.K, ra.N), items_a = row_items(D, c, ra.N), items_b = token_items(D, c, rb.M, rb.N), grid = items_a + items_b;
     // rows of a token contraction's tile on average (the host does not know the routing), against K of a row GEMM's.  bwd_fc2 at
     // 4096 x 384 x 1536 of 8 (1024 against 384): row GEMM first 195 us, token contraction first 191 (on a machine 2 % slower)
     const long long rows = D.A / (D.E < D.A ? D.E : D.A), chunk = f32_chunk_len(D);
     const bool b_first = (rows < chunk ? rows : chunk) > ra.K;
-    const auto kern = !small ? f32_gemm_pair<2, 16, true, OPA, OPB>
-                      : short_blocks(grid) ? f32_gemm_pair<1, 32, false, OPA, OPB> : f32_gemm_pair<1, 64, false, OPA, OPB>;
+    const int items = b_first ? items_b : items_a;
     ProfScope ps(st, label);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, ra, rb, b_first ? items_b : items_a, (int)b_first);
+    if (c == 128) pair_launch_as<4, 16, true, OPA, OPB>(grid, ra, rb, items, b_first, st);
+    else if (c == 64) pair_launch_as<2, 16, true, OPA, OPB>(grid, ra, rb, items, b_first, st);
+    else if (short_blocks(grid)) pair_launch_as<1, 32, false, OPA, OPB>(grid, ra, rb, items, b_first, st);
+    else pair_launch_as<1, 64, false, OPA, OPB>(grid, ra, rb, items, b_first, st);
+}
+
+template <int OP>
+hipError_t allow_rows() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(f32_gemm<4, 16, true, OP>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               dynamic_bytes<4, 16, true>());
+}
+template <int OPA, int OPB>
+hipError_t allow_pair() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(f32_gemm_pair<4, 16, true, OPA, OPB>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               dynamic_bytes<4, 16, true>());
 }
 
 }  // namespace
@@ -605,17 +925,29 @@ int f32_chunk_len(const MoeDims& D) {
     if (L < 256) L = 256;
     return (int)(L < 0x7fffffc0 ? L : 0x7fffffc0);
 }
+// (32 or 64: what a tile is multiplied with; wide tiles: see f32_wide)
 void f32_tile_classes(const MoeDims& D, int (&tile)[4]) {
     tile[0] = tile[2] = small_rows(D, D.f) ? 32 : 64;
     tile[1] = tile[3] = small_rows(D, D.d) ? 32 : 64;
 }
-int f32_dgrad2_row_tile(const MoeDims& D) { return small_rows(D, D.f) ? 32 : 64; }
+void f32_wide(const MoeDims& D, bool (&wide)[4]) {
+    wide[0] = wide[2] = rows_class(D, D.d, D.f) == 128;
+    wide[1] = wide[3] = rows_class(D, D.f, D.d) == 128;
+}
+int f32_dgrad2_row_tile(const MoeDims& D) { return rows_class(D, D.d, D.f); }
+hipError_t f32_device_init() {
+    hipError_t e = allow_rows<F32_FC1>();
+    if (e == hipSuccess) e = allow_rows<F32_FC2>();
+    if (e == hipSuccess) e = allow_pair<F32_DGRAD2, F32_WGRAD2>();
+    if (e == hipSuccess) e = allow_pair<F32_DGRAD1, F32_WGRAD1>();
+    return e;
+}
 
 hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, const float* b1,
                           const float* W2, const float* b2, const hexa_moe_idx& idx,
                           const MoeWorkspace& ws, hipStream_t st) {
     TileArgs a{};
-    a.offsets = idx.offsets; a.perm = idx.perm; a.k = D.k; a.E = D.E; a.act = D.act;
+    a.offsets = idx.offsets; a.perm = idx.perm; a.k = D.k; a.E = D.E; a.act = D.act; a.T = D.T;
     // fc1: pre = x W1 + b1, h = F(pre), F'(pre)
     a.A = x; a.B = W1; a.bias = b1; a.out0 = (float*)ws.pre; a.out1 = (float*)ws.h; a.K = D.d; a.N = D.f;
     rows_launch<F32_FC1>(D, a, st, "fc1");
@@ -629,7 +961,7 @@ hipError_t launch_f32_bwd(const MoeDims& D, const float* x, const float* W1, con
                           const hexa_moe_idx& idx, const MoeWorkspace& ws, float* dW1, float* dW2,
                           hipStream_t st) {
     TileArgs g{};
-    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act; g.chunk_len = f32_chunk_len(D);
+    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act; g.T = D.T; g.chunk_len = f32_chunk_len(D);
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     TileArgs r = g, t = g;
     r.A = (const float*)ws.dout; r.B = W2; r.pre_in = (const float*)ws.pre; r.out0 = (float*)ws.dpre;
