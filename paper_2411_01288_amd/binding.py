@@ -40,7 +40,7 @@ class Idx(ctypes.Structure):
 class Plan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("fc1_tile", "fc2_tile", "bwd_fc2_tile", "bwd_fc1_tile", "fc2_shares",
                                               "chunk_rows")] + \
-               [(n, ctypes.c_int64) for n in ("partial_buffers", "index_chunk_ids", "index_chunks", "prologue_blocks")] + [("wide", ctypes.c_int32)]
+               [(n, ctypes.c_int64) for n in ("partial_buffers", "index_chunk_ids", "index_chunks", "prologue_blocks")] + [(n, ctypes.c_int32) for n in ("wide", "thin")]
 
 
 def _load():

@@ -27,7 +27,7 @@ __device__ __forceinline__ void grouped_tile(int local, int tm, int tn, int& til
 // neighbouring row tiles (mostly one expert) at any time; what is left after rounds of eight groups is shared out tile by tile,
 // every XCD taking neighbouring ones, so that no XCD is a whole group behind the others at the end; with many
 // groups (kSplitBelow) all are dealt whole (an XCD's CUs finish their tiles one tile-time apart either way, and whole
-// groups keep their L2 locality).  128x128 tiles are for smaller problems: an eighth of all tiles in a row per XCD.  Or,
+// groups keep their L2 locality).  128x128 and 32x128 tiles are for smaller problems: an eighth of all tiles in a row per XCD.  Or,
 // where experts have less than a tile of rows and their weights are read once and come from HBM (`streamed`), every group cut in eight, so that the
 // whole chip reads whole rows of eight experts' weights at a time.  Both ways, in us: 64 tokens, 2048 x 8192 x 64, a
 // serving pass 519 / 504 streamed; steps at 3001 x 320 x 448 of 17 80.3 / 86.6, 4096 x 384 x 1536 of 8 143 / 152.
@@ -38,12 +38,12 @@ struct RowTiles {
     int tm, tn, per_group, dealt;   // the first `dealt` tiles go out by group
     __device__ __forceinline__ RowTiles(int tm_, int tn_, bool streamed) : tm(tm_), tn(tn_), per_group(GM * tn_) {
         const int total = tm * tn;
-        if (BM == 128) dealt = streamed ? total / per_group * per_group : 0;
+        if (BM != 256) dealt = streamed ? total / per_group * per_group : 0;
         else dealt = ceil_div(tm, GM) >= kSplitBelow ? total : total / (kXcds * per_group) * (kXcds * per_group);
     }
     // tiles of XCD x among the dealt ones, and how many the XCDs in front of it (first) and it itself (n) have of the others
     __device__ __forceinline__ int dealt_to(int x) const {
-        if (BM == 128) return dealt / kXcds;
+        if (BM != 256) return dealt / kXcds;
         const int round = kXcds * per_group, r = dealt / round;
         return r * per_group + min(max(dealt - r * round - x * per_group, 0), per_group);
     }
@@ -62,7 +62,7 @@ struct RowTiles {
         const int mine = dealt_to(x);
         int lin, n;
         if (loc < mine) {
-            const int part = BM == 128 ? per_group / kXcds : per_group;
+            const int part = BM != 256 ? per_group / kXcds : per_group;
             lin = loc + (loc / part * (kXcds - 1) + x) * part;
         } else {
             shared(x, lin, n);
@@ -73,7 +73,7 @@ struct RowTiles {
     // the most that any XCD can have with at most tm_max row tiles
     static int most(int tm_max, int tn) {
         const int even = ceil_div(tm_max * tn, kXcds), ngroups = ceil_div(tm_max, GM);
-        const int whole = BM != 128 && ngroups >= kSplitBelow ? ceil_div(ngroups, kXcds) * GM * tn : 0;
+        const int whole = BM == 256 && ngroups >= kSplitBelow ? ceil_div(ngroups, kXcds) * GM * tn : 0;
         return even > whole ? even : whole;
     }
 };

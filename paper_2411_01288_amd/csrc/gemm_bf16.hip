@@ -368,21 +368,21 @@ __device__ __forceinline__ ChunkItem list_entry(const int32_t* p) {
 struct Tile { ChunkItem it; int tile_m, tile_n; };
 
 // A row GEMM on its own.  False: no tile.
-template <int EPL, int BM>
+template <int EPL, int BM, int BN>
 __device__ __forceinline__ bool pick_rows_wave(const GemmArgs& g, int x, int loc, Tile& t) {
     const ExpertLanes<EPL> s(g.offsets, g.E);
     int mine;
     const int incl = s.template pieces<false>(BM, false, mine);
-    const RowTiles<BM> rows(__builtin_amdgcn_readlane(incl, 63), ceil_div(g.N, BM), g.streamed != 0);
+    const RowTiles<BM> rows(__builtin_amdgcn_readlane(incl, 63), ceil_div(g.N, BN), g.streamed != 0);
     if (loc >= rows.count(x)) return false;
     rows.tile(x, loc, t.tile_m, t.tile_n);
     t.it = s.template find<false, false>(t.tile_m, BM, incl, mine);
     return true;
 }
-template <int BM>
+template <int BM, int BN>
 __device__ __forceinline__ bool pick_rows_small(const GemmArgs& g, int x, int loc, Tile& t) {
-    return g.E <= 64 ? pick_rows_wave<1, BM>(g, x, loc, t)
-           : g.E <= 256 ? pick_rows_wave<4, BM>(g, x, loc, t) : pick_rows_wave<16, BM>(g, x, loc, t);
+    return g.E <= 64 ? pick_rows_wave<1, BM, BN>(g, x, loc, t)
+           : g.E <= 256 ? pick_rows_wave<4, BM, BN>(g, x, loc, t) : pick_rows_wave<16, BM, BN>(g, x, loc, t);
 }
 __device__ __forceinline__ bool pick_rows_big(const GemmArgs& g, int x, int loc, Tile& t, int& quarter) {
     const RowTiles<256> rows(g.lists[WL_TILES], ceil_div(g.N, 256), false);
@@ -1114,7 +1114,7 @@ __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16(Gem
             if (t.it.beg < t.it.end && t.tile_n * 128 < g.N) gemm_tile<128, 128, WM, WN, OP, ACT, F16, 4>(g, t);
             return;
         }
-    } else if (!pick_rows_small<BM>(g, x, loc, t)) return;
+    } else if (!pick_rows_small<BM, BN>(g, x, loc, t)) return;
     gemm_tile<BM, BN, WM, WN, OP, ACT, F16>(g, t);
 }
 
@@ -1130,6 +1130,151 @@ __global__ __launch_bounds__(WM * WN * 64, BM == 256 ? 1 : 2) void gemm_bf16_pai
     else if (which == 1) gemm_tile<BM, BN, WM, WN, OPA, HEXA_ACT_GELU_TANH, F16>(ga, t);
 }
 
+
+// A row GEMM of a forward pass with few rows per expert, as in a decode step: what it takes is reading the weights once, which is bound by the bytes that are
+// on their way.  32x128 tiles; each wavefront takes every fourth 32-k step of the tile's contraction by itself, from memory to registers without
+// LDS or barriers, four steps on their way (8 KB each; eight wavefronts on a CU, 256 KB): a lane loads 16 bytes, 8 columns, of 8 k-rows and transposes
+// the 8x8 block with 32 v_perm into the operands of matrix instruction c = 0 .. 7, for columns c, 8 + c, ...; token rows come straight in operand
+// order.  The four wavefronts' sums meet in LDS, in order.
+// The columns are 16-byte chunks (N is a multiple of 64); past the edge a lane repeats the last one.  Token rows past the segment are zeros.
+constexpr int kThinRows = 32, kThinCols = 128, kThinDepth = 4;
+template <int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_thin(GemmArgs g) {
+    static_assert(OP == OP_FC1 || OP == OP_FC2 || OP == OP_FC2P, "weights [K][N]");
+    constexpr int PITCH = kThinCols + 4;
+    __shared__ __align__(16) float sums[4][16][PITCH];
+    if constexpr (OP == OP_FC2P) {
+        g.share = (int)blockIdx.y;
+        g.out0 = reinterpret_cast<float*>(g.out0) + (size_t)g.share * g.a_rows * g.N;
+    }
+    Tile t;
+    if (!pick_rows_small<kThinRows, kThinCols>(g, (int)blockIdx.x % kXcds, (int)blockIdx.x / kXcds, t)) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l16 = lane & 15, grp = lane >> 4;
+    const int e = t.it.e, m0 = t.it.beg, rows = t.it.end - m0, n0 = t.tile_n * kThinCols, cols = min(kThinCols, g.N - n0);
+    const int first = OP == OP_FC2P ? 2 * g.share * g.share_blocks : 0;
+    const int steps = OP == OP_FC2P ? min(2 * g.share_blocks, g.K / 32 - first) : g.K / 32;
+    const int n = (steps - wave + 3) / 4;        // this wavefront's: first + wave, + 4, ...
+
+    const uint32_t nb = (uint32_t)g.N * 2u, kb = (uint32_t)g.K * 2u;
+    auto resource = [](const bf16_t* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, (int)bytes, 0x00020000); };
+    const __amdgpu_buffer_rsrc_t rw = resource(g.B + (size_t)e * g.K * g.N, (uint32_t)g.K * nb);
+    const uint32_t wv = (uint32_t)(8 * grp) * nb + (uint32_t)(n0 + min(8 * l16, cols - 8)) * 2u;
+    const __amdgpu_buffer_rsrc_t ra = OP == OP_FC1 ? resource(g.A, (uint32_t)g.a_rows * kb) : resource(g.A + (size_t)m0 * g.K, (uint32_t)rows * kb);
+    uint32_t av[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = 16 * h + l16;
+        const uint32_t row = OP != OP_FC1 ? (uint32_t)r : (uint32_t)(r < rows ? g.perm[m0 + r] / g.topk : g.a_rows);
+        av[h] = row * kb + 16u * grp;
+    }
+    u32x4 w[kThinDepth][8], a[kThinDepth][2];
+    auto load = [&](int s, int i) __attribute__((always_inline)) {
+        // past the end: the last step again for A, no weights (behind the range)
+        const uint32_t k0 = 32u * (uint32_t)(first + wave + 4 * min(i, n - 1)), k0w = i < n ? k0 : (uint32_t)g.K;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            w[s][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)wv, (int)((k0w + q) * nb), 0));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            a[s][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)av[h], (int)(k0 * 2u), 0));
+    };
+    f32x4 acc[2][8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[h][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            u32x4 b;
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                b[p] = __builtin_amdgcn_perm(w[s][2 * p + 1][c / 2], w[s][2 * p][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
+            // (weights first: a lane then holds row l16 and columns 8 (4 grp + r) + c, r = 0 .. 3)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (F16) acc[h][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b), __builtin_bit_cast(f16x8, a[s][h]), acc[h][c], 0, 0, 0);
+                else acc[h][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a[s][h]), acc[h][c], 0, 0, 0);
+            }
+        }
+    };
+    if (n > 0) {
+#pragma unroll
+        for (int s = 0; s < kThinDepth; ++s) load(s, s);
+        int i = 0;
+        for (; i + kThinDepth <= n; i += kThinDepth) {
+#pragma unroll
+            for (int s = 0; s < kThinDepth; ++s) {
+                multiply(s);
+                load(s, i + s + kThinDepth);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kThinDepth - 1; ++s)
+            if (i + s < n) multiply(s);
+    }
+
+    // ---- the four wavefronts' sums, 16 rows at a time: a thread adds up 8 columns of one row
+    const int row = (int)threadIdx.x / 16, col = (int)threadIdx.x % 16 * 8;
+    u32x4 bias = {0, 0, 0, 0};
+    if ((OP != OP_FC2P || g.share == 0) && col < cols) bias = *reinterpret_cast<const u32x4*>(g.bias + (size_t)e * g.N + n0 + col);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (16 * h >= rows) break;
+        if (h) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c4 = 0; c4 < 2; ++c4)
+                *reinterpret_cast<f32x4*>(&sums[wave][l16][8 * (4 * grp + r) + 4 * c4]) =
+                    f32x4{acc[h][4 * c4][r], acc[h][4 * c4 + 1][r], acc[h][4 * c4 + 2][r], acc[h][4 * c4 + 3][r]};
+        __syncthreads();
+        if (16 * h + row >= rows || col >= cols) continue;
+        float v[8];
+#pragma unroll
+        for (int c4 = 0; c4 < 2; ++c4) {
+            f32x4 s = *reinterpret_cast<const f32x4*>(&sums[0][row][col + 4 * c4]);
+#pragma unroll
+            for (int q = 1; q < 4; ++q) s += *reinterpret_cast<const f32x4*>(&sums[q][row][col + 4 * c4]);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float b0, b1;
+                unpack2<F16>(bias[2 * c4 + q], b0, b1);
+                v[4 * c4 + 2 * q] = s[2 * q] + b0;
+                v[4 * c4 + 2 * q + 1] = s[2 * q + 1] + b1;
+            }
+        }
+        const size_t o = (size_t)(m0 + 16 * h + row) * g.N + n0 + col;
+        if constexpr (OP == OP_FC2P) {
+            float* out = reinterpret_cast<float*>(g.out0) + o;
+            *reinterpret_cast<f32x4*>(out) = f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<f32x4*>(out + 4) = f32x4{v[4], v[5], v[6], v[7]};
+        } else {
+            u32x4 z, z1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (OP == OP_FC1) {
+                    float h0, g0, h1, g1;
+                    act_both<ACT>(v[2 * q], h0, g0);
+                    act_both<ACT>(v[2 * q + 1], h1, g1);
+                    z[q] = pack2<F16>(g0, g1);
+                    z1[q] = pack2<F16>(h0, h1);
+                } else {
+                    z[q] = pack2<F16>(v[2 * q], v[2 * q + 1]);
+                }
+            }
+            *reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(g.out0) + o) = z;
+            if constexpr (OP == OP_FC1) *reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(g.out1) + o) = z1;
+        }
+    }
+}
+template <int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
+void launch_thin(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char* label, int shares = 1) {
+    ProfScope ps(st, label);
+    auto kern = gemm_bf16_thin<OP, ACT, F16>;
+    const int grid = kXcds * RowTiles<kThinRows>::most(D.A / kThinRows + std::min(D.E, D.A), ceil_div(g.N, kThinCols));
+    hipLaunchKernelGGL(kern, dim3(grid, shares), dim3(256), 0, st, g);
+}
 
 template <int BM, int BN, int WM, int WN, int OP, int ACT = HEXA_ACT_GELU_TANH, bool F16 = false>
 void launch_rows(const MoeDims& D, const GemmArgs& g, hipStream_t st, const char* label, int shares = 1) {
@@ -1226,6 +1371,23 @@ inline bool small_fc2(const MoeDims& D) { return small_rows(D, D.f, D.d); }
 inline bool small_bwd2(const MoeDims& D) { return small_pair(D, D.d, D.f); }
 inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 
+// Which forward passes take the thin tiles: with more rows, experts have several of them, which fetch the weights again.  Measured, us with the
+// profile's events, 128x128 tiles / thin, fc1 and fc2 + combine: 16 tokens, 768 x 3072 of 16, top-2 (2 rows per expert) 20.2 / 17.7, 24.9 /
+// 24.2; 64 tokens, 2048 x 8192 of 64 (2) 274 / 259, 259 / 259; 128 there (4) 337 / 321, 332 / 327; 128 tokens, 1024 x 4096 of 32 (8) 59.0 / 56.7, 61.9 /
+// 62.4; 512 of the second (16) 411 / 432, 389 / 399; 300 tokens, 1536 x 6144 of 24, top-1 (12.5) 101 / 97, 97 / 121; 16 tokens, 1536 x 6144 of 2 (8, one
+// tile each) 19.6 / 13.9, 45.7 / 18.0.  (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
+constexpr int kThinUpTo = 6;
+inline bool thin(const MoeDims& D) {
+    const double wider = D.d > D.f ? D.d : D.f, other = D.d > D.f ? D.f : D.d;
+    return (D.A <= kThinRows || D.A <= (long long)kThinUpTo * std::min(D.E, D.A)) && (wider * other + 64 * wider) * 2 < 4294967296.0;
+}
+// Shares of K for FC2 on thin tiles: what makes two workgroups per CU, at least three 64-k blocks each (the fourth case above in us at 1 / 2 / 4 / 8
+// shares: 61 / 62 / 65 / 70; the first 31 / 24 / 24 / 23.5, the last 36 / 25 / 20 / 18; 20 tokens, 320 x 448 of 30, 15.4 / 13.0 / 14.6 / 15.2).
+inline int thin_fc2_shares(const MoeDims& D) {
+    const int tiles = std::min(D.E, D.A) * ceil_div(D.d, kThinCols);
+    return std::max(1, std::min({8, 2 * kNumCUs / tiles, D.f / BK / 3}));
+}
+
 // FC2 in shares of K: with few rows its tiles are few and long (K = d_ff), so a decode step leaves most CUs idle.
 // The workgroups of a share write unrounded sums, combine_split adds them up in order; that traffic and the
 // number of shares are weighed by the same estimate.  It was checked against 1, 2, 4 and 8 shares on 13 shapes of
@@ -1234,6 +1396,7 @@ inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 // 64 tokens, 2048 x 8192 x 64: 287 / 251 / 257 / 263; 1024 tokens, 512 x 2048 x 8: 28 / 28 / 25 / 31; 2048 tokens,
 // 768 x 3072 x 16: 47 / 56 / 62 / 83 (one share is taken).
 int choose_fc2_shares(const MoeDims& D) {
+    if (thin(D)) return thin_fc2_shares(D);
     if (!small_fc2(D)) return 1;
     const int blocks = D.f / BK;
     int best = 1;
@@ -1283,6 +1446,7 @@ hipError_t gemm_bf16_device_init() {
     return e;
 }
 
+bool gemm_thin(const MoeDims& D) { return thin(D); }
 void gemm_tile_classes(const MoeDims& D, int (&tile)[4]) {
     const bool small[4] = {small_fc1(D), small_fc2(D), small_bwd2(D), small_bwd1(D)};
     for (int i = 0; i < 4; ++i) tile[i] = small[i] ? SMALL : BIG;
@@ -1328,6 +1492,13 @@ static void launch_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
 }
 
 template <bool F16>
+static void thin_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
+    if (D.act == HEXA_ACT_RELU) launch_thin<OP_FC1, HEXA_ACT_RELU, F16>(D, g, st, "fc1");
+    else if (D.act == HEXA_ACT_SILU) launch_thin<OP_FC1, HEXA_ACT_SILU, F16>(D, g, st, "fc1");
+    else launch_thin<OP_FC1, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc1");
+}
+
+template <bool F16>
 static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, const bf16_t* b1,
                            const bf16_t* W2, const bf16_t* b2, const hexa_moe_idx& idx,
                            const MoeWorkspace& ws, hipStream_t st) {
@@ -1342,13 +1513,16 @@ static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
                            ws.worklist, g.rt_cap, D.d, D.f);
     }
     g.A = x; g.a_rows = D.T; g.B = W1; g.bias = b1; g.out0 = ws.pre; g.out1 = ws.h; g.K = D.d; g.N = D.f;
-    if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
+    if (thin(D)) thin_fc1<F16>(D, g, st);
+    else if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
     else launch_fc1<BIG, F16>(D, g, st);
     g.A = (const bf16_t*)ws.h; g.B = W2; g.bias = b2; g.out0 = ws.o; g.out1 = nullptr; g.K = D.f; g.N = D.d;
     if (fc2_shares(D) > 1) {
         g.out0 = ws.fc2part; g.a_rows = D.A; g.share_blocks = fc2_share_blocks(D);
-        launch_rows<SMALL, SMALL, 2, 2, OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
-    } else if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+        if (thin(D)) launch_thin<OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
+        else launch_rows<SMALL, SMALL, 2, 2, OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
+    } else if (thin(D)) launch_thin<OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+    else if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     else launch_rows<BIG, BIG, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     return hipGetLastError();
 }
