@@ -1,6 +1,6 @@
 // fp32 path: the same dataflow as the 16-bit MFMA path (App. B Table 5 rows 1-10 on the re-index
 // vector), for workloads whose products and sums must be fp32.  Any size and any (dword) alignment of rows is taken:
-// 16-byte loads where a block is whole, element by element where a tile meets an edge; tiles are small (64x64, 128x64 for long
+// 16-byte range-checked loads, element-by-element stores where a tile meets an edge; tiles are small (64x64, 128x64 for long
 // contractions, or 32x32 where those are too few for 256 CUs) and several workgroups share a CU and hide each other's latencies.
 //
 // 32x32 tiles run on v_mfma_f32_16x16x4_f32: 256 FLOP per clock and CU (157 TFLOP/s on the chip), a sixteenth of the bf16
@@ -37,6 +37,7 @@ struct TileArgs {
     const int32_t* offsets;
     int K, N, M, E, k, act;
     int T;                 // rows of x
+    int far;               // some operand has more than 4 GB
     int chunk_len;         // token contraction: rows per chunk that are aimed at (see chunk_count)
 };
 
@@ -179,10 +180,108 @@ struct SplitOperand {
 // contraction), number of the row tile (row GEMM).
 struct TilePlace { int e, m0, n0, rows, K, kbeg, row_tile; };
 
+// p / k for 0 <= p < 2^31 by a product: with 2^(s-1) < k <= 2^s and m = floor(2^(31+s) / k) + 1 it is 2 p m / 2^(32+s), as m k exceeds 2^(31+s)
+// by 2^s at most.
+struct DivideBy {
+    uint32_t m, s;
+    __device__ __forceinline__ explicit DivideBy(uint32_t k) : s(k > 1 ? 32 - __builtin_clz(k - 1) : 0) { m = (uint32_t)((1ull << (31 + s)) / k + 1); }
+    __device__ __forceinline__ uint32_t operator()(uint32_t p) const { return __umulhi(2 * p, m) >> s; }
+};
+
+// A tensor's floats from p on; what is read behind them is zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t floats_at(const float* p, size_t floats) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(uint32_t)(floats * 4), 0x00020000);
+}
+// First of the four columns that a thread at `col` of a K-strided block fetches: the last ones at the edge (what lies past it is the next row's
+// and the results of those columns are not stored; at most three floats are read past the end of a row).
+__device__ __forceinline__ uint32_t edge_column(int n0, int col, int N) { return (uint32_t)(n0 + min(col, (N - n0 - 1) / 4 * 4)) * 4u; }
+
 // What both ways of multiplying share: the loads of K-block k0 (a thread's NC chunks of four floats per operand; OA, OB:
-// Operand or SplitOperand), masked where the block is not whole.
+// Operand or SplitOperand), range-checked by buffer resources, so that no edge of a tensor takes a branch: k-rows past the end of a K-strided
+// operand are zeros, and the last elements of a K-contiguous one are cleared where the last block is not whole.  (Masked element by element
+// at edges and in the first and last blocks of every tile, a step of 1001 x 90 x 362 of 5, top-2, took 58.4 us; so 51.7.)  For operands
+// of up to 4 GB (TileArgs::far: larger ones, FarLoader).
 template <int BM, int BN, int BK, int OP, typename OA, typename OB>
 struct BlockLoader {
+    static constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1, GATHER = OP == F32_WGRAD1;
+    static constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
+    const TileArgs& a;
+    const TilePlace& t;
+    const int ar, ac, br, bc;
+    const DivideBy token;
+    __amdgpu_buffer_rsrc_t ra, rb;
+    uint32_t ao[TOKENS ? 1 : OA::NC], bo[B_KS ? 1 : OB::NC];   // K-strided: one, the rest is in the scalar offset
+    int prow[OA::NC] = {};    // WGRAD1: perm entries of the block that is loaded next
+    int nwhole;               // blocks of BK
+
+    __device__ __forceinline__ BlockLoader(const TileArgs& a_, const TilePlace& t_)
+        : a(a_), t(t_), ar(OA::row()), ac(OA::col()), br(OB::row()), bc(OB::col()), token((uint32_t)a_.k), nwhole(t_.K / BK) {
+        if constexpr (TOKENS) rb = floats_at(a.B + (size_t)t.kbeg * a.N, (size_t)t.K * a.N);
+        else rb = floats_at(a.B + (size_t)t.e * a.K * a.N, (size_t)a.K * a.N);
+        if constexpr (B_KS) {
+            bo[0] = (uint32_t)br * (uint32_t)a.N * 4u + edge_column(t.n0, bc, a.N);
+        } else {
+#pragma unroll
+            for (int i = 0; i < OB::NC; ++i) bo[i] = ((uint32_t)min(t.n0 + br + OB::STEP * i, a.N - 1) * (uint32_t)a.K + (uint32_t)bc) * 4u;
+        }
+        if constexpr (TOKENS) {
+            ra = GATHER ? floats_at(a.A, (size_t)a.T * a.M) : floats_at(a.A + (size_t)t.kbeg * a.M, (size_t)t.K * a.M);
+            ao[0] = (GATHER ? 0u : (uint32_t)ar * (uint32_t)a.M * 4u) + edge_column(t.m0, ac, a.M);
+        } else {
+            ra = OP == F32_FC1 ? floats_at(a.A, (size_t)a.T * a.K) : floats_at(a.A + (size_t)t.m0 * a.K, (size_t)t.rows * a.K);
+#pragma unroll
+            for (int i = 0; i < OA::NC; ++i) {   // rows past the segment repeat its last one (their results are not stored)
+                const int r = min(ar + OA::STEP * i, t.rows - 1);
+                ao[i] = ((OP == F32_FC1 ? token((uint32_t)a.perm[t.m0 + r]) : (uint32_t)r) * (uint32_t)a.K + (uint32_t)ac) * 4u;
+            }
+        }
+    }
+    __device__ __forceinline__ void load_perm(int k0) {
+        if constexpr (GATHER) {
+#pragma unroll
+            for (int i = 0; i < OA::NC; ++i) prow[i] = a.perm[t.kbeg + min(k0 + ar + OA::STEP * i, t.K - 1)];
+        }
+    }
+    // loads block k0 (WGRAD1: and the perm entries of the block behind it, ahead of the data, so that waiting
+    // for them does not wait for the data)
+    template <bool WHOLE>
+    __device__ __forceinline__ void load(int k0, f32x4 (&va)[OA::NC], f32x4 (&vb)[OB::NC]) {
+        auto get = [](__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t s) __attribute__((always_inline)) {
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)v, (int)s, 0));
+        };
+        uint32_t o[OA::NC];
+#pragma unroll
+        for (int i = 0; i < OA::NC; ++i) {
+            o[i] = ao[TOKENS ? 0 : i];
+            if constexpr (GATHER) {
+                o[i] += token((uint32_t)prow[i]) * (uint32_t)a.M * 4u;
+                if (!WHOLE && k0 + ar + OA::STEP * i >= t.K) o[i] = 0xfffffff0u;   // behind any range
+            }
+        }
+        load_perm(k0 + BK);
+#pragma unroll
+        for (int i = 0; i < OA::NC; ++i)
+            va[i] = get(ra, o[i], GATHER ? 0u : TOKENS ? (uint32_t)(k0 + OA::STEP * i) * (uint32_t)a.M * 4u : (uint32_t)k0 * 4u);
+#pragma unroll
+        for (int i = 0; i < OB::NC; ++i)
+            vb[i] = get(rb, bo[B_KS ? 0 : i], B_KS ? (uint32_t)(k0 + OB::STEP * i) * (uint32_t)a.N * 4u : (uint32_t)k0 * 4u);
+        if (!WHOLE && k0 + BK > t.K) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (!TOKENS)
+#pragma unroll
+                    for (int i = 0; i < OA::NC; ++i) va[i][q] = k0 + ac + q < t.K ? va[i][q] : 0.f;
+                if constexpr (!B_KS)
+#pragma unroll
+                    for (int i = 0; i < OB::NC; ++i) vb[i][q] = k0 + bc + q < t.K ? vb[i][q] : 0.f;
+            }
+        }
+    }
+};
+
+// The same for operands of any size: 64-bit addresses, masked where the block is not whole.
+template <int BM, int BN, int BK, int OP, typename OA, typename OB>
+struct FarLoader {
     static constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     static constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
     const TileArgs& a;
@@ -193,7 +292,7 @@ struct BlockLoader {
     int prow[OA::NC] = {};    // WGRAD1: perm entries of the block that is loaded next
     int nwhole;               // blocks that need no masking: none in a tile at an edge of the output
 
-    __device__ __forceinline__ BlockLoader(const TileArgs& a_, const TilePlace& t_)
+    __device__ __forceinline__ FarLoader(const TileArgs& a_, const TilePlace& t_)
         : a(a_), t(t_), ar(OA::row()), ac(OA::col()), br(OB::row()), bc(OB::col()) {
         if constexpr (!TOKENS) {
 #pragma unroll
@@ -254,7 +353,7 @@ template <int R, int BK>
 constexpr int f32_image() { return Operand<false, R, BK>::FLOATS > Operand<true, R, BK>::FLOATS ? Operand<false, R, BK>::FLOATS : Operand<true, R, BK>::FLOATS; }
 template <int FM, int BK>
 constexpr int f32_floats() { return 2 * (f32_image<32 * FM, BK>() + f32_image<32 * frag_cols(FM), BK>()); }
-template <int FM, int BK, int OP>
+template <int FM, int BK, int OP, bool FAR>
 __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace& t, float* smem, f32x4 (&acc)[FM][frag_cols(FM)]) {
     constexpr int BM = 32 * FM, FN = frag_cols(FM), BN = 32 * FN;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
@@ -266,7 +365,7 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, grp = lane >> 4;
     const int nk = ceil_div(t.K, BK);
-    BlockLoader<BM, BN, BK, OP, OA, OB> in(a, t);
+    typename std::conditional<FAR, FarLoader<BM, BN, BK, OP, OA, OB>, BlockLoader<BM, BN, BK, OP, OA, OB>>::type in(a, t);
     // Block j + 2 is on its way to registers and block j + 1 already there while block j is multiplied.
     f32x4 va0[OA::NC], vb0[OB::NC], va1[OA::NC], vb1[OB::NC];
     if (nk > 0) {
@@ -334,7 +433,7 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
 constexpr int kSplitFrom = 33;
 template <int FM>
 constexpr int split_bytes() { return 3 * 64 * 64 * FM; }
-template <int FM, int OP>
+template <int FM, int OP, bool FAR>
 __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlace& t, uint8_t* smem, f32x4 (&acc)[FM][FM], uint32_t& lost) {
     constexpr int BM = 32 * FM, BK = 32;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
@@ -346,7 +445,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
     const int l16 = lane & 15, grp = lane >> 4;
     uint8_t* const sb = smem + 3 * OA::PLANE;
     const int nk = ceil_div(t.K, BK);
-    BlockLoader<BM, BM, BK, OP, OA, OB> in(a, t);
+    typename std::conditional<FAR, FarLoader<BM, BM, BK, OP, OA, OB>, BlockLoader<BM, BM, BK, OP, OA, OB>>::type in(a, t);
     // Block j + 1 is on its way to registers while block j is multiplied.
     f32x4 va[OA::NC], vb[OB::NC];
     if (nk > 0) {
@@ -535,14 +634,6 @@ struct WideOperand {
     }
 };
 
-// p / k for 0 <= p < 2^31 by a product: with 2^(s-1) < k <= 2^s and m = floor(2^(31+s) / k) + 1 it is 2 p m / 2^(32+s), as m k exceeds 2^(31+s)
-// by 2^s at most.
-struct DivideBy {
-    uint32_t m, s;
-    __device__ __forceinline__ explicit DivideBy(uint32_t k) : s(k > 1 ? 32 - __builtin_clz(k - 1) : 0) { m = (uint32_t)((1ull << (31 + s)) / k + 1); }
-    __device__ __forceinline__ uint32_t operator()(uint32_t p) const { return __umulhi(2 * p, m) >> s; }
-};
-
 // f(0), f(1), ... as compile-time constants
 template <typename F, int... I>
 __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
@@ -717,8 +808,8 @@ __device__ __forceinline__ uint8_t* tile_lds() {
 }
 template <int FM, int BK, bool SPLIT>
 constexpr int dynamic_bytes() { return tile_bytes<FM, BK, SPLIT>() > 65536 ? tile_bytes<FM, BK, SPLIT>() : 0; }
-template <int FM, int BK, bool SPLIT, int OP>
-__device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint8_t* smem) {
+template <int FM, int BK, bool SPLIT, int OP, bool FAR>
+__device__ __forceinline__ void f32_tile_of(const TileArgs& a, const int item, uint8_t* smem) {
     constexpr int BM = 32 * FM, FN = frag_cols(FM), BN = 32 * FN;
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -761,7 +852,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
     if constexpr (SPLIT) if (t.K >= kSplitFrom) {
         uint32_t lost = 0;
         if constexpr (FM == 4) multiply_wide<OP>(a, t, smem, acc, lost);
-        else multiply_split<FM, OP>(a, t, smem, acc, lost);
+        else multiply_split<FM, OP, FAR>(a, t, smem, acc, lost);
         // An infinity has no planes (inf - inf is NaN): a tile whose sums are not all finite is multiplied again on the fp32
         // instruction, too.
         float z = 0.f;
@@ -774,7 +865,7 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
         plain = __syncthreads_or(z != z || (lost & 0xffffu) != 0) != 0;
         if (plain) clear();
     }
-    if (plain) multiply_f32<FM, BK, OP>(a, t, reinterpret_cast<float*>(smem), acc);
+    if (plain) multiply_f32<FM, BK, OP, FAR>(a, t, reinterpret_cast<float*>(smem), acc);
 
     // ---- epilogue
     float* out = TOKENS ? tok_out : a.out0;
@@ -816,6 +907,12 @@ __device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint
     }
 }
 
+template <int FM, int BK, bool SPLIT, int OP>
+__device__ __forceinline__ void f32_tile(const TileArgs& a, const int item, uint8_t* smem) {
+    if constexpr (FM == 4) f32_tile_of<FM, BK, SPLIT, OP, false>(a, item, smem);   // (not for larger operands)
+    else if (a.far) f32_tile_of<FM, BK, SPLIT, OP, true>(a, item, smem);
+    else f32_tile_of<FM, BK, SPLIT, OP, false>(a, item, smem);
+}
 template <int FM, int BK, bool SPLIT, int OP>
 __global__ __launch_bounds__(256, FM == 4 ? 2 : SPLIT ? 4 : 1) void f32_gemm(TileArgs a) {
     uint8_t* const smem = tile_lds<FM, BK, SPLIT>();
@@ -863,11 +960,13 @@ bool short_blocks(int tiles) { return tiles > 4 * 256; }
 // 1000 of 16 (512) 92 / 95; bwd_fc1 at the first (1536) 166 / 147, bwd_fc2 (384, with token contractions of 1024 rows) 158 / 156.  fc2 of 2048 rows
 // at that layer, 144 tiles, 37.7 / 36.7.
 constexpr int kWideFrom = 576;
-bool wide_rows(const MoeDims& D, int K) {
-    constexpr long long most = 0xffff0000LL;   // bytes that an operand's 32-bit offsets reach
+// Whether a tile's operands (x, an expert's weights, a chunk's or a tile's rows) lie beyond what 32-bit byte offsets reach.
+bool far_operands(const MoeDims& D) {
+    constexpr long long most = 0xffff0000LL;
     const long long chunk = 9LL * f32_chunk_len(D) / 8 + 256, wider = D.d > D.f ? D.d : D.f;
-    return K >= kWideFrom && 4LL * D.T * D.d <= most && 4LL * D.d * D.f <= most && 4 * chunk * wider <= most;
+    return 4LL * D.T * D.d > most || 4LL * D.d * D.f + 256 * wider > most || 4 * chunk * wider > most;
 }
+bool wide_rows(const MoeDims& D, int K) { return K >= kWideFrom && !far_operands(D); }
 // 32: fp32 instruction, 64: planes, 128: planes on wide tiles
 int rows_class(const MoeDims& D, int K, int N) { return small_rows(D, N) ? 32 : wide_rows(D, K) ? 128 : 64; }
 
@@ -947,7 +1046,7 @@ hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, con
                           const float* W2, const float* b2, const hexa_moe_idx& idx,
                           const MoeWorkspace& ws, hipStream_t st) {
     TileArgs a{};
-    a.offsets = idx.offsets; a.perm = idx.perm; a.k = D.k; a.E = D.E; a.act = D.act; a.T = D.T;
+    a.offsets = idx.offsets; a.perm = idx.perm; a.k = D.k; a.E = D.E; a.act = D.act; a.T = D.T; a.far = far_operands(D);
     // fc1: pre = x W1 + b1, h = F(pre), F'(pre)
     a.A = x; a.B = W1; a.bias = b1; a.out0 = (float*)ws.pre; a.out1 = (float*)ws.h; a.K = D.d; a.N = D.f;
     rows_launch<F32_FC1>(D, a, st, "fc1");
@@ -961,7 +1060,7 @@ hipError_t launch_f32_bwd(const MoeDims& D, const float* x, const float* W1, con
                           const hexa_moe_idx& idx, const MoeWorkspace& ws, float* dW1, float* dW2,
                           hipStream_t st) {
     TileArgs g{};
-    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act; g.T = D.T; g.chunk_len = f32_chunk_len(D);
+    g.offsets = idx.offsets; g.perm = idx.perm; g.k = D.k; g.E = D.E; g.act = D.act; g.T = D.T; g.far = far_operands(D); g.chunk_len = f32_chunk_len(D);
     // 2nd linear layer: dpre = (do W2^T) * F'(pre)  and  dW2[e] = h^T do
     TileArgs r = g, t = g;
     r.A = (const float*)ws.dout; r.B = W2; r.pre_in = (const float*)ws.pre; r.out0 = (float*)ws.dpre;
