@@ -196,6 +196,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t floats_at(const float* p, size
 // and the results of those columns are not stored; at most three floats are read past the end of a row).
 __device__ __forceinline__ uint32_t edge_column(int n0, int col, int N) { return (uint32_t)(n0 + min(col, (N - n0 - 1) / 4 * 4)) * 4u; }
 
+// Of the four columns from there, the last ones at the edge: zeros where they lie past it.
+template <int NC>
+__device__ __forceinline__ void clear_edge(f32x4 (&v)[NC], int n0, int col, int N) {
+    const int valid = N - n0 - min(col, (N - n0 - 1) / 4 * 4);
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int q = 1; q < 4; ++q) v[i][q] = q < valid ? v[i][q] : 0.f;
+}
+
 // What both ways of multiplying share: the loads of K-block k0 (a thread's NC chunks of four floats per operand; OA, OB:
 // Operand or SplitOperand), range-checked by buffer resources, so that no edge of a tensor takes a branch: k-rows past the end of a K-strided
 // operand are zeros, and the last elements of a K-contiguous one are cleared where the last block is not whole.  (Masked element by element
@@ -235,6 +245,14 @@ struct BlockLoader {
                 ao[i] = ((OP == F32_FC1 ? token((uint32_t)a.perm[t.m0 + r]) : (uint32_t)r) * (uint32_t)a.K + (uint32_t)ac) * 4u;
             }
         }
+    }
+    // What a block holds past the edge of the output is the next row's (weights of other columns, another expert's token): no part of what
+    // decides how this tile is multiplied (see split2), so zeros before it is split.
+    __device__ __forceinline__ void clear(f32x4 (&va)[OA::NC], f32x4 (&vb)[OB::NC]) {
+        if constexpr (TOKENS)
+            if (t.m0 + BM > a.M && a.M % 4) clear_edge(va, t.m0, ac, a.M);
+        if constexpr (B_KS)
+            if (t.n0 + BN > a.N && a.N % 4) clear_edge(vb, t.n0, bc, a.N);
     }
     __device__ __forceinline__ void load_perm(int k0) {
         if constexpr (GATHER) {
@@ -313,6 +331,7 @@ struct FarLoader {
         const bool inner = (!TOKENS || t.m0 + BM <= a.M) && (!B_KS || t.n0 + BN <= a.N);
         nwhole = inner ? t.K / BK : 0;
     }
+    __device__ __forceinline__ void clear(f32x4 (&)[OA::NC], f32x4 (&)[OB::NC]) {}   // (the masks leave none)
     __device__ __forceinline__ void load_perm(int k0) {
         if constexpr (OP == F32_WGRAD1) {
 #pragma unroll
@@ -459,6 +478,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         for (int jj = 0; jj < FM; ++jj) low[i][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto step = [&](auto whole, auto odd, int j) __attribute__((always_inline)) {
         constexpr bool WHOLE = decltype(whole)::value, ODD = decltype(odd)::value;
+        in.clear(va, vb);
         OA::template put<ODD>(smem, va, lost);
         OB::template put<false>(sb, vb, lost);
         __syncthreads();
@@ -559,8 +579,7 @@ __device__ __forceinline__ uint32_t split_off(float& a, float& b) {
 // One operand's share of a K-step, R rows (or columns) x 32 contraction elements, 256 threads: a thread has N = R / 32 times four consecutive k, of
 // rows row, row + 32, ... (K contiguous: N loads of four floats), or of N consecutive columns (K strided: four loads of N floats).  Neighbouring
 // threads have rows or columns four apart, which spreads their 64-bit stores over all banks.  All loads are range-checked by the buffer resource:
-// k-rows past the end are zeros, columns past the edge are another row's and their results not stored; at most three floats past the end of a row
-// are read.  LDS holds the planes as in SplitOperand, twice.  (A key of more than two bits would put rows that are read in the same cycle, of
+// k-rows past the end are zeros (or masked), and so are columns past the edge; at most three floats past the end of a row are read.  LDS holds the planes as in SplitOperand, twice.  (A key of more than two bits would put rows that are read in the same cycle, of
 // different chunks, on the same banks: fragment reads took twice as long.)
 template <bool KS, bool GATHER, int R>
 struct WideOperand {
@@ -600,14 +619,27 @@ struct WideOperand {
         if constexpr (W == 4) v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, (int)s, 0));
         else v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)o, (int)s, 0));
     }
-    // zeros for k >= K of block k0 (K contiguous)
+    // zeros for k >= K of block k0.  (K strided: the resource's zeros, but for gathered rows)
     __device__ __forceinline__ void mask(int set, int k0, int K) {
-        if constexpr (!KS) {
+        if constexpr (!KS || GATHER) {
 #pragma unroll
             for (int i = 0; i < NL; ++i)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (k0 + 4 * group() + q >= K) v[set][i][q] = 0.f;
+                for (int q = 0; q < W; ++q)
+                    if (k0 + 4 * group() + (KS ? i : q) >= K) v[set][i][q] = 0.f;
+        }
+    }
+    // zeros for columns past the edge (see BlockLoader::clear)
+    __device__ __forceinline__ void clear(int set, int n0, int n) {
+        if constexpr (KS) {
+            if (n0 + R > n && n % W) {
+                const int valid = n - n0 - min(W * line(), (n - n0 - 1) / W * W);
+#pragma unroll
+                for (int i = 0; i < NL; ++i)
+#pragma unroll
+                    for (int q = 1; q < W; ++q)
+                        if (q >= valid) v[set][i][q] = 0.f;
+            }
         }
     }
     // Piece P of splitting a set into the planes of buffer `set`: P / 7 is the row (K contiguous) or column (K strided), whose
@@ -658,7 +690,7 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
     ob.place(smem + 2 * oa.BUFFER, (wave & 1) * 32);
     const int group = oa.group(), row = oa.row();
     const DivideBy token((uint32_t)a.k);
-    // WGRAD1: perm entries of the block whose offsets are computed next (past the end: zeros, whose rows meet zeros of the other operand)
+    // WGRAD1: perm entries of the block whose offsets are computed next (past the end: zeros, and what their rows hold is masked)
     __amdgpu_buffer_rsrc_t perm_rsrc;
     if constexpr (GATHER) perm_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.perm + t.kbeg), 0, t.K * 4, 0x00020000);
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -707,6 +739,8 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
     perm_load(0);
     take_and_load(0, 0);
     take_and_load(1, 1);
+    oa.clear(0, t.m0, a.M);
+    ob.clear(0, t.n0, a.N);
     for_each_of([&](auto p) __attribute__((always_inline)) { oa.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, oa.PIECES>{});
     for_each_of([&](auto p) __attribute__((always_inline)) { ob.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, ob.PIECES>{});
     take_and_load(0, 2);
@@ -731,9 +765,13 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
         constexpr bool ODD = decltype(odd)::value;
         constexpr int cur = ODD, nxt = !ODD;
         const int kb = min(j + 3, nk - 1);
-        if constexpr (!A_KS && !B_KS) {   // the other contractions have zeros there in their K-strided operand
-            if (j + 2 == nk && 32 * nk > t.K) oa.mask(nxt, 32 * (j + 1), t.K);
+        // (a neighbour's values are no part of what decides how this tile is multiplied; the last step splits the last block once more)
+        if (j + 2 >= nk && 32 * nk > t.K) {
+            oa.mask(nxt, 32 * (nk - 1), t.K);
+            ob.mask(nxt, 32 * (nk - 1), t.K);
         }
+        oa.clear(nxt, t.m0, a.M);
+        ob.clear(nxt, t.n0, a.N);
         f32x4 hi[6];
         __builtin_amdgcn_sched_barrier(0);
         for_each_of([&](auto slot) __attribute__((always_inline)) {

@@ -245,3 +245,38 @@ def test_not_finite_in_every_contraction(name, at, value):
         if fine.any():
             assert nrm_err(got[fine].cpu().numpy(), r[fine].cpu().numpy()) <= TOL["f32"], n
     assert reached >= {"x": {"dW1"}, "dY": {"dx", "dW1", "db1", "dW2", "db2"}, "W1": {"y", "dx", "dW2"}, "W2": {"y", "dx", "dW1", "db1"}}[name]
+
+
+# 64x64 tiles, 128x64 tiles; rows of every tensor at any alignment, segments of 2000 and 1100 rows (no whole number of steps)
+@pytest.mark.parametrize("T,d,f,wide", [(6000, 517, 523, 0), (3300, 1030, 1055, 15)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e-38])
+def test_values_of_a_neighbour(T, d, f, wide, value):
+    """A value that no plane holds changes no bit of what other experts' tokens or other columns of weights give, also where it lies
+    behind the end of one of their rows in memory."""
+    w = MoEWorkload("neighbour", T, d, f, 3, 1, "f32", "topk", 13)
+    assert_tiles(w, [64, 64, 64, 64])
+    assert B.launch_plan(B.make_shape(T, d, f, 3, 1, "f32"))["wide"] == wide
+    data = generate(w, DEV)
+    ids = torch.arange(T, device=DEV) % 3
+    data["topk_idx"] = ids.to(torch.int32).view(T, 1).contiguous()
+
+    def run(name, at):
+        for v in (0.0, value):
+            t = data[name].clone()
+            t[at] = v
+            _, y, g = run_hip_layer(w, {**data, name: t})
+            yield {"y": y, **g}
+
+    for token in (0, 1501):
+        base, got = run("x", (token, slice(0, 3)))
+        e = int(ids[token])
+        for n in base:
+            others = ids != e if n in ("y", "dx", "dgate") else torch.arange(3, device=DEV) != e
+            assert torch.equal(base[n][others], got[n][others]), (token, n)
+        if value == value and value < 1:
+            assert not torch.equal(base["dW1"][e], got["dW1"][e])           # (its own tiles are summed the other way)
+    base, got = run("W2", (0, 5, 1))
+    if value < 1:                                                           # (y past the first tile of columns; no sum sees 1e-38)
+        assert torch.equal(base["y"][:, 128:], got["y"][:, 128:])
+    base, got = run("dY", (1501, 1))
+    assert torch.equal(base["dW2"][:, :, 128:], got["dW2"][:, :, 128:])
