@@ -211,7 +211,7 @@ __device__ __forceinline__ void clear_edge(f32x4 (&v)[NC], int n0, int col, int 
 // operand are zeros, and the last elements of a K-contiguous one are cleared where the last block is not whole.  (Masked element by element
 // at edges and in the first and last blocks of every tile, a step of 1001 x 90 x 362 of 5, top-2, took 58.4 us; so 51.7.)  For operands
 // of up to 4 GB (TileArgs::far: larger ones, FarLoader).
-template <int BM, int BN, int BK, int OP, typename OA, typename OB>
+template <int BM, int BN, int BK, int OP, typename OA, typename OB, bool SPLIT>
 struct BlockLoader {
     static constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1, GATHER = OP == F32_WGRAD1;
     static constexpr bool B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
@@ -222,10 +222,10 @@ struct BlockLoader {
     __amdgpu_buffer_rsrc_t ra, rb;
     uint32_t ao[TOKENS ? 1 : OA::NC], bo[B_KS ? 1 : OB::NC];   // K-strided: one, the rest is in the scalar offset
     int prow[OA::NC] = {};    // WGRAD1: perm entries of the block that is loaded next
-    int nwhole;               // blocks of BK
+    int nwhole;               // blocks that need no masking
 
     __device__ __forceinline__ BlockLoader(const TileArgs& a_, const TilePlace& t_)
-        : a(a_), t(t_), ar(OA::row()), ac(OA::col()), br(OB::row()), bc(OB::col()), token((uint32_t)a_.k), nwhole(t_.K / BK) {
+        : a(a_), t(t_), ar(OA::row()), ac(OA::col()), br(OB::row()), bc(OB::col()), token((uint32_t)a_.k), nwhole(SPLIT && (ragged_a() || ragged_b()) ? 0 : t_.K / BK) {
         if constexpr (TOKENS) rb = floats_at(a.B + (size_t)t.kbeg * a.N, (size_t)t.K * a.N);
         else rb = floats_at(a.B + (size_t)t.e * a.K * a.N, (size_t)a.K * a.N);
         if constexpr (B_KS) {
@@ -246,13 +246,13 @@ struct BlockLoader {
             }
         }
     }
+    __device__ __forceinline__ bool ragged_a() const { return TOKENS && t.m0 + BM > a.M && a.M % 4; }
+    __device__ __forceinline__ bool ragged_b() const { return B_KS && t.n0 + BN > a.N && a.N % 4; }
     // What a block holds past the edge of the output is the next row's (weights of other columns, another expert's token): no part of what
     // decides how this tile is multiplied (see split2), so zeros before it is split.
     __device__ __forceinline__ void clear(f32x4 (&va)[OA::NC], f32x4 (&vb)[OB::NC]) {
-        if constexpr (TOKENS)
-            if (t.m0 + BM > a.M && a.M % 4) clear_edge(va, t.m0, ac, a.M);
-        if constexpr (B_KS)
-            if (t.n0 + BN > a.N && a.N % 4) clear_edge(vb, t.n0, bc, a.N);
+        if (ragged_a()) clear_edge(va, t.m0, ac, a.M);
+        if (ragged_b()) clear_edge(vb, t.n0, bc, a.N);
     }
     __device__ __forceinline__ void load_perm(int k0) {
         if constexpr (GATHER) {
@@ -384,7 +384,7 @@ __device__ __forceinline__ void multiply_f32(const TileArgs& a, const TilePlace&
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, grp = lane >> 4;
     const int nk = ceil_div(t.K, BK);
-    typename std::conditional<FAR, FarLoader<BM, BN, BK, OP, OA, OB>, BlockLoader<BM, BN, BK, OP, OA, OB>>::type in(a, t);
+    typename std::conditional<FAR, FarLoader<BM, BN, BK, OP, OA, OB>, BlockLoader<BM, BN, BK, OP, OA, OB, false>>::type in(a, t);
     // Block j + 2 is on its way to registers and block j + 1 already there while block j is multiplied.
     f32x4 va0[OA::NC], vb0[OB::NC], va1[OA::NC], vb1[OB::NC];
     if (nk > 0) {
@@ -464,7 +464,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
     const int l16 = lane & 15, grp = lane >> 4;
     uint8_t* const sb = smem + 3 * OA::PLANE;
     const int nk = ceil_div(t.K, BK);
-    typename std::conditional<FAR, FarLoader<BM, BM, BK, OP, OA, OB>, BlockLoader<BM, BM, BK, OP, OA, OB>>::type in(a, t);
+    typename std::conditional<FAR, FarLoader<BM, BM, BK, OP, OA, OB>, BlockLoader<BM, BM, BK, OP, OA, OB, true>>::type in(a, t);
     // Block j + 1 is on its way to registers while block j is multiplied.
     f32x4 va[OA::NC], vb[OB::NC];
     if (nk > 0) {
@@ -478,7 +478,7 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
         for (int jj = 0; jj < FM; ++jj) low[i][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto step = [&](auto whole, auto odd, int j) __attribute__((always_inline)) {
         constexpr bool WHOLE = decltype(whole)::value, ODD = decltype(odd)::value;
-        in.clear(va, vb);
+        if constexpr (!WHOLE) in.clear(va, vb);
         OA::template put<ODD>(smem, va, lost);
         OB::template put<false>(sb, vb, lost);
         __syncthreads();
@@ -630,16 +630,15 @@ struct WideOperand {
         }
     }
     // zeros for columns past the edge (see BlockLoader::clear)
+    static __device__ __forceinline__ bool ragged(int n0, int n) { return KS && n0 + R > n && n % W; }
     __device__ __forceinline__ void clear(int set, int n0, int n) {
         if constexpr (KS) {
-            if (n0 + R > n && n % W) {
-                const int valid = n - n0 - min(W * line(), (n - n0 - 1) / W * W);
+            const int valid = n - n0 - min(W * line(), (n - n0 - 1) / W * W);
 #pragma unroll
-                for (int i = 0; i < NL; ++i)
+            for (int i = 0; i < NL; ++i)
 #pragma unroll
-                    for (int q = 1; q < W; ++q)
-                        if (q >= valid) v[set][i][q] = 0.f;
-            }
+                for (int q = 1; q < W; ++q)
+                    if (q >= valid) v[set][i][q] = 0.f;
         }
     }
     // Piece P of splitting a set into the planes of buffer `set`: P / 7 is the row (K contiguous) or column (K strided), whose
@@ -739,8 +738,14 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
     perm_load(0);
     take_and_load(0, 0);
     take_and_load(1, 1);
-    oa.clear(0, t.m0, a.M);
-    ob.clear(0, t.n0, a.N);
+    // a neighbour's values are no part of what decides how this tile is multiplied (the last step splits the last block once more)
+    const bool ragged_a = oa.ragged(t.m0, a.M), ragged_b = ob.ragged(t.n0, a.N);
+    const int clear_from = ragged_a || ragged_b ? 0 : t.K % 32 ? nk - 2 : nk;
+    auto clear = [&](int set) __attribute__((always_inline)) {
+        if (ragged_a) oa.clear(set, t.m0, a.M);
+        if (ragged_b) ob.clear(set, t.n0, a.N);
+    };
+    clear(0);
     for_each_of([&](auto p) __attribute__((always_inline)) { oa.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, oa.PIECES>{});
     for_each_of([&](auto p) __attribute__((always_inline)) { ob.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, ob.PIECES>{});
     take_and_load(0, 2);
@@ -765,13 +770,13 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
         constexpr bool ODD = decltype(odd)::value;
         constexpr int cur = ODD, nxt = !ODD;
         const int kb = min(j + 3, nk - 1);
-        // (a neighbour's values are no part of what decides how this tile is multiplied; the last step splits the last block once more)
-        if (j + 2 >= nk && 32 * nk > t.K) {
-            oa.mask(nxt, 32 * (nk - 1), t.K);
-            ob.mask(nxt, 32 * (nk - 1), t.K);
+        if (j >= clear_from) {
+            if (j + 2 >= nk) {
+                oa.mask(nxt, 32 * (nk - 1), t.K);
+                ob.mask(nxt, 32 * (nk - 1), t.K);
+            }
+            clear(nxt);
         }
-        oa.clear(nxt, t.m0, a.M);
-        ob.clear(nxt, t.n0, a.N);
         f32x4 hi[6];
         __builtin_amdgcn_sched_barrier(0);
         for_each_of([&](auto slot) __attribute__((always_inline)) {
