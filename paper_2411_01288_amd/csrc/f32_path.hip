@@ -68,7 +68,8 @@ __device__ __forceinline__ void act_both(float u, int act, float& h, float& g) {
     const float r = fmaf(fmaf(d - 1.f - e, r0, fmaf(-d, r0, 1.f)), r0, r0), er = e * r;
     const float s = u > 0.f ? r : er;
     h = u * s;
-    g = s + h * (u > 0.f ? er : r) * fmaf((float)(6 * C * 0.044715), u2, (float)(2 * C));
+    // (from |u| = 1.8e19 on u^2 is infinite and the smaller of s and 1 - s 0: their product is 0)
+    g = s + h * (u > 0.f ? er : r) * (x > 90.f ? 0.f : fmaf((float)(6 * C * 0.044715), u2, (float)(2 * C)));
 }
 
 // One operand's share of a K-block: R rows (or columns) x BK contraction elements, 256 threads, NC chunks of

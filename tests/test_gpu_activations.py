@@ -74,3 +74,21 @@ def test_f32_gelu_and_its_derivative(lo, hi):
     off = (4 + t.abs()) * torch.minimum(s, s1) + torch.maximum(s, s1)
     assert ((y.double() - u * s).abs() <= 2.0 ** -24 * u.abs() * (off + s) + 1e-26).all()
     assert ((g.double() - (s + u * s * s1 * q)).abs() <= 2.0 ** -24 * (off + u.abs() * q * (off * s + (off + 3 * s) * s1) + 1) + 1e-26).all()
+
+
+def test_f32_gelu_far_out():
+    """Finite pre-activations up to the ends of fp32: F is u or 0, F' 1 or 0; at infinities F' is NaN as in the formula (0 times infinity)."""
+    from paper_2411_01288_amd import binding as B
+    far = torch.cat([torch.logspace(1.2, 38.5, 3001, device=DEV), torch.tensor([1.8446744e19, 1.85e19, 2e19, 5.04e19, 5.1e19, 3.4028234e38], device=DEV)])
+    x = torch.cat([far, -far, torch.tensor([float("inf"), float("-inf"), float("nan")], device=DEV)]).view(-1, 1)
+    T = x.shape[0]
+    shape = B.make_shape(T, 1, 1, 1, 1, "f32")
+    ones, zeros = torch.ones(T, 1, device=DEV), torch.zeros(1, 1, device=DEV)
+    ids, W = torch.zeros(T, 1, dtype=torch.int32, device=DEV), ones[:1].view(1, 1, 1)
+    idx, ws = B.hexa_moe_index(shape, ids), B.alloc_workspace(shape, DEV)
+    y = B.hexa_moe_fwd(shape, x, ids, ones, W, zeros, W, zeros, idx, ws)[:, 0]
+    g = B.hexa_moe_bwd(shape, ones, x, ids, ones, W, W, idx, ws)["dx"][:, 0]
+    n = far.numel()
+    assert torch.equal(y[:n], far) and (g[:n] == 1).all()
+    assert (y[n:2 * n] == 0).all() and (g[n:2 * n] == 0).all()
+    assert torch.isposinf(y[-3]) and torch.isnan(y[-2:]).all() and torch.isnan(g[-3:]).all()
