@@ -112,7 +112,7 @@ bool needs_device_init(const MoeDims& D, int dtype) {
     if (dtype != HEXA_F32) return true;
     bool wide[4];
     f32_wide(D, wide);
-    return wide[0] || wide[1];
+    return wide[0] || wide[1] || wide[2] || wide[3];
 }
 
 template <typename T>

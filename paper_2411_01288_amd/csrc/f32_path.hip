@@ -13,6 +13,7 @@
 // 1.7e-7, dx 8.0e-7 -> 1.7e-7, dW1 6.8e-7 -> 1.5e-7, db1 3.8e-7 -> 1.4e-7; at other lengths see split2, multiply_split and kSplitFrom.  Tried
 // and not kept: all fragments read at once (three workgroups per CU, 12 % slower), two LDS buffers with the split between the products
 // (12 % slower), 64x128 tiles (fc2 3 % faster, fc1 20 % slower).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -998,32 +999,52 @@ bool small_rows(const MoeDims& D, int N) {
 // x 512 x 2048 of 16 110 / 85, fc2 at 8192 x 256 x 301 of 2 (2064) 25.7 / 22.8; fc2 at 1024 x 384 x 1536 of 8 (864) 38.5 / 39.5.
 bool short_blocks(int tiles) { return tiles > 4 * 256; }
 
-// Planes on 128x64 tiles, two workgroups per CU, or on 64x64, four: a tile's start and epilogue are better hidden under three others' K loops, so
-// the line is the contraction's length.  Measured on both sides, us, 64x64 / 128x64: fc2 at 8192 rows, 384 x 1536 of 8 experts (K = 1536) 91 / 81,
-// at 10000 rows, 450 x 600 of 9 (600) 64.7 / 54.7, at 16384 rows, 512 x 300 of 4 (300) 52 / 55; fc1 at the first (384) 94 / 108, at 9000 rows, 512 x
-// 1000 of 16 (512) 92 / 95; bwd_fc1 at the first (1536) 166 / 147, bwd_fc2 (384, with token contractions of 1024 rows) 158 / 156.  fc2 of 2048 rows
-// at that layer, 144 tiles, 37.7 / 36.7.
-constexpr int kWideFrom = 576;
 // Whether a tile's operands (x, an expert's weights, a chunk's or a tile's rows) lie beyond what 32-bit byte offsets reach.
 bool far_operands(const MoeDims& D) {
     constexpr long long most = 0xffff0000LL;
     const long long chunk = 9LL * f32_chunk_len(D) / 8 + 256, wider = D.d > D.f ? D.d : D.f;
     return 4LL * D.T * D.d > most || 4LL * D.d * D.f + 256 * wider > most || 4 * chunk * wider > most;
 }
-bool wide_rows(const MoeDims& D, int K) { return K >= kWideFrom && !far_operands(D); }
-// 32: fp32 instruction, 64: planes, 128: planes on wide tiles
-int rows_class(const MoeDims& D, int K, int N) { return small_rows(D, N) ? 32 : wide_rows(D, K) ? 128 : 64; }
+// Planes on 128x64 tiles, two workgroups per CU, or on 64x64, four.  Wide tiles split and fetch less per product, and that is worth more the
+// longer the contraction; against it stand the rows that an expert's last tile pads (64 on average instead of 32) and a start and an epilogue that
+// are hidden under one other workgroup's K loop instead of three.  So the line lies at the length K and, for the padding, at the
+// rows per expert n: 1024, or 512 where K is 1536.  Measured on both sides, us, 64x64 / 128x64 (tokens = rows, d x f of experts):
+//   fc2 (K = f): 8192 rows, 384 x 1536 of 8 (n = 1024) 92 / 86, 8192 x 640 x 640 of 4 62 / 59, 4096 x 768 x 3072 of 8 (n = 512) 176 / 160, 4096 x 1024 x
+//     1024 of 8 (n = 512) 83 / 85, 4096 x 1024 x 2048 of 16 (n = 256) 165 / 168, 3000 x 768 x 768 of 64 (n = 47) 52 / 79; one column of tiles,
+//     whose A nothing else reads: 300000 x 64 x 600 of 4 263 / 270.
+//   bwd_fc1 (K = f) at the same: 164 / 151, 117 / 114, 310 / 302, 147 / 146, 298 / 310, 117 / 158.
+//   bwd_fc2 (K = d, long epilogue: from 1024): 4096 rows of 4, 1536 x 1536 302 / 285, 2048 x 2048 511 / 489, 8192 x 1024 x 2048 of 8 521 / 493; 8192 x
+//     640 x 640 of 4 112 / 114, 5000 top-2 x 600 x 1000 of 9 206 / 213, 4096 x 768 x 3072 of 8 306 / 306.
+//   fc1 (K = d, epilogue longer yet): 4096 top-2 x 576 x 2304 of 8 186 / 193, 4096 x 1024 x 1024 of 8 90 / 94, 8192 x 1024 x 2048 of 8 271 / 269, 4096 x 2048 x 2048 of
+//     4 274 / 267, 2048 x 4096 x 1024 of 4 184 / 182: stays on 64x64.
+// A backward grid's token contraction takes the same tiles: its chunks have to be as long, and its M must not pad much on 128 rows (bwd_fc1 at 300000 x 64 x
+// 600 of 4 508 / 729, at 16384 x 576 x 576 of 2 180 / 184).
+constexpr int kWideFrom = 576;
+bool wide_rows(const MoeDims& D, int K) {
+    const int n = D.A / std::min(D.E, D.A);
+    return n >= (K >= 1536 ? 512 : 1024) && K >= kWideFrom && !far_operands(D);
+}
+bool wide_tokens(const MoeDims& D, int M) {
+    const int half = ceil_div(M, 64), padded = 2 * ceil_div(M, 128);
+    return f32_chunk_len(D) >= 512 && 16 * (padded - half) <= half;
+}
+// what the launches run on.  32: fp32 instruction, 64: planes, 128: planes on wide tiles
+int fc1_class(const MoeDims& D) { return small_rows(D, D.f) ? 32 : 64; }
+int fc2_class(const MoeDims& D) { return small_rows(D, D.d) ? 32 : wide_rows(D, D.f) && D.d > 64 ? 128 : 64; }
+int bwd_fc2_class(const MoeDims& D) { return small_rows(D, D.f) ? 32 : D.d >= 1024 && wide_rows(D, D.d) && wide_tokens(D, D.f) ? 128 : 64; }
+int bwd_fc1_class(const MoeDims& D) { return small_rows(D, D.d) ? 32 : wide_rows(D, D.f) && wide_tokens(D, D.d) ? 128 : 64; }
 
 template <int FM, int BK, bool SPLIT, int OP>
 void rows_launch_as(int grid, const TileArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((f32_gemm<FM, BK, SPLIT, OP>), dim3(grid), dim3(256), (dynamic_bytes<FM, BK, SPLIT>()), st, a);
 }
 template <int OP>
-void rows_launch(const MoeDims& D, const TileArgs& a, hipStream_t st, const char* label) {
-    const int c = rows_class(D, a.K, a.N), grid = row_items(D, c, a.N);
+void rows_launch(const MoeDims& D, int c, const TileArgs& a, hipStream_t st, const char* label) {
+    const int grid = row_items(D, c, a.N);
     ProfScope ps(st, label);
-    if (c == 128) rows_launch_as<4, 16, true, OP>(grid, a, st);
-    else if (c == 64) rows_launch_as<2, 16, true, OP>(grid, a, st);
+    if constexpr (OP == F32_FC2)
+        if (c == 128) return rows_launch_as<4, 16, true, OP>(grid, a, st);
+    if (c == 64) rows_launch_as<2, 16, true, OP>(grid, a, st);
     else if (short_blocks(grid)) rows_launch_as<1, 32, false, OP>(grid, a, st);
     else rows_launch_as<1, 64, false, OP>(grid, a, st);
 }
@@ -1033,8 +1054,8 @@ void pair_launch_as(int grid, const TileArgs& ra, const TileArgs& rb, int items,
                        (int)b_first);
 }
 template <int OPA, int OPB>
-void pair_launch(const MoeDims& D, const TileArgs& ra, const TileArgs& rb, hipStream_t st, const char* label) {
-    const int c = rows_class(D, ra.K, ra.N), items_a = row_items(D, c, ra.N), items_b = token_items(D, c, rb.M, rb.N), grid = items_a + items_b;
+void pair_launch(const MoeDims& D, int c, const TileArgs& ra, const TileArgs& rb, hipStream_t st, const char* label) {
+    const int items_a = row_items(D, c, ra.N), items_b = token_items(D, c, rb.M, rb.N), grid = items_a + items_b;
     // rows of a token contraction's tile on average (the host does not know the routing), against K of a row GEMM's.  bwd_fc2 at
     // 4096 x 384 x 1536 of 8 (1024 against 384): row GEMM first 195 us, token contraction first 191 (on a machine 2 % slower)
     const long long rows = D.A / (D.E < D.A ? D.E : D.A), chunk = f32_chunk_len(D);
@@ -1047,15 +1068,9 @@ void pair_launch(const MoeDims& D, const TileArgs& ra, const TileArgs& rb, hipSt
     else pair_launch_as<1, 64, false, OPA, OPB>(grid, ra, rb, items, b_first, st);
 }
 
-template <int OP>
-hipError_t allow_rows() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(f32_gemm<4, 16, true, OP>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               dynamic_bytes<4, 16, true>());
-}
-template <int OPA, int OPB>
-hipError_t allow_pair() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(f32_gemm_pair<4, 16, true, OPA, OPB>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               dynamic_bytes<4, 16, true>());
+template <typename KERNEL>
+hipError_t allow_wide(KERNEL* kern) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, dynamic_bytes<4, 16, true>());
 }
 
 }  // namespace
@@ -1074,15 +1089,16 @@ void f32_tile_classes(const MoeDims& D, int (&tile)[4]) {
     tile[1] = tile[3] = small_rows(D, D.d) ? 32 : 64;
 }
 void f32_wide(const MoeDims& D, bool (&wide)[4]) {
-    wide[0] = wide[2] = rows_class(D, D.d, D.f) == 128;
-    wide[1] = wide[3] = rows_class(D, D.f, D.d) == 128;
+    wide[0] = false;
+    wide[1] = fc2_class(D) == 128;
+    wide[2] = bwd_fc2_class(D) == 128;
+    wide[3] = bwd_fc1_class(D) == 128;
 }
-int f32_dgrad2_row_tile(const MoeDims& D) { return rows_class(D, D.d, D.f); }
+int f32_dgrad2_row_tile(const MoeDims& D) { return bwd_fc2_class(D); }
 hipError_t f32_device_init() {
-    hipError_t e = allow_rows<F32_FC1>();
-    if (e == hipSuccess) e = allow_rows<F32_FC2>();
-    if (e == hipSuccess) e = allow_pair<F32_DGRAD2, F32_WGRAD2>();
-    if (e == hipSuccess) e = allow_pair<F32_DGRAD1, F32_WGRAD1>();
+    hipError_t e = allow_wide(f32_gemm<4, 16, true, F32_FC2>);
+    if (e == hipSuccess) e = allow_wide(f32_gemm_pair<4, 16, true, F32_DGRAD2, F32_WGRAD2>);
+    if (e == hipSuccess) e = allow_wide(f32_gemm_pair<4, 16, true, F32_DGRAD1, F32_WGRAD1>);
     return e;
 }
 
@@ -1093,10 +1109,10 @@ hipError_t launch_f32_fwd(const MoeDims& D, const float* x, const float* W1, con
     a.offsets = idx.offsets; a.perm = idx.perm; a.k = D.k; a.E = D.E; a.act = D.act; a.T = D.T; a.far = far_operands(D);
     // fc1: pre = x W1 + b1, h = F(pre), F'(pre)
     a.A = x; a.B = W1; a.bias = b1; a.out0 = (float*)ws.pre; a.out1 = (float*)ws.h; a.K = D.d; a.N = D.f;
-    rows_launch<F32_FC1>(D, a, st, "fc1");
+    rows_launch<F32_FC1>(D, fc1_class(D), a, st, "fc1");
     // fc2: o = h W2 + b2
     a.A = (const float*)ws.h; a.B = W2; a.bias = b2; a.out0 = (float*)ws.o; a.out1 = nullptr; a.K = D.f; a.N = D.d;
-    rows_launch<F32_FC2>(D, a, st, "fc2");
+    rows_launch<F32_FC2>(D, fc2_class(D), a, st, "fc2");
     return hipGetLastError();
 }
 
@@ -1110,11 +1126,11 @@ hipError_t launch_f32_bwd(const MoeDims& D, const float* x, const float* W1, con
     r.A = (const float*)ws.dout; r.B = W2; r.pre_in = (const float*)ws.pre; r.out0 = (float*)ws.dpre;
     r.colpart = ws.colpart1; r.K = D.d; r.N = D.f;
     t.A = (const float*)ws.h; t.B = (const float*)ws.dout; t.out0 = dW2; t.kpart = ws.kpart2; t.M = D.f; t.N = D.d;
-    pair_launch<F32_DGRAD2, F32_WGRAD2>(D, r, t, st, "bwd_fc2");
+    pair_launch<F32_DGRAD2, F32_WGRAD2>(D, bwd_fc2_class(D), r, t, st, "bwd_fc2");
     // 1st linear layer: dxp = dpre W1^T  and  dW1[e] = x[perm/k]^T dpre
     r = g; t = g;
     r.A = (const float*)ws.dpre; r.B = W1; r.out0 = (float*)ws.dxp; r.K = D.f; r.N = D.d;
     t.A = x; t.B = (const float*)ws.dpre; t.out0 = dW1; t.kpart = ws.kpart1; t.M = D.d; t.N = D.f;
-    pair_launch<F32_DGRAD1, F32_WGRAD1>(D, r, t, st, "bwd_fc1");
+    pair_launch<F32_DGRAD1, F32_WGRAD1>(D, bwd_fc1_class(D), r, t, st, "bwd_fc1");
     return hipGetLastError();
 }

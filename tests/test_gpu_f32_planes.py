@@ -247,8 +247,8 @@ def test_not_finite_in_every_contraction(name, at, value):
     assert reached >= {"x": {"dW1"}, "dY": {"dx", "dW1", "db1", "dW2", "db2"}, "W1": {"y", "dx", "dW2"}, "W2": {"y", "dx", "dW1", "db1"}}[name]
 
 
-# 64x64 tiles, 128x64 tiles; rows of every tensor at any alignment, segments of 2000 and 1100 rows (no whole number of steps)
-@pytest.mark.parametrize("T,d,f,wide", [(6000, 517, 523, 0), (3300, 1030, 1055, 15)])
+# 64x64 tiles; 128x64 tiles but for fc1; rows of every tensor at any alignment, segments of 2000 and 1100 rows (no whole number of steps)
+@pytest.mark.parametrize("T,d,f,wide", [(6000, 517, 523, 0), (3300, 1030, 1055, 14)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e-38])
 def test_values_of_a_neighbour(T, d, f, wide, value):
     """A value that no plane holds changes no bit of what other experts' tokens or other columns of weights give, also where it lies
