@@ -596,17 +596,19 @@ struct WideOperand {
     const uint8_t* frag_at;
     load_t v[2][NL];            // blocks j + 1 and j + 2
 
-    static __device__ __forceinline__ int group() { return (int)threadIdx.x & 7; }
-    static __device__ __forceinline__ int line() { return (int)threadIdx.x >> 3; }
-    static __device__ __forceinline__ int row() { return (line() & 3) << 2 | (line() >> 2 & 3) | (line() & 16); }
+    const int tid;              // threadIdx.x
+    __device__ __forceinline__ explicit WideOperand(int t) : tid(t) {}
+    __device__ __forceinline__ int group() const { return tid & 7; }
+    __device__ __forceinline__ int line() const { return tid >> 3; }
+    __device__ __forceinline__ int row() const { return (line() & 3) << 2 | (line() >> 2 & 3) | (line() & 16); }
     // a thread's columns of a K-strided operand, the last ones at the edge
-    static __device__ __forceinline__ uint32_t column(int n0, int n) { return (uint32_t)(n0 + min(W * line(), (n - n0 - 1) / W * W)) * 4u; }
+    __device__ __forceinline__ uint32_t column(int n0, int n) const { return (uint32_t)(n0 + min(W * line(), (n - n0 - 1) / W * W)) * 4u; }
     __device__ __forceinline__ void resource(const float* p, size_t floats) {
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(uint32_t)(floats * 4), 0x00020000);
     }
     // base: first row or column of the wavefront's fragments
     __device__ __forceinline__ void place(uint8_t* s, int base) {
-        const int chunk = group() >> 1, l16 = (int)threadIdx.x & 15, grp = (int)threadIdx.x >> 4 & 3;
+        const int chunk = group() >> 1, l16 = tid & 15, grp = tid >> 4 & 3;
 #pragma unroll
         for (int i = 0; i < (KS ? N : 1); ++i)
             put_at[i] = s + (chunk * R + ((KS ? N * line() + i : row()) ^ chunk)) * 16 + (group() & 1) * 8;
@@ -621,21 +623,23 @@ struct WideOperand {
         if constexpr (W == 4) v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, (int)s, 0));
         else v[set][i] = __builtin_bit_cast(load_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)o, (int)s, 0));
     }
-    // zeros for k >= K of block k0.  (K strided: the resource's zeros, but for gathered rows)
+    // zeros for k >= K of block k0 (K contiguous)
     __device__ __forceinline__ void mask(int set, int k0, int K) {
-        if constexpr (!KS || GATHER) {
+        if constexpr (!KS) {
 #pragma unroll
             for (int i = 0; i < NL; ++i)
 #pragma unroll
-                for (int q = 0; q < W; ++q)
-                    if (k0 + 4 * group() + (KS ? i : q) >= K) v[set][i][q] = 0.f;
+                for (int q = 0; q < 4; ++q)
+                    if (k0 + 4 * group() + q >= K) v[set][i][q] = 0.f;
         }
     }
     // zeros for columns past the edge (see BlockLoader::clear)
     static __device__ __forceinline__ bool ragged(int n0, int n) { return KS && n0 + R > n && n % W; }
     __device__ __forceinline__ void clear(int set, int n0, int n) {
         if constexpr (KS) {
-            const int valid = n - n0 - min(W * line(), (n - n0 - 1) / W * W);
+            int at = W * line();
+            asm volatile("" : "+v"(at));   // (computed again in every step: registers)
+            const int valid = n - n0 - min(at, (n - n0 - 1) / W * W);
 #pragma unroll
             for (int i = 0; i < NL; ++i)
 #pragma unroll
@@ -680,18 +684,27 @@ __device__ __forceinline__ void large_product(f32x4& c, bf16x8 fb, bf16x8 fa) {
 }
 
 constexpr int kWideLds = 2 * 3 * 64 * (128 + 64);   // two buffers of three planes of both operands
+// RAGGED: the tile holds columns past the edge of a K-strided operand, which are cleared (see BlockLoader::clear)
 template <int OP>
+__device__ __forceinline__ bool wide_ragged(const TileArgs& a, const TilePlace& t) {
+    constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1;
+    return WideOperand<TOKENS, false, 128>::ragged(t.m0, a.M) || WideOperand<TOKENS || OP == F32_FC2, false, 64>::ragged(t.n0, a.N);
+}
+template <int OP, bool RAGGED>
 __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace& t, uint8_t* smem, f32x4 (&acc)[4][2], uint32_t& lost) {
+    static_assert(OP != F32_FC1, "fc1 takes no wide tiles");
     constexpr bool TOKENS = OP == F32_WGRAD2 || OP == F32_WGRAD1, GATHER = OP == F32_WGRAD1;
-    constexpr bool A_KS = TOKENS, B_KS = TOKENS || OP == F32_FC1 || OP == F32_FC2;
-    const int wave = (int)threadIdx.x >> 6, nk = ceil_div(t.K, 32);    // at least two steps
-    WideOperand<A_KS, GATHER, 128> oa;
-    WideOperand<B_KS, false, 64> ob;
+    constexpr bool A_KS = TOKENS, B_KS = TOKENS || OP == F32_FC2;
+    int tid = (int)threadIdx.x;
+    if constexpr (RAGGED) asm volatile("" : "+v"(tid));   // (the compiler would compute ahead for both variants together, and spill)
+    const int wave = tid >> 6, nk = ceil_div(t.K, 32);    // at least two steps
+    WideOperand<A_KS, GATHER, 128> oa(tid);
+    WideOperand<B_KS, false, 64> ob(tid);
     oa.place(smem, (wave >> 1) * 64);
     ob.place(smem + 2 * oa.BUFFER, (wave & 1) * 32);
     const int group = oa.group(), row = oa.row();
     const DivideBy token((uint32_t)a.k);
-    // WGRAD1: perm entries of the block whose offsets are computed next (past the end: zeros, and what their rows hold is masked)
+    // WGRAD1: perm entries of the block whose offsets are computed next (past the end: zeros; see perm_end)
     __amdgpu_buffer_rsrc_t perm_rsrc;
     if constexpr (GATHER) perm_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.perm + t.kbeg), 0, t.K * 4, 0x00020000);
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -702,6 +715,15 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
     };
     auto perm_take = [&](int i) __attribute__((always_inline)) {
         if constexpr (GATHER) oa.voff[i] = token(pv[i]) * oa.pitch + col;
+    };
+    // block kb's rows past the end of the chunk: behind any range, so zeros
+    auto perm_end = [&](int kb) __attribute__((always_inline)) {
+        if constexpr (GATHER)
+            if (kb + 1 >= nk && t.K % 32) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (32 * (nk - 1) + 4 * group + i >= t.K) oa.voff[i] = 0xfffffff0u;
+            }
     };
     if constexpr (B_KS) {
         ob.pitch = (uint32_t)a.N * 4u;
@@ -722,30 +744,29 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
             oa.voff[0] = (uint32_t)(4 * group) * oa.pitch + col;
         }
     } else {
-        if constexpr (OP == F32_FC1) oa.resource(a.A, (size_t)a.T * a.K);
-        else oa.resource(a.A + (size_t)t.m0 * a.K, (size_t)t.rows * a.K);
+        oa.resource(a.A + (size_t)t.m0 * a.K, (size_t)t.rows * a.K);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {    // rows past the segment repeat its last one (their results are not stored)
-            const int r = min(row + 32 * i, t.rows - 1);
-            oa.voff[i] = (OP == F32_FC1 ? token((uint32_t)a.perm[t.m0 + r]) : (uint32_t)r) * (uint32_t)a.K * 4u + 16u * group;
-        }
+        for (int i = 0; i < 4; ++i)      // rows past the segment repeat its last one (their results are not stored)
+            oa.voff[i] = (uint32_t)min(row + 32 * i, t.rows - 1) * (uint32_t)a.K * 4u + 16u * group;
     }
     auto take_and_load = [&](int set, int kb) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < ob.NL; ++i) ob.load(set, i, 32 * min(kb, nk - 1));
 #pragma unroll
-        for (int i = 0; i < oa.NL; ++i) { perm_take(i); oa.load(set, i, 32 * min(kb, nk - 1)); }
+        for (int i = 0; i < oa.NL; ++i) perm_take(i);
+        perm_end(kb);
+#pragma unroll
+        for (int i = 0; i < oa.NL; ++i) oa.load(set, i, 32 * min(kb, nk - 1));
         perm_load(kb + 1);
     };
     perm_load(0);
     take_and_load(0, 0);
     take_and_load(1, 1);
-    // a neighbour's values are no part of what decides how this tile is multiplied (the last step splits the last block once more)
-    const bool ragged_a = oa.ragged(t.m0, a.M), ragged_b = ob.ragged(t.n0, a.N);
-    const int clear_from = ragged_a || ragged_b ? 0 : t.K % 32 ? nk - 2 : nk;
     auto clear = [&](int set) __attribute__((always_inline)) {
-        if (ragged_a) oa.clear(set, t.m0, a.M);
-        if (ragged_b) ob.clear(set, t.n0, a.N);
+        if constexpr (RAGGED) {
+            oa.clear(set, t.m0, a.M);
+            ob.clear(set, t.n0, a.N);
+        }
     };
     clear(0);
     for_each_of([&](auto p) __attribute__((always_inline)) { oa.template piece<false, 0, decltype(p)::value>(lost); }, std::make_integer_sequence<int, oa.PIECES>{});
@@ -759,6 +780,7 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
     for (int i = 0; i < 2; ++i) b1[i] = ob.frag(0, 0, i);
 #pragma unroll
     for (int i = 0; i < 4; ++i) perm_take(i);
+    perm_end(3);
     perm_load(4);
     f32x4 low[2][4][2];    // the small products of the even and of the odd steps, which have signs of their own
 #pragma unroll
@@ -772,13 +794,14 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
         constexpr bool ODD = decltype(odd)::value;
         constexpr int cur = ODD, nxt = !ODD;
         const int kb = min(j + 3, nk - 1);
-        if (j >= clear_from) {
-            if (j + 2 >= nk) {
+        // (FC2: what A holds there is of the tile's own rows, and meets zeros.  The last step splits the last block once more)
+        if constexpr (!A_KS && !B_KS) {
+            if (j + 2 >= nk && t.K % 32) {
                 oa.mask(nxt, 32 * (nk - 1), t.K);
                 ob.mask(nxt, 32 * (nk - 1), t.K);
             }
-            clear(nxt);
         }
+        clear(nxt);
         f32x4 hi[6];
         __builtin_amdgcn_sched_barrier(0);
         for_each_of([&](auto slot) __attribute__((always_inline)) {
@@ -806,7 +829,10 @@ __device__ __forceinline__ void multiply_wide(const TileArgs& a, const TilePlace
             }
             if constexpr (GATHER) {
                 if constexpr (m >= 34 && m < 38) perm_take(m - 34);
-                if constexpr (m == 38) perm_load(j + 5);
+                if constexpr (m == 38) {
+                    perm_end(j + 4);
+                    perm_load(j + 5);
+                }
             }
             if constexpr (m == 41) __syncthreads();
             if constexpr (m >= 42 && m < 46) a3[m - 42] = oa.frag(nxt, 2, m - 42);
@@ -896,7 +922,10 @@ __device__ __forceinline__ void f32_tile_of(const TileArgs& a, const int item, u
     bool plain = true;
     if constexpr (SPLIT) if (t.K >= kSplitFrom) {
         uint32_t lost = 0;
-        if constexpr (FM == 4) multiply_wide<OP>(a, t, smem, acc, lost);
+        if constexpr (FM == 4) {
+            if (!wide_ragged<OP>(a, t)) multiply_wide<OP, false>(a, t, smem, acc, lost);
+            else multiply_wide<OP, true>(a, t, smem, acc, lost);
+        }
         else multiply_split<FM, OP, FAR>(a, t, smem, acc, lost);
         // An infinity has no planes (inf - inf is NaN): a tile whose sums are not all finite is multiplied again on the fp32
         // instruction, too.
