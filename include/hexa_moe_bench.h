@@ -43,7 +43,7 @@ typedef struct {
     int64_t index_chunk_ids, index_chunks;   /* index build: ids per workgroup, workgroups */
     int64_t prologue_blocks;   /* workgroups of the backward prologue (with dgate) */
     int32_t wide;              /* fp32: bit i set where launch i (in the order of the tiles) takes tiles of 128 rows and 64 columns */
-    int32_t thin;              /* 16 bits: fc1 and fc2 take tiles of 32 rows and 128 columns (few rows per expert) */
+    int32_t thin;              /* 16 bits: bits 0, 1 set where fc1, fc2 take tiles of 32 rows and 128 columns (few rows) */
 } hexa_moe_plan;
 HEXA_API hexa_status hexa_moe_launch_plan(const hexa_moe_shape *shape, hexa_moe_plan *plan);
 

@@ -85,9 +85,10 @@ hexa_status hexa_moe_launch_plan(const hexa_moe_shape* shape, hexa_moe_plan* pla
     plan->partial_buffers = (int64_t)split_slots(D, plan->chunk_rows);
     index_chunks(D, &plan->index_chunk_ids, &plan->index_chunks);
     plan->prologue_blocks = prologue_blocks(D, !f32, true);
-    plan->thin = !f32 && gemm_thin(D);
-    bool wide[4] = {};
+    bool wide[4] = {}, thin[2] = {};
     if (f32) f32_wide(D, wide);
+    else gemm_thin(D, thin);
+    plan->thin = thin[0] | thin[1] << 1;
     for (int i = 0; i < 4; ++i) plan->wide |= (int32_t)wide[i] << i;
     return HEXA_OK;
 }

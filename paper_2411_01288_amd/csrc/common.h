@@ -211,7 +211,7 @@ struct MoeWorkspace {
 
 // tile sizes of the launches fc1, fc2, bwd_fc2, bwd_fc1
 void gemm_tile_classes(const MoeDims& D, int (&tile)[4]);
-bool gemm_thin(const MoeDims& D);             // whether the forward pass takes 32x128 tiles instead
+void gemm_thin(const MoeDims& D, bool (&thin)[2]);  // whether fc1 and fc2 take 32x128 tiles instead
 void f32_tile_classes(const MoeDims& D, int (&tile)[4]);
 void f32_wide(const MoeDims& D, bool (&wide)[4]);   // which of them take 128x64 tiles
 int gemm_dgrad2_row_tile(const MoeDims& D);   // rows of a DGRAD2 tile of the 16-bit path

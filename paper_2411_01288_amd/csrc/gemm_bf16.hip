@@ -1371,21 +1371,33 @@ inline bool small_fc2(const MoeDims& D) { return small_rows(D, D.f, D.d); }
 inline bool small_bwd2(const MoeDims& D) { return small_pair(D, D.d, D.f); }
 inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 
-// Which forward passes take the thin tiles: with more rows, experts have several of them, which fetch the weights again.  Measured, us with the
-// profile's events, 128x128 tiles / thin, fc1 and fc2 + combine: 16 tokens, 768 x 3072 of 16, top-2 (2 rows per expert) 20.2 / 17.7, 24.9 /
-// 24.2; 64 tokens, 2048 x 8192 of 64 (2) 274 / 259, 259 / 259; 128 there (4) 337 / 321, 332 / 327; 128 tokens, 1024 x 4096 of 32 (8) 59.0 / 56.7, 61.9 /
-// 62.4; 512 of the second (16) 411 / 432, 389 / 399; 300 tokens, 1536 x 6144 of 24, top-1 (12.5) 101 / 97, 97 / 121; 16 tokens, 1536 x 6144 of 2 (8, one
-// tile each) 19.6 / 13.9, 45.7 / 18.0.  (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
-constexpr int kThinUpTo = 6;
-inline bool thin(const MoeDims& D) {
+// Which forward launches take the thin tiles: with more rows, experts have several of them, which fetch the weights again (all launches of 16 rows per
+// expert on average, 512 tokens, 2048 x 8192 of 64, top-2, us, 128x128 / thin: fc1 411 / 432, fc2 389 / 399; 300, 1536 x 6144 of 24 (12.5) 101 / 97, 97 / 121; 16
+// tokens, 1536 x 6144 of 2, one tile each 19.6 / 13.9, 45.7 / 18.0).  (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
+// An expert with more than 32 rows has several tiles, so skewed routing sets the lines: few rows per expert on average, and few in
+// all.  Measured on both sides under the benchmark's "bias" routing, Zipf (exponent 1.2), three quarters of the tokens on four experts, all tokens
+// on the first ones, us, 128x128 / thin:
+//   fc1: 32 tokens, 1024 x 4096 of 4 16 / 12, 16 / 13, 16 / 12, 15 / 12; 192, 1024 x 4096 of 32 56 / 53, 31 / 30, 48 / 41, 15 / 13; 64, 2048 x 8192 of 64,
+//     top-2 275 / 258, 111 / 103, 148 / 146, 32 / 25; 128 there 322 / 309, 132 / 126, 212 / 204, 33 / 37; 384, 512 x 2048 of 64 35 / 32, 13 / 15, 31 / 27, 12 / 10;
+//     192 there, top-2, at 2048 x 8192 357 / 346, 140 / 148, 253 / 258, 33 / 45; 1500, 512 x 1024 of 256 61 / 53, 14 / 17, 45 / 42, 13 / 16.
+//     (Where they are one round either way: 8, 2048 x 8192 of 8 44 / 45, 33 / 25, 41 / 44, 21 / 14.)
+//   fc2, whose shares are sized for all experts (lines: 64 rows, 96 tiles, or 128 where f is 3072 at most): 16, 768 x 3072 of 16, top-2 (96 tiles) 20 / 17, 14 / 12,
+//     17 / 15, 11 / 9; 64 there, top-1 21 / 20, 14 / 14, 19 / 17, 12 / 10; 24, 1536 x 6144 of 8, top-2 (96) 42 / 35, 41 / 34, 41 / 34, 18 / 17; 1, 2048 x 8192 of 64, top-2 (32)
+//     56 / 19; 32, 2048 x 2048 of 8 (128) 20 / 19, 17 / 16, 20 / 20, 12 / 10; 32, 1024 x 4096 of 16, top-2 (128) 28 / 29, 26 / 27, 27 / 28, 16 / 12; 8, 2048 x 8192 of 8 (128) 37 / 41,
+//     31 / 35, 34 / 38, 22 / 22; 24, 1024 x 4096 of 24, top-2 (192) 42 / 42, 24 / 35, 26 / 36, 15 / 15; 32, 2048 x 8192 of 64, top-2 (1024) 216 / 213, 79 / 85, 95 / 100, 54 / 67;
+//     64 there 253 / 251, 108 / 120, 152 / 153, 55 / 62; 128, 1024 x 4096 of 32 50 / 49, 26 / 38, 39 / 43, 14 / 15.
+constexpr int kThinUpTo = 6, kThinFc1Rows = 192, kThinFc2Rows = 64;
+inline bool thin_up_to(const MoeDims& D, int rows) {
     const double wider = D.d > D.f ? D.d : D.f, other = D.d > D.f ? D.f : D.d;
-    return (D.A <= kThinRows || D.A <= (long long)kThinUpTo * std::min(D.E, D.A)) && (wider * other + 64 * wider) * 2 < 4294967296.0;
+    return (D.A <= kThinRows || (D.A <= rows && D.A <= (long long)kThinUpTo * std::min(D.E, D.A))) && (wider * other + 64 * wider) * 2 < 4294967296.0;
 }
-// Shares of K for FC2 on thin tiles: what makes two workgroups per CU, at least three 64-k blocks each (the fourth case above in us at 1 / 2 / 4 / 8
-// shares: 61 / 62 / 65 / 70; the first 31 / 24 / 24 / 23.5, the last 36 / 25 / 20 / 18; 20 tokens, 320 x 448 of 30, 15.4 / 13.0 / 14.6 / 15.2).
+inline long long thin_fc2_tiles(const MoeDims& D) { return (long long)std::min(D.E, D.A) * ceil_div(D.d, kThinCols); }
+inline bool thin_fc1(const MoeDims& D) { return thin_up_to(D, kThinFc1Rows); }
+inline bool thin_fc2(const MoeDims& D) { return thin_up_to(D, kThinFc2Rows) && thin_fc2_tiles(D) <= (D.f <= 3072 ? 128 : 96); }
+// Shares of K for FC2 on thin tiles: what makes two workgroups per CU, at least three 64-k blocks each (fc2 + combine in us at 1 / 2 / 4 / 8 shares: 16
+// tokens, 768 x 3072 of 16, top-2 31 / 24 / 24 / 23.5; 16, 1536 x 6144 of 2 36 / 25 / 20 / 18; 20 tokens, 320 x 448 of 30, 15.4 / 13.0 / 14.6 / 15.2).
 inline int thin_fc2_shares(const MoeDims& D) {
-    const int tiles = std::min(D.E, D.A) * ceil_div(D.d, kThinCols);
-    return std::max(1, std::min({8, 2 * kNumCUs / tiles, D.f / BK / 3}));
+    return std::max(1, std::min({8, 2 * kNumCUs / (int)thin_fc2_tiles(D), D.f / BK / 3}));
 }
 
 // FC2 in shares of K: with few rows its tiles are few and long (K = d_ff), so a decode step leaves most CUs idle.
@@ -1396,7 +1408,7 @@ inline int thin_fc2_shares(const MoeDims& D) {
 // 64 tokens, 2048 x 8192 x 64: 287 / 251 / 257 / 263; 1024 tokens, 512 x 2048 x 8: 28 / 28 / 25 / 31; 2048 tokens,
 // 768 x 3072 x 16: 47 / 56 / 62 / 83 (one share is taken).
 int choose_fc2_shares(const MoeDims& D) {
-    if (thin(D)) return thin_fc2_shares(D);
+    if (thin_fc2(D)) return thin_fc2_shares(D);
     if (!small_fc2(D)) return 1;
     const int blocks = D.f / BK;
     int best = 1;
@@ -1446,7 +1458,10 @@ hipError_t gemm_bf16_device_init() {
     return e;
 }
 
-bool gemm_thin(const MoeDims& D) { return thin(D); }
+void gemm_thin(const MoeDims& D, bool (&thin)[2]) {
+    thin[0] = thin_fc1(D);
+    thin[1] = thin_fc2(D);
+}
 void gemm_tile_classes(const MoeDims& D, int (&tile)[4]) {
     const bool small[4] = {small_fc1(D), small_fc2(D), small_bwd2(D), small_bwd1(D)};
     for (int i = 0; i < 4; ++i) tile[i] = small[i] ? SMALL : BIG;
@@ -1492,7 +1507,7 @@ static void launch_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
 }
 
 template <bool F16>
-static void thin_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
+static void launch_thin_fc1(const MoeDims& D, const GemmArgs& g, hipStream_t st) {
     if (D.act == HEXA_ACT_RELU) launch_thin<OP_FC1, HEXA_ACT_RELU, F16>(D, g, st, "fc1");
     else if (D.act == HEXA_ACT_SILU) launch_thin<OP_FC1, HEXA_ACT_SILU, F16>(D, g, st, "fc1");
     else launch_thin<OP_FC1, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc1");
@@ -1513,15 +1528,15 @@ static hipError_t fwd_impl(const MoeDims& D, const bf16_t* x, const bf16_t* W1, 
                            ws.worklist, g.rt_cap, D.d, D.f);
     }
     g.A = x; g.a_rows = D.T; g.B = W1; g.bias = b1; g.out0 = ws.pre; g.out1 = ws.h; g.K = D.d; g.N = D.f;
-    if (thin(D)) thin_fc1<F16>(D, g, st);
+    if (thin_fc1(D)) launch_thin_fc1<F16>(D, g, st);
     else if (small_fc1(D)) launch_fc1<SMALL, F16>(D, g, st);
     else launch_fc1<BIG, F16>(D, g, st);
     g.A = (const bf16_t*)ws.h; g.B = W2; g.bias = b2; g.out0 = ws.o; g.out1 = nullptr; g.K = D.f; g.N = D.d;
     if (fc2_shares(D) > 1) {
         g.out0 = ws.fc2part; g.a_rows = D.A; g.share_blocks = fc2_share_blocks(D);
-        if (thin(D)) launch_thin<OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
+        if (thin_fc2(D)) launch_thin<OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
         else launch_rows<SMALL, SMALL, 2, 2, OP_FC2P, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2", fc2_shares(D));
-    } else if (thin(D)) launch_thin<OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
+    } else if (thin_fc2(D)) launch_thin<OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     else if (small_fc2(D)) launch_rows<SMALL, SMALL, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     else launch_rows<BIG, BIG, 2, 2, OP_FC2, HEXA_ACT_GELU_TANH, F16>(D, g, st, "fc2");
     return hipGetLastError();

@@ -16,24 +16,36 @@ def plan(w):
     return B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))
 
 
-@pytest.mark.parametrize("T,d,f,E,k,dtype,routing,split", [
-    (1, 64, 64, 1, 1, "bf16", "topk", False), (3, 128, 192, 5, 2, "f16", "topk", False), (16, 768, 3072, 16, 2, "bf16", "bias", True),
-    (40, 320, 448, 14, 2, "bf16", "zipf", True), (64, 576, 832, 48, 4, "bf16", "zipf", True), (200, 192, 704, 104, 3, "f16", "zipf", True),
-    (300, 64, 1088, 300, 2, "bf16", "zipf", False), (900, 1024, 320, 160, 1, "bf16", "topk", False),
+# thin: bits of fc1 and fc2
+@pytest.mark.parametrize("T,d,f,E,k,dtype,routing,thin,split", [
+    (1, 64, 64, 1, 1, "bf16", "topk", 3, False), (3, 128, 192, 5, 2, "f16", "topk", 3, False), (16, 768, 3072, 16, 2, "bf16", "bias", 3, True),
+    (30, 320, 448, 14, 2, "bf16", "zipf", 3, True), (16, 576, 832, 25, 4, "f16", "zipf", 3, True), (64, 192, 704, 90, 1, "f16", "zipf", 3, True),
+    (30, 64, 1088, 300, 2, "bf16", "zipf", 3, True), (63, 320, 704, 120, 3, "bf16", "zipf", 1, False), (190, 1024, 320, 260, 1, "f16", "topk", 1, False),
+    (96, 192, 2112, 32, 2, "bf16", "bias", 1, True), (64, 192, 448, 1024, 1, "bf16", "topk", 3, True),
 ])
-def test_thin(oracle, T, d, f, E, k, dtype, routing, split):
+def test_thin(oracle, T, d, f, E, k, dtype, routing, thin, split):
     w = MoEWorkload("thin", T, d, f, E, k, dtype, routing, 40 + T)
     p = plan(w)
-    assert p["thin"] and (p["fc2_shares"] > 1) == split
+    assert p["thin"] == thin and (p["fc2_shares"] > 1) == split
     full_parity(oracle, w, generate(w, DEV), label=f"thin T{T} d{d} f{f} E{E} k{k}")
 
 
 # From two rows on: a single dgate = <dY, o> is off by up to 2^-9 |dY| |o| (o is rounded), which has no bound relative to a sum that happens
 # to cancel (one row, d = 192: z |dY| |o| / sqrt(192) with z = 0.03); two and more are judged by the largest.
-@pytest.mark.parametrize("rows", [2, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65])
+@pytest.mark.parametrize("rows", [2, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 191, 192])
 def test_rows_of_one_expert(oracle, rows):
-    w = MoEWorkload("rows", rows, 192, 320, 12, 1, "bf16", "topk", rows)      # the other experts are empty
-    assert plan(w)["thin"]
+    w = MoEWorkload("rows", rows, 192, 320, 32, 1, "bf16", "topk", rows)      # the other experts are empty
+    assert plan(w)["thin"] == (3 if rows <= 64 else 1)
     data = generate(w, DEV)
     data["topk_idx"].fill_(4)
     full_parity(oracle, w, data, label=f"thin, {rows} rows")
+
+
+# at both sides of each line: 32 rows, 6 per expert, 192 and 64 rows in all, 128 tiles of fc2, 96 where f exceeds 3072
+@pytest.mark.parametrize("T,d,f,E,thin", [
+    (32, 192, 1024, 1, 3), (33, 192, 1024, 1, 0), (36, 192, 1024, 6, 3), (37, 192, 1024, 6, 0), (64, 192, 1024, 32, 3), (65, 192, 1024, 32, 1),
+    (192, 192, 1024, 32, 1), (193, 192, 1024, 33, 0), (32, 512, 3072, 33, 3), (33, 512, 3072, 33, 1), (32, 1024, 3072, 16, 3), (32, 1024, 3072, 17, 1),
+    (32, 1024, 3136, 12, 3), (32, 1024, 3136, 13, 1),
+])
+def test_rule(T, d, f, E, thin):
+    assert plan(MoEWorkload("rule", T, d, f, E, 1, "bf16", "topk", 1))["thin"] == thin
