@@ -44,11 +44,11 @@
  *     Same sizes, same bits: a row's result does not depend on its place in the
  *     batch, only on the sizes of the call and, in its last bits, on whether such
  *     a value stands in the same tile of rows or weights.
- *   - The first hexa_moe_workspace_bytes, hexa_moe_fwd or hexa_moe_bwd call for a
- *     16-bit shape on a device raises the shared-memory limit of the contraction
- *     kernels there (once per device, thread-safe).  That set-up call must not
- *     fall inside a stream capture; sizing the workspace on the device before
- *     capturing takes care of it.
+ *   - The first hexa_moe_workspace_bytes, hexa_moe_fwd or hexa_moe_bwd call on a
+ *     device for a 16-bit shape, or for an HEXA_F32 shape with d or f of 576 and
+ *     more, raises the shared-memory limit of the contraction kernels there (once
+ *     per device, thread-safe).  That set-up call must not fall inside a stream
+ *     capture; sizing the workspace on the device before capturing takes care of it.
  *   - Expert ids must satisfy 0 <= topk_idx < E (App. B Table 4).  An id outside
  *     that range is not an error return (the host cannot see it): that
  *     assignment is dropped from the index (inv = -1, offsets[E] < A), it
@@ -109,9 +109,9 @@ HEXA_API size_t hexa_moe_index_scratch_bytes(const hexa_moe_shape *shape);
 
 /* Bytes of device workspace shared by hexa_moe_fwd and hexa_moe_bwd (0 on an
  * invalid shape).  It holds what the forward pass saves for the backward pass
- * (pre-activations or the activation's derivative at them, activations,
- * per-assignment expert outputs, in perm order, and the tile lists derived from
- * the index) plus backward staging.  256-byte alignment of the base is required. */
+ * (the activation's derivative at the pre-activations, activations, per-assignment
+ * expert outputs, in perm order, and the tile lists derived from the index) plus
+ * backward staging.  256-byte alignment of the base is required. */
 HEXA_API size_t hexa_moe_workspace_bytes(const hexa_moe_shape *shape);
 
 /* Text for a status code; any other integer gives "unknown status" (hence int, not the enum). */

@@ -1,7 +1,7 @@
 """The whole step (index, forward, backward) recorded into a HIP graph and replayed: the library
 allocates nothing, synchronises nothing and issues no memset nodes, so a capture of its launches
 must reproduce the eager results bit for bit on every replay (launch-latency regime, workload C2;
-and a shape whose contractions read work lists)."""
+a shape whose contractions read work lists; an fp32 one whose launches ask for dynamic shared memory)."""
 import pytest
 import torch
 
@@ -12,12 +12,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("name", ["C1", "C2", "lists"])
+@pytest.mark.parametrize("name", ["C1", "C2", "lists", "wide"])
 def test_graph_replays_equal_eager(name):
     from paper_2411_01288_amd import binding as B
     if name == "lists":                      # 256x256 contractions, which read work lists
         w = MoEWorkload("lists", 80000, 256, 256, 64, 2, "bf16", "zipf", 3)
         assert_tiles(w, [256, 256, 256, 256])
+    elif name == "wide":                     # fp32 on 128x64 tiles: fc2 and both backward launches
+        w = MoEWorkload("wide", 3300, 1024, 1024, 3, 1, "f32", "topk", 3)
+        assert B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))["wide"] == 14
     else:
         w = workload(name)
     data = generate(w, DEV)
