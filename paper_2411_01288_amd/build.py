@@ -26,8 +26,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 # (a reloaded resource word or offset read too early fetched the previous tile's rows).  (About 1 KB of scratch per
 # lane in one instantiation means its K loop was left rolled: LLVM ignores "#pragma unroll" past a
 # size threshold, -mllvm -pragma-unroll-threshold=N, and the accumulator and fragment arrays are
-# then indexed dynamically and live in scratch.)
-NO_SCRATCH = {"gemm_bf16.hip"}
+# then indexed dynamically and live in scratch.)  The fp32 path's 128x64 tiles keep sums in inline assembly's
+# registers (see lint_asm_mfma), with few to spare: a spill would stand between those instructions.
+NO_SCRATCH = {"gemm_bf16.hip": "gemm_bf16", "f32_path.hip": "f32_gemm"}   # source: its kernels' common name
 
 
 def _compile(src: str) -> str:
@@ -45,7 +46,7 @@ def _compile(src: str) -> str:
         if m:
             name = m.group(1)
         m = re.search(r"(ScratchSize \[bytes/lane\]|SGPRs Spill|VGPRs Spill): (\d+)", line)
-        if m and int(m.group(2)) > 0 and name and "gemm_bf16" in name:
+        if m and int(m.group(2)) > 0 and name and NO_SCRATCH[src] in name:
             bad.append((name, m.group(1), int(m.group(2))))
     if bad:
         raise RuntimeError(f"{src}: kernels spill registers: {bad}")
@@ -118,13 +119,75 @@ def lint_asm_hazards(text: str) -> list:
     return bad
 
 
-def lint_staging_hazards(src: str = "gemm_bf16.hip") -> None:
-    """Refuses the build if the generated ISA of `src` holds a hazard (see lint_asm_hazards)."""
+# v_mfma_f32_16x16x32_bf16 (8 passes) on gfx950: wait states from it to any other instruction that reads or writes its result, to a matrix
+# instruction that adds to exactly it, and from a vector instruction that writes one of its operands to it.
+MFMA_RESULT, MFMA_CHAIN, MFMA_OPERAND = 12, 2, 2
+
+
+def lint_asm_mfma(text: str) -> list:
+    """Wait states around matrix instructions written as inline assembly (between the compiler's ASMSTART and ASMEND), which its hazard
+    recogniser takes for any instruction: (line, matrix instruction, the other one, registers) of every violation, along all paths."""
+    ops, labels, asm = [], {}, False
+    for ln, line in enumerate(text.splitlines(), 1):
+        t = line.strip()
+        if t.startswith(";;#ASM"):
+            asm = t.startswith(";;#ASMSTART")
+            continue
+        t = t.split(";")[0].split("//")[0].strip()
+        if t.endswith(":"):
+            labels[t[:-1]] = len(ops)
+        elif t and t[0] not in ".#":
+            ops.append((ln, t, asm))
+    names = [t.split()[0] for _, t, _ in ops]
+    after = [[] if n in ("s_branch", "s_endpgm", "s_setpc_b64") else [i + 1] for i, n in enumerate(names)]
+    before = [[] for _ in range(len(ops) + 1)]
+    for i, n in enumerate(names):
+        if n.startswith(("s_cbranch", "s_branch")):
+            after[i].append(labels[ops[i][1].split()[1]])
+        for j in after[i]:
+            before[j].append(i)
+    states = [int(t.split()[1], 0) + 1 if n == "s_nop" else 1 for n, (_, t, _) in zip(names, ops)]
+    regs = [[_vgprs(o) for o in t.split(None, 1)[1].split(",")] if n.startswith(("v_", "ds_", "buffer_", "global_", "flat_", "scratch_")) else []
+            for n, (_, t, _) in zip(names, ops)]
+    bad = []
+
+    def walk(first, edges, most, visit):
+        seen, todo = {}, [(j, 0) for j in first]
+        while todo:
+            j, gone = todo.pop()
+            if gone >= most or j >= len(ops) or seen.get(j, most) <= gone:
+                continue
+            seen[j] = gone
+            visit(j, gone)
+            todo += [(n, gone + states[j]) for n in edges[j]]
+
+    for i, (ln, t, asm) in enumerate(ops):
+        if not (asm and names[i].startswith("v_mfma")):
+            continue
+        result, operands = regs[i][0], set().union(*regs[i][1:])
+
+        def reader(j, gone):
+            used = set().union(*regs[j])
+            chain = names[j].startswith("v_mfma") and regs[j][3] == result and not result & (regs[j][1] | regs[j][2])
+            if gone < (MFMA_CHAIN if chain else MFMA_RESULT) and used & result:
+                bad.append((ln, t, ops[j][1], sorted(used & result)))
+
+        def writer(j, gone):
+            if names[j].startswith("v_") and not names[j].startswith("v_mfma") and regs[j][0] & operands:
+                bad.append((ln, t, ops[j][1], sorted(regs[j][0] & operands)))
+
+        walk(after[i], after, MFMA_RESULT, reader)
+        walk(before[i], before, MFMA_OPERAND, writer)
+    return bad
+
+
+def lint_staging_hazards(src: str) -> None:
+    """Refuses the build if the generated ISA of `src` holds a hazard (see lint_asm_hazards, lint_asm_mfma)."""
     res = subprocess.run(["hipcc", *FLAGS, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", "-"],
                          stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc -S failed on {src}")
-    bad = lint_asm_hazards(res.stdout)
+    bad = lint_asm_hazards(res.stdout) + lint_asm_mfma(res.stdout)
     if bad:
         raise RuntimeError(f"{src}: wait-state hazards: {bad[:5]}")
 
@@ -149,10 +212,11 @@ def build_marshal() -> str:
 def build_library(jobs: int = 8) -> str:
     """Compile every translation unit and link the shared library and the binding's marshalling.  Always rebuilds."""
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        lint = ex.submit(lint_staging_hazards)
+        lints = [ex.submit(lint_staging_hazards, src) for src in NO_SCRATCH]
         marshal = ex.submit(build_marshal)
         objs = list(ex.map(_compile, SOURCES))
-        lint.result()
+        for lint in lints:
+            lint.result()
         marshal.result()
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     return LIB
