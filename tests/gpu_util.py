@@ -12,11 +12,13 @@ def poisoned(shape, dtype, device):
     return torch.full(shape, float("nan"), dtype=dtype, device=device)
 
 
-def assert_tiles(w, tiles):
-    """The launch rule gives fc1, fc2, bwd_fc2 and bwd_fc1 of this workload tiles of these sizes."""
+def assert_tiles(w, tiles, wide=0, thin=0):
+    """The launch rule gives fc1, fc2, bwd_fc2 and bwd_fc1 of this workload tiles of these sizes, but for those with a bit set (in that
+    order) in `wide` (fp32: 128x64) or `thin` (16 bits: 32x128)."""
     from paper_2411_01288_amd import binding as B
     p = B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))
     assert [p[n] for n in ("fc1_tile", "fc2_tile", "bwd_fc2_tile", "bwd_fc1_tile")] == tiles
+    assert (p["wide"], p["thin"]) == (wide, thin)
 
 
 def run_hip_layer(w, data, want_dgate=True, activation=0):

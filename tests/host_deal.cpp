@@ -49,7 +49,9 @@ int main(int argc, char** argv) {
     if (!std::strcmp(argv[1], "rows")) {
         if (argc != 7) return 2;
         if (arg(2) == 256) rows<256>(arg(3), arg(4), arg(5), arg(6) != 0);
-        else rows<128>(arg(3), arg(4), arg(5), arg(6) != 0);
+        else if (arg(2) == 128) rows<128>(arg(3), arg(4), arg(5), arg(6) != 0);
+        else if (arg(2) != 32) return 2;
+        else rows<32>(arg(3), arg(4), arg(5), arg(6) != 0);
         return 0;
     }
     if (!std::strcmp(argv[1], "quarters")) {

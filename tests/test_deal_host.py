@@ -22,8 +22,8 @@ def run(exe, *args):
     return [[int(v) for v in l.split()] for l in lines[:8]], int(lines[8])
 
 
-# one tile; a few; groups of 4 or 8 row tiles just full and one over; 128 groups of 4 (the line of the whole deal) and around
-@pytest.mark.parametrize("BM,streamed", [(128, 0), (128, 1), (256, 0)])
+# one tile; a few; groups of 4, 8 or 32 row tiles just full and one over; 128 groups of 4 (the line of the whole deal) and around
+@pytest.mark.parametrize("BM,streamed", [(32, 0), (32, 1), (128, 0), (128, 1), (256, 0)])
 @pytest.mark.parametrize("tm", [1, 3, 4, 7, 8, 9, 31, 32, 33, 65, 263, 508, 509, 511, 512, 513, 1057])
 @pytest.mark.parametrize("tn", [1, 3, 12])
 def test_row_tiles(program, BM, streamed, tm, tn):
@@ -32,7 +32,7 @@ def test_row_tiles(program, BM, streamed, tm, tn):
     counts = [len(t) for t in tiles]
     assert max(counts) <= most
     group = 1024 // BM
-    if BM == 128 or -(-tm // group) < 128:
+    if BM != 256 or -(-tm // group) < 128:
         assert max(counts) - min(counts) <= 1
     else:
         assert max(counts) - min(counts) <= group * tn

@@ -1,4 +1,4 @@
-"""The 64x64 tiles of the fp32 path, whose operands are split into three bf16 planes: sums of values of very different sizes,
+"""The 64x64 and 128x64 tiles of the fp32 path, whose operands are split into three bf16 planes: sums of values of very different sizes,
 values at the ends of the fp32 range, and infinities and NaN, whose tiles are multiplied on the fp32 instruction instead."""
 import numpy as np
 import pytest
@@ -12,27 +12,37 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def workload():
-    w = MoEWorkload("planes", 6001, 229, 517, 3, 1, "f32", "topk", 77)     # rows at any dword alignment, ragged ends
-    assert_tiles(w, [64, 32, 64, 32])
+# T, d, f of one expert and the launches on 128x64 tiles: none; fc2 and bwd_fc1; all but fc1
+CLASSES = pytest.mark.parametrize("T,d,f,wide", [(5000, 560, 570, 0), (5000, 640, 704, 10), (3300, 1030, 1055, 14)])
+# of three experts: fc1 and bwd_fc2 on 64x64 tiles, the others on 32x32; all but fc1 on 128x64
+WORKLOADS = pytest.mark.parametrize("sizes", [(6001, 229, 517, [64, 32, 64, 32], 0), (3300, 1030, 1055, [64, 64, 64, 64], 14)])
+
+
+def workload(sizes):
+    T, d, f, tiles, wide = sizes
+    w = MoEWorkload("planes", T, d, f, 3, 1, "f32", "topk", 77)            # rows at any dword alignment, ragged ends
+    assert_tiles(w, tiles, wide)
     return w, generate(w, DEV)
 
 
-def test_wide():
-    """All four launches on 64x64 tiles against fp64 torch, one expert: errors of a few roundings per sum."""
-    w = MoEWorkload("wide", 5000, 640, 704, 1, 1, "f32", "topk", 5)
-    assert_tiles(w, [64, 64, 64, 64])
+@CLASSES
+def test_many_decades(T, d, f, wide):
+    """All launches against fp64 torch, one expert: errors of a few roundings per sum."""
+    w = MoEWorkload("decades", T, d, f, 1, 1, "f32", "topk", 5)
+    assert_tiles(w, [64, 64, 64, 64], wide)
     data = generate(w, DEV)
     scale = torch.logspace(-6, 6, w.d_model, device=DEV)                   # features over twelve decades
     data["x"] *= scale
     data["W1"] /= scale[None, :, None]
-    _, y, g = run_hip_layer(w, data, activation=B.ACT_RELU)
+    # (smooth: of some three million pre-activations one or two lie within a rounding, 2^-24, of zero, where ReLU' takes the other side)
+    _, y, g = run_hip_layer(w, data, activation=B.ACT_SILU)
     d = {k: v.double() for k, v in data.items() if k != "topk_idx"}
     pre = d["x"] @ d["W1"][0] + d["b1"][0]
-    h = torch.relu(pre)
+    s = torch.sigmoid(pre)
+    h = pre * s
     o = h @ d["W2"][0] + d["b2"][0]
     do = d["gate"] * d["dY"]
-    dpre = (do @ d["W2"][0].t()) * (pre > 0)
+    dpre = (do @ d["W2"][0].t()) * s * (1 + pre * (1 - s))
     ref = {"y": d["gate"] * o, "dx": dpre @ d["W1"][0].t(), "dW1": (d["x"].t() @ dpre)[None], "dW2": (h.t() @ do)[None],
            "db1": dpre.sum(0)[None], "db2": do.sum(0)[None]}
     got = {"y": y, **g}
@@ -48,8 +58,9 @@ def test_wide():
 
 # the largest finite values; values whose last bit is still a multiple of 2^-133, the smallest number of the third plane
 @pytest.mark.parametrize("big,weight", [(3.4e38, 1e-32), (2e-33, 1e33)])
-def test_ends_of_the_range(oracle, big, weight):
-    w, data = workload()
+@WORKLOADS
+def test_ends_of_the_range(oracle, sizes, big, weight):
+    w, data = workload(sizes)
     data["x"][:, 7] = 0.0
     data["x"][100] = 0.0
     data["x"][100, 7] = big
@@ -70,9 +81,10 @@ def rounding(got, ref, mag):
 
 # bits below 2^-133 have no place in the planes
 @pytest.mark.parametrize("scale", [1e-34, 1e-36, 1e-38])
-def test_tiny_operands(scale):
-    w = MoEWorkload("tiny", 5000, 640, 704, 1, 1, "f32", "topk", 6)
-    assert_tiles(w, [64, 64, 64, 64])
+@CLASSES
+def test_tiny_operands(scale, T, d, f, wide):
+    w = MoEWorkload("tiny", T, d, f, 1, 1, "f32", "topk", 6)
+    assert_tiles(w, [64, 64, 64, 64], wide)
     data = generate(w, DEV)
     data["W1"].zero_()
     data["b1"] = data["b1"].abs() + 100.0                                  # h = b1, exactly
@@ -94,9 +106,9 @@ def randn(gen, *shape):
     return torch.randn(shape, generator=gen, device=DEV)
 
 
-def make(T, d, f, E, seed, tiles):
+def make(T, d, f, E, seed, tiles, wide=0):
     w = MoEWorkload("made", T, d, f, E, 1, "f32", "topk", seed)
-    assert_tiles(w, tiles)
+    assert_tiles(w, tiles, wide)
     data = generate(w, DEV)
     data["gate"].fill_(1.0)
     gen = torch.Generator(device=DEV).manual_seed(seed)
@@ -106,20 +118,22 @@ def make(T, d, f, E, seed, tiles):
 # A sum of K products is off by at most K roundings of 2^-24 of the products' sizes.  A rounding is at most 2^-24 / sqrt(3) in the root mean
 # square, and all K together make no more: the partial sums that are rounded grow like a square root, the sizes add up.
 # 32 is the longest contraction that is not split, 64 and 65 are two steps and the first row of a third.
-@pytest.mark.parametrize("rows", [1, 2, 3, 4, 8, 31, 32, 33, 64, 65])
-def test_short_token_contractions(rows):
-    w, data, _ = make(64 * rows, 704, 704, 64, rows, [64, 64, 64, 64])
-    data["topk_idx"] = (torch.arange(w.T, device=DEV, dtype=torch.int32) % 64).view(w.T, 1).contiguous()
+# (On 128x64 tiles, which take many rows per expert: three experts of `rows` rows, the others' on a fourth.)
+@pytest.mark.parametrize("rows,T,size,E,wide", [(r, 64 * r, 704, 64, 0) for r in (1, 2, 3, 4, 8, 31, 32, 33, 64, 65)] + [(r, 4300, 1024, 4, 14) for r in (1, 32, 33, 64, 65)])
+def test_short_token_contractions(rows, T, size, E, wide):
+    w, data, _ = make(T, size, size, E, rows, [64, 64, 64, 64], wide)
+    n = min(T, rows * (E if wide == 0 else E - 1)) // rows                  # experts of `rows` rows
+    data["topk_idx"] = torch.where(torch.arange(T, device=DEV) < n * rows, torch.arange(T, device=DEV) % n, E - 1).to(torch.int32).view(T, 1).contiguous()
     data["W1"].zero_()
     data["b1"] = data["b1"].abs() + 0.5                                     # h = b1, exactly
-    data["W2"].copy_(torch.eye(704, device=DEV))                            # dpre = dY, exactly
+    data["W2"].copy_(torch.eye(size, device=DEV))                           # dpre = dY, exactly
     _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
-    x, dY = (data[n].double().view(rows, 64, 704) for n in ("x", "dY"))
-    h = data["b1"].double()[:, :, None]
+    x, dY = (data[n_][:n * rows].double().view(rows, n, size) for n_ in ("x", "dY"))
+    h = data["b1"][:n].double()[:, :, None]
     for name, ref, mag in (("dW1", torch.matmul(x.permute(1, 2, 0).contiguous(), dY.permute(1, 0, 2).contiguous()),
                             torch.matmul(x.abs().permute(1, 2, 0).contiguous(), dY.abs().permute(1, 0, 2).contiguous())),
                            ("dW2", h * dY.sum(0)[:, None, :], h * dY.abs().sum(0)[:, None, :])):
-        top, rms = rounding(g[name], ref, mag)
+        top, rms = rounding(g[name][:n], ref, mag)
         assert top <= rows * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, (name, top, rms)
 
 
@@ -173,21 +187,46 @@ def test_sparse_rows(count, value):
         assert abs(float((y[on].double() - ref[on]).sum() / mag[on].sum())) <= 0.05 * 2.0 ** -24
 
 
-def test_results_do_not_depend_on_the_place_in_the_batch():
-    w, data, _ = make(5000, 608, 704, 1, 9, [64, 64, 64, 64])               # 19 and 22 steps
+# the same on 128x64 tiles, in fc2, whose other operand fc1 passes on as it is
+@pytest.mark.parametrize("count,value", [(1, None), (1, 1 + 2.0 ** -7 - 2.0 ** -23), (2, None), (4, None), (16, None)])
+def test_sparse_rows_on_wide_tiles(count, value):
+    w, data, gen = make(5000, 640, 640, 1, 50 + count, [64, 64, 64, 64], 10)
+    x = torch.zeros(w.T, 640, device=DEV)
+    for _ in range(count):
+        at = torch.randint(0, 640, (w.T,), generator=gen, device=DEV)
+        x[torch.arange(w.T, device=DEV), at] = randn(gen, w.T).abs() if value is None else torch.full((w.T,), value, device=DEV)
+    data["x"] = x
+    data["W1"].copy_(torch.eye(640, device=DEV))
+    data["W2"] = randn(gen, 1, 640, 640)
+    if value is not None:
+        data["W2"].copy_(torch.where(data["W2"] > 0, value, -0.5 * value))
+    data["b1"].zero_(), data["b2"].zero_()
+    _, y, _ = run_hip_layer(w, data, activation=B.ACT_RELU)
+    W2 = data["W2"][0].double()
+    ref, mag = x.double() @ W2, x.double() @ W2.abs()
+    top, rms = rounding(y, ref, mag)
+    assert top <= 2 * count * 2.0 ** -24 and rms <= 0.58 * 2.0 ** -24, (top, rms)
+    if value is None:
+        assert abs(float((y.double() - ref).sum() / mag.sum())) <= 0.05 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("T,d,f,wide", [(5000, 560, 570, 0), (5000, 608, 704, 10), (3300, 1030, 1055, 14)])   # 18, 19, 22 and 33 steps
+def test_results_do_not_depend_on_the_place_in_the_batch(T, d, f, wide):
+    w, data, _ = make(T, d, f, 1, 9, [64, 64, 64, 64], wide)
     data["x"], data["dY"] = (data[n][:1].expand(w.T, -1).contiguous() for n in ("x", "dY"))
     _, y, g = run_hip_layer(w, data)
     assert torch.equal(y, y[:1].expand_as(y)) and torch.equal(g["dx"], g["dx"][:1].expand_as(g["dx"]))
 
 
-def test_column_sums_over_many_rows():
+@pytest.mark.parametrize("d,wide", [(512, 0), (1024, 4)])
+def test_column_sums_over_many_rows(d, wide):
     """db1 as a sum over 300000 results: what is cut off to one side in each of them adds up in it."""
-    w, data, _ = make(300000, 512, 256, 1, 10, [64, 64, 64, 64])
+    w, data, _ = make(300000, d, 256, 1, 10, [64, 64, 64, 64], wide)
     data["W1"].zero_(), data["b1"].fill_(1.0)                               # dpre = dY W2^T
     _, _, g = run_hip_layer(w, data, activation=B.ACT_RELU)
     ref = sum(c.double().sum(0) for c in data["dY"].split(50000)) @ data["W2"][0].double().t()
     err = g["db1"][0].double() - ref
-    # A result is off by about 2^-23 of its size at random (errors of fp32 sums of 512 products); so is their sum, and adding up 300000 is
+    # A result is off by about 2^-23 of its size at random (errors of fp32 sums of 512 or 1024 products); so is their sum, and adding up 300000 is
     # good for three times that.  The mean over 256 columns is a sixteenth of one column's, four times which is allowed.
     rms = float(ref.square().mean().sqrt())
     assert float(err.square().mean().sqrt()) <= 5 * 2.0 ** -23 * rms
@@ -195,8 +234,9 @@ def test_column_sums_over_many_rows():
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
-def test_not_finite(value):
-    w, data = workload()
+@WORKLOADS
+def test_not_finite(value, sizes):
+    w, data = workload(sizes)
     _, y0, g0 = run_hip_layer(w, data, activation=B.ACT_RELU)
     x = data["x"].clone()
     x[1234, 56] = value
@@ -215,12 +255,13 @@ def test_not_finite(value):
     assert torch.equal(g["dW1"][others], g0["dW1"][others]) and torch.isfinite(g["dx"][rest]).all()
 
 
-@pytest.mark.parametrize("name,at,value", [("x", (1234, 56), float("inf")), ("x", (4999, 639), float("nan")), ("dY", (1234, 5), float("-inf")),
-                                           ("dY", (64, 639), float("nan")), ("W1", (0, 56, 17), float("inf")), ("W2", (0, 703, 5), float("-inf"))])
-def test_not_finite_in_every_contraction(name, at, value):
-    """All four launches on 64x64 tiles: what is infinite, of which sign, and what is NaN in every output, and the rest as accurate
+@pytest.mark.parametrize("name,at,value", [("x", (1234, 56), float("inf")), ("x", (-1, -1), float("nan")), ("dY", (1234, 5), float("-inf")),
+                                           ("dY", (64, -1), float("nan")), ("W1", (0, 56, 17), float("inf")), ("W2", (0, -1, 5), float("-inf"))])
+@CLASSES
+def test_not_finite_in_every_contraction(name, at, value, T, d, f, wide):
+    """All launches: what is infinite, of which sign, and what is NaN in every output, and the rest as accurate
     as ever.  Columns of one sign in W2 keep infinities of y from meeting their opposites."""
-    w, data, _ = make(5000, 640, 704, 1, 12, [64, 64, 64, 64])
+    w, data, _ = make(T, d, f, 1, 12, [64, 64, 64, 64], wide)
     data["W2"][0, :, 0].abs_(), data["W2"][0, :, 1].abs_().neg_()
     # pre-activations are odd multiples of 2^-12, so that no rounding decides which hidden units are on
     data["x"] = torch.round(data["x"] * 8) / 8
@@ -254,8 +295,7 @@ def test_values_of_a_neighbour(T, d, f, wide, value):
     """A value that no plane holds changes no bit of what other experts' tokens or other columns of weights give, also where it lies
     behind the end of one of their rows in memory."""
     w = MoEWorkload("neighbour", T, d, f, 3, 1, "f32", "topk", 13)
-    assert_tiles(w, [64, 64, 64, 64])
-    assert B.launch_plan(B.make_shape(T, d, f, 3, 1, "f32"))["wide"] == wide
+    assert_tiles(w, [64, 64, 64, 64], wide)
     data = generate(w, DEV)
     ids = torch.arange(T, device=DEV) % 3
     data["topk_idx"] = ids.to(torch.int32).view(T, 1).contiguous()

@@ -30,5 +30,5 @@ def test_edges_of_a_tile(oracle, T, d, f):
 ])
 def test_mixed_tile_classes(oracle, T, d, f, E, k, routing, tiles):
     w = MoEWorkload("mixed", T, d, f, E, k, "f32", routing, 33 + T)
-    assert_tiles(w, tiles)
+    assert_tiles(w, tiles)                                # (none of them on 128x64)
     full_parity(oracle, w, generate(w, DEV), label=f"f32 T{T} d{d} f{f} E{E} k{k}")

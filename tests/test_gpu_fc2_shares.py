@@ -14,21 +14,26 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("T,d,f,E,k,dtype", [
-    (1, 64, 4096, 1, 1, "bf16"), (5, 64, 2112, 4, 2, "f16"), (16, 192, 1088, 16, 2, "bf16"), (130, 320, 1024, 3, 1, "bf16"),
-    (33, 128, 704, 70, 8, "f16"), (300, 64, 2048, 2, 2, "bf16"),
+# thin: bits of fc1 and fc2 on 32x128 tiles.  (With few rows fc2 keeps 128x128 tiles where it has many columns.)
+@pytest.mark.parametrize("T,d,f,E,k,dtype,thin", [
+    (1, 64, 4096, 1, 1, "bf16", 3), (5, 64, 2112, 4, 2, "f16", 3), (16, 192, 1088, 16, 2, "bf16", 3), (130, 320, 1024, 3, 1, "bf16", 0),
+    (33, 128, 704, 70, 8, "f16", 0), (300, 64, 2048, 2, 2, "bf16", 0), (5, 1728, 1088, 10, 2, "f16", 1), (16, 1152, 1088, 16, 2, "bf16", 1),
+    (1, 8512, 4160, 2, 2, "bf16", 1), (70, 64, 2112, 4, 2, "f16", 0),
 ])
-def test_split_fc2(oracle, T, d, f, E, k, dtype):
+def test_split_fc2(oracle, T, d, f, E, k, dtype, thin):
     w = MoEWorkload("shares", T, d, f, E, k, dtype, "topk", 210 + T)
-    assert B.launch_plan(B.make_shape(T, d, f, E, k, dtype))["fc2_shares"] > 1
+    plan = B.launch_plan(B.make_shape(T, d, f, E, k, dtype))
+    assert plan["fc2_shares"] > 1 and plan["thin"] == thin
     full_parity(oracle, w, generate(w, DEV), label=f"{dtype} T{T} d{d} f{f} E{E} k{k}")
 
 
-def test_split_fc2_drops_out_of_range_ids(oracle):
-    w = MoEWorkload("shares", 20, 128, 2048, 6, 2, "bf16", "topk", 4)
+@pytest.mark.parametrize("E,thin", [(6, 0), (16, 3)])
+def test_split_fc2_drops_out_of_range_ids(oracle, E, thin):
+    w = MoEWorkload("shares", 20, 128, 2048, E, 2, "bf16", "topk", 4)
     data = generate(w, DEV)
-    data["topk_idx"][:, 1] = torch.tensor([6, -1] * 10, device=DEV, dtype=torch.int32)
-    assert B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))["fc2_shares"] > 1
+    data["topk_idx"][:, 1] = torch.tensor([E, -1] * 10, device=DEV, dtype=torch.int32)
+    plan = B.launch_plan(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.dtype))
+    assert plan["fc2_shares"] > 1 and plan["thin"] == thin
     _, y, g = run_hip_layer(w, data)     # the backward reads the expert outputs that this path stores
     c = host_inputs(data)
     kept = lambda a: np.ascontiguousarray(a[:, :1])

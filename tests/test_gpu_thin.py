@@ -1,11 +1,13 @@
 """The 32x128 tiles of forward passes with few rows per expert, against the oracle, every element: segments around the 16 and 32
 rows of a tile, contractions of two to many 32-k steps (fewer than wavefronts, no multiple of what is on its way), column tails, FC2 in
-one share and in several, empty experts, one, four and sixteen experts per lane in the look-up."""
+one share and in several, empty experts, one, four and sixteen experts per lane in the look-up; all activations; no valid id; the
+rule that takes them."""
 import pytest
 import torch
 
 from paper_2411_01288_amd import binding as B
 from paper_2411_01288_amd.workloads import MoEWorkload, generate
+from gpu_util import run_hip_layer
 from test_gpu_parity import full_parity
 
 pytestmark = pytest.mark.gpu
@@ -39,6 +41,30 @@ def test_rows_of_one_expert(oracle, rows):
     data = generate(w, DEV)
     data["topk_idx"].fill_(4)
     full_parity(oracle, w, data, label=f"thin, {rows} rows")
+
+
+@pytest.mark.parametrize("kind", [B.ACT_RELU, B.ACT_SILU])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_activations(oracle, kind, dtype):
+    w = MoEWorkload("act", 40, 192, 704, 20, 1, dtype, "topk", 70 + kind)
+    assert plan(w)["thin"] == 3
+    oracle.set_activation(kind)
+    try:
+        full_parity(oracle, w, generate(w, DEV), label=f"thin {dtype} {kind}", activation=kind)
+    finally:
+        oracle.set_activation(0)
+
+
+@pytest.mark.parametrize("f", [192, 1088])                                    # fc2 in one share, in several
+def test_all_ids_out_of_range(f):
+    w = MoEWorkload("none", 20, 128, f, 16, 2, "bf16", "topk", 5)
+    assert plan(w)["thin"] == 3 and (plan(w)["fc2_shares"] > 1) == (f > 192)
+    data = generate(w, DEV)
+    data["topk_idx"].copy_(torch.tensor([16, -1], device=DEV, dtype=torch.int32).expand(20, 2))
+    idx, y, g = run_hip_layer(w, data)
+    assert int(idx["offsets"][-1]) == 0
+    for name, t in {"y": y, **g}.items():
+        assert not t.any(), name
 
 
 # at both sides of each line: 32 rows, 6 per expert, 192 and 64 rows in all, 128 tiles of fc2, 96 where f exceeds 3072
