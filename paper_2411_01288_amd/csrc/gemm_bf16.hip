@@ -1371,33 +1371,35 @@ inline bool small_fc2(const MoeDims& D) { return small_rows(D, D.f, D.d); }
 inline bool small_bwd2(const MoeDims& D) { return small_pair(D, D.d, D.f); }
 inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 
-// Which forward launches take the thin tiles: with more rows, experts have several of them, which fetch the weights again (all launches of 16 rows per
-// expert on average, 512 tokens, 2048 x 8192 of 64, top-2, us, 128x128 / thin: fc1 411 / 432, fc2 389 / 399; 300, 1536 x 6144 of 24 (12.5) 101 / 97, 97 / 121; 16
-// tokens, 1536 x 6144 of 2, one tile each 19.6 / 13.9, 45.7 / 18.0).  (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
-// An expert with more than 32 rows has several tiles, so skewed routing sets the lines: few rows per expert on average, and few in
-// all.  Measured on both sides under the benchmark's "bias" routing, Zipf (exponent 1.2), three quarters of the tokens on four experts, all tokens
+// Which forward launches take the thin tiles: with more rows, experts have several of them, which fetch the weights again (16 rows per expert, 512
+// tokens, 2048 x 8192 of 64, top-2, us, 128x128 / thin: fc1 411 / 432, fc2 389 / 399; 300, 1536 x 6144 of 24 (12.5) 101 / 97, 97 / 121; 16 tokens, 1536 x 6144 of 2, one tile
+// each 19.6 / 13.9, 45.7 / 18.0).  Under skewed routing some experts have more than 32 rows at fewer on average, which sets the other line, rows in all.
+// Measured on both sides under the benchmark's "bias" routing, Zipf (exponent 1.2), three quarters of the tokens on four experts, all tokens
 // on the first ones, us, 128x128 / thin:
 //   fc1: 32 tokens, 1024 x 4096 of 4 16 / 12, 16 / 13, 16 / 12, 15 / 12; 192, 1024 x 4096 of 32 56 / 53, 31 / 30, 48 / 41, 15 / 13; 64, 2048 x 8192 of 64,
 //     top-2 275 / 258, 111 / 103, 148 / 146, 32 / 25; 128 there 322 / 309, 132 / 126, 212 / 204, 33 / 37; 384, 512 x 2048 of 64 35 / 32, 13 / 15, 31 / 27, 12 / 10;
-//     192 there, top-2, at 2048 x 8192 357 / 346, 140 / 148, 253 / 258, 33 / 45; 1500, 512 x 1024 of 256 61 / 53, 14 / 17, 45 / 42, 13 / 16.
-//     (Where they are one round either way: 8, 2048 x 8192 of 8 44 / 45, 33 / 25, 41 / 44, 21 / 14.)
-//   fc2, whose shares are sized for all experts (lines: 64 rows, 96 tiles, or 128 where f is 3072 at most): 16, 768 x 3072 of 16, top-2 (96 tiles) 20 / 17, 14 / 12,
-//     17 / 15, 11 / 9; 64 there, top-1 21 / 20, 14 / 14, 19 / 17, 12 / 10; 24, 1536 x 6144 of 8, top-2 (96) 42 / 35, 41 / 34, 41 / 34, 18 / 17; 1, 2048 x 8192 of 64, top-2 (32)
-//     56 / 19; 32, 2048 x 2048 of 8 (128) 20 / 19, 17 / 16, 20 / 20, 12 / 10; 32, 1024 x 4096 of 16, top-2 (128) 28 / 29, 26 / 27, 27 / 28, 16 / 12; 8, 2048 x 8192 of 8 (128) 37 / 41,
-//     31 / 35, 34 / 38, 22 / 22; 24, 1024 x 4096 of 24, top-2 (192) 42 / 42, 24 / 35, 26 / 36, 15 / 15; 32, 2048 x 8192 of 64, top-2 (1024) 216 / 213, 79 / 85, 95 / 100, 54 / 67;
-//     64 there 253 / 251, 108 / 120, 152 / 153, 55 / 62; 128, 1024 x 4096 of 32 50 / 49, 26 / 38, 39 / 43, 14 / 15.
-constexpr int kThinUpTo = 6, kThinFc1Rows = 192, kThinFc2Rows = 64;
-inline bool thin_up_to(const MoeDims& D, int rows) {
+//     192 there, top-2, at 2048 x 8192 357 / 346, 140 / 148, 253 / 258, 33 / 45; 1500, 512 x 1024 of 256 61 / 53, 14 / 17, 45 / 42, 13 / 16.  (Where the tiles are one
+//     round either way: 8, 2048 x 8192 of 8 44 / 45, 33 / 25, 41 / 44, 21 / 14.)
+//   fc2 + combine, whose shares are sized for all experts, so up to 512 tiles: 16, 768 x 3072 of 16, top-2 (96 tiles) 26 / 23, 20 / 19, 23 / 20, 18 / 16; 32, 1024 x 4096 of 16,
+//     top-2 (128) 34 / 37, 32 / 30, 33 / 33, 22 / 21; 24, 1024 x 4096 of 24, top-2 (192) 47 / 40, 31 / 29, 31 / 30, 21 / 21; 64, 1024 x 4096 of 32 (256) 52 / 47, 30 / 30, 34 / 36,
+//     22 / 18; 48 there, top-3 60 / 62, 47 / 47, 52 / 49, 23 / 24; 13, 1216 x 4864 of 41, top-4 (410) 92 / 75, 50 / 50, 51 / 51, 41 / 27; 8, 2048 x 8192 of 64, top-4 (512) 139 / 134, 91 / 92,
+//     88 / 88, 47 / 45; 32 there, top-2 (1024) 218 / 216, 82 / 89, 100 / 105, 59 / 73; 64 there 248 / 256, 112 / 126, 160 / 163, 61 / 68.
+// (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
+constexpr int kThinUpTo = 6, kThinMostRows = 192, kThinFc2Tiles = 512;
+inline bool thin_fc1(const MoeDims& D) {
     const double wider = D.d > D.f ? D.d : D.f, other = D.d > D.f ? D.f : D.d;
-    return (D.A <= kThinRows || (D.A <= rows && D.A <= (long long)kThinUpTo * std::min(D.E, D.A))) && (wider * other + 64 * wider) * 2 < 4294967296.0;
+    return (D.A <= kThinRows || (D.A <= kThinMostRows && D.A <= (long long)kThinUpTo * std::min(D.E, D.A))) &&
+           (wider * other + 64 * wider) * 2 < 4294967296.0;
 }
 inline long long thin_fc2_tiles(const MoeDims& D) { return (long long)std::min(D.E, D.A) * ceil_div(D.d, kThinCols); }
-inline bool thin_fc1(const MoeDims& D) { return thin_up_to(D, kThinFc1Rows); }
-inline bool thin_fc2(const MoeDims& D) { return thin_up_to(D, kThinFc2Rows) && thin_fc2_tiles(D) <= (D.f <= 3072 ? 128 : 96); }
-// Shares of K for FC2 on thin tiles: what makes two workgroups per CU, at least three 64-k blocks each (fc2 + combine in us at 1 / 2 / 4 / 8 shares: 16
-// tokens, 768 x 3072 of 16, top-2 31 / 24 / 24 / 23.5; 16, 1536 x 6144 of 2 36 / 25 / 20 / 18; 20 tokens, 320 x 448 of 30, 15.4 / 13.0 / 14.6 / 15.2).
+inline bool thin_fc2(const MoeDims& D) { return thin_fc1(D) && thin_fc2_tiles(D) <= kThinFc2Tiles; }
+// Shares of K for FC2 on thin tiles: what makes four workgroups per CU, so that half of the experts fill the chip, at least three 64-k blocks each.
+// At most 7: of eight, all workgroups start at the same offset of a power of two, where f is one (fc2 + combine in us at 8 / 7 / 6 / 5 shares: 8 tokens, 2048
+// x 8192 of 8 48 / 45 / 46 / 45; 32, 1024 x 4096 of 16, top-2 38 / 37 / 36 / 37; 32 there of 4 19 / 18 / 17 / 17; 20, 1280 x 5120 of 12 33 / 33 / 33 / 35; 24, 1536 x 6144 of 8, top-2
+// 41 / 41 / 44 / 41).  Two workgroups per CU / four: 24 tokens, 1024 x 4096 of 24, top-2 48 / 40, under Zipf 41 / 29; 12, 2048 x 8192 of 12 69 / 59; 16, 768 x 3072 of
+// 16, top-2 24 / 23.
 inline int thin_fc2_shares(const MoeDims& D) {
-    return std::max(1, std::min({8, 2 * kNumCUs / (int)thin_fc2_tiles(D), D.f / BK / 3}));
+    return std::max(1, std::min({7, 4 * kNumCUs / (int)thin_fc2_tiles(D), D.f / BK / 3}));
 }
 
 // FC2 in shares of K: with few rows its tiles are few and long (K = d_ff), so a decode step leaves most CUs idle.

@@ -21,9 +21,9 @@ def plan(w):
 # thin: bits of fc1 and fc2
 @pytest.mark.parametrize("T,d,f,E,k,dtype,routing,thin,split", [
     (1, 64, 64, 1, 1, "bf16", "topk", 3, False), (3, 128, 192, 5, 2, "f16", "topk", 3, False), (16, 768, 3072, 16, 2, "bf16", "bias", 3, True),
-    (30, 320, 448, 14, 2, "bf16", "zipf", 3, True), (16, 576, 832, 25, 4, "f16", "zipf", 3, True), (64, 192, 704, 90, 1, "f16", "zipf", 3, True),
-    (30, 64, 1088, 300, 2, "bf16", "zipf", 3, True), (63, 320, 704, 120, 3, "bf16", "zipf", 1, False), (190, 1024, 320, 260, 1, "f16", "topk", 1, False),
-    (96, 192, 2112, 32, 2, "bf16", "bias", 1, True), (64, 192, 448, 1024, 1, "bf16", "topk", 3, True),
+    (40, 320, 448, 14, 2, "bf16", "zipf", 3, True), (40, 576, 832, 48, 4, "f16", "zipf", 3, True), (64, 192, 704, 104, 3, "f16", "zipf", 3, True),
+    (90, 64, 1088, 300, 2, "bf16", "zipf", 3, True), (63, 320, 704, 180, 3, "bf16", "zipf", 1, False), (190, 1024, 320, 260, 1, "f16", "topk", 1, False),
+    (96, 192, 2112, 32, 2, "bf16", "bias", 3, True), (64, 192, 448, 1024, 1, "bf16", "topk", 3, True),
 ])
 def test_thin(oracle, T, d, f, E, k, dtype, routing, thin, split):
     w = MoEWorkload("thin", T, d, f, E, k, dtype, routing, 40 + T)
@@ -37,7 +37,7 @@ def test_thin(oracle, T, d, f, E, k, dtype, routing, thin, split):
 @pytest.mark.parametrize("rows", [2, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 191, 192])
 def test_rows_of_one_expert(oracle, rows):
     w = MoEWorkload("rows", rows, 192, 320, 32, 1, "bf16", "topk", rows)      # the other experts are empty
-    assert plan(w)["thin"] == (3 if rows <= 64 else 1)
+    assert plan(w)["thin"] == 3
     data = generate(w, DEV)
     data["topk_idx"].fill_(4)
     full_parity(oracle, w, data, label=f"thin, {rows} rows")
@@ -67,11 +67,8 @@ def test_all_ids_out_of_range(f):
         assert not t.any(), name
 
 
-# at both sides of each line: 32 rows, 6 per expert, 192 and 64 rows in all, 128 tiles of fc2, 96 where f exceeds 3072
-@pytest.mark.parametrize("T,d,f,E,thin", [
-    (32, 192, 1024, 1, 3), (33, 192, 1024, 1, 0), (36, 192, 1024, 6, 3), (37, 192, 1024, 6, 0), (64, 192, 1024, 32, 3), (65, 192, 1024, 32, 1),
-    (192, 192, 1024, 32, 1), (193, 192, 1024, 33, 0), (32, 512, 3072, 33, 3), (33, 512, 3072, 33, 1), (32, 1024, 3072, 16, 3), (32, 1024, 3072, 17, 1),
-    (32, 1024, 3136, 12, 3), (32, 1024, 3136, 13, 1),
-])
-def test_rule(T, d, f, E, thin):
-    assert plan(MoEWorkload("rule", T, d, f, E, 1, "bf16", "topk", 1))["thin"] == thin
+# at both sides of each line: 32 rows, 6 per expert, 192 rows in all, 512 tiles of fc2
+@pytest.mark.parametrize("T,d,E,thin", [(32, 192, 1, 3), (33, 192, 1, 0), (36, 192, 6, 3), (37, 192, 6, 0), (192, 192, 32, 3), (193, 192, 33, 0),
+                                        (128, 512, 128, 3), (129, 512, 129, 1), (16, 4096, 16, 3), (16, 4160, 16, 1)])
+def test_rule(T, d, E, thin):
+    assert plan(MoEWorkload("rule", T, d, 1024, E, 1, "bf16", "topk", 1))["thin"] == thin
