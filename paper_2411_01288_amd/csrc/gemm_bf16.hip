@@ -1380,12 +1380,13 @@ inline bool small_bwd1(const MoeDims& D) { return small_pair(D, D.f, D.d); }
 //     top-2 275 / 258, 111 / 103, 148 / 146, 32 / 25; 128 there 322 / 309, 132 / 126, 212 / 204, 33 / 37; 384, 512 x 2048 of 64 35 / 32, 13 / 15, 31 / 27, 12 / 10;
 //     192 there, top-2, at 2048 x 8192 357 / 346, 140 / 148, 253 / 258, 33 / 45; 1500, 512 x 1024 of 256 61 / 53, 14 / 17, 45 / 42, 13 / 16.  (Where the tiles are one
 //     round either way: 8, 2048 x 8192 of 8 44 / 45, 33 / 25, 41 / 44, 21 / 14.)
-//   fc2 + combine, whose shares are sized for all experts, so up to 512 tiles: 16, 768 x 3072 of 16, top-2 (96 tiles) 26 / 23, 20 / 19, 23 / 20, 18 / 16; 32, 1024 x 4096 of 16,
+//   fc2 + combine, up to 1024 tiles: 16, 768 x 3072 of 16, top-2 (96 tiles) 26 / 23, 20 / 19, 23 / 20, 18 / 16; 32, 1024 x 4096 of 16,
 //     top-2 (128) 34 / 37, 32 / 30, 33 / 33, 22 / 21; 24, 1024 x 4096 of 24, top-2 (192) 47 / 40, 31 / 29, 31 / 30, 21 / 21; 64, 1024 x 4096 of 32 (256) 52 / 47, 30 / 30, 34 / 36,
 //     22 / 18; 48 there, top-3 60 / 62, 47 / 47, 52 / 49, 23 / 24; 13, 1216 x 4864 of 41, top-4 (410) 92 / 75, 50 / 50, 51 / 51, 41 / 27; 8, 2048 x 8192 of 64, top-4 (512) 139 / 134, 91 / 92,
-//     88 / 88, 47 / 45; 32 there, top-2 (1024) 218 / 216, 82 / 89, 100 / 105, 59 / 73; 64 there 248 / 256, 112 / 126, 160 / 163, 61 / 68.
+//     88 / 88, 47 / 45; 40, 1088 x 1280 of 108, top-2 (720) 36 / 36, 23 / 20, 29 / 26, 21 / 18; 96, 1024 x 4096 of 96, top-2 (768) 123 / 116, 51 / 50, 77 / 71, 28 / 27; 64, 2048 x 8192 of
+//     64, top-2 (1024) 250 / 260, 115 / 115, 163 / 157, 61 / 44; 48, 2048 x 1024 of 64, top-4 (1024) 55 / 56, 32 / 35, 35 / 41, 20 / 21.
 // (K + 64 rows of weights have to fit the 32-bit offsets of requests past the end.)
-constexpr int kThinUpTo = 6, kThinMostRows = 192, kThinFc2Tiles = 512;
+constexpr int kThinUpTo = 6, kThinMostRows = 192, kThinFc2Tiles = 1024;
 inline bool thin_fc1(const MoeDims& D) {
     const double wider = D.d > D.f ? D.d : D.f, other = D.d > D.f ? D.f : D.d;
     return (D.A <= kThinRows || (D.A <= kThinMostRows && D.A <= (long long)kThinUpTo * std::min(D.E, D.A))) &&
@@ -1393,13 +1394,14 @@ inline bool thin_fc1(const MoeDims& D) {
 }
 inline long long thin_fc2_tiles(const MoeDims& D) { return (long long)std::min(D.E, D.A) * ceil_div(D.d, kThinCols); }
 inline bool thin_fc2(const MoeDims& D) { return thin_fc1(D) && thin_fc2_tiles(D) <= kThinFc2Tiles; }
-// Shares of K for FC2 on thin tiles: what makes four workgroups per CU, so that half of the experts fill the chip, at least three 64-k blocks each.
+// Shares of K for FC2 on thin tiles: what makes four workgroups per CU, so that half of the experts fill the chip, two at least (one, with 1024 tiles: 64
+// tokens, 2048 x 8192 of 64, top-2 258, under Zipf 127, with two 260, 115), at least three 64-k blocks each.
 // At most 7: of eight, all workgroups start at the same offset of a power of two, where f is one (fc2 + combine in us at 8 / 7 / 6 / 5 shares: 8 tokens, 2048
 // x 8192 of 8 48 / 45 / 46 / 45; 32, 1024 x 4096 of 16, top-2 38 / 37 / 36 / 37; 32 there of 4 19 / 18 / 17 / 17; 20, 1280 x 5120 of 12 33 / 33 / 33 / 35; 24, 1536 x 6144 of 8, top-2
 // 41 / 41 / 44 / 41).  Two workgroups per CU / four: 24 tokens, 1024 x 4096 of 24, top-2 48 / 40, under Zipf 41 / 29; 12, 2048 x 8192 of 12 69 / 59; 16, 768 x 3072 of
 // 16, top-2 24 / 23.
 inline int thin_fc2_shares(const MoeDims& D) {
-    return std::max(1, std::min({7, 4 * kNumCUs / (int)thin_fc2_tiles(D), D.f / BK / 3}));
+    return std::max(1, std::min({7, std::max(2, 4 * kNumCUs / (int)thin_fc2_tiles(D)), D.f / BK / 3}));
 }
 
 // FC2 in shares of K: with few rows its tiles are few and long (K = d_ff), so a decode step leaves most CUs idle.

@@ -22,7 +22,7 @@ def plan(w):
 @pytest.mark.parametrize("T,d,f,E,k,dtype,routing,thin,split", [
     (1, 64, 64, 1, 1, "bf16", "topk", 3, False), (3, 128, 192, 5, 2, "f16", "topk", 3, False), (16, 768, 3072, 16, 2, "bf16", "bias", 3, True),
     (40, 320, 448, 14, 2, "bf16", "zipf", 3, True), (40, 576, 832, 48, 4, "f16", "zipf", 3, True), (64, 192, 704, 104, 3, "f16", "zipf", 3, True),
-    (90, 64, 1088, 300, 2, "bf16", "zipf", 3, True), (63, 320, 704, 180, 3, "bf16", "zipf", 1, False), (190, 1024, 320, 260, 1, "f16", "topk", 1, False),
+    (90, 64, 1088, 300, 2, "bf16", "zipf", 3, True), (63, 320, 704, 180, 3, "bf16", "zipf", 3, True), (150, 1024, 128, 200, 1, "bf16", "zipf", 1, False), (190, 1024, 320, 260, 1, "f16", "topk", 1, False),
     (96, 192, 2112, 32, 2, "bf16", "bias", 3, True), (64, 192, 448, 1024, 1, "bf16", "topk", 3, True),
 ])
 def test_thin(oracle, T, d, f, E, k, dtype, routing, thin, split):
@@ -67,8 +67,8 @@ def test_all_ids_out_of_range(f):
         assert not t.any(), name
 
 
-# at both sides of each line: 32 rows, 6 per expert, 192 rows in all, 512 tiles of fc2
+# at both sides of each line: 32 rows, 6 per expert, 192 rows in all, 1024 tiles of fc2
 @pytest.mark.parametrize("T,d,E,thin", [(32, 192, 1, 3), (33, 192, 1, 0), (36, 192, 6, 3), (37, 192, 6, 0), (192, 192, 32, 3), (193, 192, 33, 0),
-                                        (128, 512, 128, 3), (129, 512, 129, 1), (16, 4096, 16, 3), (16, 4160, 16, 1)])
+                                        (128, 1024, 128, 3), (129, 1024, 129, 1), (16, 8192, 16, 3), (16, 8256, 16, 1)])
 def test_rule(T, d, E, thin):
     assert plan(MoEWorkload("rule", T, d, 1024, E, 1, "bf16", "topk", 1))["thin"] == thin

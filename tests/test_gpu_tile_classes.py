@@ -49,10 +49,10 @@ def test_expert_look_up(oracle, E):
 
 # more than 256 MB of weights and fewer than 128 rows per expert: the forward pass deals groups of tiles in eighths.  Column tiles
 # with a tail, groups of row tiles with a rest, empty experts
-# (thin: fc1 or both on 32x128 tiles, in groups of 32 row tiles; the third and fourth case have a group and a rest of them)
+# (thin: both on 32x128 tiles, in groups of 32 row tiles; the third and fourth case have a group and a rest of them)
 @pytest.mark.parametrize("T,d,f,E,k,dtype,routing,thin", [
     (300, 1024, 2112, 62, 2, "bf16", "zipf", 0), (9, 2048, 3264, 20, 1, "f16", "topk", 3), (60, 704, 3136, 61, 1, "f16", "topk", 3),
-    (96, 1024, 1344, 100, 2, "bf16", "bias", 1), (1200, 704, 3136, 61, 1, "bf16", "bias", 0)])
+    (96, 1024, 1344, 100, 2, "bf16", "bias", 3), (1200, 704, 3136, 61, 1, "bf16", "bias", 0)])
 def test_streamed_weights(oracle, T, d, f, E, k, dtype, routing, thin):
     w = MoEWorkload("streamed", T, d, f, E, k, dtype, routing, 31 + T)
     assert w.A < 128 * E and 2 * E * d * f > 256e6
