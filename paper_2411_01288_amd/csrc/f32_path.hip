@@ -557,10 +557,10 @@ __device__ __forceinline__ void multiply_split(const TileArgs& a, const TilePlac
 // reads and of the loads per product.  The work of a K-step is laid out by hand: behind each of a wavefront's 48 matrix instructions stand
 // a fragment read of this step, a piece of the splitting of the next step's operands, the stores of its planes, a load, the additions of the large
 // products.  Two LDS buffers, one barrier a step, two steps of operands on their way to registers.
-// What bounds a step is the issue of vector instructions: with matrix instructions between them, one in 4.3 cycles and SIMD, matrix instructions
-// counted, 96 + 2 * 176 a step of both workgroups, 0.95 us, against 0.71 us of the matrix pipe.  (v_dot2_f32_bf16 would take a plane off in one
-// instruction instead of two, but waits for the matrix pipe: two of them behind a matrix instruction take as long as four.)  Tried and not
-// kept: 128x128 tiles, one workgroup per CU (fc1 at 8192 rows, 384 x 1536 of 8 experts, 94 -> 116 us: nothing runs under a tile's start and
+// What a wavefront does with its cycles (counters, fc2 / bwd_fc1 at 8192 rows, 384 x 1536 of 8 experts): it issues in 47 / 43 % (vector and matrix instructions 32 / 29), waits
+// to issue in 30 / 31, for loads, LDS and the barrier in 23 / 26, two to a SIMD at most and 1.15 / 1.58 on average; the matrix pipe is busy in 30 / 35 % of
+// the launch.  fc2's 432 tiles are less than one round of 512.  Tried and not kept: v_dot2_f32_bf16, which takes a plane off in one instruction instead
+// of two (the same time); 128x128 tiles, one workgroup per CU (fc1 there 94 -> 116 us: nothing runs under a tile's start and
 // epilogue, 13 us; with four wavefronts of 64x64, 142).
 // (a, b), or their negatives, as a bf16 pair; what is left of them, or of their negatives, is left in a and b.
 template <bool NEG>
